@@ -410,7 +410,6 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   float hpv = jok ? hsg[(long)rowc * H + jc] : 0.f;
   float4 xa[XB][2];  // this step's fragments of the layer input, loaded one step ahead
   float gxn[3] = {0.f, 0.f, 0.f};  // ... or its input projection
-  const float gxm = jok ? 1.f : 0.f;  // (a unit beyond H has no input: its h stays zero)
   if (XP) {
     fragment_loads<XB, KW>(tile_rsrc(xin + g * s_x + (long)r0 * width), width, B - r0, rsel, kw, xa);
   } else if (act) {
@@ -421,7 +420,7 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   __syncthreads();
   for (int t = 0; t < T; ++t) {
     // what does not depend on the recurrence is computed in front of the wait
-    float gxv[3] = {gxn[0] * gxm, gxn[1] * gxm, gxn[2] * gxm};
+    const float gxv[3] = {gxn[0], gxn[1], gxn[2]};
     floatx4 acc[2][3], accx[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -466,7 +465,9 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       const float z = sigm_1ulp(gxv[1] + biasx[1] + (gh[1] + bias[1]));
       const float q2 = gh[2] + bias[2];
       const float n = tanh_1ulp((XP ? gh[NP - 1] + biasx[2] : gxv[2]) + r * q2);
-      const float hn = (1.0f - z) * n + z * hpv;
+      // (the lanes beyond H compute with unit H-1's projection, or an infinite input times a zero weight: whatever
+      // that is - a NaN too, which a zero factor would keep - the h that the others multiply is zero)
+      const float hn = jok ? (1.0f - z) * n + z * hpv : 0.f;
       if (row < B) st_dev(hxg + (long)(t + 1) * xblk + xoff(row, nchx, j), hn, l2x);
       if (ok) {
         hsg[((long)(t + 1) * B + row) * H + j] = hn;
