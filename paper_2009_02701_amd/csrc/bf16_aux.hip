@@ -346,7 +346,6 @@ softmax_ce_bf16_rows_kernel(const float* __restrict__ logits, long ld_l, long s_
     const int t = row / Bp, b = row - t * Bp;
     const bool real = b < B;  // (uniform)
     const int label = y[g * s_y + (long)t * B + min(b, B - 1)];
-    const float row_n = real ? inv_n : 0.f;
     float4 v[V4];
     float m = -INFINITY;
 #pragma unroll
@@ -391,10 +390,12 @@ softmax_ce_bf16_rows_kernel(const float* __restrict__ logits, long ld_l, long s_
     for (int i = 0; i < V4; ++i) {
       const int c = 4 * (tid + NT * i);
       if (c < C) {
-        const float4 d4 = make_float4((v[i].x * inv_sum - (c + 0 == label ? 1.0f : 0.0f)) * row_n,
-                                      (v[i].y * inv_sum - (c + 1 == label ? 1.0f : 0.0f)) * row_n,
-                                      (v[i].z * inv_sum - (c + 2 == label ? 1.0f : 0.0f)) * row_n,
-                                      (v[i].w * inv_sum - (c + 3 == label ? 1.0f : 0.0f)) * row_n);
+        float4 d4 = make_float4((v[i].x * inv_sum - (c + 0 == label ? 1.0f : 0.0f)) * inv_n,
+                                (v[i].y * inv_sum - (c + 1 == label ? 1.0f : 0.0f)) * inv_n,
+                                (v[i].z * inv_sum - (c + 2 == label ? 1.0f : 0.0f)) * inv_n,
+                                (v[i].w * inv_sum - (c + 3 == label ? 1.0f : 0.0f)) * inv_n);
+        // (selected: a padding row's logits are NaN where a weight is infinite)
+        if (!real) d4 = make_float4(0.f, 0.f, 0.f, 0.f);
         acc[i].x += d4.x; acc[i].y += d4.y; acc[i].z += d4.z; acc[i].w += d4.w;
         bf16x4 o;
         o[0] = (__bf16)d4.x; o[1] = (__bf16)d4.y; o[2] = (__bf16)d4.z; o[3] = (__bf16)d4.w;

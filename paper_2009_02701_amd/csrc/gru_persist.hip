@@ -797,7 +797,7 @@ __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(1, 2))
 gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih,
                             const float* __restrict__ b_hh, long s_rep, int Hc, const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs,
                             __bf16* __restrict__ hb, long s_hb, __bf16* hx, long s_hx, float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT,
-                            long s_hT, int B, int H, int T, int sg0, int n_sg, unsigned* sync, unsigned base,
+                            long s_hT, int Bc, int B, int H, int T, int sg0, int n_sg, unsigned* sync, unsigned base,
                             unsigned spin_limit, unsigned* tickets, unsigned ticket_base, unsigned per_xcd) {
   extern __shared__ __attribute__((aligned(16))) float persist_lds[];
   float* red = persist_lds;                                     // [8][2][6][4][64]
@@ -835,6 +835,7 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
   const int j = j0 + u0;
   const int ro = ((rl >> 4) * 6) * 256 + (rl & 3) * 64 + ((rl >> 2) & 3) * 16 + (u0 & 15);  // + cb * 256 + w * 3072
   const int half = u0 >> 4;
+  const bool ok0 = row < Bc && j < Hc, ok1 = row < Bc && j + 1 < Hc;  // of the model, not of its padding
   // the biases: arrays of the model's own width (units beyond it have none)
   float2 bias[3], biasx[3];
 #pragma unroll
@@ -912,9 +913,13 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
       gh[q].x = (((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x))) + bias[q].x;
       gh[q].y = (((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y))) + bias[q].y;
     }
-    const float r0v = sigm_fast(gxv[0].x + gh[0].x), r1v = sigm_fast(gxv[0].y + gh[0].y);
-    const float z0v = sigm_fast(gxv[1].x + gh[1].x), z1v = sigm_fast(gxv[1].y + gh[1].y);
-    const float n0v = tanh_fast(gxv[2].x + r0v * gh[2].x), n1v = tanh_fast(gxv[2].y + r1v * gh[2].y);
+    float r0v = sigm_fast(gxv[0].x + gh[0].x), r1v = sigm_fast(gxv[0].y + gh[0].y);
+    float z0v = sigm_fast(gxv[1].x + gh[1].x), z1v = sigm_fast(gxv[1].y + gh[1].y);
+    float n0v = tanh_fast(gxv[2].x + r0v * gh[2].x), n1v = tanh_fast(gxv[2].y + r1v * gh[2].y);
+    // rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model times
+    // their zero operands is NaN, which their h and gate gradients would hand to everyone
+    if (!ok0) r0v = z0v = n0v = gh[2].x = 0.f;
+    if (!ok1) r1v = z1v = n1v = gh[2].y = 0.f;
     const float2 hn = make_float2((1.0f - z0v) * n0v + z0v * hpv.x, (1.0f - z1v) * n1v + z1v * hpv.y);
     if (row < B) {
       const long e = ((long)(t + 1) * B + row) * H + j;
@@ -1353,10 +1358,10 @@ size_t gru_persist_bf16_exchange_elems(int B, int width) { return (size_t)((B + 
 hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                        const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
-                                       float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int B, int H, int T,
+                                       float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
                                        int groups, unsigned* sync, unsigned base, unsigned spin_limit, bool device_scope,
                                        unsigned* ticket_launches, hipStream_t s) {
-  if (!gru_persist_bf16_supported(B, H) || Hc < 1 || Hc > H || T < 1) return hipErrorInvalidValue;
+  if (!gru_persist_bf16_supported(B, H) || Hc < 1 || Hc > H || Bc < 1 || Bc > B || T < 1) return hipErrorInvalidValue;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (!hx || !a16(hx) || (s_hx & 7) != 0) return hipErrorInvalidValue;
   if (!a16(Wb) || !a16(hb) || !a16(hs) || !a16(gx) || !a16(sv) || (hT && !a16(hT)) || (s_wb & 7) != 0 ||
@@ -1377,7 +1382,7 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
 #define HPSGD_FWD_PB(N)                                                                                            \
   hipLaunchKernelGGL(gru_fwd_persist_bf16_kernel<N>, dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, b_hh, s_rep, Hc, \
-                     gx, s_gx, hs, s_hs, (__bf16*)hb, s_hb, (__bf16*)hx, s_hx, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, B, H, T, sg0, n_sg,    \
+                     gx, s_gx, hs, s_hs, (__bf16*)hb, s_hb, (__bf16*)hx, s_hx, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, Bc, B, H, T, sg0, n_sg,    \
                      sync, base, spin_limit, pl.tickets, pl.ticket_base, pl.per_xcd)
   const int NJ = H / QJ, SG = groups * ((B + PR - 1) / PR), per = groups_per_launch(NJ, SG);
   for (int sg0 = 0; sg0 < SG; sg0 += per) {

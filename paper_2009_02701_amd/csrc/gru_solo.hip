@@ -430,7 +430,7 @@ __global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_
 gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih, const float* __restrict__ b_hh,
                          long s_rep, int Hc, const float* __restrict__ gx, long s_gx, __bf16* __restrict__ hb, long s_hb,
                          float* __restrict__ hs, long s_hs, float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT,
-                         long s_hT, int B, int T, int RT) {
+                         long s_hT, int Bc, int B, int T, int RT) {
   using S = SoloB<HB, UB>;
   constexpr int HP = S::HP, LP = S::LP, NC = S::NC;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
@@ -532,6 +532,9 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
         rr[u][v] = sigm_fast(G[u][0][v] + acc[u][0][v]);
         zz[u][v] = sigm_fast(G[u][1][v] + acc[u][1][v]);
         nn[u][v] = tanh_fast((G[u][2][v] + bx[u]) + rr[u][v] * acc[u][2][v]);
+        // Rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model
+        // times their zero operands is NaN, which their h and gate gradients would hand to everyone.
+        if (r0 + 2 * lg + v >= Bc || (w * UB + u) * 16 + lr >= Hc) rr[u][v] = zz[u][v] = nn[u][v] = acc[u][2][v] = 0.f;
       }
     }
     const __amdgpu_buffer_rsrc_t rh = rsrc_b(hsg + (long)t * step_out, blk * 4), rv = rsrc_b(svg + (long)t * step_out * 4, blk * 16);
@@ -731,8 +734,8 @@ int gru_solo_bf16_row_tiles(int B) { return B / kSoloBRows; }
 
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int B, int H, int T, int groups, hipStream_t s) {
-  if (!gru_solo_bf16_supported(B, H) || T < 1 || Hc < 1 || Hc > H || (ld_hT & 1) != 0 || (s_hT & 1) != 0 ||
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, hipStream_t s) {
+  if (!gru_solo_bf16_supported(B, H) || T < 1 || Hc < 1 || Hc > H || Bc < 1 || Bc > B || (ld_hT & 1) != 0 || (s_hT & 1) != 0 ||
       (long)H * ld_hT * 2 >= 0x7fffffe0L)
     return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
@@ -749,7 +752,7 @@ hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih
       ready = true;                                                                                                   \
     }                                                                                                                 \
     hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s, (const __bf16*)Wb, \
-                       s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, B, \
+                       s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, Bc, B, \
                        T, RT);                                                                                        \
   } while (0)
   HPSGD_SOLOB_CASES(HPSGD_SOLOB_FWD)

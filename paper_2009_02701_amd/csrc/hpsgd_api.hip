@@ -1001,12 +1001,12 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_solo_fwd_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx,
-                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, B, H, T, groups, s));
+                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, s));
         ++c->last_resident;
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_fwd_persist_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx, hs, s_hs, hb, s_hb,
-                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, B, H, T, groups,
+                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups,
                                             psync, pbase, c->spin_limit, c->device_scope, &ticket_launches, s));
         pbase += (unsigned)T * gru_persist_bf16_count_per_step(H);
         ++c->last_resident;

@@ -218,7 +218,7 @@ bool gru_solo_bf16_supported(int B, int H);
 int gru_solo_bf16_row_tiles(int B);
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int B, int H, int T, int groups, hipStream_t s);
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, hipStream_t s);
 hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* above, long s_above, const float* sv, long s_sv,
                                     const float* hs, long s_hs, void* dg4, long s_dg4, float* dbp, int Hc, int B, int H, int T,
                                     int groups, hipStream_t s);
@@ -296,13 +296,14 @@ hipError_t launch_reduce_parts(const float* parts, int n_parts, size_t n, const 
 // The backward launch always leaves the partial bias-gradient sums in dbp and writes no fp32
 // gate gradients.  Counters advance by steps * gru_persist_bf16_count_per_step().
 // H: the width of every internal buffer (a multiple of 32); Hc <= H: the width of the model's own
-// arrays (b_ih, b_hh, dbp).  What lies beyond Hc stays zero.  b_ih is added by the forward launch.
+// arrays (b_ih, b_hh, dbp).  Bc <= B: the batch rows that are the model's own.  Of units beyond Hc and rows
+// beyond Bc the forward launch leaves zeros, whatever their input projections are.  b_ih is added by the forward launch.
 // More workgroups than the chip has CUs are issued as several launches of whole synchronisation groups.
 bool gru_persist_bf16_supported(int B, int H);
 unsigned gru_persist_bf16_count_per_step(int H);
 hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc, const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
-                                       float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int B, int H, int T,
+                                       float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
                                        int groups, unsigned* sync, unsigned base, unsigned spin_limit, bool device_scope,
                                        unsigned* ticket_launches, hipStream_t s);
 // bf16 elements of one time step's block of an exchange buffer whose rows are `width` wide
