@@ -176,6 +176,8 @@ __device__ __forceinline__ bool persist_place(unsigned* tickets, unsigned ticket
   return sg >= 0;
 }
 
+constexpr int kBeyond = 0x7ffffff0;  // a byte offset outside every tile's buffer: such a load gives zeros
+
 // 16 bytes at byte offset `off` of the buffer, as a device-scope load
 __device__ __forceinline__ float4 ld16_dev(__amdgpu_buffer_rsrc_t rs, int off) {
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -215,7 +217,8 @@ __device__ __forceinline__ void load_resident(float* wres, int wp, const float* 
 
 // The loads of NB chunks of this wave, first chunk c0, + KW per chunk.  rs: buffer
 // over the workgroup's activation tile (row pitch KD words); rows >= rows_valid are read from
-// row 0 (their results are never stored), columns beyond KD from column 0 (they meet a zero weight).
+// row 0 (their results are never stored), columns beyond KD are loaded as zeros (they meet a zero weight, which
+// an infinite input of another column would turn into NaN).
 template <int NB, int KW>
 __device__ __forceinline__ void fragment_loads(__amdgpu_buffer_rsrc_t rs, int KD, int rows_valid, int rsel, int c0,
                                                float4 (&a)[NB][2]) {
@@ -227,8 +230,8 @@ __device__ __forceinline__ void fragment_loads(__amdgpu_buffer_rsrc_t rs, int KD
   for (int i = 0; i < NB; ++i) {
     const int k0 = PC * (c0 + KW * i) + 4 * lg;
     // (KD is a multiple of 16: each piece is all in or all out)
-    a[i][0] = ld16_dev(rs, (rowoff + (k0 < KD ? k0 : 0)) * 4);
-    a[i][1] = ld16_dev(rs, (rowoff + (k0 + 16 < KD ? k0 + 16 : 0)) * 4);
+    a[i][0] = ld16_dev(rs, k0 < KD ? (rowoff + k0) * 4 : kBeyond);
+    a[i][1] = ld16_dev(rs, k0 + 16 < KD ? (rowoff + k0 + 16) * 4 : kBeyond);
   }
 }
 
@@ -324,7 +327,7 @@ __device__ __forceinline__ void resident_contraction_x(const float* wres, int wp
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const float* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7fffffff, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7fffffe0, 0x00020000);
 }
 
 // The KW partial sums of an output, in a fixed order (PL words apart)
