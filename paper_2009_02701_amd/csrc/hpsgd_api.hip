@@ -250,7 +250,8 @@ int build_layout(hpsgd_ctx* c) {
     c->prow = c->solo || d.prec == HPSGD_BF16_MFMA || c->lean == 2 || (c->lean && d.hidden % 16 != 0)
                   ? 0
                   : gru_persist_rows(d.batch, d.hidden, c->K);
-    c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : 32));
+    // (no step of a narrow model waits for another workgroup)
+    if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : 32));
     if (c->solo) c->dbp = c->alloc_packed((size_t)gru_solo_row_tiles(d.batch) * 6 * H);
     else if (c->prow) c->dbp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 6 * H);
     else if (c->solo_b) c->dbp = c->alloc_packed((size_t)gru_solo_bf16_row_tiles((int)Bi) * 6 * H);
@@ -812,6 +813,9 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const bool use_solo_b = pad && c->solo_b;  // (a kind of use_persist_b without the exchange)
     const bool exchange = use_persist || (use_persist_b && !use_solo_b);
     unsigned* psync = exchange ? (unsigned*)reg(c->psync) : nullptr;
+    // the abort words of all workers of this step, cleared whether it exchanges or not: what is reported is this
+    // step, not an earlier one of another form or what the memory held
+    unsigned* aborts = c->psync.stride ? (unsigned*)reg(c->psync) : nullptr;
     unsigned pbase = 0;
     unsigned ticket_launches = 0;  // launches of this step that placed their workgroups by ticket
     if (exchange) {
@@ -878,6 +882,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       fp.max_groups = 0;
       bool ok = true;
       if (psync) ok = ok && fill_pack_push(fp, (float*)psync, 0, 1, (long)gru_persist_sync_words(B, groups, prow), 0, 1);
+      if (aborts) ok = ok && fill_pack_push(fp, (float*)aborts, 0, 1, 1, c->psync.stride, groups);
       const bool solo_any = use_solo || use_solo_b;  // (those launches write h_0 themselves)
       for (int l = 0; l < L && ok && !solo_any; ++l) {
         ok = ok && fill_pack_push(fp, reg(c->hs[l]), 0, 1, (long)B * H, c->hs[l].stride, groups);
@@ -904,6 +909,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       if (!cleared) {
         HIP_TRY(launch_fill_zero(hs, (size_t)B * H, (size_t)s_hs, groups, s, l == 0 ? (float*)psync : nullptr,
                                  l == 0 && psync ? gru_persist_sync_words(B, groups, prow) : 0));
+        if (aborts && l == 0) HIP_TRY(launch_fill_zero((float*)aborts, 1, c->psync.stride, groups, s));
         if (use_persist && l == 0)
           HIP_TRY(launch_fill_zero(reg(c->hx), gru_persist_exchange_words(B, H, 1), c->hx.stride, groups, s));
       }

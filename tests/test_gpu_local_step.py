@@ -917,3 +917,37 @@ def test_overlapped_rounds_replayed_from_a_hip_graph(name):
     for a, b in zip(snaps_g2, snaps_e2):
         assert torch.equal(a, b)
     assert torch.isfinite(snaps_g[-1]).all()
+
+
+# (model, changes): the recurrence without an exchange in fp32 and bf16, one launch per step, resident launches with
+# more workers than the flag words of one step reach
+NEVER_GAVE_UP = {
+    "narrow_fp32": ("gru_cls", dict(layers=1, input=16, hidden=64, seq_len=3, batch=8, K=3)),
+    "narrow_bf16": ("gru_lm", dict(vocab=99, embed=24, hidden=100, seq_len=3, batch=8, K=3)),
+    "per_step": ("gru_cls", dict(layers=1, input=16, hidden=144, seq_len=3, batch=40, K=16)),
+    "resident": ("gru_cls", dict(layers=1, input=16, hidden=160, seq_len=3, batch=8, K=8)),
+    "resident_many_layers": ("gru_cls", dict(layers=14, input=16, hidden=160, seq_len=2, batch=8, K=2)),
+}
+
+
+@pytest.mark.parametrize("name", NEVER_GAVE_UP)
+def test_no_wait_is_reported_that_the_last_step_did_not_give_up(name):
+    """Whatever the workspace held before the step, and whatever an earlier step of one worker left in it."""
+    base, changes = NEVER_GAVE_UP[name]
+    cfg = wl.scaled(wl.CONFIGS[base], **changes)
+    init, shards, orders, _ = workload(cfg)
+    tr = harness.Trainer(cfg, init, shards, orders, device=DEV)
+    tr.ws[0] = tr.ctx.new_workspace(DEV)
+    tr.ws[0].view(torch.int32).fill_(1)
+    last = cfg["K"] - 1
+    tr.gather(0)
+    for spin in (None, 0):
+        tr.sync_all(0)
+        if spin is not None:
+            tr.ctx.set_recurrence(True, spin)
+            tr.ctx.local_step(last, tr.R[0][last], tr.R[0][last], tr.xb[last], tr.yb[last], 0.1, tr.loss[last:], tr.ws[0])
+            tr.sync_all(0)
+        tr.ctx.set_recurrence(True)
+        tr.local_step(0, 0.1)
+        torch.cuda.synchronize()
+        assert not tr.ctx.recurrence_gave_up(tr.ws[0]) and torch.isfinite(tr.loss).all()
