@@ -464,10 +464,10 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
 #pragma unroll
       for (int q = 0; q < NP; ++q)
         gh[q] = sum_planes<KW>(red, ((rsel * NP + q) * 4 + qv) * 64 + lane, RB * NP * 256);
-      const float r = sigm_1ulp(gxv[0] + biasx[0] + (gh[0] + bias[0]));
-      const float z = sigm_1ulp(gxv[1] + biasx[1] + (gh[1] + bias[1]));
+      const float r = sigm_f32(gxv[0] + biasx[0] + (gh[0] + bias[0]));
+      const float z = sigm_f32(gxv[1] + biasx[1] + (gh[1] + bias[1]));
       const float q2 = gh[2] + bias[2];
-      const float n = tanh_1ulp((XP ? gh[NP - 1] + biasx[2] : gxv[2]) + r * q2);
+      const float n = tanh_f32((XP ? gh[NP - 1] + biasx[2] : gxv[2]) + r * q2);
       // (the lanes beyond H compute with unit H-1's projection, or an infinite input times a zero weight: whatever
       // that is - a NaN too, which a zero factor would keep - the h that the others multiply is zero)
       const float hn = jok ? (1.0f - z) * n + z * hpv : 0.f;

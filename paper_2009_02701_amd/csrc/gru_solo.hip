@@ -160,9 +160,9 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
     for (int v = 0; v < 4; ++v) {
       rr[v] = zz[v] = nn[v] = 0.f;
       if (v < nv) {  // uniform
-        rr[v] = sigm_1ulp(G[0][v] + acc[0][v]);
-        zz[v] = sigm_1ulp(G[1][v] + acc[1][v]);
-        nn[v] = tanh_1ulp(G[2][v] + rr[v] * acc[2][v]);
+        rr[v] = sigm_f32(G[0][v] + acc[0][v]);
+        zz[v] = sigm_f32(G[1][v] + acc[1][v]);
+        nn[v] = tanh_f32(G[2][v] + rr[v] * acc[2][v]);
         hp[v] = (1.0f - zz[v]) * nn[v] + zz[v] * hp[v];
         hout[(4 * lg + v) * LP + j] = hp[v];
       }
