@@ -60,4 +60,10 @@ __device__ __forceinline__ float tanh_fast(float a) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(2.88539008f * a));
 }
 
+// EX: a launch's choice between the two
+template <bool EX>
+__device__ __forceinline__ float sigm_of(float a) { return EX ? sigm_f32(a) : sigm_fast(a); }
+template <bool EX>
+__device__ __forceinline__ float tanh_of(float a) { return EX ? tanh_f32(a) : tanh_fast(a); }
+
 }  // namespace hpsgd

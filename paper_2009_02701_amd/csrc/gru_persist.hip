@@ -794,8 +794,8 @@ __device__ __forceinline__ void st16_nt(void* p, uint4 v) {
 // Forward.  Wb: bf16 W_hh [3H][H]; hx: bf16 h_0 .. h_T fragment-major (blocks of 16 ceil(B/16) x H,
 // h_0 given), the exchanged operand; hb: the same row-major (blocks of B x H; written, not read);
 // hs: the same in fp32; hT (nullable): bf16 transposed copy [H][ld_hT], column (t+1)*B + row.
-// NCF: chunks per wave (H <= 256 * NCF).
-template <int NCF>
+// NCF: chunks per wave (H <= 256 * NCF).  EX: the gates of the fp32 launches (gru_bf16_exact_gates).
+template <int NCF, bool EX>
 __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih,
                             const float* __restrict__ b_hh, long s_rep, int Hc, const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs,
@@ -916,9 +916,9 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
       gh[q].x = (((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x))) + bias[q].x;
       gh[q].y = (((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y))) + bias[q].y;
     }
-    float r0v = sigm_fast(gxv[0].x + gh[0].x), r1v = sigm_fast(gxv[0].y + gh[0].y);
-    float z0v = sigm_fast(gxv[1].x + gh[1].x), z1v = sigm_fast(gxv[1].y + gh[1].y);
-    float n0v = tanh_fast(gxv[2].x + r0v * gh[2].x), n1v = tanh_fast(gxv[2].y + r1v * gh[2].y);
+    float r0v = sigm_of<EX>(gxv[0].x + gh[0].x), r1v = sigm_of<EX>(gxv[0].y + gh[0].y);
+    float z0v = sigm_of<EX>(gxv[1].x + gh[1].x), z1v = sigm_of<EX>(gxv[1].y + gh[1].y);
+    float n0v = tanh_of<EX>(gxv[2].x + r0v * gh[2].x), n1v = tanh_of<EX>(gxv[2].y + r1v * gh[2].y);
     // rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model times
     // their zero operands is NaN, which their h and gate gradients would hand to everyone
     if (!ok0) r0v = z0v = n0v = gh[2].x = 0.f;
@@ -1354,6 +1354,13 @@ bool gru_persist_bf16_supported(int B, int H) {
   return H % 32 == 0 && H >= 32 && H <= 1024 && B >= 8 && B % 8 == 0 && H / QJ <= device_cus();
 }
 
+// The gates of a model whose sizes are the launches' own and whose K workers fit one launch are the hardware's
+// (sigm_fast, tanh_fast); every other bf16 model has those of the fp32 launches, as the step kernels that it would
+// take without these launches.  (H, B: padded; padded: they are not the model's own.)
+bool gru_bf16_exact_gates(int B, int H, int K, bool padded) {
+  return padded || (long)(H / QJ) * ((B + PR - 1) / PR) * K > kPlanCus;
+}
+
 unsigned gru_persist_bf16_count_per_step(int) { return 1u; }
 
 size_t gru_persist_bf16_exchange_elems(int B, int width) { return (size_t)((B + 15) / 16) * 16 * (size_t)width; }
@@ -1362,8 +1369,8 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
                                        const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
                                        float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
-                                       int groups, unsigned* sync, unsigned base, unsigned spin_limit, bool device_scope,
-                                       unsigned* ticket_launches, hipStream_t s) {
+                                       int groups, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
+                                       bool device_scope, unsigned* ticket_launches, hipStream_t s) {
   if (!gru_persist_bf16_supported(B, H) || Hc < 1 || Hc > H || Bc < 1 || Bc > B || T < 1) return hipErrorInvalidValue;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (!hx || !a16(hx) || (s_hx & 7) != 0) return hipErrorInvalidValue;
@@ -1373,27 +1380,26 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
     return hipErrorInvalidValue;
   const size_t lds = (size_t)8 * 12 * 256 * sizeof(float) + (size_t)QJ * TP * 2 + 16;
   const int ncf = H <= 256 ? 1 : H <= 512 ? 2 : 4;
-  static size_t allowed[3] = {0, 0, 0};
-  const int slot = ncf == 1 ? 0 : ncf == 2 ? 1 : 2;
-  const void* fn = ncf == 1   ? (const void*)gru_fwd_persist_bf16_kernel<1>
-                   : ncf == 2 ? (const void*)gru_fwd_persist_bf16_kernel<2>
-                              : (const void*)gru_fwd_persist_bf16_kernel<4>;
-  {
-    const hipError_t e = allow_lds(fn, lds > kLdsAlone ? lds : kLdsAlone, allowed[slot]);
-    if (e != hipSuccess) return e;
-  }
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_FWD_PB(N)                                                                                            \
-  hipLaunchKernelGGL(gru_fwd_persist_bf16_kernel<N>, dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, b_hh, s_rep, Hc, \
-                     gx, s_gx, hs, s_hs, (__bf16*)hb, s_hb, (__bf16*)hx, s_hx, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, Bc, B, H, T, sg0, n_sg,    \
-                     sync, base, spin_limit, pl.tickets, pl.ticket_base, pl.per_xcd)
+#define HPSGD_FWD_PB(N, EX)                                                                                        \
+  do {                                                                                                             \
+    static size_t allowed = 0;                                                                                     \
+    const hipError_t e = allow_lds((const void*)gru_fwd_persist_bf16_kernel<N, EX>, pl.lds, allowed);              \
+    if (e != hipSuccess) return e;                                                                                 \
+    hipLaunchKernelGGL((gru_fwd_persist_bf16_kernel<N, EX>), dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, \
+                       b_hh, s_rep, Hc, gx, s_gx, hs, s_hs, (__bf16*)hb, s_hb, (__bf16*)hx, s_hx, sv, s_sv, (__bf16*)hT, ld_hT, \
+                       s_hT, Bc, B, H, T, sg0, n_sg, sync, base, spin_limit, pl.tickets, pl.ticket_base, pl.per_xcd);  \
+  } while (0)
   const int NJ = H / QJ, SG = groups * ((B + PR - 1) / PR), per = groups_per_launch(NJ, SG);
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
     const Placement pl = placement(sync, SG, n_sg, NJ, lds, device_scope, ticket_launches);
-    if (ncf == 1) HPSGD_FWD_PB(1);
-    else if (ncf == 2) HPSGD_FWD_PB(2);
-    else HPSGD_FWD_PB(4);
+    if (ncf == 1 && exact) HPSGD_FWD_PB(1, true);
+    else if (ncf == 1) HPSGD_FWD_PB(1, false);
+    else if (ncf == 2 && exact) HPSGD_FWD_PB(2, true);
+    else if (ncf == 2) HPSGD_FWD_PB(2, false);
+    else if (exact) HPSGD_FWD_PB(4, true);
+    else HPSGD_FWD_PB(4, false);
   }
 #undef HPSGD_FWD_PB
   return hipGetLastError();

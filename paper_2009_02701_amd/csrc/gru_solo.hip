@@ -399,6 +399,8 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
 //   H           64    96   128   160   192   224   256
 //   forward   0.61  0.78  1.01  1.55  1.77  2.28  2.40 us
 //   backward  0.63  0.99  1.09  1.33  1.79  2.12  2.51 us
+// (gates of the hardware's exp2 and reciprocal; a forward step with those of the fp32 launches, EX, takes 0.4 us
+// more at 224 units)
 // against 3.3 and 3.5 us of the resident-weight launches, whose workgroups exchange h through L2, at all of
 // these widths; 256 is as far as one CU's registers and LDS hold the weights.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -425,7 +427,7 @@ struct SoloB {
   static constexpr size_t BWD_LDS = (size_t)2 * 8 * LP4 * 2 + (size_t)HB * NCL * 1024;
 };
 
-template <int HB, int UB>
+template <int HB, int UB, bool EX>
 __global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih, const float* __restrict__ b_hh,
                          long s_rep, int Hc, const float* __restrict__ gx, long s_gx, __bf16* __restrict__ hb, long s_hb,
@@ -529,9 +531,9 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
     for (int u = 0; u < UB; ++u) {
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
-        rr[u][v] = sigm_fast(G[u][0][v] + acc[u][0][v]);
-        zz[u][v] = sigm_fast(G[u][1][v] + acc[u][1][v]);
-        nn[u][v] = tanh_fast((G[u][2][v] + bx[u]) + rr[u][v] * acc[u][2][v]);
+        rr[u][v] = sigm_of<EX>(G[u][0][v] + acc[u][0][v]);
+        zz[u][v] = sigm_of<EX>(G[u][1][v] + acc[u][1][v]);
+        nn[u][v] = tanh_of<EX>((G[u][2][v] + bx[u]) + rr[u][v] * acc[u][2][v]);
         // Rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model
         // times their zero operands is NaN, which their h and gate gradients would hand to everyone.
         if (r0 + 2 * lg + v >= Bc || (w * UB + u) * 16 + lr >= Hc) rr[u][v] = zz[u][v] = nn[u][v] = acc[u][2][v] = 0.f;
@@ -734,28 +736,35 @@ int gru_solo_bf16_row_tiles(int B) { return B / kSoloBRows; }
 
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, hipStream_t s) {
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, bool exact,
+                                    hipStream_t s) {
   if (!gru_solo_bf16_supported(B, H) || T < 1 || Hc < 1 || Hc > H || Bc < 1 || Bc > B || (ld_hT & 1) != 0 || (s_hT & 1) != 0 ||
       (long)H * ld_hT * 2 >= 0x7fffffe0L)
     return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
   const int RT = gru_solo_bf16_row_tiles(B);
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_SOLOB_FWD(HB, UB)                                                                                       \
+#define HPSGD_SOLOB_FWD_EX(HB, UB, EX)                                                                                \
   do {                                                                                                                \
     using S = SoloB<HB, UB>;                                                                                          \
     static bool ready = false;                                                                                        \
     if (!ready) {                                                                                                     \
-      const hipError_t e = hipFuncSetAttribute((const void*)gru_solo_fwd_bf16_kernel<HB, UB>,                         \
+      const hipError_t e = hipFuncSetAttribute((const void*)gru_solo_fwd_bf16_kernel<HB, UB, EX>,                     \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::FWD_LDS);          \
       if (e != hipSuccess) return e;                                                                                  \
       ready = true;                                                                                                   \
     }                                                                                                                 \
-    hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s, (const __bf16*)Wb, \
-                       s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, (__bf16*)hT, ld_hT, s_hT, Bc, B, \
-                       T, RT);                                                                                        \
+    hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB, EX>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s,         \
+                       (const __bf16*)Wb, s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, \
+                       (__bf16*)hT, ld_hT, s_hT, Bc, B, T, RT);                                                       \
+  } while (0)
+#define HPSGD_SOLOB_FWD(HB, UB)                    \
+  do {                                             \
+    if (exact) HPSGD_SOLOB_FWD_EX(HB, UB, true);   \
+    else HPSGD_SOLOB_FWD_EX(HB, UB, false);        \
   } while (0)
   HPSGD_SOLOB_CASES(HPSGD_SOLOB_FWD)
+#undef HPSGD_SOLOB_FWD_EX
 #undef HPSGD_SOLOB_FWD
   return hipGetLastError();
 }

@@ -811,6 +811,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // (the padded layout of a language model has them by construction)
     const bool use_persist_b = bf && c->resident && gru_persist_bf16_supported(B, H) && ntc && width0 % 8 == 0;
     const bool use_solo_b = pad && c->solo_b;  // (a kind of use_persist_b without the exchange)
+    const bool exact_gates = gru_bf16_exact_gates(B, H, c->K, B != Bc || H != Hc || width0 != Ec);
     const bool exchange = use_persist || (use_persist_b && !use_solo_b);
     unsigned* psync = exchange ? (unsigned*)reg(c->psync) : nullptr;
     // the abort words of all workers of this step, cleared whether it exchanges or not: what is reported is this
@@ -1007,12 +1008,12 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_solo_fwd_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx,
-                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, s));
+                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, exact_gates, s));
         ++c->last_resident;
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_fwd_persist_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx, hs, s_hs, hb, s_hb,
-                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups,
+                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, exact_gates,
                                             psync, pbase, c->spin_limit, c->device_scope, &ticket_launches, s));
         pbase += (unsigned)T * gru_persist_bf16_count_per_step(H);
         ++c->last_resident;

@@ -218,7 +218,8 @@ bool gru_solo_bf16_supported(int B, int H);
 int gru_solo_bf16_row_tiles(int B);
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, hipStream_t s);
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, bool exact,
+                                    hipStream_t s);
 hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* above, long s_above, const float* sv, long s_sv,
                                     const float* hs, long s_hs, void* dg4, long s_dg4, float* dbp, int Hc, int B, int H, int T,
                                     int groups, hipStream_t s);
@@ -300,12 +301,14 @@ hipError_t launch_reduce_parts(const float* parts, int n_parts, size_t n, const 
 // beyond Bc the forward launch leaves zeros, whatever their input projections are.  b_ih is added by the forward launch.
 // More workgroups than the chip has CUs are issued as several launches of whole synchronisation groups.
 bool gru_persist_bf16_supported(int B, int H);
+// whether the bf16 forward launches compute a model's gates as the fp32 ones do (their argument `exact`)
+bool gru_bf16_exact_gates(int B, int H, int K, bool padded);
 unsigned gru_persist_bf16_count_per_step(int H);
 hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc, const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
                                        float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
-                                       int groups, unsigned* sync, unsigned base, unsigned spin_limit, bool device_scope,
-                                       unsigned* ticket_launches, hipStream_t s);
+                                       int groups, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
+                                       bool device_scope, unsigned* ticket_launches, hipStream_t s);
 // bf16 elements of one time step's block of an exchange buffer whose rows are `width` wide
 size_t gru_persist_bf16_exchange_elems(int B, int width);
 hipError_t launch_gru_bwd_persist_bf16(const void* WT, long s_wt, void* dghx, long s_dgh, long s_dgb, float* D, long s_D,
