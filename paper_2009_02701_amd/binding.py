@@ -319,13 +319,18 @@ class PtrList:
     def of_rows(cls, t, n):
         """The first n rows of a 2-D tensor, without a view of each."""
         self = cls.__new__(cls)
-        step, base = t.stride(0) * t.element_size(), t.data_ptr()
         self.tensors = t
-        self.array = _array_type(n)(*[base + k * step for k in range(n)])
+        self.array = _array_type(n)(*row_ptrs(t, n))
         return self
 
     def __len__(self):
         return len(self.array)
+
+
+def row_ptrs(t, n):
+    """Addresses of the first n rows of a tensor."""
+    step, base = t.stride(0) * t.element_size(), t.data_ptr()
+    return [base + k * step for k in range(n)]
 
 
 _ARRAY_TYPES = {}
@@ -400,23 +405,43 @@ def gather_batch_all(shards, idxs, n_chunks, chunk_elems, outs, row_elems=None, 
            "hpsgd_gather_batch_all")
 
 
+class GatherArgs:
+    """The host arrays of hpsgd_gather_batches for K workers, to be filled before each call.  sizes: up to two
+    (row_elems, n_chunks, chunk_elems) of 4-byte elements."""
+
+    def __init__(self, K, sizes):
+        self.idx = _array_type(K)()
+        self.arrays = [(_array_type(K)(), _array_type(K)()) for _ in sizes]
+        self.parts = (GatherPart * len(sizes))()
+        for q, (row, n_chunks, chunk), (sh, out) in zip(self.parts, sizes, self.arrays):
+            q.shards, q.outs = C.cast(sh, C.POINTER(C.c_void_p)), C.cast(out, C.POINTER(C.c_void_p))
+            q.row_bytes, q.n_chunks, q.chunk_bytes = 4 * row, n_chunks, 4 * chunk
+
+    def fill(self, parts, idx):
+        """parts: (shards, outs) per array, and idx: lists of K addresses each."""
+        self.idx[:] = idx
+        for (sh, out), p in zip(self.arrays, parts):
+            sh[:], out[:] = p
+
+    def run(self, n_idx, stream=None):
+        _check(load_library().hpsgd_gather_batches(self.parts, len(self.parts), self.idx, len(self.idx), n_idx,
+                                                   _stream(stream)), "hpsgd_gather_batches")
+
+
 class GatherPlan:
-    """The argument lists of hpsgd_gather_batches, made once for a mini-batch whose shards, index slice and output
-    buffers stay where they are.  parts: up to two (shards, outs, row_elems, n_chunks, chunk_elems) of 4-byte
-    elements, lists of K tensors each."""
+    """The arguments of hpsgd_gather_batches, filled once for a mini-batch whose shards, index slice and output
+    buffers stay where they are (and are kept alive here).  parts: up to two (shards, outs, row_elems, n_chunks,
+    chunk_elems), lists of K tensors each."""
 
     def __init__(self, parts, idxs):
-        self.idx = PtrList(idxs)
+        self.keep = parts, idxs
         self.n_idx = idxs[0].numel()
-        self.keep = [(PtrList(p[0]), PtrList(p[1])) for p in parts]
-        self.parts = (GatherPart * len(parts))()
-        for q, p, (sh, out) in zip(self.parts, parts, self.keep):
-            q.shards, q.outs = C.cast(sh.array, C.POINTER(C.c_void_p)), C.cast(out.array, C.POINTER(C.c_void_p))
-            q.row_bytes, q.n_chunks, q.chunk_bytes = 4 * p[2], p[3], 4 * p[4]
+        self.args = GatherArgs(len(idxs), [p[2:] for p in parts])
+        self.args.fill([([x.data_ptr() for x in p[0]], [x.data_ptr() for x in p[1]]) for p in parts],
+                       [i.data_ptr() for i in idxs])
 
     def run(self, stream=None):
-        _check(load_library().hpsgd_gather_batches(self.parts, len(self.parts), self.idx.array, len(self.idx), self.n_idx,
-                                                   _stream(stream)), "hpsgd_gather_batches")
+        self.args.run(self.n_idx, stream)
 
 
 def probe_mfma_rate(prec, operands, iterations, result, sink, stream=None):

@@ -71,8 +71,15 @@ class Trainer:
             T = cfg["seq_len"]
             self.xb = torch.zeros(K, T, B, dtype=torch.int32, device=dev)
             self.yb = torch.zeros(K, T, B, dtype=torch.int32, device=dev)
-        # gather arguments of each mini-batch of a shard, made once (and again if a buffer is replaced or moves)
-        self._gathers, self._gather_src = {}, None
+        # the gather's argument arrays; every call writes the addresses into them.  A language model's sample is
+        # T + 1 tokens: inputs and, one token later, targets
+        if kind == "gru_cls":
+            sizes = [(T * I, T, I), (1, 1, 1)]
+        elif kind == "mlp":
+            sizes = [(cfg["dims"][0], 1, cfg["dims"][0]), (1, 1, 1)]
+        else:
+            sizes = [(T + 1, T, 1), (T + 1, T, 1)]
+        self._gather = hb.GatherArgs(K, sizes)
         self.stream_a = torch.cuda.Stream(device=dev)
         self.stream_b = torch.cuda.Stream(device=dev)
         # third stream: weight-gradient GEMMs beside the BPTT recurrence, inside a local step
@@ -83,16 +90,13 @@ class Trainer:
     # ------------------------------------------------------------------ pieces
     def gather(self, step: int, stream=None):
         """Assemble every worker's mini-batch `step` from its resident shard (bit-exact)."""
-        s = step % self.n_batches
-        # (addresses, not objects: a tensor may be given other memory under the same name)
-        bufs = [self.xb, self.yb, *self.xs, *(t for t in self.ys if t is not None), *self.order]
-        src = [t.data_ptr() for t in bufs] + [t.numel() for t in bufs]
-        if src != self._gather_src:
-            self._gathers, self._gather_src = {}, src
-        plan = self._gathers.get(s)
-        if plan is None:
-            plan = self._gathers[s] = self._gather_plan(s)
-        plan.run(stream)
+        K, B = self.K, self.cfg["batch"]
+        first = step % self.n_batches * B
+        xs = [x.data_ptr() for x in self.xs[:K]]
+        ys = [p + 4 for p in xs] if self.kind == "gru_lm" else [y.data_ptr() for y in self.ys[:K]]
+        self._gather.fill([(xs, hb.row_ptrs(self.xb, K)), (ys, hb.row_ptrs(self.yb, K))],
+                          [o.data_ptr() + 4 * first for o in self.order[:K]])
+        self._gather.run(max(0, min(B, self.order[0].numel() - first)), stream)
 
     def _flat(self, t):
         """The P parameters of a flat buffer (global model, snapshot)."""
@@ -101,22 +105,6 @@ class Trainer:
     def _rows(self, gen):
         """Pointers to the K replicas of generation `gen`."""
         return hb.PtrList.of_rows(self.R[gen], self.K)
-
-    def _gather_plan(self, s):
-        cfg, B, K = self.cfg, self.cfg["batch"], self.K
-        idx = [self.order[k][s * B:(s + 1) * B] for k in range(K)]
-        xb, yb = list(self.xb), list(self.yb)
-        if self.kind == "gru_cls":
-            T, I = cfg["seq_len"], cfg["input"]
-            parts = [(self.xs, xb, T * I, T, I), (self.ys, yb, 1, 1, 1)]
-        elif self.kind == "mlp":
-            d0 = cfg["dims"][0]
-            parts = [(self.xs, xb, d0, 1, d0), (self.ys, yb, 1, 1, 1)]
-        else:  # a sample is T + 1 tokens: inputs and, one token later, targets
-            T = cfg["seq_len"]
-            tok = [x.view(-1) for x in self.xs]
-            parts = [(tok, xb, T + 1, T, 1), ([t[1:] for t in tok], yb, T + 1, T, 1)]
-        return hb.GatherPlan(parts, idx)
 
     def local_step_cloned(self, gen: int, lr: float, stream=None, ws=0):
         """The local step of generation `gen` whose replicas are still clones of its snapshot."""
