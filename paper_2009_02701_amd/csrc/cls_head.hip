@@ -204,13 +204,8 @@ hipError_t launch_cls_head(const float* feats, long s_feats, const float* W_in, 
   const size_t lds = (size_t)cpad * H * sizeof(float);
 #define HPSGD_HEAD_FWD(CP)                                                                                         \
   do {                                                                                                             \
-    static size_t allowed = 0;                                                                                     \
-    if (lds > allowed && lds > 64 * 1024) {                                                                        \
-      hipError_t e_ = hipFuncSetAttribute((const void*)cls_head_fwd_kernel<CP>,                                    \
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                  \
-      if (e_ != hipSuccess) return e_;                                                                             \
-      allowed = lds;                                                                                               \
-    }                                                                                                              \
+    static std::atomic<size_t> allowed{64 * 1024};                                                                 \
+    if (const hipError_t e_ = allow_lds((const void*)cls_head_fwd_kernel<CP>, lds, allowed)) return e_;            \
     hipLaunchKernelGGL(cls_head_fwd_kernel<CP>, dim3((N + HROWS - 1) / HROWS, groups), dim3(256), lds, s, feats,   \
                        s_feats, W_in, b_in, s_in, y, s_y, dlog, s_dlog, rowloss, s_rowloss, N, C, H);               \
   } while (0)

@@ -658,13 +658,8 @@ gemm_bf16_dlx_pair_kernel(GemmNtDesc d0, GemmNtDesc d1, unsigned blocks0) {
 template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED>
 hipError_t launch_dlx_form(const GemmNtDesc& d, hipStream_t s) {
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
-  static bool ready = false;
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)Sh::LDS);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};
+  if (const hipError_t e = allow_lds((const void*)gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED>, Sh::LDS, allowed)) return e;
   const int tm = (d.M + Sh::BM - 1) / Sh::BM, tn = (d.N + Sh::BN - 1) / Sh::BN;
   const int total = tm * tn * d.groups * (d.splits > 1 ? d.splits : 1);
   const int kid = (TM == 2 ? KID_GEMM_BF16_DLX128 : TM == 3 ? KID_GEMM_BF16_DLX192 : KID_GEMM_BF16_DLX256) + (COMMIT ? 1 : 0);
@@ -701,13 +696,8 @@ bool gemm_bf16_update_pair_supported(const GemmBf16Args& p0, const GemmBf16Args&
 template <bool GATED>
 static hipError_t launch_pair_form(const GemmNtDesc& d0, const GemmNtDesc& d1, hipStream_t s) {
   using Sh = DlxShape<2, 4, 3, 2, 2>;
-  static bool ready = false;
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_dlx_pair_kernel<true, 2, 4, 3, 2, 2, GATED>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)Sh::LDS);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};
+  if (const hipError_t e = allow_lds((const void*)gemm_bf16_dlx_pair_kernel<true, 2, 4, 3, 2, 2, GATED>, Sh::LDS, allowed)) return e;
   auto blocks = [](const GemmNtDesc& d) {
     const long total = (long)((d.M + Sh::BM - 1) / Sh::BM) * ((d.N + Sh::BN - 1) / Sh::BN) * d.groups;
     return (unsigned)(8 * ((total + 7) / 8));
@@ -767,13 +757,8 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
   const double flops = 2.0 * M * N * (double)(splits > 1 ? Kall : Kd) * groups;
 #define HPSGD_NT1(TA, TB, CM)                                                                     \
   do {                                                                                            \
-    static bool ready = false; /* per instantiation: allow the large dynamic LDS allocation */    \
-    if (!ready) {                                                                                 \
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_nt_kernel<TA, TB, CM>,            \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);  \
-      if (e != hipSuccess) return e;                                                              \
-      ready = true;                                                                               \
-    }                                                                                             \
+    static std::atomic<size_t> allowed{0};  /* per instantiation: allow the large dynamic LDS allocation */           \
+    if (const hipError_t e = allow_lds((const void*)gemm_bf16_nt_kernel<TA, TB, CM>, smem, allowed)) return e;        \
     KernelTimer kt(KID_GEMM_BF16_NT, flops, s);                                                   \
     hipLaunchKernelGGL((gemm_bf16_nt_kernel<TA, TB, CM>), grid, block, smem, s, d);               \
   } while (0)
@@ -786,13 +771,8 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
     constexpr size_t dl_smem = (size_t)NBM * (NBN + 4) * sizeof(float);  // the epilogue tile; operands need 64 KB
 #define HPSGD_DL(CM, GA)                                                                              \
   do {                                                                                            \
-    static bool ready = false;                                                                    \
-    if (!ready) {                                                                                 \
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_dl_kernel<CM, GA>,                    \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)dl_smem); \
-      if (e != hipSuccess) return e;                                                              \
-      ready = true;                                                                               \
-    }                                                                                             \
+    static std::atomic<size_t> allowed{0};                                                                            \
+    if (const hipError_t e = allow_lds((const void*)gemm_bf16_dl_kernel<CM, GA>, dl_smem, allowed)) return e;         \
     KernelTimer kt(CM ? KID_GEMM_BF16_DL_COMMIT : KID_GEMM_BF16_DL, flops, s);                    \
     hipLaunchKernelGGL((gemm_bf16_dl_kernel<CM, GA>), grid, block, dl_smem, s, d);                    \
   } while (0)

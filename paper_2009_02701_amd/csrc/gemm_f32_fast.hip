@@ -364,13 +364,8 @@ static hipError_t launch_fast_cfg(const GemmDesc& d, hipStream_t s) {
   using OpA = FastOperand<BM, !TA, RAG>;
   using OpB = FastOperand<BN, TB, RAG>;
   constexpr size_t smem = (size_t)2 * (OpA::LDS_FLOATS + OpB::LDS_FLOATS) * sizeof(float);
-  static bool ready = false;  // per instantiation: allow dynamic LDS above 64 KB
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_f32_fast_kernel<BM, BN, TA, TB, RAG>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};  // per instantiation: allow dynamic LDS above 64 KB
+  if (const hipError_t e = allow_lds((const void*)gemm_f32_fast_kernel<BM, BN, TA, TB, RAG>, smem, allowed)) return e;
   const long ntiles = (long)((d.N + BN - 1) / BN) * ((d.M + BM - 1) / BM) * d.groups * (d.splits > 1 ? d.splits : 1);
   dim3 grid((unsigned)(8 * ((ntiles + 7) / 8)));
   KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);

@@ -290,13 +290,8 @@ static hipError_t launch_fwd_rb(const float* W_hh, const float* b_hh, long s_rep
                                 int H, int groups, hipStream_t s) {
   constexpr size_t slabs = 2 * (48 + 16 * RB) * (W + 4), redn = 4 * 3 * RB * 4 * 64;
   constexpr size_t lds = (slabs > redn ? slabs : redn) * sizeof(float);
-  static bool ready = false;  // allow the dynamic LDS allocation above 64 KB once
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gru_fwd_step_kernel<RB, NW, W>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};  // allow the dynamic LDS allocation above 64 KB once
+  if (const hipError_t e = allow_lds((const void*)gru_fwd_step_kernel<RB, NW, W>, lds, allowed)) return e;
   dim3 grid((H / FJ) * ((B + 16 * RB - 1) / (16 * RB)) * groups);
   KernelTimer kt(KID_GRU_STEP, 2.0 * B * 3 * H * (double)H * groups, s);
   hipLaunchKernelGGL((gru_fwd_step_kernel<RB, NW, W>), grid, dim3(64 * NW), lds, s, W_hh, b_hh, s_rep, gx_t, s_gx, h_prev,
@@ -402,13 +397,8 @@ static hipError_t launch_bwd_rb(const float* WT, long s_wt, const float* dgh_nex
                                 int groups, hipStream_t s) {
   constexpr size_t slabs = 2 * (16 + 16 * RB) * (W + 4), redn = 4 * RB * 4 * 64;
   constexpr size_t lds = (slabs > redn ? slabs : redn) * sizeof(float);
-  static bool ready = false;  // allow the dynamic LDS allocation above 64 KB once
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gru_bwd_step_kernel<RB, NW, W>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};  // allow the dynamic LDS allocation above 64 KB once
+  if (const hipError_t e = allow_lds((const void*)gru_bwd_step_kernel<RB, NW, W>, lds, allowed)) return e;
   dim3 grid((H / FJ) * ((B + 16 * RB - 1) / (16 * RB)) * groups);
   KernelTimer kt(KID_GRU_STEP, 2.0 * B * 3 * H * (double)H * groups, s);
   hipLaunchKernelGGL((gru_bwd_step_kernel<RB, NW, W>), grid, dim3(64 * NW), lds, s, WT, s_wt, dgh_next, s_dg, D, s_D, above,
@@ -527,13 +517,8 @@ hipError_t launch_gru_fwd_step_bf16(const void* Wb, long s_wb, const float* b_hh
                                     long s_hs, const void* hb_prev, void* hb_out, long s_hb, float* sv_t,
                                     long s_sv, void* hT_out, long ld_hT, long s_hT, int B, int H,
                                     int groups, hipStream_t s) {
-  static bool ready = false;  // allow the dynamic LDS allocation above 64 KB once
-  if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)gru_fwd_step_bf16_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFwdBf16Lds);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
+  static std::atomic<size_t> allowed{0};  // allow the dynamic LDS allocation above 64 KB once
+  if (const hipError_t e = allow_lds((const void*)gru_fwd_step_bf16_kernel, kFwdBf16Lds, allowed)) return e;
   dim3 grid((H / FJ) * ((B + FR - 1) / FR) * groups);
   KernelTimer kt(KID_GRU_STEP, 2.0 * B * 3 * H * (double)H * groups, s);
   hipLaunchKernelGGL(gru_fwd_step_bf16_kernel, grid, dim3(256), kFwdBf16Lds, s, (const __bf16*)Wb, s_wb,

@@ -1206,13 +1206,6 @@ size_t persist_xp_lds_bytes(int H, int width) {
          sizeof(float);
 }
 
-hipError_t allow_lds(const void* fn, size_t lds, size_t& allowed) {
-  if (lds <= allowed) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e == hipSuccess) allowed = lds;
-  return e;
-}
-
 }  // namespace
 
 // Batch rows per workgroup for a layer of K workers, or 0 if the resident slice plus the partial sums do
@@ -1275,7 +1268,7 @@ hipError_t launch_gru_fwd_persist(const float* W_hh, const float* b_hh, long s_r
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * ((double)H + (xin ? width : 0)) * T * groups, s);
 #define HPSGD_FWD_PERSIST(N, R)                                                                                   \
   do {                                                                                                            \
-    static size_t allowed = 0;                                                                                    \
+    static std::atomic<size_t> allowed{0};                                                                                    \
     const hipError_t e = allow_lds((const void*)gru_fwd_persist_kernel<N, R>, pl.lds, allowed);                   \
     if (e != hipSuccess) return e;                                                                                \
     hipLaunchKernelGGL((gru_fwd_persist_kernel<N, R>), dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
@@ -1314,7 +1307,7 @@ hipError_t launch_gru_bwd_persist(const float* W_hh, long s_rep, float* dgh, flo
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * (dWp ? 2 : 1), s);
 #define HPSGD_BWD_PERSIST(R)                                                                                        \
   do {                                                                                                              \
-    static size_t allowed = 0;                                                                                      \
+    static std::atomic<size_t> allowed{0};                                                                                      \
     const hipError_t e = allow_lds((const void*)gru_bwd_persist_kernel<R>, pl.lds, allowed);                        \
     if (e != hipSuccess) return e;                                                                                  \
     hipLaunchKernelGGL(gru_bwd_persist_kernel<R>, dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, s_rep, dgh, dghx, s_dghx, dgx, \
@@ -1383,7 +1376,7 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
 #define HPSGD_FWD_PB(N, EX)                                                                                        \
   do {                                                                                                             \
-    static size_t allowed = 0;                                                                                     \
+    static std::atomic<size_t> allowed{0};                                                                                     \
     const hipError_t e = allow_lds((const void*)gru_fwd_persist_bf16_kernel<N, EX>, pl.lds, allowed);              \
     if (e != hipSuccess) return e;                                                                                 \
     hipLaunchKernelGGL((gru_fwd_persist_bf16_kernel<N, EX>), dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, \
@@ -1421,7 +1414,7 @@ hipError_t launch_gru_bwd_persist_bf16(const void* WT, long s_wt, void* dghx, lo
   const int ncf = H <= 256 ? 1 : H <= 512 ? 2 : 4;
   const int ncl = 3 * ncf - 3 * ncf / 2;
   const size_t lds = (size_t)8 * 4 * 256 * sizeof(float) + (size_t)4 * QJ * TP * 2 + (size_t)8 * ncl * 2 * 64 * 16 + 16;
-  static size_t allowed[3] = {0, 0, 0};
+  static std::atomic<size_t> allowed[3];
   const int slot = ncf == 1 ? 0 : ncf == 2 ? 1 : 2;
   const void* fn = ncf == 1   ? (const void*)gru_bwd_persist_bf16_kernel<3>
                    : ncf == 2 ? (const void*)gru_bwd_persist_bf16_kernel<6>

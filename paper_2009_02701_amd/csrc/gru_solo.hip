@@ -747,13 +747,8 @@ hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih
 #define HPSGD_SOLOB_FWD_EX(HB, UB, EX)                                                                                \
   do {                                                                                                                \
     using S = SoloB<HB, UB>;                                                                                          \
-    static bool ready = false;                                                                                        \
-    if (!ready) {                                                                                                     \
-      const hipError_t e = hipFuncSetAttribute((const void*)gru_solo_fwd_bf16_kernel<HB, UB, EX>,                     \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::FWD_LDS);          \
-      if (e != hipSuccess) return e;                                                                                  \
-      ready = true;                                                                                                   \
-    }                                                                                                                 \
+    static std::atomic<size_t> allowed{0};                                                                            \
+    if (const hipError_t e = allow_lds((const void*)gru_solo_fwd_bf16_kernel<HB, UB, EX>, S::FWD_LDS, allowed)) return e;\
     hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB, EX>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s,         \
                        (const __bf16*)Wb, s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, \
                        (__bf16*)hT, ld_hT, s_hT, Bc, B, T, RT);                                                       \
@@ -780,13 +775,8 @@ hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* abov
 #define HPSGD_SOLOB_BWD(HB, UB)                                                                                       \
   do {                                                                                                                \
     using S = SoloB<HB, UB>;                                                                                          \
-    static bool ready = false;                                                                                        \
-    if (!ready) {                                                                                                     \
-      const hipError_t e = hipFuncSetAttribute((const void*)gru_solo_bwd_bf16_kernel<HB, UB>,                         \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::BWD_LDS);          \
-      if (e != hipSuccess) return e;                                                                                  \
-      ready = true;                                                                                                   \
-    }                                                                                                                 \
+    static std::atomic<size_t> allowed{0};                                                                            \
+    if (const hipError_t e = allow_lds((const void*)gru_solo_bwd_bf16_kernel<HB, UB>, S::BWD_LDS, allowed)) return e; \
     hipLaunchKernelGGL((gru_solo_bwd_bf16_kernel<HB, UB>), dim3(groups * RT), dim3(S::NT), S::BWD_LDS, s, (const __bf16*)WT, \
                        s_wt, above, s_above, sv, s_sv, hs, s_hs, (__bf16*)dg4, s_dg4, dbp, Hc, B, T, RT);             \
   } while (0)

@@ -3,10 +3,24 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <atomic>
+#include <mutex>
 
 #define HPSGD_KMAX 32
 
 namespace hpsgd {
+
+// Allows kernel fn `lds` bytes of dynamic LDS.  `allowed` (one per kernel): what it may have already; any thread may
+// come first, and a smaller amount never replaces a larger one.
+inline hipError_t allow_lds(const void* fn, size_t lds, std::atomic<size_t>& allowed) {
+  if (lds <= allowed.load(std::memory_order_acquire)) return hipSuccess;
+  static std::mutex mu;
+  std::lock_guard<std::mutex> lock(mu);
+  if (lds <= allowed.load(std::memory_order_relaxed)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e == hipSuccess) allowed.store(lds, std::memory_order_release);
+  return e;
+}
 
 struct PtrPack {  // K device pointers passed by value as a kernel argument
   float* p[HPSGD_KMAX];
