@@ -414,7 +414,7 @@ class GatherArgs:
         self.arrays = [(_array_type(K)(), _array_type(K)()) for _ in sizes]
         self.parts = (GatherPart * len(sizes))()
         for q, (row, n_chunks, chunk), (sh, out) in zip(self.parts, sizes, self.arrays):
-            q.shards, q.outs = C.cast(sh, C.POINTER(C.c_void_p)), C.cast(out, C.POINTER(C.c_void_p))
+            q.shards, q.outs = sh, out  # (kept alive by parts; a cast would leave a reference cycle for each)
             q.row_bytes, q.n_chunks, q.chunk_bytes = 4 * row, n_chunks, 4 * chunk
 
     def fill(self, parts, idx):
