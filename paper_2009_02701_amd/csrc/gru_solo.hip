@@ -10,11 +10,12 @@
 // flag, no residency requirement and no ordering against other streams: any number of workgroups
 // may be launched.
 //
-// What bounds a step: the matrix work of 16 rows on one CU, 3 H H / 1024 instructions of 32 cycles
+// What bounds a step: the matrix work of 16 rows on one CU, 3 H H / 256 instructions of 32 cycles
 // per SIMD (H = 128: 2.6 us; H = 64: 0.64 us), then the cell math of a wave's 16 x 16 outputs, about
 // 0.3 us, which overlaps with the other wave's products where a SIMD has two.
-// Measured, all kernels of a round: the tiny configuration (H = 32, 8 steps, 2 workers) 158 -> 65 us; two layers
-// of H = 100, batch 20, 50 steps, 4 workers (one to four launches per step before) 2454 -> 770 us.
+// Measured, a whole round with and without these launches: the tiny configuration (H = 32, 8 steps, 2 workers)
+// 158 -> 65 us (50 with the launches that its other phases share); two layers of H = 100, batch 20, 50 steps,
+// 4 workers (one to four launches per step before) 2454 -> 764 us.
 //
 // v_mfma_f32_16x16x4_f32 lane layout: A lane l holds A[m = l%16][k = l/16], B lane l holds
 // B[k = l/16][n = l%16], accumulator register v holds C[4*(l/16) + v][l%16].  The contraction index is

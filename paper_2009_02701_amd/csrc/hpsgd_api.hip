@@ -28,7 +28,8 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // thousands: the parts run side by side, about three workgroups per CU over all K workers, and the
 // kernel that applies the update adds them in order.  A part is at least 128 long (four k-tiles: below
 // that a part is mostly first loads and epilogue), and 1 means the update stays in the epilogue.
-// Depends on the context's K, not on how many workers a call steps: the sums are the same either way.
+// Goes by the context's K, not by how many workers a call steps: the cuts of a context are always the same.  (Whether
+// dW_hh is cut at all may still depend on the call: where gru_persist_pays sends it to a launch per step.)
 int wgrad_splits(int M, int N, int Kd, int K) {
   const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64) * K;
   long n = (768 + tiles - 1) / tiles;
@@ -1076,7 +1077,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       // the head's bias gradient: column sums of the unrounded logit gradient, per block of rows
       // in the loss kernel, added up below
       // (the partial sums of the groups lie back to back, as the adding kernel reads them)
-      // (sized for all K workers also when fewer are stepped: the sums then do not depend on the entry point)
+      // (sized for all K workers also when fewer are stepped: these sums then do not depend on the entry point)
       const int n_colparts = softmax_ce_bf16_row_blocks(nrows, c->K, classes);
       const long colpitch = (long)round_up(classes, 8), s_colpart = (long)n_colparts * colpitch;
       HIP_TRY(launch_softmax_ce_bf16(logits, ldl, s_log, y, lm ? TBc : Bc, bfreg(c->dlogb), clp, s_dlb, rowloss,
