@@ -29,7 +29,7 @@ static inline int stream_blocks(size_t n_items) {
   return (int)b;
 }
 
-// The three kernels below are bound by HBM: 5.5 TB/s where as much is written as read, up to 6.4 where most of it
+// The merges and the clone below are bound by HBM: 5.5 TB/s where as much is written as read, up to 6.4 where most of it
 // is read.  What is left to choose is how many buffers are in flight at a time: V, the vectors of 256 lanes per
 // workgroup and buffer (4 KB x V contiguous), and UN, how far the loop over the replicas is unrolled (0: as far as the
 // compiler will), or KT > 0, their number, known when compiled.  Short runs of many buffers at once cost more in HBM than they hide once there are enough
@@ -37,12 +37,22 @@ static inline int stream_blocks(size_t n_items) {
 // once -> what is taken; replicas x parameters):
 //   merge          8 x 100M 752 -> 688, 12 x 50M 523 -> 455, 5 x 45M 244 -> 229, 16 x 20M 255 -> 230 (UN 2, V 4);
 //                  4 x 9M 41 (42.7), 7 x 7.5M 47.5 (52.8), 5 x 1M 8.5 (11.5) stay: the line is at 16M
+//                  (one replica keeps one vector: 90M 227 against 232, 60M 151 against 155)
 //   sync           8 x 100M 755 -> 722, 12 x 50M 602 -> 525, 5 x 45M 233 -> 224, 4 x 3M 12.0 -> 12.1 (UN 1, V 1)
 //   merge + clone  8 x 100M 1505 -> 1454, 5 x 45M 475 -> 439, 4 x 9M 82 -> 74, 5 x 1M 9.4 -> 8.4 (UN 4, V 2)
-//   merge + snapshot  8 x 100M 825 -> 779, 12 x 50M 588 -> 496, 5 x 45M 281 -> 259 (UN 2, V 4, from 16M on)
-// Below 2M parameters a launch is one trip to memory, and K known when compiled is the shortest one (merge + snapshot,
-// 5 x 1M: 7.1 -> 6.5, 12 x 800k 10.3 -> 9.2; merge + clone, 6 x 600k 8.3 -> 7.1).
+//   merge + snapshot  8 x 100M 825 -> 779, 12 x 50M 588 -> 496, 5 x 45M 281 -> 259 (UN 2, V 4, from 16M on;
+//                  two or three replicas keep one vector: 2 x 24M 92 against 96, 2 x 90M 341 against 357, 3 x 90M 407 against 417)
+// Where one vector and all replicas at once stays, K known when compiled is the shortest form (merge + snapshot,
+// 5 x 1M: 7.1 -> 6.5, 12 x 800k 10.3 -> 9.2, 5 x 2.2M 13.4 -> 11.6; merge, 5 x 2.2M 11.9 -> 9.9; merge + clone,
+// 6 x 600k 8.3 -> 7.1), with two exceptions where K is no power of two, that is, for loops that the compiler unrolls no
+// further than eight replicas: merge + clone from 32 MB of buffers on (6 x 1.2M 12.5 known, 11.8 not, 7 x 1.6M 20.2 and
+// 17.3, 12 x 1.2M 24.2 and 22.6; 5 x 900k 7.1 and 7.8), and the merge of gradients from 4M parameters on (6 x 13M 68.6
+// and 66.4, 5 x 5M 22.5 and 21.7; 6 x 2.2M 10.1 and 12.4, 5 x 3M 12.3 and 13.3).  The latter reads one buffer less and
+// from 16M on never wants K known (8 x 100M 687 and 649, 4 x 60M 235 and 229; below, 8 x 4.5M 27.9 and 30.1,
+// 16 x 9M 103 and 108).
 static constexpr size_t kManyVectors = (size_t)1 << 22, kFewVectors = (size_t)1 << 19;
+
+static inline bool power_of_two(int K) { return (K & (K - 1)) == 0; }
 
 #define HPSGD_K_CASES(M)                                                                          \
   switch (K) {                                                                                    \
@@ -130,8 +140,7 @@ hipError_t launch_merge(float* global, const PtrPack& replicas, const float* sna
   hipLaunchKernelGGL((merge_kernel<KT, UN, V>), dim3(onepass_blocks((n4 + V - 1) / V)), dim3(kThreads), 0, s, global, replicas, \
                      snapshot, K, inv_k, n4, P)
 #define HPSGD_MERGE_FEW(KT) HPSGD_MERGE(KT, 0, 1)
-  if (n4 >= kManyVectors) HPSGD_MERGE(0, 2, 4);
-  else if (n4 >= kFewVectors) HPSGD_MERGE(0, 0, 1);
+  if (n4 >= kManyVectors && K > 1) HPSGD_MERGE(0, 2, 4);
   else HPSGD_K_CASES(HPSGD_MERGE_FEW)
 #undef HPSGD_MERGE_FEW
 #undef HPSGD_MERGE
@@ -215,15 +224,13 @@ hipError_t launch_merge_sync(float* global, const PtrPack& replicas, float* snap
                      replicas, snapshot, K, inv_k, n4, P)
 #define HPSGD_MS_CLONE_FEW(KT) HPSGD_MS(true, KT, 0, 1)
 #define HPSGD_MS_SNAP_FEW(KT) HPSGD_MS(false, KT, 0, 1)
-  if (n4 < kFewVectors) {
-    if (clone) HPSGD_K_CASES(HPSGD_MS_CLONE_FEW)
-    else HPSGD_K_CASES(HPSGD_MS_SNAP_FEW)
-  } else if (clone) {
-    HPSGD_MS(true, 0, 4, 2);
-  } else if (n4 >= kManyVectors) {
-    HPSGD_MS(false, 0, 2, 4);
+  if (clone) {
+    if (n4 >= kFewVectors) HPSGD_MS(true, 0, 4, 2);
+    else if (!power_of_two(K) && (K + 2) * n4 >= (size_t)1 << 21) HPSGD_MS(true, 0, 0, 1);
+    else HPSGD_K_CASES(HPSGD_MS_CLONE_FEW)
   } else {
-    HPSGD_MS(false, 0, 0, 1);
+    if (n4 >= kManyVectors && K != 2 && K != 3) HPSGD_MS(false, 0, 2, 4);
+    else HPSGD_K_CASES(HPSGD_MS_SNAP_FEW)
   }
 #undef HPSGD_MS_SNAP_FEW
 #undef HPSGD_MS_CLONE_FEW
@@ -507,8 +514,11 @@ hipError_t launch_commit_acc(const float* in, size_t in_stride, float* out, size
 }
 
 // global[j] -= lr * (1/K) * sum_k acc_k[j], the sum in worker order (Eq. 1 as printed)
+// (KT: their number, known when compiled, 0: it is not)
+template <int KT>
 __global__ void __launch_bounds__(kThreads)
-merge_grad_kernel(float* global, PtrPack acc, int K, float scale, size_t n4, size_t P) {
+merge_grad_kernel(float* global, PtrPack acc, int Krt, float scale, size_t n4, size_t P) {
+  const int K = KT > 0 ? KT : Krt;
   const size_t stride = (size_t)gridDim.x * kThreads;
   for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n4; i += stride) {
     f4v t = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(acc.p[0]) + i);
@@ -532,7 +542,10 @@ hipError_t launch_merge_grad(float* global, const PtrPack& accs, float lr, int K
   const size_t n4 = P / 4;
   const int blocks = onepass_blocks(n4);
   const float scale = lr / (float)K;
-  hipLaunchKernelGGL(merge_grad_kernel, dim3(blocks), dim3(kThreads), 0, s, global, accs, K, scale, n4, P);
+#define HPSGD_MG(KT) hipLaunchKernelGGL(merge_grad_kernel<KT>, dim3(blocks), dim3(kThreads), 0, s, global, accs, K, scale, n4, P)
+  if (n4 >= (power_of_two(K) ? kManyVectors : (size_t)1 << 20)) HPSGD_MG(0);
+  else HPSGD_K_CASES(HPSGD_MG)
+#undef HPSGD_MG
   return hipGetLastError();
 }
 

@@ -222,6 +222,32 @@ def test_merge_sync_equals_merge_then_sync_bit_for_bit(P, K):
             assert np.array_equal(t, outs[1][0])   # replicas and snapshot are clones of the merged model
 
 
+# on both sides of the sizes from which other forms of the kernels are taken (2^19, 2^20 and 2^22 vectors; 32 MB of
+# buffers), a ragged tail each; K a power of two, another one, and beyond the compiled ones
+@pytest.mark.parametrize("P,K", [(932_063, 7), (932_071, 7), (2_097_149, 5), (2_097_157, 4), (4_194_301, 3), (4_194_309, 3),
+                                 (4_194_309, 8), (4_194_309, 17), (16_777_213, 2), (16_777_219, 2), (16_777_219, 1), (16_777_219, 4)])
+def test_every_form_of_the_merges(P, K):
+    """The four merges against the sum over the replicas in worker order, in 64 bits."""
+    g = torch.Generator(device=DEV).manual_seed(P + K)
+    G0, S0 = (torch.randn(P, device=DEV, generator=g) for _ in range(2))
+    R0 = [S0 + 1e-2 * torch.randn(P, device=DEV, generator=g) for _ in range(K)]
+    delta, grad = torch.zeros(P, dtype=torch.float64, device=DEV), torch.zeros(P, dtype=torch.float64, device=DEV)
+    for r in R0:
+        delta += r.double() - S0
+        grad += r.double()
+    # every one of the K + 2 sums and products is off by at most 2^-24 of what it holds: of values below `big`
+    big = float(G0.abs().max() + S0.abs().max() * K)
+    tol = (K + 2) * 2.0 ** -24 * big
+    for name in ("merge", "merge_snapshot", "merge_sync", "merge_grad"):
+        G, S, R = G0.clone(), S0.clone(), [r.clone() for r in R0]
+        hb.merge_grad(G, R, 0.5) if name == "merge_grad" else getattr(hb, name)(G, R, S)
+        want = G0.double() - 0.5 / K * grad if name == "merge_grad" else G0.double() + delta / K
+        assert float((G.double() - want).abs().max()) <= tol, name
+        assert torch.equal(S, G if name in ("merge_snapshot", "merge_sync") else S0), name
+        for r, r0 in zip(R, R0):
+            assert torch.equal(r, G if name == "merge_sync" else r0), name
+
+
 @pytest.mark.parametrize("P", [0, 1, 5, 4096, 1000003])
 @pytest.mark.parametrize("K", [1, 3, 8])
 def test_merge_snapshot_equals_merge_then_snapshot_bit_for_bit(P, K):
