@@ -4,30 +4,32 @@
 // then hand each other h_t (backward: the gate gradients) through memory at every step: 4 to 9 us per
 // step, whatever the width.  A layer of up to 128 units needs none of that: W_hh (196 KB at H = 128)
 // fits the registers of ONE compute unit, and batch rows are independent of each other.  So here a
-// workgroup owns up to 16 batch rows of one worker and ALL hidden units, and runs all T steps by
-// itself: wave w holds the weights of units 16w .. 16w+15 (3 gates x H, at most 96 registers per
-// lane) and h_t goes from step to step through LDS, one workgroup barrier per step.  There is no
-// flag, no residency requirement and no ordering against other streams: any number of workgroups
-// may be launched.
+// workgroup owns 4 batch rows of one worker (or 8: solo_two_tiles) and ALL hidden units, and runs all
+// T steps by itself.  There is no flag, no residency requirement and no ordering against other streams:
+// any number of workgroups may be launched.
 //
-// What bounds a step: the matrix work of 16 rows on one CU, 3 H H / 256 instructions of 32 cycles
-// per SIMD (H = 128: 2.6 us; H = 64: 0.64 us), then the cell math of a wave's 16 x 16 outputs, about
-// 0.3 us, which overlaps with the other wave's products where a SIMD has two.
-// Measured, a whole round with and without these launches: the tiny configuration (H = 32, 8 steps, 2 workers)
-// 158 -> 65 us (50 with the launches that its other phases share); two layers of H = 100, batch 20, 50 steps,
-// 4 workers (one to four launches per step before) 2454 -> 764 us.
+// The products are v_mfma_f32_4x4x1_16b_f32 with the first operand broadcast: one instruction of 8 cycles
+// multiplies 4 batch rows x 1 step of the contraction with 64 columns of weights, at the full fp32 matrix
+// rate and with no row unused, where a 16 x 16 x 4 instruction has 16 rows whatever the batch.  Lane l of a
+// weight register holds column l; block b = k % 16 of an operand register is lanes 4b .. 4b+3, one row
+// each (row l % 4); accumulator register v of lane l is row v of column l.
 //
-// v_mfma_f32_16x16x4_f32 lane layout: A lane l holds A[m = l%16][k = l/16], B lane l holds
-// B[k = l/16][n = l%16], accumulator register v holds C[4*(l/16) + v][l%16].  The contraction index is
-// taken in the order k = 16c + 4*(l/16) + e (c-th chunk, e-th instruction), so that a lane reads its
-// A values of four instructions as one 16-byte LDS word.  All three gates of a unit are accumulated by
-// the same lane: the cell math needs nothing of another lane.  Matrix row m = 4*lg + v is batch row
-// r0 + 4*v + lg: a tile of n rows fills ceil(n/4) of the four registers in every lane group, and
-// the cell math of the others is skipped.
+// The contraction is cut into 4 parts, one per wave (H > 64: the columns into 2 groups too, 8 waves).  A step:
+// operands from LDS, products, partial sums to LDS, barrier, cell math of one output per thread and tile
+// (a wave has one row and up to 64 neighbouring units: its accesses to memory are whole lines), results to
+// LDS, barrier.  Of a forward step of 1.05 us at H = 100, 0.43 us are the matrix instructions (65 per wave, two
+// waves per SIMD) and 0.1 the gates; the rest is four trips through LDS and two barriers.
 //
-// Any H from 1 to 128: units beyond H have zero weights and zero inputs, so h stays zero there.
-// Accesses outside the batch or beyond H carry an out-of-range buffer offset: loads give zero,
-// stores are dropped, and the step has no branch around a memory access.
+// Measured per step, forward / backward, against the form before it (16 x 16 x 4 instructions, 16 rows per
+// workgroup): H = 100 batch 20, K = 4: 3.5 / 3.3 -> 1.05 / 1.05 us (two layers of 50 steps 764 -> 308 us a round);
+// H = 64, batch 16, K = 1: 2.0 / 1.5 -> 0.8 / 0.6 us.  A local step of 20 time steps at H = 128, K = 16: batch 64
+// 290 -> 172 us, batch 128 356 -> 276 us.
+//
+// Any H from 1 to 128: contraction steps beyond H have zero weights and finite operands, columns beyond
+// 3H are not read.  Accesses outside the batch or beyond H carry an out-of-range buffer offset: loads
+// give zero, stores are dropped, and the step has no branch around a memory access.
+#include <utility>
+
 #include "cell_math.h"
 #include "kernels.h"
 
@@ -40,27 +42,56 @@ namespace {
 constexpr int kSoloMaxH = 128;
 constexpr unsigned kOut = 0x7ffffff0u;  // beyond every buffer's length
 
-struct SoloTiles {  // row tiles of a batch: RT tiles of `rows` rows (the last one may have fewer)
-  int RT, rows;
+inline int solo_tiles(int B) { return (B + 3) / 4; }
+
+// H8 = ceil(H / 8): extents of the launches for a width
+template <int H8>
+struct Solo {
+  static constexpr int CG = H8 > 8 ? 2 : 1;                          // column groups
+  static constexpr int NT = 256 * CG;                                // threads: a wave per column group and part
+  static constexpr int UP = 64 * CG;                                 // units, padded
+  // forward: contraction of a part; column blocks, all of them and those of the first group (its waves and the
+  // second group's of the same part share a SIMD, so an odd number is no loss)
+  static constexpr int KF = 2 * H8, NF = (24 * H8 + 63) / 64, CF = (NF + CG - 1) / CG;
+  static constexpr int KB = 6 * H8;                                  // backward: contraction of a part (one column block per wave)
+  // LDS words of a row of h, of gate gradients: the last part's operand chunk ends inside, 16 (mod 64), so that the
+  // four rows of a chunk are in different banks
+  static constexpr int pitch(int k) { return (3 * k + (k + 15) / 16 * 16 + 47) / 64 * 64 + 16; }
+  static constexpr int LF = pitch(KF) > UP ? pitch(KF) : UP + 16, LB = pitch(KB);
+  static constexpr int PF = 64 * NF, PB = UP;                        // words of a row of a part's sums
 };
-inline SoloTiles solo_tiles(int B) {
-  const int n = (B + 15) / 16;
-  const int rows = ((B + n - 1) / n + 3) / 4 * 4;  // spread evenly, in whole registers
-  return SoloTiles{(B + rows - 1) / rows, rows};
+
+template <class F, int... I>
+__device__ __forceinline__ void unroll_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
 }
+// f(0) .. f(N - 1) with the index a constant expression (the matrix instruction's block index is one)
+template <int N, class F>
+__device__ __forceinline__ void unroll(F&& f) {
+  unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Every load so far has landed: the compiler then puts no wait for them into the loop behind, where it would
+// also wait for the step's own loads and stores.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0), the other counts at their most
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const float* base, long words) {
   const long bytes = words * 4;
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(bytes < 0x7fffffe0L ? bytes : 0x7fffffe0L),
                                            0x00020000);
 }
-__device__ __forceinline__ float ld_b32(__amdgpu_buffer_rsrc_t rs, unsigned off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+__device__ __forceinline__ float ld_b32(__amdgpu_buffer_rsrc_t rs, unsigned off, int soff = 0) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, soff, 0));
 }
 __device__ __forceinline__ void st_b32(__amdgpu_buffer_rsrc_t rs, unsigned off, float v, int soff = 0) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, (int)off, soff, 0);
 }
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2s __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ floatx2 ld_b64(__amdgpu_buffer_rsrc_t rs, unsigned off) {
+  return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0));
+}
 __device__ __forceinline__ floatx4 ld_b128(__amdgpu_buffer_rsrc_t rs, unsigned off) {
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
 }
@@ -68,266 +99,292 @@ __device__ __forceinline__ void st_b128(__amdgpu_buffer_rsrc_t rs, unsigned off,
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4s, v), rs, (int)off, 0, 0);
 }
 
-// Saved gates: (r, z, n, q) of one output as one 16-byte word, in the order the backward launch's lanes
-// read them: [step][row tile][unit block][register v][lane].
-template <int HB>
-__device__ __forceinline__ long sv_block() { return (long)HB * 4 * 64 * 4; }
-
 }  // namespace
 
-// grid: groups * RT workgroups of HB waves (HB = ceil(H / 16)).  gx: input projections, b_ih included.
-// hs: h_0 .. h_T ((T+1) blocks of B x H; h_0 = 0 is written here).
-template <int HB>
-__global__ void __launch_bounds__(64 * HB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// grid: groups * ceil(RT / R) workgroups; RT = ceil(B / 4) tiles of 4 rows, R of them per workgroup.
+// gx: input projections, b_ih included.  hs: h_0 .. h_T ((T+1) blocks of B x H; h_0 = 0 is written here).
+// sv: (r, z, n, q) of one output as one 16-byte word, [step][tile][row][unit].
+template <int H8, int R>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
                     const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs, float* __restrict__ sv,
-                    long s_sv, int B, int H, int T, int RT, int rows) {
-  constexpr int HP = 16 * HB, LP = HP + 4;  // LDS pitch: an odd number of 16-byte words, no bank conflicts
-  __shared__ __attribute__((aligned(16))) float hb[2][16 * LP];
+                    long s_sv, int B, int H, int T, int RT) {
+  using S = Solo<H8>;
+  constexpr int KW = S::KF, CB = S::CF, NC = (KW + 15) / 16;
+  __shared__ float hl[R * 4 * S::LF];
+  __shared__ float part[R * 16 * S::PF];  // [tile][part][row][column]
   // (the wave's number in a scalar register: buffer descriptors derived from it stay scalar)
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT;
-  const int r0 = ty * rows, nrow = min(rows, B - r0), nv = (nrow + 3) >> 2;
-  const int j = 16 * w + lr;
-  const bool jok = j < H;
-  float wt[3][4 * HB];
+  const int s = w & 3, cg = w >> 2;  // part of the contraction, column group
+  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
+  // column c = q * H + unit of the products is row c of W_hh
+  float wt[CB][KW];
   {
     const __amdgpu_buffer_rsrc_t rw = rsrc_of(W_hh + g * s_rep, 3L * H * H);
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int cb = 0; cb < CB; ++cb) {
+      const int col = (cg * CB + cb) * 64 + lane;
+      if ((H & 1) == 0) {  // (whole 8-byte pieces of a row)
 #pragma unroll
-      for (int c = 0; c < HB; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = 16 * c + 4 * lg + e;
-          wt[q][4 * c + e] = ld_b32(rw, jok && k < H ? (unsigned)((q * H + j) * H + k) * 4u : kOut);
+        for (int i = 0; i < KW; i += 2) {
+          const int k = s * KW + i;
+          const floatx2 v = ld_b64(rw, col < 3 * H && k < H ? (unsigned)(col * H + k) * 4u : kOut);
+          wt[cb][i] = v[0];
+          wt[cb][i + 1] = v[1];
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+          const int k = s * KW + i;
+          wt[cb][i] = ld_b32(rw, col < 3 * H && k < H ? (unsigned)(col * H + k) * 4u : kOut);
+        }
+      }
+    }
   }
+  const int j = cg * 64 + lane, m = w & 3;  // this thread's unit and its row of a tile
+  const bool act = j < H;
   float bias[3];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) bias[q] = jok ? (b_hh + g * s_rep)[q * H + j] : 0.f;
-  // byte offsets of this lane's four outputs inside a step's block of gx and of hs
-  unsigned ox[4], oh[4];
-  float hp[4];
+  for (int q = 0; q < 3; ++q) bias[q] = act ? (b_hh + g * s_rep)[q * H + j] : 0.f;
+  // byte offsets of this thread's outputs inside a step's block of gx, of hs and of the saved gates
+  unsigned ox[R], oh[R], ov[R];
+  float hp[R];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int row = r0 + 4 * v + lg;
-    const bool ok = jok && 4 * v + lg < nrow;
-    ox[v] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
-    oh[v] = ok ? (unsigned)(row * H + j) * 4u : kOut;
-    hp[v] = 0.f;
+  for (int r = 0; r < R; ++r) {
+    const int row = 4 * (ty + r) + m;
+    const bool ok = act && row < B;
+    ox[r] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
+    oh[r] = ok ? (unsigned)(row * H + j) * 4u : kOut;
+    ov[r] = ok ? (unsigned)((4 * r + m) * H + j) * 16u : kOut;
+    hp[r] = 0.f;
   }
   const float* gxg = gx + g * s_gx;
   float* hsg = hs + g * s_hs;
-  float* svg = sv + g * s_sv + ((long)ty * HB + w) * 1024 + lane * 4;
-  const long sv_step = (long)RT * sv_block<HB>();
-  const long BH = (long)B * H;
+  float* svg = sv + g * s_sv + (long)ty * 16 * H;
+  const long sv_step = (long)RT * 16 * H, BH = (long)B * H;
   {
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(hsg, BH);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) st_b32(rs, oh[v], 0.f);
+    for (int r = 0; r < R; ++r) st_b32(rs, oh[r], 0.f);
   }
-  for (int i = tid; i < 16 * LP; i += 64 * HB) hb[0][i] = 0.f;
-  auto load_gx = [&](int t, float (&G)[3][4]) {
+  for (int i = tid; i < R * 4 * S::LF; i += S::NT) hl[i] = 0.f;
+  struct In { float x[R][3]; };
+  auto load_gx = [&](int t, In& I) {
     const __amdgpu_buffer_rsrc_t rs = rsrc_of(gxg + (long)min(t, T - 1) * 3 * BH, 3 * BH);
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) G[q][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)ox[v], q * H * 4, 0));
+      for (int q = 0; q < 3; ++q) I.x[r][q] = ld_b32(rs, ox[r], q * H * 4);
   };
-  float ga[3][4], gb[3][4];
-  load_gx(0, ga);
-  load_gx(1, gb);
+  In ia, ib;
+  load_gx(0, ia);
+  load_gx(1, ib);
+  wait_loads();
   __syncthreads();
-  // one step; G holds its input projection and receives the one of step t + 2
-  auto step = [&](int t, const float* hin, float* hout, float (&G)[3][4]) {
-    floatx4 acc[3];
+  // one step; I holds its input projection and receives the one of step t + 2
+  auto step = [&](int t, In& I) {
+    float a[R][NC];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[q] = (floatx4){bias[q], bias[q], bias[q], bias[q]};
-    floatx4 a[HB];
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int c = 0; c < HB; ++c) a[c] = *reinterpret_cast<const floatx4*>(&hin[lr * LP + 16 * c + 4 * lg]);
-    __builtin_amdgcn_sched_barrier(0);  // every LDS read is issued before the first product waits for one
+      for (int c = 0; c < NC; ++c) a[r][c] = hl[(4 * r + (lane & 3)) * S::LF + s * KW + 16 * c + (lane >> 2)];
+    auto products = [&](auto n) {
+      constexpr int N = n;
+      floatx4 acc[R][N];
 #pragma unroll
-    for (int c = 0; c < HB; ++c)
+      for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int cb = 0; cb < N; ++cb) acc[r][cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      unroll<KW>([&](auto k) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][e], wt[q][4 * c + e], acc[q], 0, 0, 0);
-    float rr[4], zz[4], nn[4];
+        for (int cb = 0; cb < N; ++cb)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      rr[v] = zz[v] = nn[v] = 0.f;
-      if (v < nv) {  // uniform
-        rr[v] = sigm_f32(G[0][v] + acc[0][v]);
-        zz[v] = sigm_f32(G[1][v] + acc[1][v]);
-        nn[v] = tanh_f32(G[2][v] + rr[v] * acc[2][v]);
-        hp[v] = (1.0f - zz[v]) * nn[v] + zz[v] * hp[v];
-        hout[(4 * lg + v) * LP + j] = hp[v];
+          for (int r = 0; r < R; ++r)
+            acc[r][cb] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[r][k / 16], wt[cb][k], acc[r][cb], 4, k % 16, 0);
+      });
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int cb = 0; cb < N; ++cb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) part[((4 * r + s) * 4 + v) * S::PF + (cg * CB + cb) * 64 + lane] = acc[r][cb][v];
+    };
+    if (cg == 0) products(std::integral_constant<int, CB>{});
+    else products(std::integral_constant<int, S::NF - CB>{});
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t ro = rsrc_of(hsg + (long)(t + 1) * BH, BH), rv = rsrc_of(svg + (long)t * sv_step, R * 16L * H);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float y[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const float* p = &part[(16 * r + m) * S::PF + min(q * H + j, S::PF - 1)];
+        y[q] = (p[0] + p[4 * S::PF]) + (p[8 * S::PF] + p[12 * S::PF]) + bias[q];
       }
+      const float rr = sigm_f32(I.x[r][0] + y[0]), zz = sigm_f32(I.x[r][1] + y[1]), nn = tanh_f32(I.x[r][2] + rr * y[2]);
+      hp[r] = (1.0f - zz) * nn + zz * hp[r];
+      hl[(4 * r + m) * S::LF + j] = act ? hp[r] : 0.f;
+      st_b32(ro, oh[r], hp[r]);
+      st_b128(rv, ov[r], (floatx4){rr, zz, nn, y[2]});
     }
-    load_gx(t + 2, G);
-    const __amdgpu_buffer_rsrc_t ro = rsrc_of(hsg + (long)(t + 1) * BH, BH);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) st_b32(ro, oh[v], hp[v]);
-    const __amdgpu_buffer_rsrc_t rv = rsrc_of(svg + (long)t * sv_step - lane * 4, 1024);
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      st_b128(rv, v < nv ? (unsigned)(v * 64 + lane) * 16u : kOut, (floatx4){rr[v], zz[v], nn[v], acc[2][v]});
+    load_gx(t + 2, I);
     __syncthreads();
   };
-  // (rows of hb[1] that no output lane writes are multiplied into outputs nobody stores; they must
-  // only be finite)
-  for (int i = tid; i < 16 * LP; i += 64 * HB) hb[1][i] = 0.f;
-  __syncthreads();
-  // the first of a SIMD's two waves goes ahead: its cell math then runs under the other's products
-  if (HB > 4 && w < 4) __builtin_amdgcn_s_setprio(2);
   int t = 0;
   for (; t + 1 < T; t += 2) {
-    step(t, hb[0], hb[1], ga);
-    step(t + 1, hb[1], hb[0], gb);
+    step(t, ia);
+    step(t + 1, ib);
   }
-  if (t < T) step(t, hb[0], hb[1], ga);
+  if (t < T) step(t, ia);
 }
 
 // BPTT of all steps.  dgx / dgh: gate gradients (blocks of B x 3H).  D: the gradient carried into the
 // last step (nullptr: zero); above: per-step gradient from the layer above (blocks of B x H) or
-// nullptr.  dbp[(g * RT + ty)][6H]: partial sums of the bias gradients (b_ih: r z n, b_hh: r z q).
-template <int HB>
-__global__ void __launch_bounds__(64 * HB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// nullptr.  dbp[(g * RT + tile)][6H]: partial sums of the bias gradients (b_ih: r z n, b_hh: r z q).
+template <int H8, int R>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx, float* __restrict__ dgh, long s_dg,
                     const float* __restrict__ D, long s_D, const float* __restrict__ above, long s_above,
                     const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
-                    int B, int H, int T, int RT, int rows) {
-  constexpr int HP = 16 * HB, LP = 3 * HP + 4;
-  __shared__ __attribute__((aligned(16))) float db[2][16 * LP];
-  // (the wave's number in a scalar register: buffer descriptors derived from it stay scalar)
+                    int B, int H, int T, int RT) {
+  using S = Solo<H8>;
+  constexpr int KW = S::KB, NC = (KW + 15) / 16;
+  __shared__ float dl[R * 4 * S::LB];
+  __shared__ float part[R * 16 * S::PB];  // [tile][part][row][unit]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT;
-  const int r0 = ty * rows, nrow = min(rows, B - r0);
-  const int j = 16 * w + lr;
-  const bool jok = j < H;
-  // B[k][n] = W_hh[q*H + k][j]: the transposed weights, 64-byte pieces of rows
-  float wt[3][4 * HB];
+  const int s = w & 3, cg = w >> 2;
+  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
+  // the contraction runs over the rows of W_hh, q * H + unit; column j is its column j
+  float wt[KW];
   {
     const __amdgpu_buffer_rsrc_t rw = rsrc_of(W_hh + g * s_rep, 3L * H * H);
+    const int col = cg * 64 + lane;
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int c = 0; c < HB; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = 16 * c + 4 * lg + e;
-          wt[q][4 * c + e] = ld_b32(rw, jok && k < H ? (unsigned)((q * H + k) * H + j) * 4u : kOut);
-        }
+    for (int i = 0; i < KW; ++i) {
+      const int k = s * KW + i;
+      wt[i] = ld_b32(rw, col < H && k < 3 * H ? (unsigned)(k * H + col) * 4u : kOut);
+    }
   }
-  unsigned ox[4], oh[4], ov[4];
-  float dc[4], bs[4] = {0.f, 0.f, 0.f, 0.f};
+  const int j = cg * 64 + lane, m = w & 3;
+  const bool act = j < H;
+  unsigned ox[R], oh[R], ov[R];
+  float dc[R], bs[R][4];
   const long BH = (long)B * H;
   const __amdgpu_buffer_rsrc_t rD = rsrc_of(D ? D + g * s_D : hs, D ? BH : 0);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int row = r0 + 4 * v + lg;
-    const bool ok = jok && 4 * v + lg < nrow;
-    ox[v] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
-    oh[v] = ok ? (unsigned)(row * H + j) * 4u : kOut;
-    ov[v] = ok ? (unsigned)(v * 64 + lane) * 16u : kOut;
-    dc[v] = ld_b32(rD, oh[v]);
+  for (int r = 0; r < R; ++r) {
+    const int row = 4 * (ty + r) + m;
+    const bool ok = act && row < B;
+    ox[r] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
+    oh[r] = ok ? (unsigned)(row * H + j) * 4u : kOut;
+    ov[r] = ok ? (unsigned)((4 * r + m) * H + j) * 16u : kOut;
+    dc[r] = ld_b32(rD, oh[r]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bs[r][i] = 0.f;
   }
   const float* hsg = hs + g * s_hs;
   const float* abg = above ? above + g * s_above : hs;
-  const float* svg = sv + g * s_sv + ((long)ty * HB + w) * 1024;
-  const long sv_step = (long)RT * sv_block<HB>();
-  struct In { floatx4 s[4]; float hp[4], ab[4]; };
+  const float* svg = sv + g * s_sv + (long)ty * 16 * H;
+  const long sv_step = (long)RT * 16 * H;
+  struct In { floatx4 s[R]; float hp[R], ab[R]; };
   auto load_in = [&](int t, In& I) {
     const int tc = max(t, 0);
-    const __amdgpu_buffer_rsrc_t rv = rsrc_of(svg + (long)tc * sv_step, 1024), rh = rsrc_of(hsg + (long)tc * BH, BH),
+    const __amdgpu_buffer_rsrc_t rv = rsrc_of(svg + (long)tc * sv_step, R * 16L * H), rh = rsrc_of(hsg + (long)tc * BH, BH),
                                  ra = rsrc_of(abg + (long)tc * BH, above ? BH : 0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      I.s[v] = ld_b128(rv, ov[v]);
-      I.hp[v] = ld_b32(rh, oh[v]);
-      I.ab[v] = ld_b32(ra, oh[v]);
+    for (int r = 0; r < R; ++r) {
+      I.s[r] = ld_b128(rv, ov[r]);
+      I.hp[r] = ld_b32(rh, oh[r]);
+      I.ab[r] = ld_b32(ra, oh[r]);
     }
   };
   In ia, ib;
   load_in(T - 1, ia);
   load_in(T - 2, ib);
-  for (int i = tid; i < 2 * 16 * LP; i += 64 * HB) db[0][i] = 0.f;  // (both buffers)
+  for (int i = tid; i < R * 4 * S::LB; i += S::NT) dl[i] = 0.f;
+  static_assert(S::LB > 24 * H8, "a word beyond the gate gradients of a row");
+  // where this thread's gate gradients go, r, z and q (a thread without an output: that word)
+  const int od = act ? j : S::LB - 1, oq = act ? H : 0;
+  wait_loads();
   __syncthreads();
-  auto step = [&](int t, const float* din, float* dout, In& I) {
-    floatx4 acc[3];
+  auto step = [&](int t, In& I) {
+    float a[R][NC];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int c = 0; c < HB; ++c) {
-      floatx4 a[3];
+      for (int c = 0; c < NC; ++c) a[r][c] = dl[(4 * r + (lane & 3)) * S::LB + s * KW + 16 * c + (lane >> 2)];
+    floatx4 acc[R][2];  // (two chains: an instruction does not wait for the one before it)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const floatx4*>(&din[lr * LP + q * HP + 16 * c + 4 * lg]);
+    for (int r = 0; r < R; ++r) acc[r][0] = acc[r][1] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    unroll<KW>([&](auto k) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int r = 0; r < R; ++r)
+        acc[r][k & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[r][k / 16], wt[k], acc[r][k & 1], 4, k % 16, 0);
+    });
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][e], wt[q][4 * c + e], acc[q], 0, 0, 0);
-    }
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[((4 * r + s) * 4 + v) * S::PB + cg * 64 + lane] = acc[r][0][v] + acc[r][1][v];
+    __syncthreads();
     const __amdgpu_buffer_rsrc_t rx = rsrc_of(dgx + g * s_dg + (long)t * 3 * BH, 3 * BH),
                                  rh = rsrc_of(dgh + g * s_dg + (long)t * 3 * BH, 3 * BH);
-    float da_r[4], da_z[4], da_n[4], dq[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      // (outside the batch or beyond H every input is zero, and so is every gradient)
-      const float r = I.s[v][0], z = I.s[v][1], n = I.s[v][2], q = I.s[v][3];
-      const float dh = (dc[v] + I.ab[v]) + (acc[0][v] + acc[1][v] + acc[2][v]);
+    for (int r = 0; r < R; ++r) {
+      // (outside the batch every input is zero, and so is every gradient)
+      const float* p = &part[(16 * r + m) * S::PB + j];
+      const float rr = I.s[r][0], z = I.s[r][1], n = I.s[r][2], q = I.s[r][3];
+      const float dh = (dc[r] + I.ab[r]) + ((p[0] + p[4 * S::PB]) + (p[8 * S::PB] + p[12 * S::PB]));
       const float dn = dh * (1.0f - z);
-      const float dz = dh * (I.hp[v] - n);
-      da_n[v] = dn * (1.0f - n * n);
-      dq[v] = da_n[v] * r;
-      da_r[v] = da_n[v] * q * r * (1.0f - r);
-      da_z[v] = dz * z * (1.0f - z);
-      dc[v] = dh * z;
-      float* o = &dout[(4 * lg + v) * LP + j];
-      o[0] = da_r[v];
-      o[HP] = da_z[v];
-      o[2 * HP] = dq[v];
-      bs[0] += da_r[v];
-      bs[1] += da_z[v];
-      bs[2] += da_n[v];
-      bs[3] += dq[v];
+      const float dz = dh * (I.hp[r] - n);
+      const float da_n = dn * (1.0f - n * n);
+      const float dq = da_n * rr;
+      const float da_r = da_n * q * rr * (1.0f - rr);
+      const float da_z = dz * z * (1.0f - z);
+      dc[r] = dh * z;
+      float* o = &dl[(4 * r + m) * S::LB + od];
+      o[0] = act ? da_r : 0.f;
+      o[oq] = act ? da_z : 0.f;
+      o[2 * oq] = act ? dq : 0.f;
+      bs[r][0] += da_r;
+      bs[r][1] += da_z;
+      bs[r][2] += da_n;
+      bs[r][3] += dq;
+      st_b32(rx, ox[r], da_r);
+      st_b32(rx, ox[r], da_z, H * 4);
+      st_b32(rx, ox[r], da_n, H * 8);
+      st_b32(rh, ox[r], da_r);
+      st_b32(rh, ox[r], da_z, H * 4);
+      st_b32(rh, ox[r], dq, H * 8);
     }
     load_in(t - 2, I);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      st_b32(rx, ox[v], da_r[v]);
-      st_b32(rx, ox[v], da_z[v], H * 4);
-      st_b32(rx, ox[v], da_n[v], H * 8);
-      st_b32(rh, ox[v], da_r[v]);
-      st_b32(rh, ox[v], da_z[v], H * 4);
-      st_b32(rh, ox[v], dq[v], H * 8);
-    }
     __syncthreads();
   };
-  if (HB > 4 && w < 4) __builtin_amdgcn_s_setprio(2);
   int t = T - 1;
   for (; t >= 1; t -= 2) {
-    step(t, db[0], db[1], ia);
-    step(t - 1, db[1], db[0], ib);
+    step(t, ia);
+    step(t - 1, ib);
   }
-  if (t >= 0) step(t, db[0], db[1], ia);
-  // bias gradients: the four lane groups hold disjoint rows
+  if (t >= 0) step(t, ia);
+  // bias gradients: a tile's sums over its four rows are its own, whatever R is
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    bs[i] += __shfl_xor(bs[i], 16);
-    bs[i] += __shfl_xor(bs[i], 32);
-  }
-  if (lg == 0 && jok) {
-    float* out = dbp + (long)(g * RT + ty) * 6 * H;
-    out[j] = out[3 * H + j] = bs[0];
-    out[H + j] = out[4 * H + j] = bs[1];
-    out[2 * H + j] = bs[2];
-    out[5 * H + j] = bs[3];
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part[((4 * r + i) * 4 + m) * S::PB + j] = bs[r][i];
+  __syncthreads();
+  if (m != 0 || !act) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (ty + r >= RT) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* p = &part[(4 * r + i) * 4 * S::PB + j];
+      bs[r][i] = (p[0] + p[S::PB]) + (p[2 * S::PB] + p[3 * S::PB]);
+    }
+    float* out = dbp + (long)(g * RT + ty + r) * 6 * H;
+    out[j] = out[3 * H + j] = bs[r][0];
+    out[H + j] = out[4 * H + j] = bs[r][1];
+    out[2 * H + j] = bs[r][2];
+    out[5 * H + j] = bs[r][3];
   }
 }
 
@@ -335,13 +392,11 @@ bool gru_solo_supported(int B, int H) {
   // (one step's block of gate gradients is addressed with 31-bit byte offsets)
   return H >= 1 && H <= kSoloMaxH && (long)B * 3 * H * 4 < 0x7fffffe0L;
 }
-int gru_solo_row_tiles(int B) { return solo_tiles(B).RT; }
-size_t gru_solo_saved_words(int B, int H, int T) {
-  return (size_t)T * solo_tiles(B).RT * ((H + 15) / 16) * 1024;
-}
+int gru_solo_row_tiles(int B) { return solo_tiles(B); }
+size_t gru_solo_saved_words(int B, int H, int T) { return (size_t)T * solo_tiles(B) * 16 * H; }
 
 #define HPSGD_SOLO_CASES(LAUNCH) \
-  switch ((H + 15) / 16) {       \
+  switch ((H + 7) / 8) {         \
     case 1: LAUNCH(1); break;    \
     case 2: LAUNCH(2); break;    \
     case 3: LAUNCH(3); break;    \
@@ -350,18 +405,39 @@ size_t gru_solo_saved_words(int B, int H, int T) {
     case 6: LAUNCH(6); break;    \
     case 7: LAUNCH(7); break;    \
     case 8: LAUNCH(8); break;    \
+    case 9: LAUNCH(9); break;    \
+    case 10: LAUNCH(10); break;  \
+    case 11: LAUNCH(11); break;  \
+    case 12: LAUNCH(12); break;  \
+    case 13: LAUNCH(13); break;  \
+    case 14: LAUNCH(14); break;  \
+    case 15: LAUNCH(15); break;  \
+    case 16: LAUNCH(16); break;  \
     default: return hipErrorInvalidValue; \
   }
+
+// Two tiles per workgroup where single ones are more than run at once: two share a step's LDS round trips and
+// barriers.  Up to 80 units a CU holds two workgroups or more, whose steps cover each other's waits.  A local step
+// of 20 time steps with 512 tiles, one / two per workgroup: H = 128 294 / 276 us, H = 100 246 / 236, H = 64 153 / 160;
+// 384 tiles: H = 80 172 / 180, H = 40 114 / 122; 1024 tiles: H = 80 339 / 348, H = 64 225 / 218, H = 32 175 / 165.
+static bool solo_two_tiles(int B, int H, int groups) {
+  const long n = (long)groups * solo_tiles(B);
+  return H <= 64 ? n > 512 : H > 80 && n > 256;
+}
 
 hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep, const float* gx, long s_gx, float* hs,
                                long s_hs, float* sv, long s_sv, int B, int H, int T, int groups, hipStream_t s) {
   if (!gru_solo_supported(B, H) || T < 1) return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
-  const SoloTiles ti = solo_tiles(B);
+  const int RT = solo_tiles(B);
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_SOLO_FWD(HB)                                                                                             \
-  hipLaunchKernelGGL(gru_solo_fwd_kernel<HB>, dim3(groups* ti.RT), dim3(64 * HB), 0, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
-                     s_hs, sv, s_sv, B, H, T, ti.RT, ti.rows)
+#define HPSGD_SOLO_FWD(H8)                                                                                                  \
+  if (solo_two_tiles(B, H, groups))                                                                                          \
+    hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, b_hh, s_rep, \
+                       gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, RT);                                                           \
+  else                                                                                                                      \
+    hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, 1>), dim3(groups * RT), dim3(Solo<H8>::NT), 0, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
+                       s_hs, sv, s_sv, B, H, T, RT)
   HPSGD_SOLO_CASES(HPSGD_SOLO_FWD)
 #undef HPSGD_SOLO_FWD
   return hipGetLastError();
@@ -372,11 +448,15 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
                                float* dbp, int B, int H, int T, int groups, hipStream_t s) {
   if (!gru_solo_supported(B, H) || T < 1) return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
-  const SoloTiles ti = solo_tiles(B);
+  const int RT = solo_tiles(B);
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_SOLO_BWD(HB)                                                                                           \
-  hipLaunchKernelGGL(gru_solo_bwd_kernel<HB>, dim3(groups* ti.RT), dim3(64 * HB), 0, s, W_hh, s_rep, dgx, dgh, s_dg, D, s_D, \
-                     above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, ti.RT, ti.rows)
+#define HPSGD_SOLO_BWD(H8)                                                                                                     \
+  if (solo_two_tiles(B, H, groups))                                                                                             \
+    hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, s_rep, dgx, dgh, \
+                       s_dg, D, s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT);                                    \
+  else                                                                                                                         \
+    hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, 1>), dim3(groups * RT), dim3(Solo<H8>::NT), 0, s, W_hh, s_rep, dgx, dgh, s_dg, D,  \
+                       s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT)
   HPSGD_SOLO_CASES(HPSGD_SOLO_BWD)
 #undef HPSGD_SOLO_BWD
   return hipGetLastError();

@@ -244,7 +244,8 @@ int build_layout(hpsgd_ctx* c) {
     }
     c->gx = c->alloc(TB * 3 * H);
     c->dgh = c->alloc(TB * 3 * H);
-    c->gh = c->alloc(Bi * 3 * H);
+    const size_t dbp_solo = c->solo ? (size_t)gru_solo_row_tiles(d.batch) * 6 * H : 0;
+    c->gh = c->alloc(dbp_solo > Bi * 3 * H ? dbp_solo : Bi * 3 * H);
     c->D = c->alloc(Bi * H);
     c->wt = c->alloc(3 * H * H);
     // batch rows per workgroup of the fp32 resident-weight launches (0: they do not take this layer)
@@ -253,8 +254,10 @@ int build_layout(hpsgd_ctx* c) {
                   : gru_persist_rows(d.batch, d.hidden, c->K);
     // (no step of a narrow model waits for another workgroup)
     if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : 32));
-    if (c->solo) c->dbp = c->alloc_packed((size_t)gru_solo_row_tiles(d.batch) * 6 * H);
-    else if (c->prow) c->dbp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 6 * H);
+    if (c->solo) {  // (in the place of `gh`, which a step of such launches does not use)
+      c->dbp.offset = c->gh.offset;
+      c->dbp.stride = dbp_solo;
+    } else if (c->prow) c->dbp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 6 * H);
     else if (c->solo_b) c->dbp = c->alloc_packed((size_t)gru_solo_bf16_row_tiles((int)Bi) * 6 * H);
     else if (d.prec == HPSGD_BF16_MFMA && gru_fused_bf16_supported((int)H)) c->dbp = c->alloc_packed(((Bi + 31) / 32) * 6 * H);
     if (c->prow && gru_persist_dw_supported((int)H)) c->dwp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 3 * H * H);
