@@ -293,6 +293,134 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
   }
 }
 
+// ---------------------------------------------------------------------------- few tiles
+// A product of few tiles is bound by one wave's chain: in the form above a 64 x 64 tile's k-tile of 32 takes 0.8 us
+// (16 MFMAs of 64 cycles per wave, two barriers' worth of waits), one after the other, while most of the chip is idle.
+// Here a workgroup has a 32 x 32 tile and its four waves take a quarter of the contraction each, so that there
+// are four times the workgroups and a chain is a quarter as long.  A wave loads its operands straight into the MFMA
+// layout, four steps of 8 ahead, and waits for nobody before the sums of the four meet in LDS.
+template <bool CK, bool RAG>
+struct SlimOperand {
+  const float* p;
+  long ld;
+  float4 r[4];
+  __device__ __forceinline__ void init(const float* __restrict__ base, long ld_, int i, int imax) {
+    ld = ld_;
+    p = base + (CK ? (long)min(i, imax - 1) * ld_ : (long)min(i, imax - 1));
+  }
+  // the values k .. k + 3, clamped into the contraction
+  __device__ __forceinline__ void load(int u, int k, int Kd) {
+    if (CK) {
+      r[u] = ld16<RAG>(p + max(min(k, Kd - 4), 0));
+    } else {
+      r[u] = make_float4(p[(long)min(k, Kd - 1) * ld], p[(long)min(k + 1, Kd - 1) * ld], p[(long)min(k + 2, Kd - 1) * ld],
+                         p[(long)min(k + 3, Kd - 1) * ld]);
+    }
+  }
+  // ... with zeros beyond it
+  __device__ __forceinline__ float4 tail(int u, int k, int Kd) const {
+    float4 v = r[u];
+    if (CK) return k >= Kd ? make_float4(0.f, 0.f, 0.f, 0.f) : shift_down(v, k - min(k, Kd - 4));
+    return make_float4(k < Kd ? v.x : 0.f, k + 1 < Kd ? v.y : 0.f, k + 2 < Kd ? v.z : 0.f, k + 3 < Kd ? v.w : 0.f);
+  }
+};
+
+template <bool TA, bool TB, bool RAG>
+__device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
+  constexpr int PITCH = 36;  // floats of a row of a wave's sums
+  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lrow = lane & 31, lk = lane >> 5;
+  const int tn = (d.N + 31) / 32, tm = (d.M + 31) / 32;
+  const int splits = d.splits > 1 ? d.splits : 1;
+  const long ntiles = (long)tn * tm * d.groups * splits, per = (ntiles + 7) / 8;  // (a run of tiles per XCD, as above)
+  const long tile = (long)(bid & 7) * per + (bid >> 3);
+  if ((long)(bid >> 3) >= per || tile >= ntiles) return;
+  const int gp = (int)(tile / ((long)tn * tm));
+  const int g = gp / splits, part = gp - g * splits;
+  const int m0 = (int)((tile / tn) % tm) * 32, n0 = (int)(tile % tn) * 32;
+  const long ka = (long)part * d.Kd * (TA ? d.lda : 1), kb = (long)part * d.Kd * (TB ? 1 : d.ldb);
+  if (splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
+  SlimOperand<!TA, RAG> a;
+  SlimOperand<TB, RAG> b;
+  a.init(d.A + (long)g * d.strideA + ka, d.lda, m0 + lrow, d.M);
+  b.init(d.B + (long)g * d.strideB + kb, d.ldb, n0 + lrow, d.N);
+  const int nc = (d.Kd + 7) / 8, ncw = (nc + 3) / 4, c0 = wave * ncw, c1 = min(nc, c0 + ncw);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    a.load(u, 8 * (c0 + u) + 4 * lk, d.Kd);
+    b.load(u, 8 * (c0 + u) + 4 * lk, d.Kd);
+  }
+  // the epilogue's extra matrix operand, behind the first operands (see above)
+  float* C = d.C + (long)(splits > 1 ? gp : g) * d.strideC;
+  const float* aux = d.aux ? d.aux + (long)g * d.strideAux : nullptr;
+  const int epi = d.epilogue;
+  const float* X = epi == EPI_ACCUM ? C : (epi == EPI_RELU_MASK || epi == EPI_COMMIT) ? aux : nullptr;
+  const int row = m0 + (tid >> 3), col = n0 + ((tid & 7) << 2);
+  const bool in = row < d.M, whole = col + 3 < d.N;
+  const long off = (long)min(row, d.M - 1) * d.ldc + col;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (X) {
+    if (whole) x = ld16<true>(X + off);
+    else x = make_float4(X[off - max(col - d.N + 1, 0)], X[off - max(col + 1 - (d.N - 1), 0) + 1], X[off - max(col + 2 - (d.N - 1), 0) + 2], 0.f);
+  }
+  floatx16 acc[2];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+  for (int c = c0; c < c1; c += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (c + u < c1) {  // (uniform)
+        const int k = 8 * (c + u) + 4 * lk;
+        float4 fa = a.r[u], fb = b.r[u];
+        if (8 * (c + u) + 8 > d.Kd) {  // (uniform)
+          fa = a.tail(u, k, d.Kd);
+          fb = b.tail(u, k, d.Kd);
+        }
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.x, fb.x, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.y, fb.y, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.z, fb.z, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.w, fb.w, acc[1], 0, 0, 0);
+      }
+      a.load(u, 8 * (c + 4 + u) + 4 * lk, d.Kd);
+      b.load(u, 8 * (c + 4 + u) + 4 * lk, d.Kd);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    fast_lds[(wave * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * PITCH + lrow] = acc[0][v] + acc[1][v];
+  __syncthreads();
+  if (!in || col >= d.N) return;
+  float4 o[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) o[w] = *reinterpret_cast<const float4*>(&fast_lds[(w * 32 + (tid >> 3)) * PITCH + ((tid & 7) << 2)]);
+  const float4 s = make_float4((o[0].x + o[1].x) + (o[2].x + o[3].x), (o[0].y + o[1].y) + (o[2].y + o[3].y),
+                               (o[0].z + o[1].z) + (o[2].z + o[3].z), (o[0].w + o[1].w) + (o[2].w + o[3].w));
+  auto one = [&](float v, float xv, int e) -> float {
+    switch (epi) {
+      case EPI_BIAS: return v + aux[col + e];
+      case EPI_BIAS_RELU: return fmaxf(v + aux[col + e], 0.f);
+      case EPI_ACCUM: return v + xv;
+      case EPI_RELU_MASK: return xv > 0.f ? v : 0.f;
+      case EPI_COMMIT: return xv - d.alpha * v;
+      default: return v;
+    }
+  };
+  if (whole) {
+    st16<true>(C + off, make_float4(one(s.x, x.x, 0), one(s.y, x.y, 1), one(s.z, x.z, 2), one(s.w, x.w, 3)));
+  } else {
+    C[off] = one(s.x, x.x, 0);
+    if (col + 1 < d.N) C[off + 1] = one(s.y, x.y, 1);
+    if (col + 2 < d.N) C[off + 2] = one(s.z, x.z, 2);
+  }
+}
+constexpr size_t kSlimLds = 4 * 32 * 36 * sizeof(float);
+
+template <bool TA, bool TB, bool RAG>
+__global__ void __launch_bounds__(FTHREADS) gemm_f32_slim_kernel(GemmDesc d) {
+  slim_body<TA, TB, RAG>(d, blockIdx.x);
+}
+
 template <int BM, int BN, bool TA, bool TB, bool RAG>
 __global__ void __launch_bounds__(FTHREADS) gemm_f32_fast_kernel(GemmDesc d) {
   fast_body<BM, BN, TA, TB, RAG>(d, blockIdx.x);
@@ -343,8 +471,9 @@ __device__ __forceinline__ void colsum_body(const ColsumPack& pk, unsigned bid, 
 // Several products that need nothing of each other, and column sums, in one launch (64 x 64 tiles): each of
 // them leaves most of the chip idle, and a launch of its own costs 4.5 us before it does anything.
 // Product i owns the workgroups blk0[i] .. blk0[i+1]-1 (whole rounds over the XCDs), the column sums the rest.
-template <bool RAG>
-__global__ void __launch_bounds__(FTHREADS) gemm_f32_multi_kernel(GemmPack pk, ColsumPack cs, int groups) {
+// SLIM: those of the bits of `slim` are products of few tiles.
+template <bool RAG, bool SLIM>
+__global__ void __launch_bounds__(FTHREADS) gemm_f32_multi_kernel(GemmPack pk, ColsumPack cs, int groups, unsigned slim) {
   int i = 0;
   while (i < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
   const unsigned bid = blockIdx.x - pk.blk0[i];
@@ -354,6 +483,12 @@ __global__ void __launch_bounds__(FTHREADS) gemm_f32_multi_kernel(GemmPack pk, C
     return;
   }
   const GemmDesc& d = pk.d[i];
+  if (SLIM && (slim >> i & 1)) {
+    if (d.transA) slim_body<true, false, RAG>(d, bid);
+    else if (d.transB) slim_body<false, true, RAG>(d, bid);
+    else slim_body<false, false, RAG>(d, bid);
+    return;
+  }
   if (d.transA) fast_body<64, 64, true, false, RAG>(d, bid);
   else if (d.transB) fast_body<64, 64, false, true, RAG>(d, bid);
   else fast_body<64, 64, false, false, RAG>(d, bid);
@@ -405,12 +540,38 @@ static bool fast_large(const GemmDesc& d) {
   return d.M > 64 && d.N > 64 && t >= 512 && d.Kd > 256;
 }
 
+// The form for few tiles: up to 64 tiles of 64 x 64, up to 256 with a contraction that makes a long chain, and
+// up to 128 where the launch holds nothing else.  (Beyond, the chip is busy either way and the larger tile reads its
+// operands fewer times.)  Measured, one / the other form of every product of at most that many tiles:
+//   to  64: MLP 30-64-896-8, batch 224, K = 2     90 /  52 us a round; 28-832-672-32-13, batch 16, K = 3   94 /  72
+//   to 256: MLP 596-928-140-7, batch 145, K = 3   83 /  74;  two GRU layers of H = 544, batch 4, K = 4  1148 / 1134
+//   but     two GRU layers of H = 100, batch 20, K = 4 (128 tiles, contraction 300, beside 560 others)   311 /  315
+//           fp32 language model, 248 tiles, contraction 192   233 / 240
+//   to 512: MLP 784-1024-1024-10, batch 128, K = 16  288 / 375
+static bool fast_slim(const GemmDesc& d, bool shared) {
+  const long t = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
+  return !(d.transA && d.transB) && (t <= 64 || (t <= 256 && d.Kd >= 512) || (t <= 128 && !shared));
+}
+static long slim_blocks(const GemmDesc& d) {
+  const long t = (long)((d.N + 31) / 32) * ((d.M + 31) / 32) * d.groups * (d.splits > 1 ? d.splits : 1);
+  return 8 * ((t + 7) / 8);
+}
+template <bool RAG>
+static hipError_t launch_slim(const GemmDesc& d, hipStream_t s) {
+  const dim3 grid((unsigned)slim_blocks(d));
+  KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
+  if (d.transA) hipLaunchKernelGGL((gemm_f32_slim_kernel<true, false, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  else if (d.transB) hipLaunchKernelGGL((gemm_f32_slim_kernel<false, true, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  else hipLaunchKernelGGL((gemm_f32_slim_kernel<false, false, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  return hipGetLastError();
+}
+
 bool gemm_pack_push(GemmPack& pk, const GemmDesc& d) {
   if (pk.n >= GemmPack::MAX || d.bf16 || d.background || (d.transA && d.transB) || !fast_kind(d) || fast_large(d)) return false;
   if (d.M <= 0 || d.N <= 0 || d.groups <= 0) return false;
   const long t = (long)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.groups * (d.splits > 1 ? d.splits : 1);
   pk.d[pk.n] = d;
-  pk.blk0[pk.n + 1] = pk.blk0[pk.n] + (unsigned)(8 * ((t + 7) / 8));
+  pk.blk0[pk.n + 1] = pk.blk0[pk.n] + (unsigned)(fast_slim(d, true) ? slim_blocks(d) : 8 * ((t + 7) / 8));
   ++pk.n;
   return true;
 }
@@ -420,10 +581,12 @@ hipError_t launch_gemm_pack(const GemmPack& pk, const ColsumPack& cs, int groups
   if (pk.n == 0) return launch_colsum_pack(cs, groups, s);
   if (pk.n == 1 && cs.n == 0) return launch_gemm_f32_fast(pk.d[0], s);
   bool rag = false;
+  unsigned slim = 0;
   double flops = 0.;
   for (int i = 0; i < pk.n; ++i) {
     const GemmDesc& d = pk.d[i];
     rag = rag || fast_kind(d) == 2;
+    slim |= fast_slim(d, true) ? 1u << i : 0u;
     flops += 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups;
   }
   using OpC = FastOperand<64, true, false>;
@@ -433,8 +596,9 @@ hipError_t launch_gemm_pack(const GemmPack& pk, const ColsumPack& cs, int groups
   static_assert(smem <= 64 * 1024, "within the default limit of dynamic LDS");
   dim3 grid(pk.blk0[pk.n] + (cs.n ? cs.blk0[cs.n] * (unsigned)groups : 0u));
   KernelTimer kt(KID_GEMM_F32_FAST, flops, s);
-  if (rag) hipLaunchKernelGGL(gemm_f32_multi_kernel<true>, grid, dim3(FTHREADS), smem, s, pk, cs, groups);
-  else hipLaunchKernelGGL(gemm_f32_multi_kernel<false>, grid, dim3(FTHREADS), smem, s, pk, cs, groups);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(FTHREADS), smem, s, pk, cs, groups, slim); };
+  if (rag) slim ? launch(gemm_f32_multi_kernel<true, true>) : launch(gemm_f32_multi_kernel<true, false>);
+  else slim ? launch(gemm_f32_multi_kernel<false, true>) : launch(gemm_f32_multi_kernel<false, false>);
   return hipGetLastError();
 }
 
@@ -445,6 +609,7 @@ hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s) {
   const int kind = fast_kind(d);
   if (!kind) return hipErrorNotSupported;
   const bool rag = kind == 2;
+  if (fast_slim(d, false)) return rag ? launch_slim<true>(d, s) : launch_slim<false>(d, s);
   if (fast_large(d)) return rag ? launch_fast_layout<128, 128, true>(d, s) : launch_fast_layout<128, 128, false>(d, s);
   return rag ? launch_fast_layout<64, 64, true>(d, s) : launch_fast_layout<64, 64, false>(d, s);
 }

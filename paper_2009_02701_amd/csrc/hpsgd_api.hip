@@ -406,6 +406,7 @@ GemmDesc gemm_desc(int groups, int bf16, int M, int N, int Kd, const float* A, l
   g.C = C; g.ldc = ldc; g.strideC = sC;
   g.aux = aux; g.strideAux = sAux;
   g.M = M; g.N = N; g.Kd = Kd; g.groups = groups;
+  g.workers = t_step_ctx ? t_step_ctx->K : groups;
   g.epilogue = epi; g.bf16 = bf16;
   return g;
 }

@@ -152,6 +152,9 @@ struct GemmDesc {
   float alpha;                                         // EPI_COMMIT: the learning rate
   int background;                                      // runs beside latency-critical kernels: keep the
                                                        // LDS footprint small so both fit on a CU
+  // all workers of the context, of which `groups` are stepped (0: groups): what decides the order of a sum goes by
+  // it, so that a worker's result is the same however many are stepped with it
+  int workers;
 };
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s);
 
