@@ -5,10 +5,16 @@
 // With N <= 128 rows and C <= 32 classes each of the three products is a fraction of a
 // megaflop per worker: as three GEMM launches, two reductions, a softmax and a loss launch
 // they cost seven launch gaps and little else.  Here the forward part is cut over the rows
-// (8 rows per workgroup, 32 threads per row share a dot product) and the backward part over
-// the feature columns (64 per workgroup), so that a worker's head is spread over 16 CUs (a
-// single workgroup per worker with everything in LDS was measured at ~95 us: bound by one
-// CU's LDS rate).  Every sum runs in a fixed order.
+// (16 per workgroup) and the backward part over the feature columns (32 per workgroup), so that a
+// worker's head is spread over several CUs (a single workgroup per worker with everything in LDS was
+// measured at ~95 us: bound by one CU's LDS rate).  Every sum runs in a fixed order.
+//
+// All three products are v_mfma_f32_16x16x4_f32 with the classes in blocks of 16 (A lane l holds A[m = l%16][k = l/16],
+// B lane l holds B[k = l/16][n = l%16], accumulator register v holds C[4*(l/16) + v][l%16]); eight waves cut the
+// contraction, so that a launch is one trip to memory, a handful of instructions and one or two trips through LDS.
+// Measured against multiply-adds from LDS with rows, then columns, in series per thread (forward + backward launch):
+// N = 128, C = 10, H = 1024, 16 workers 17.5 + 28.3 -> 6.7 + 8.5 us; N = 16, C = 21, H = 64, one worker 12.6 + 7.9 -> 4.5 + 5.0; N = 14, C = 27,
+// H = 130, 6 workers 16.5 + 11.0 -> 4.9 + 7.5.
 #include <cmath>
 
 #include "kernels.h"
@@ -19,170 +25,201 @@ namespace {
 
 constexpr int HMAXC = 32;     // classes
 constexpr int HMAXN = 128;    // rows
-constexpr int HROWS = 8;      // rows per workgroup, forward
-constexpr int HCOLS = 64;     // feature columns per workgroup, backward
+constexpr int HROWS = 16;     // rows per workgroup, forward
+constexpr int HCOLS = 32;     // feature columns per workgroup, backward
 
-// Trips 0 .. n-1 of a copy loop, U at a time: the U loads go out before the first value is used
-// (a load whose value is stored at once waits out the memory latency on every trip).
-template <int U, typename Load, typename Store>
-__device__ __forceinline__ void batched_copy(int n, Load load, Store store) {
-  for (int base = 0; base < n; base += U) {
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = load(min(base + u, n - 1));
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (base + u < n) store(base + u, v[u]);
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Values k .. k + 3 of a row of H, zeros beyond it (any alignment)
+__device__ __forceinline__ floatx4 row4(const float* __restrict__ p, int k, int H) {
+  if (k + 3 < H) {
+    const f4u v = *reinterpret_cast<const f4u*>(p + k);
+    return (floatx4){v.x, v.y, v.z, v.w};
   }
+  floatx4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = p[min(k + e, H - 1)];
+    v[e] = k + e < H ? x : 0.f;
+  }
+  return v;
 }
 
-// grid (ceil(N / 8), groups), 256 threads: thread t works for row t / 32 of the slice on the
-// contraction indices t % 32, + 32, ...
-template <int CPAD>  // classes rounded up to 8, 16 or 32: the rows of W beyond C are zero in LDS, so that
-                     // the inner loops carry no guards (a guard per class keeps the LDS reads from being batched)
-__global__ void __launch_bounds__(256)
+// grid (ceil(N / 16), groups), 512 threads: wave w takes the contraction's chunks of 16 w, w + 8, ..; behind the
+// products thread t has class t % 32 of row t / 32.  CB: blocks of 16 classes
+template <int CB>
+__global__ void __launch_bounds__(512)
 cls_head_fwd_kernel(const float* __restrict__ feats, long s_feats, const float* __restrict__ W,
                     const float* __restrict__ b, long s_in, const int32_t* __restrict__ y, long s_y,
                     float* __restrict__ dlog, long s_dlog, float* __restrict__ rowloss, long s_rowloss, int N, int C,
                     int H) {
-  extern __shared__ __attribute__((aligned(16))) float head_lds[];
-  float* sW = head_lds;  // [CPAD][H]
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int part = tid & 31, row = blockIdx.x * HROWS + (tid >> 5);
-  const int rowc = min(row, N - 1);
-  const float* Wg = W + g * s_in;
-  const int nW = C * H;
-  const float* fr = feats + g * s_feats + (long)rowc * H;
-  const int nk = (H - part + 31) / 32;  // this thread's share of the row: k = part + 32 i < H
-  // the first 8 values of the row are requested before W is copied, so that they arrive with it
-  float f[8];
+  constexpr int LP = 16 * CB + 1;
+  __shared__ float red[8][HROWS][LP];
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const float* fr = feats + g * s_feats + (long)min((int)blockIdx.x * HROWS + lr, N - 1) * H;
+  const float* wr[CB];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) f[u] = fr[part + 32 * min(u, nk - 1)];
-  batched_copy<24>((nW + 255) / 256, [&](int i) { return Wg[min(tid + 256 * i, nW - 1)]; },
-                   [&](int i, float v) {
-                     if (tid + 256 * i < nW) sW[tid + 256 * i] = v;
-                   });
-  for (int i = nW + tid; i < CPAD * H; i += 256) sW[i] = 0.f;
-  float acc[CPAD];
+  for (int cb = 0; cb < CB; ++cb) wr[cb] = W + g * s_in + (long)min(16 * cb + lr, C - 1) * H;
+  // (what the last part needs arrives with the operands)
+  const int c = tid & 31, row = blockIdx.x * HROWS + (tid >> 5), rowc = min(row, N - 1);
+  const float bias = b[g * s_in + min(c, C - 1)];
+  const int label = y[g * s_y + rowc];
+  floatx4 acc[CB];
 #pragma unroll
-  for (int c = 0; c < CPAD; ++c) acc[c] = 0.f;
+  for (int cb = 0; cb < CB; ++cb) acc[cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  const int nc = (H + 15) / 16;
+  for (int i = w; i < nc; i += 32) {  // four chunks at a time
+    floatx4 f[4], v[4][CB];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i + 8 * u < nc) {  // (uniform)
+        const int k = 16 * (i + 8 * u) + 4 * lg;
+        f[u] = row4(fr, k, H);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) v[u][cb] = row4(wr[cb], k, H);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i + 8 * u < nc) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u][e], v[u][cb][e], acc[cb], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[w][4 * lg + v][16 * cb + lr] = acc[cb][v];
   __syncthreads();
-  for (int base = 0; base < nk; base += 8) {
-    if (base > 0) {
+  if (row >= N) return;  // (the 32 threads of a row together)
+  const bool ok = c < C;
+  float z = 0.f;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) f[u] = fr[part + 32 * min(base + u, nk - 1)];
-    }
+  for (int i = 0; i < 8; ++i) z += red[i][tid >> 5][min(c, 16 * CB - 1)];
+  z = ok ? z + bias : -INFINITY;
+  float m = z;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (base + u < nk) {
-        const int k = part + 32 * (base + u);
+  for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 32));
+  const float zl = __shfl(z, label & 31, 32);
+  const float ez = ok ? expf(z - m) : 0.f;
+  float sum = ez;
 #pragma unroll
-        for (int c = 0; c < CPAD; ++c) acc[c] += f[u] * sW[c * H + k];
-      }
-  }
-  // the 32 partial sums of a row: butterfly inside its half of the wave
-#pragma unroll
-  for (int c = 0; c < CPAD; ++c) {
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) acc[c] += __shfl_xor(acc[c], o);
-  }
-  if (part == 0 && row < N) {
-    const float* bg = b + g * s_in;
-    const int label = y[g * s_y + row];
-    float m = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < CPAD; ++c)
-      if (c < C) {
-        acc[c] += bg[c];
-        m = fmaxf(m, acc[c]);
-      }
-    float sum = 0.f, zl = 0.f;
-#pragma unroll
-    for (int c = 0; c < CPAD; ++c)
-      if (c < C) {
-        if (c == label) zl = acc[c];
-        acc[c] = expf(acc[c] - m);
-        sum += acc[c];
-      }
-    rowloss[g * s_rowloss + row] = -((zl - m) - logf(sum));
-    const float inv_sum = 1.0f / sum, inv_n = 1.0f / (float)N;
-    float* dr = dlog + g * s_dlog + (long)row * C;
-#pragma unroll
-    for (int c = 0; c < CPAD; ++c)
-      if (c < C) dr[c] = (acc[c] * inv_sum - (c == label ? 1.0f : 0.0f)) * inv_n;
-  }
+  for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 32);
+  const float inv_sum = 1.0f / sum, inv_n = 1.0f / (float)N;
+  if (c == 0) rowloss[g * s_rowloss + row] = -(((label >= 0 && label < C ? zl : 0.f) - m) - logf(sum));
+  if (ok) dlog[g * s_dlog + (long)row * C + c] = (ez * inv_sum - (c == label ? 1.0f : 0.0f)) * inv_n;
 }
 
-// grid (ceil(H / 64), groups), 256 threads: thread t owns column t % 64 of the slice
-__global__ void __launch_bounds__(256)
+// grid (ceil(H / 32), groups), 512 threads: wave w has the columns of block w % 2 and rows 32 (w / 2) .. + 31.  Step s of
+// the weight gradient's contraction takes row 16 (s / 4) + 4 (l / 16) + s % 4 of those in lane l: the row of register s
+// of the input gradient's two blocks, so that a lane's features are its outputs' ReLU mask too.
+template <int CB>
+__global__ void __launch_bounds__(512)
 cls_head_bwd_kernel(const float* __restrict__ feats, long s_feats, const float* W_in, const float* b_in, long s_in,
                     const float* __restrict__ dlog, long s_dlog, const float* __restrict__ rowloss, long s_rowloss,
                     float* __restrict__ dfeat, long s_dfeat, float* W_out, float* b_out, long s_out, float lr,
                     int commit, float* __restrict__ loss, int N, int C, int H, int relu_mask) {
-  __shared__ float sD[HMAXN * HMAXC];          // dlogits [N][C]
-  __shared__ float sF[HMAXN][HCOLS + 1];       // the slice of the features
-  __shared__ float sW[HMAXC][HCOLS + 1];       // the slice of W
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int jl = tid & 63, q = tid >> 6, j = blockIdx.x * HCOLS + jl;
-  const bool jv = j < H;
-  const int jc = jv ? j : 0;
-  const int nD = N * C;
-  // the slice of W (at most 8 values per thread) and the first 1024 logit gradients are requested
-  // first and stored last: they arrive while the features are copied
-  const int nWq = (C - q + 3) / 4;
-  float wv[HMAXC / 4], dv[4];
+  constexpr int DP = 16 * CB + 1;
+  __shared__ float sD[HMAXN * DP];                   // dlogits [N][classes], zeros beyond N and C
+  __shared__ float red[4][16 * CB][HCOLS + 1];       // the weight gradient's sums per quarter of the rows
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr_ = lane & 15, lg = lane >> 4, rq = w >> 1, r0 = 32 * rq;
+  const int j = blockIdx.x * HCOLS + 16 * (w & 1) + lr_, jc = min(j, H - 1);
+  const float* dl = dlog + g * s_dlog;
+  const float* fe = feats + g * s_feats + jc;
+  const float* Wg = W_in + g * s_in;
+  float f[8], wv[4 * CB];
 #pragma unroll
-  for (int u = 0; u < HMAXC / 4; ++u) wv[u] = W_in[g * s_in + (long)min(q + 4 * u, C - 1) * H + jc];
+  for (int s = 0; s < 8; ++s) f[s] = fe[(long)min(r0 + 16 * (s / 4) + 4 * lg + s % 4, N - 1) * H];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) dv[u] = dlog[g * s_dlog + min(tid + 256 * u, nD - 1)];
-  batched_copy<16>((N - q + 3) / 4, [&](int i) { return feats[g * s_feats + (long)(q + 4 * i) * H + jc]; },
-                   [&](int i, float v) { sF[q + 4 * i][jl] = v; });
+  for (int s = 0; s < 4 * CB; ++s) wv[s] = Wg[(long)min(4 * s + lg, C - 1) * H + jc];
+  // the old values of this thread's outputs of the update
+  float wo[CB];
 #pragma unroll
-  for (int u = 0; u < HMAXC / 4; ++u)
-    if (u < nWq) sW[q + 4 * u][jl] = wv[u];
+  for (int u = 0; u < CB; ++u) {
+    const int cc = (tid >> 5) + 16 * u, jo = blockIdx.x * HCOLS + (tid & 31);
+    wo[u] = Wg[(long)min(cc, C - 1) * H + min(jo, H - 1)];
+  }
+  // (all loads before the first store: none waits for another's value)
+  const int rows = (N + 31) / 32 * 32, n = rows * 16 * CB;
+  float dv[4 * CB];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (tid + 256 * u < nD) sD[tid + 256 * u] = dv[u];
-  if (nD > 1024)
-    batched_copy<4>((nD - 1024 + 255) / 256, [&](int i) { return dlog[g * s_dlog + min(1024 + tid + 256 * i, nD - 1)]; },
-                    [&](int i, float v) {
-                      if (1024 + tid + 256 * i < nD) sD[1024 + tid + 256 * i] = v;
-                    });
+  for (int u = 0; u < 4 * CB; ++u)
+    if (512 * u < n) {  // (uniform)
+      const int i = tid + 512 * u, r = i / (16 * CB), c = i % (16 * CB);
+      dv[u] = dl[(long)min(r, N - 1) * C + min(c, C - 1)];
+    }
+#pragma unroll
+  for (int u = 0; u < 4 * CB; ++u) {
+    const int i = tid + 512 * u, r = i / (16 * CB), c = i % (16 * CB);
+    if (i < n) sD[r * DP + c] = r < N && c < C ? dv[u] : 0.f;
+  }
   __syncthreads();
-  for (int r = q; r < N; r += 4) {
-    float a = 0.f;
-    for (int c = 0; c < C; ++c) a += sD[r * C + c] * sW[c][jl];
-    // the features are the output of a ReLU layer: the gradient passes where the feature is positive
-    if (relu_mask && !(sF[r][jl] > 0.f)) a = 0.f;
-    if (jv) dfeat[g * s_dfeat + (long)r * H + j] = a;
-  }
-  for (int c = q; c < C; c += 4) {
-    float a0 = 0.f, a1 = 0.f;
-    int r = 0;
-    for (; r + 1 < N; r += 2) {
-      a0 += sD[r * C + c] * sF[r][jl];
-      a1 += sD[(r + 1) * C + c] * sF[r + 1][jl];
+  floatx4 aw[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) aw[cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  if (r0 < N) {  // (uniform)
+    floatx4 ad[2];
+    ad[0] = ad[1] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int r = r0 + 16 * (s / 4) + 4 * lg + s % 4;
+      const float fv = r < N ? f[s] : 0.f;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) aw[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[r * DP + 16 * cb + lr_], fv, aw[cb], 0, 0, 0);
     }
-    if (r < N) a0 += sD[r * C + c] * sF[r][jl];
-    const float dw = a0 + a1;
-    if (jv) W_out[g * s_out + (long)c * H + j] = commit ? sW[c][jl] - lr * dw : dw;
-  }
-  if (blockIdx.x == 0) {
-    if (tid < C) {
-      float a = 0.f;
-      for (int r = 0; r < N; ++r) a += sD[r * C + tid];
-      b_out[g * s_out + tid] = commit ? b_in[g * s_in + tid] - lr * a : a;
+#pragma unroll
+    for (int s = 0; s < 4 * CB; ++s) {
+      const float v = 4 * s + lg < C ? wv[s] : 0.f;
+#pragma unroll
+      for (int bl = 0; bl < 2; ++bl)
+        ad[bl] = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[(r0 + 16 * bl + lr_) * DP + 4 * s + lg], v, ad[bl], 0, 0, 0);
     }
-    if (tid == 64 && loss) {
-      float v = 0.f;
-      for (int r = 0; r < N; ++r) v += rowloss[g * s_rowloss + r];
-      loss[g] = v / (float)N;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int r = r0 + 16 * (s / 4) + 4 * lg + s % 4;
+      // the features are the output of a ReLU layer: the gradient passes where the feature is positive
+      const float v = relu_mask && !(f[s] > 0.f) ? 0.f : ad[s / 4][s % 4];
+      if (r < N && j < H) dfeat[g * s_dfeat + (long)r * H + j] = v;
+    }
+  }
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[rq][16 * cb + 4 * lg + v][16 * (w & 1) + lr_] = aw[cb][v];
+  __syncthreads();
+  {
+    const int jl = tid & 31, jo = blockIdx.x * HCOLS + jl;
+#pragma unroll
+    for (int u = 0; u < CB; ++u) {
+      const int c = (tid >> 5) + 16 * u;
+      const float dw = (red[0][c][jl] + red[1][c][jl]) + (red[2][c][jl] + red[3][c][jl]);
+      if (c < C && jo < H) W_out[g * s_out + (long)c * H + jo] = commit ? wo[u] - lr * dw : dw;
+    }
+  }
+  if (blockIdx.x == 0) {  // bias gradient (a wave per class) and mean loss: lane l has rows l and l + 64
+    for (int c = w; c < C; c += 8) {
+      float a = (lane < rows ? sD[lane * DP + c] : 0.f) + (lane + 64 < rows ? sD[(lane + 64) * DP + c] : 0.f);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+      if (lane == 0) b_out[g * s_out + c] = commit ? b_in[g * s_in + c] - lr * a : a;
+    }
+    if (w == 7 && loss) {
+      const float* rl = rowloss + g * s_rowloss;
+      float a = (lane < N ? rl[min(lane, N - 1)] : 0.f) + (lane + 64 < N ? rl[min(lane + 64, N - 1)] : 0.f);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+      if (lane == 0) loss[g] = a / (float)N;
     }
   }
 }
 
 }  // namespace
 
+// (H: any that the launches have taken before: a row of W per class had to fit the LDS)
 bool cls_head_supported(int N, int C, int H) {
   const int cpad = C <= 8 ? 8 : C <= 16 ? 16 : 32;
   return N >= 1 && N <= HMAXN && C >= 2 && C <= HMAXC && H >= 1 && (size_t)cpad * H * sizeof(float) <= 128 * 1024;
@@ -200,24 +237,14 @@ hipError_t launch_cls_head(const float* feats, long s_feats, const float* W_in, 
                            float* dfeat, long s_dfeat, float* W_out, float* b_out, long s_out, float lr, int commit,
                            float* loss, int N, int C, int H, int groups, hipStream_t s, int relu_mask) {
   if (!cls_head_supported(N, C, H)) return hipErrorInvalidValue;
-  const int cpad = C <= 8 ? 8 : C <= 16 ? 16 : 32;
-  const size_t lds = (size_t)cpad * H * sizeof(float);
-#define HPSGD_HEAD_FWD(CP)                                                                                         \
-  do {                                                                                                             \
-    static std::atomic<size_t> allowed{64 * 1024};                                                                 \
-    if (const hipError_t e_ = allow_lds((const void*)cls_head_fwd_kernel<CP>, lds, allowed)) return e_;            \
-    hipLaunchKernelGGL(cls_head_fwd_kernel<CP>, dim3((N + HROWS - 1) / HROWS, groups), dim3(256), lds, s, feats,   \
-                       s_feats, W_in, b_in, s_in, y, s_y, dlog, s_dlog, rowloss, s_rowloss, N, C, H);               \
-  } while (0)
-  if (cpad == 8) HPSGD_HEAD_FWD(8);
-  else if (cpad == 16) HPSGD_HEAD_FWD(16);
-  else HPSGD_HEAD_FWD(32);
-#undef HPSGD_HEAD_FWD
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cls_head_bwd_kernel, dim3((H + HCOLS - 1) / HCOLS, groups), dim3(256), 0, s, feats, s_feats,
-                     W_in, b_in, s_in, dlog, s_dlog, rowloss, s_rowloss, dfeat, s_dfeat, W_out, b_out, s_out, lr,
-                     commit, loss, N, C, H, relu_mask);
+  auto launch = [&](auto fwd, auto bwd) {
+    hipLaunchKernelGGL(fwd, dim3((N + HROWS - 1) / HROWS, groups), dim3(512), 0, s, feats, s_feats, W_in, b_in, s_in, y, s_y, dlog,
+                       s_dlog, rowloss, s_rowloss, N, C, H);
+    hipLaunchKernelGGL(bwd, dim3((H + HCOLS - 1) / HCOLS, groups), dim3(512), 0, s, feats, s_feats, W_in, b_in, s_in, dlog, s_dlog,
+                       rowloss, s_rowloss, dfeat, s_dfeat, W_out, b_out, s_out, lr, commit, loss, N, C, H, relu_mask);
+  };
+  if (C <= 16) launch(cls_head_fwd_kernel<1>, cls_head_bwd_kernel<1>);
+  else launch(cls_head_fwd_kernel<2>, cls_head_bwd_kernel<2>);
   return hipGetLastError();
 }
 
