@@ -294,6 +294,8 @@ hipError_t launch_embed_bf16(const float* E, long s_E, const int32_t* tok, long 
     return hipErrorInvalidValue;
   const int R = T * Bp;
   dim3 grid((Ep + 63) / 64, (R + 63) / 64, groups);
+  // (a copy and a transposed copy like cvt2_kernel's, and counted with them) bytes: one read of a row, one write of each
+  KernelTimer kt(KID_CVT2, 8.0 * R * Ew * groups, s);
   const bool vec = Ew % 4 == 0 && ((uintptr_t)E & 15) == 0 && s_E % 4 == 0;
 #define HPSGD_EMB(V)                                                                                                 hipLaunchKernelGGL(embed_bf16_kernel<V>, grid, dim3(256), 0, s, E, s_E, tok, s_tok, (__bf16*)xb, s_xb, (__bf16*)xT, ld_T,                      s_xT, R, B, Bp, Ew, Ep)
   if (vec) HPSGD_EMB(true);

@@ -4,8 +4,9 @@
 //
 // Each operand is either fp32 (rounded to bf16 nearest-even while it is staged) or already
 // bf16 (a rounded copy made once by its producer), chosen per operand at compile time.
-// Every GEMM of the bf16 training step is brought into this one shape by keeping transposed
-// bf16 copies of the operands whose natural layout is contraction-major (see hpsgd_api.hip).
+// Most products of the bf16 training step are of this shape by themselves or through transposed bf16 copies
+// that an operand's producer writes; the direct-to-LDS kernels also take operands whose rows are the
+// contraction's (NtOuter below).
 //
 // Tile 128 x 128 x 64 per workgroup of 4 waves (each wave 64 x 64 = 2 x 2 blocks of
 // v_mfma_f32_32x32x16_bf16), LDS double-buffered with one barrier per k-tile: while the
@@ -14,6 +15,8 @@
 // per CU, so one's barrier wait is covered by the other's MFMAs.
 // LDS rows are [i][k] with a pitch of 72 halves (144 B): the 16-byte operand reads of 16
 // consecutive rows then fall on 64 distinct banks.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace hpsgd {
@@ -83,11 +86,12 @@ struct GemmNtDesc {
   // group * splits + part, and so is the index of its C.
   int splits, Kall;
 };
-// Advances the operands of (virtual) group g to its part of the contraction.
+// Advances the operands of (virtual) group g to its part of the contraction.  AO, BO: see NtOuter.
+template <bool AO, bool BO>
 __device__ __forceinline__ void nt_part(GemmNtDesc& d, int g, const __bf16*& A, const __bf16*& B) {
   const int gg = d.splits > 1 ? g / d.splits : g, part = g - gg * (d.splits > 1 ? d.splits : 1);
-  A = reinterpret_cast<const __bf16*>(d.A) + (long)gg * d.strideA + (d.splits > 1 ? (long)part * d.Kd : 0);
-  B = reinterpret_cast<const __bf16*>(d.B) + (long)gg * d.strideB + (d.splits > 1 ? (long)part * d.Kd : 0);
+  A = reinterpret_cast<const __bf16*>(d.A) + (long)gg * d.strideA + (d.splits > 1 ? (long)part * d.Kd * (AO ? d.lda : 1) : 0);
+  B = reinterpret_cast<const __bf16*>(d.B) + (long)gg * d.strideB + (d.splits > 1 ? (long)part * d.Kd * (BO ? d.ldb : 1) : 0);
   if (d.splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
 }
 // The row of C of the product's row m < 3 gp (a compare instead of a division), or -1.
@@ -316,10 +320,50 @@ gemm_bf16_nt_kernel(GemmNtDesc d) {
 // (64 KB, raised to the 66 KB of the epilogue tile): two workgroups per CU.
 __device__ __attribute__((aligned(16))) unsigned nt_zero16[4] = {0u, 0u, 0u, 0u};
 
+// Operands whose rows are the contraction's ("outer"): X[k][i], unit-stride along the index i of C - a weight matrix
+// in an input gradient, logit gradients and activations in a weight gradient - without a transposed copy in memory.
+// A tile of BI columns x 64 steps lies in LDS as it does in memory, 64 rows of 2 BI bytes, as many loader
+// instructions as a tile of the other kind (lane j of one fills bytes 16 j .. of its 1 KB).  ds_read_b64_tr_b16 turns it
+// on the way out: in each 16 lanes, lane l names the 8 bytes of row l / 4 at columns 4 (l % 4) .. of a 4 x 16 block
+// and receives the four rows' values of column l.  Two of them are a lane's eight steps of a fragment.
+// The 16-byte chunks of a row are swizzled so that the 4 rows x 64 bytes which half a wave reads at once fall on 64
+// distinct banks: with rows of a multiple of 256 bytes chunk c of row k sits at c ^ 4 (k % 4); rows of 384 bytes already
+// alternate by half the banks, there it is c ^ 4 (k / 2 % 2).  Columns beyond I are clamped by whole chunks
+// (their products are never stored): the rows' pitch covers I rounded up to 8.
+// A product takes as long as one of the other kind; what it saves is the copy: language model of 10 000 words, H = 1024,
+// 1120 rows, 8 workers 90 us for the transposed logit gradients (2365 -> 2293 us a round with the weights' copies that
+// go too), 8640 words, H = 64, 864 rows, 14 workers 856 -> 784 us.
+template <int BI>
+struct NtOuter {
+  static constexpr int CPR = BI / 8, PITCH = BI * 2;  // chunks and bytes of a row
+  static_assert(PITCH % 256 == 0 || PITCH % 256 == 128, "the swizzle is for these");
+  __device__ __forceinline__ static int swz(int k) { return PITCH % 256 == 0 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
+  // loader instruction idx of the tile, lane `lane`: its step k, and the offset of its chunk's column from i0
+  __device__ __forceinline__ static int load_k(int idx, int lane) { return (idx * 64 + lane) / CPR; }
+  __device__ __forceinline__ static int load_col(int idx, int lane) {
+    return (((idx * 64 + lane) % CPR) ^ swz(load_k(idx, lane))) * 8;
+  }
+  // byte address in the tile of what a lane names for the block of 32 columns at i, contraction step 0, first half
+  // (step ks, half h: + frag_step(ks, h))
+  __device__ __forceinline__ static unsigned frag(int i, int lane) {
+    const int l = lane & 15, k = 8 * (lane >> 5) + (l >> 2);
+    const int c = i / 8 + 2 * ((lane >> 4) & 1) + ((l & 3) >> 1);
+    return (unsigned)(k * PITCH + ((c ^ swz(k)) << 4) + (l & 1) * 8);
+  }
+  __device__ __forceinline__ static constexpr int frag_step(int ks, int h) { return (16 * ks + 4 * h) * PITCH; }
+};
+typedef __bf16 bf16x4n __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2n __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ bf16x8 nt_join(u32x2n lo, u32x2n hi) {
+  typedef unsigned u32x4n __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x8, (u32x4n){lo.x, lo.y, hi.x, hi.y});
+}
+
 #define HPSGD_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define HPSGD_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-template <bool COMMIT, bool GATED = false>
+// AO, BO: the operand is of the outer kind.
+template <bool COMMIT, bool GATED = false, bool AO = false, bool BO = false>
 __global__ void __launch_bounds__(NTHREADS, 2)
 gemm_bf16_dl_kernel(GemmNtDesc d) {
   extern __shared__ __attribute__((aligned(16))) unsigned char nt_smem[];
@@ -330,28 +374,33 @@ gemm_bf16_dl_kernel(GemmNtDesc d) {
   if (!nt_tile(d, g, tile_m, tile_n)) return;
   const int m0 = tile_m * NBM, n0 = tile_n * NBN;
   const __bf16 *A, *B;
-  nt_part(d, g, A, B);
+  nt_part<AO, BO>(d, g, A, B);
+  using Out = NtOuter<NBM>;
   // loader: wave w, instruction i covers tile rows (4w + i)*8 .. +7; lane j: row + (j >> 3),
   // LDS chunk j & 7, which holds the row's chunk (j & 7) ^ ((row >> 1) & 7).  Rows beyond M / N
   // are clamped (their products are never stored).
   const __bf16* ga[4];
   const __bf16* gb[4];
-  int kofs[4];
+  int ka[4], kb[4];  // the lane's first contraction step in a tile
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = (wave * 4 + i) * 8 + (lane >> 3);
-    kofs[i] = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
-    ga[i] = A + (long)min(m0 + row, d.M - 1) * d.lda + kofs[i];
-    gb[i] = B + (long)min(n0 + row, d.N - 1) * d.ldb + kofs[i];
+    const int idx = wave * 4 + i, row = idx * 8 + (lane >> 3), kin = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    ka[i] = AO ? Out::load_k(idx, lane) : kin;
+    kb[i] = BO ? Out::load_k(idx, lane) : kin;
+    ga[i] = AO ? A + (long)ka[i] * d.lda + min(m0 + Out::load_col(idx, lane), (d.M - 1) & ~7)
+               : A + (long)min(m0 + row, d.M - 1) * d.lda + kin;
+    gb[i] = BO ? B + (long)kb[i] * d.ldb + min(n0 + Out::load_col(idx, lane), (d.N - 1) & ~7)
+               : B + (long)min(n0 + row, d.N - 1) * d.ldb + kin;
   }
   const __bf16* zero = reinterpret_cast<const __bf16*>(nt_zero16);
   auto issue = [&](int stage, int kt) {
     unsigned char* sa = nt_smem + stage * 32768 + wave * 4096;
+    const long oa = AO ? (long)kt * NBK * d.lda : kt * NBK, ob = BO ? (long)kt * NBK * d.ldb : kt * NBK;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const bool ok = kt * NBK + kofs[i] < d.Kd;  // Kd is a multiple of 8: a chunk is all in or all out
-      __builtin_amdgcn_global_load_lds(HPSGD_GPTR(ok ? ga[i] + kt * NBK : zero), HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(HPSGD_GPTR(ok ? gb[i] + kt * NBK : zero), HPSGD_LPTR(sa + 16384 + i * 1024),
+      // (Kd is a multiple of 8 unless both operands are outer: a chunk is all in or all out)
+      __builtin_amdgcn_global_load_lds(HPSGD_GPTR(kt * NBK + ka[i] < d.Kd ? ga[i] + oa : zero), HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(HPSGD_GPTR(kt * NBK + kb[i] < d.Kd ? gb[i] + ob : zero), HPSGD_LPTR(sa + 16384 + i * 1024),
                                        16, 0, 0);
     }
   };
@@ -367,11 +416,17 @@ gemm_bf16_dl_kernel(GemmNtDesc d) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int r = wm * 64 + i * 32 + lrow, rn = wn * 64 + i * 32 + lrow;
-    ra[i] = r * 128;
+    ra[i] = AO ? (int)Out::frag(wm * 64 + i * 32, lane) : r * 128;
     swa[i] = (r >> 1) & 7;
-    rb[i] = 16384 + rn * 128;
+    rb[i] = 16384 + (BO ? (int)Out::frag(wn * 64 + i * 32, lane) : rn * 128);
     swb[i] = (rn >> 1) & 7;
   }
+  auto outer_fragment = [&](const unsigned char* p, int ks) -> bf16x8 {
+    typedef __attribute__((address_space(3))) bf16x4n lds_bf16x4;
+    const bf16x4n lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + Out::frag_step(ks, 0)));
+    const bf16x4n hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + Out::frag_step(ks, 1)));
+    return nt_join(__builtin_bit_cast(u32x2n, lo), __builtin_bit_cast(u32x2n, hi));
+  };
   const int nk = (d.Kd + NBK - 1) / NBK;
   issue(0, 0);
   for (int kt = 0; kt < nk; ++kt) {
@@ -386,8 +441,8 @@ gemm_bf16_dl_kernel(GemmNtDesc d) {
       bf16x8 a[2], b[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        a[i] = *reinterpret_cast<const bf16x8*>(sb + ra[i] + (((2 * ks + lk) ^ swa[i]) << 4));
-        b[i] = *reinterpret_cast<const bf16x8*>(sb + rb[i] + (((2 * ks + lk) ^ swb[i]) << 4));
+        a[i] = AO ? outer_fragment(sb + ra[i], ks) : *reinterpret_cast<const bf16x8*>(sb + ra[i] + (((2 * ks + lk) ^ swa[i]) << 4));
+        b[i] = BO ? outer_fragment(sb + rb[i], ks) : *reinterpret_cast<const bf16x8*>(sb + rb[i] + (((2 * ks + lk) ^ swb[i]) << 4));
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -454,7 +509,7 @@ __device__ __forceinline__ bool dlx_tile(const GemmNtDesc& d, unsigned bid, int&
 }
 
 // bid: the workgroup's index among those of this product (blockIdx.x, unless a launch holds two products)
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO = false, bool BO = false>
 __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
   constexpr int BM = Sh::BM, BN = Sh::BN, IPW = Sh::IPW, CP = Sh::CP, NT = Sh::NT;
@@ -467,16 +522,30 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   if (!dlx_tile<BM, BN>(d, bid, g, tile_m, tile_n)) return;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const __bf16 *A, *B;
-  nt_part(d, g, A, B);
+  nt_part<AO, BO>(d, g, A, B);
   // loader: instruction i of wave w covers stage rows (w IPW + i) 8 .. +7 (rows below BM are A's);
   // lane j: row + (j >> 3), LDS chunk j & 7, which holds the row's chunk (j & 7) ^ ((row >> 1) & 7)
+  using OutA = NtOuter<BM>;
+  using OutB = NtOuter<BN>;
   const __bf16* gp[IPW];
-  int kofs[IPW];
+  int kofs[IPW];    // the lane's first contraction step in a tile
+  long kstep[IPW];  // (uniform) from a tile to the next one
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
-    const int row = (wave * IPW + i) * 8 + (lane >> 3);
-    kofs[i] = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
-    gp[i] = (row < BM ? A + (long)min(m0 + row, d.M - 1) * d.lda : B + (long)min(n0 + row - BM, d.N - 1) * d.ldb) + kofs[i];
+    const int idx = wave * IPW + i, row = idx * 8 + (lane >> 3);
+    const int kin = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    const bool is_a = idx < BM / 8;  // (uniform)
+    if (AO && is_a) {
+      kofs[i] = OutA::load_k(idx, lane);
+      gp[i] = A + (long)kofs[i] * d.lda + min(m0 + OutA::load_col(idx, lane), (d.M - 1) & ~7);
+    } else if (BO && !is_a) {
+      kofs[i] = OutB::load_k(idx - BM / 8, lane);
+      gp[i] = B + (long)kofs[i] * d.ldb + min(n0 + OutB::load_col(idx - BM / 8, lane), (d.N - 1) & ~7);
+    } else {
+      kofs[i] = kin;
+      gp[i] = (is_a ? A + (long)min(m0 + row, d.M - 1) * d.lda : B + (long)min(n0 + row - BM, d.N - 1) * d.ldb) + kin;
+    }
+    kstep[i] = is_a ? (AO ? NBK * d.lda : NBK) : (BO ? NBK * d.ldb : NBK);
   }
   const __bf16* zero = reinterpret_cast<const __bf16*>(nt_zero16);
   auto issue = [&](int stage, int kt) {
@@ -484,12 +553,14 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
     if ((kt + 1) * NBK <= d.Kd) {  // (uniform) a whole tile: no per-lane checks
 #pragma unroll
       for (int i = 0; i < IPW; ++i)
-        __builtin_amdgcn_global_load_lds(HPSGD_GPTR(gp[i] + kt * NBK), HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(HPSGD_GPTR(gp[i] + (AO || BO ? kt * kstep[i] : kt * NBK)), HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
     } else {
 #pragma unroll
       for (int i = 0; i < IPW; ++i) {
-        const bool ok = kt * NBK + kofs[i] < d.Kd;  // Kd is a multiple of 8: a chunk is all in or all out
-        __builtin_amdgcn_global_load_lds(HPSGD_GPTR(ok ? gp[i] + kt * NBK : zero), HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
+        // (Kd is a multiple of 8 unless both operands are outer: a chunk is all in or all out)
+        const bool ok = kt * NBK + kofs[i] < d.Kd;
+        __builtin_amdgcn_global_load_lds(HPSGD_GPTR(ok ? gp[i] + (AO || BO ? kt * kstep[i] : kt * NBK) : zero),
+                                         HPSGD_LPTR(sa + i * 1024), 16, 0, 0);
       }
     }
   };
@@ -512,26 +583,69 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
       ob[ks] = (BM + wn * TN * 32 + lrow) * 128 + (((2 * ks + lk) ^ sw) << 4);
     }
   }
+  // (outer operands: an address per block of 32 columns, the steps by immediate offsets)
+  unsigned pa[TM], pb[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) pa[i] = AO ? OutA::frag((wm * TM + i) * 32, lane) : 0u;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) pb[j] = BM * 128 + (BO ? OutB::frag((wn * TN + j) * 32, lane) : 0u);
   const int nk = (d.Kd + NBK - 1) / NBK;
   // The fragment reads and the waits for them are written out (ds_read_b128 / s_waitcnt): the
   // compiler's own waits are for all outstanding LDS reads at once, which would make every step
   // wait for the reads issued for the next one.  LDS returns reads in order, so "all but the
   // newest TM + TN" is exactly the older step's set.
-  bf16x8 fa[2][TM], fb[2][TN];
-  const unsigned lds0 = (unsigned)(uintptr_t)HPSGD_LPTR(nt_smem);
-  auto fragments = [&](unsigned sb, int ks, bf16x8(&fa_)[TM], bf16x8(&fb_)[TN]) {
-    const unsigned aa = sb + oa[ks], ab = sb + ob[ks];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fa_[i]) : "v"(aa), "n"(i * 4096));
-#pragma unroll
-    for (int j = 0; j < TN; ++j) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fb_[j]) : "v"(ab), "n"(j * 4096));
+  // (An outer operand's fragment is read in two halves, joined behind the wait.)
+  constexpr int READS = (AO ? 2 : 1) * TM + (BO ? 2 : 1) * TN;
+  static_assert(READS <= 15, "the wait's count");
+  struct Frag {
+    bf16x8 a[AO ? 1 : TM], b[BO ? 1 : TN];
+    u32x2n ah[AO ? TM : 1][2], bh[BO ? TN : 1][2];
   };
-  auto mfmas = [&](const bf16x8(&fa_)[TM], const bf16x8(&fb_)[TN]) {
+  Frag fr[2];
+  const unsigned lds0 = (unsigned)(uintptr_t)HPSGD_LPTR(nt_smem);
+  auto fragments = [&](unsigned sb, auto ks_, Frag& f) {
+    constexpr int ks = ks_;
+    if constexpr (AO) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const unsigned aa = sb + pa[i];
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.ah[i][0]) : "v"(aa), "n"(OutA::frag_step(ks, 0)));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.ah[i][1]) : "v"(aa), "n"(OutA::frag_step(ks, 1)));
+      }
+    } else {
+      const unsigned aa = sb + oa[ks];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[i]) : "v"(aa), "n"(i * 4096));
+    }
+    if constexpr (BO) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const unsigned ab = sb + pb[j];
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.bh[j][0]) : "v"(ab), "n"(OutB::frag_step(ks, 0)));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.bh[j][1]) : "v"(ab), "n"(OutB::frag_step(ks, 1)));
+      }
+    } else {
+      const unsigned ab = sb + ob[ks];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[j]) : "v"(ab), "n"(j * 4096));
+    }
+  };
+  auto mfmas = [&](const Frag& f) {
+    bf16x8 a[TM], b[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if constexpr (AO) a[i] = nt_join(f.ah[i][0], f.ah[i][1]);
+      else a[i] = f.a[i];
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if constexpr (BO) b[j] = nt_join(f.bh[j][0], f.bh[j][1]);
+      else b[j] = f.b[j];
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa_[i], fb_[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   };
   // Pipeline: the barrier that hands over tile kt+1 sits before the last quarter of tile kt's
   // MFMAs, and the first fragments of tile kt+1 are read between the two, so that the matrix
@@ -541,26 +655,29 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * IPW) : "memory");
   __builtin_amdgcn_s_barrier();  // tile 0 is in LDS
   issue(S - 1, S - 1);
-  fragments(lds0, 0, fa[0], fb[0]);
+  fragments(lds0, std::integral_constant<int, 0>{}, fr[0]);
   int stage = 0;
   for (int kt = 0; kt < nk; ++kt) {
     const unsigned sb = lds0 + stage * Sh::STAGE;
-#pragma unroll
-    for (int ks = 0; ks < 3; ++ks) {
-      fragments(sb, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
-      asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(TM + TN) : "memory");  // step ks has landed
+    auto quarter = [&](auto ks_) {
+      constexpr int ks = ks_;
+      fragments(sb, std::integral_constant<int, ks + 1>{}, fr[(ks + 1) & 1]);
+      asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(READS) : "memory");  // step ks has landed
       __builtin_amdgcn_sched_barrier(0);
-      mfmas(fa[ks & 1], fb[ks & 1]);
+      mfmas(fr[ks & 1]);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    };
+    quarter(std::integral_constant<int, 0>{});
+    quarter(std::integral_constant<int, 1>{});
+    quarter(std::integral_constant<int, 2>{});
     // this wave's reads of tile kt are complete, its loads of tile kt+1 have landed ...
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * IPW) : "memory");
     __builtin_amdgcn_s_barrier();  // ... and so are and have everyone's
     issue(stage, kt + S);          // into the buffer tile kt has left
     stage = stage + 1 == S ? 0 : stage + 1;
-    fragments(lds0 + stage * Sh::STAGE, 0, fa[0], fb[0]);
+    fragments(lds0 + stage * Sh::STAGE, std::integral_constant<int, 0>{}, fr[0]);
     __builtin_amdgcn_sched_barrier(0);
-    mfmas(fa[1], fb[1]);
+    mfmas(fr[1]);
     __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the reads issued for the tile after the last
@@ -638,10 +755,10 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   }
 }
 
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false, bool AO = false, bool BO = false>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gemm_bf16_dlx_kernel(GemmNtDesc d) {
-  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED>(d, blockIdx.x);
+  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO>(d, blockIdx.x);
 }
 
 // Two independent products of the same form in one launch: the first blocks0 workgroups (a
@@ -655,23 +772,27 @@ gemm_bf16_dlx_pair_kernel(GemmNtDesc d0, GemmNtDesc d1, unsigned blocks0) {
   dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED>(first ? d0 : d1, first ? blockIdx.x : blockIdx.x - blocks0);
 }
 
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO, bool BO>
 hipError_t launch_dlx_form(const GemmNtDesc& d, hipStream_t s) {
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
   static std::atomic<size_t> allowed{0};
-  if (const hipError_t e = allow_lds((const void*)gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED>, Sh::LDS, allowed)) return e;
+  const auto kernel = gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO>;
+  if (const hipError_t e = allow_lds((const void*)kernel, Sh::LDS, allowed)) return e;
   const int tm = (d.M + Sh::BM - 1) / Sh::BM, tn = (d.N + Sh::BN - 1) / Sh::BN;
   const int total = tm * tn * d.groups * (d.splits > 1 ? d.splits : 1);
   const int kid = (TM == 2 ? KID_GEMM_BF16_DLX128 : TM == 3 ? KID_GEMM_BF16_DLX192 : KID_GEMM_BF16_DLX256) + (COMMIT ? 1 : 0);
   KernelTimer kt(kid, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
-  hipLaunchKernelGGL((gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED>), dim3(8 * ((total + 7) / 8)),
-                     dim3(Sh::NT), Sh::LDS, s, d);
+  hipLaunchKernelGGL(kernel, dim3(8 * ((total + 7) / 8)), dim3(Sh::NT), Sh::LDS, s, d);
   return hipGetLastError();
 }
 
 template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S>
-hipError_t launch_dlx(const GemmNtDesc& d, hipStream_t s) {
-  return d.gp ? launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, true>(d, s) : launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, false>(d, s);
+hipError_t launch_dlx(const GemmNtDesc& d, int outer, hipStream_t s) {
+  if constexpr (!COMMIT)
+    if (outer == 2) return launch_dlx_form<false, WGM, WGN, TM, TN, S, false, false, true>(d, s);
+  if (outer == 3) return launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, false, true, true>(d, s);
+  return d.gp ? launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, true, false, false>(d, s)
+              : launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, false, false, false>(d, s);
 }
 
 static bool pair_desc(const GemmBf16Args& a, GemmNtDesc& d) {
@@ -731,8 +852,12 @@ bool gemm_bf16_nt_supported(const void* p, int is_bf16, long ld, long stride, in
 hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, const void* B, int b_bf16,
                                long ldb, long sB, float* C, long ldc, long sC, const float* bias,
                                long sBias, const float* win, long sWin, float lr, int M, int N, int Kd,
-                               int groups, hipStream_t s, int form, int gp, int gh, int splits, int Kall) {
+                               int groups, hipStream_t s, int form, int gp, int gh, int splits, int Kall, int outer) {
   if (M <= 0 || N <= 0 || groups <= 0) return hipSuccess;
+  // outer operands (bit 0: A, bit 1: B): B's in a plain product, or both; bf16, their rows covering whole chunks
+  if (outer && ((outer != 2 && outer != 3) || (outer == 2 && win) || !a_bf16 || !b_bf16 || gp || ldb < ((N + 7) & ~7) ||
+                (outer == 3 && lda < ((M + 7) & ~7))))
+    return hipErrorInvalidValue;
   if (form < 0 || form > 4 || (form > 1 && !(a_bf16 && b_bf16))) return hipErrorInvalidValue;
   GemmNtDesc d;
   d.A = A; d.lda = lda; d.strideA = sA;
@@ -747,7 +872,8 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
     return hipErrorInvalidValue;
   const int vgroups = groups * (splits > 1 ? splits : 1);
   if (gp && (gh < 1 || gh > gp || M > 3 * gp || !a_bf16 || !b_bf16)) return hipErrorInvalidValue;
-  if (!gemm_bf16_nt_supported(A, a_bf16, lda, sA, Kd) || !gemm_bf16_nt_supported(B, b_bf16, ldb, sB, Kd))
+  const int kd8 = outer == 3 ? 8 : Kd;  // (no operand is read in chunks along the contraction)
+  if (Kd < 1 || !gemm_bf16_nt_supported(A, a_bf16, lda, sA, kd8) || !gemm_bf16_nt_supported(B, b_bf16, ldb, sB, kd8))
     return hipErrorInvalidValue;
   const int tm = (M + NBM - 1) / NBM, tn = (N + NBN - 1) / NBN;
   const int ts = tn >= tm ? tn : tm, tf = tn >= tm ? tm : tn;
@@ -769,12 +895,16 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
   } while (0)
   if (a_bf16 && b_bf16) {
     constexpr size_t dl_smem = (size_t)NBM * (NBN + 4) * sizeof(float);  // the epilogue tile; operands need 64 KB
-#define HPSGD_DL(CM, GA)                                                                              \
-  do {                                                                                            \
-    static std::atomic<size_t> allowed{0};                                                                            \
-    if (const hipError_t e = allow_lds((const void*)gemm_bf16_dl_kernel<CM, GA>, dl_smem, allowed)) return e;         \
-    KernelTimer kt(CM ? KID_GEMM_BF16_DL_COMMIT : KID_GEMM_BF16_DL, flops, s);                    \
-    hipLaunchKernelGGL((gemm_bf16_dl_kernel<CM, GA>), grid, block, dl_smem, s, d);                    \
+    auto launch_dl = [&](auto kernel, bool cm, std::atomic<size_t>& allowed) -> hipError_t {
+      if (const hipError_t e = allow_lds((const void*)kernel, dl_smem, allowed)) return e;
+      KernelTimer kt(cm ? KID_GEMM_BF16_DL_COMMIT : KID_GEMM_BF16_DL, flops, s);
+      hipLaunchKernelGGL(kernel, grid, block, dl_smem, s, d);
+      return hipGetLastError();
+    };
+#define HPSGD_DL(...)                                              \
+  do {                                                             \
+    static std::atomic<size_t> allowed{0};                         \
+    return launch_dl(gemm_bf16_dl_kernel<__VA_ARGS__>, win != nullptr, allowed); \
   } while (0)
     // Which tile.  One 8-wave workgroup per CU with a tile 256 wide does more matrix work per
     // byte through LDS and per byte fetched, but nothing overlaps its first loads and its
@@ -801,9 +931,14 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
       if (c192 < best) { best = c192; form = 3; }
       if (c256 < best) { best = c256; form = 4; }
     }
-    if (form == 2) return win ? launch_dlx<true, 2, 4, 2, 2, 3>(d, s) : launch_dlx<false, 2, 4, 2, 2, 3>(d, s);
-    if (form == 3) return win ? launch_dlx<true, 2, 4, 3, 2, 2>(d, s) : launch_dlx<false, 2, 4, 3, 2, 2>(d, s);
-    if (form == 4) return win ? launch_dlx<true, 2, 4, 4, 2, 2>(d, s) : launch_dlx<false, 2, 4, 4, 2, 2>(d, s);
+    if (form == 2) return win ? launch_dlx<true, 2, 4, 2, 2, 3>(d, outer, s) : launch_dlx<false, 2, 4, 2, 2, 3>(d, outer, s);
+    if (form == 3) return win ? launch_dlx<true, 2, 4, 3, 2, 2>(d, outer, s) : launch_dlx<false, 2, 4, 3, 2, 2>(d, outer, s);
+    if (form == 4) return win ? launch_dlx<true, 2, 4, 4, 2, 2>(d, outer, s) : launch_dlx<false, 2, 4, 4, 2, 2>(d, outer, s);
+    if (outer == 2) HPSGD_DL(false, false, false, true);
+    if (outer == 3) {
+      if (win) HPSGD_DL(true, false, true, true);
+      else HPSGD_DL(false, false, true, true);
+    }
     if (gp) {
       if (win) HPSGD_DL(true, true);
       else HPSGD_DL(false, true);

@@ -76,7 +76,7 @@ struct hpsgd_ctx {
   Region xb, wihb, wob, dlogb;  // row-major bf16 copies: layer-0 input, W_ih, head.W, dlogits
   Region colpart;               // per block of logits rows: column sums of the logit gradient
   std::vector<Region> hsT;
-  std::vector<Region> whhT, wihTl;  // per layer: transposed bf16 W_hh and W_ih, made in the forward pass
+  std::vector<Region> whhT;     // per layer: transposed bf16 W_hh, made in the forward pass
   std::vector<Region> whhb, wihbl;  // per layer: row-major bf16 W_hh and W_ih
   // Marks left by hpsgd_prepare_replicas / hpsgd_prepare_clones, one per workspace (a schedule with
   // two generations of buffers prepares one while the other steps): the bf16 copies of these
@@ -292,7 +292,6 @@ int build_layout(hpsgd_ctx* c) {
       for (int l = 0; l < d.layers; ++l) {
         c->hsT.push_back(c->alloc(H * TB1p / 2));
         c->whhT.push_back(c->alloc((3 * H * H + 1) / 2));
-        c->wihTl.push_back(c->alloc(((l == 0 ? win0 : H) * 3 * H + 1) / 2));
         c->whhb.push_back(c->alloc((3 * H * H + 1) / 2));
         c->wihbl.push_back(c->alloc(((l == 0 ? win0 : H) * 3 * H + 1) / 2));
       }
@@ -447,11 +446,13 @@ struct GemmBatch {
   }
 };
 
-// A k-contiguous view of a GEMM operand for the NT kernel (p == nullptr: none available).
+// A view of a GEMM operand for the NT kernel (p == nullptr: none available): unit-stride along the contraction, or
+// (outer) with the contraction's index running over its rows.
 struct NtView {
   const void* p = nullptr;
   int bf16 = 0;
   long ld = 0, stride = 0;
+  int outer = 0;
 };
 
 // bf16 precision: use the NT kernel when both operands have a usable contraction-contiguous
@@ -460,12 +461,13 @@ int gemm2(hipStream_t s, int groups, int bf16, int M, int N, int Kd, const float
           int tA, const float* B, long ldb, long sB, int tB, float* C, long ldc, long sC, int epi,
           const float* aux, long sAux, const NtView& a, const NtView& b, float alpha = 0.f,
           bool require_nt = false, int gp = 0, int gh = 0) {
+  const int kd8 = a.outer ? 8 : Kd;  // (an outer A goes with an outer B: neither is read in chunks along the contraction)
   if (bf16 && a.p && b.p && (epi == EPI_STORE || epi == EPI_BIAS || epi == EPI_COMMIT) &&
-      gemm_bf16_nt_supported(a.p, a.bf16, a.ld, a.stride, Kd) &&
-      gemm_bf16_nt_supported(b.p, b.bf16, b.ld, b.stride, Kd) && ((uintptr_t)C & 3) == 0) {
+      gemm_bf16_nt_supported(a.p, a.bf16, a.ld, a.stride, kd8) &&
+      gemm_bf16_nt_supported(b.p, b.bf16, b.ld, b.stride, kd8) && ((uintptr_t)C & 3) == 0) {
     return launch_gemm_bf16_nt(a.p, a.bf16, a.ld, a.stride, b.p, b.bf16, b.ld, b.stride, C, ldc, sC,
                                epi == EPI_BIAS ? aux : nullptr, sAux, epi == EPI_COMMIT ? aux : nullptr, sAux,
-                               alpha, M, N, Kd, groups, s, 0, gp, gh) == hipSuccess
+                               alpha, M, N, Kd, groups, s, 0, gp, gh, 1, 0, a.outer | b.outer << 1) == hipSuccess
                ? HPSGD_OK
                : HPSGD_EHIP;
   }
@@ -544,11 +546,11 @@ struct ResidentScope {
 };
 
 // bf16 precision: the rounded copies of the weight matrices that a local step's GEMMs and
-// recurrence launches read (row-major, and transposed where an input gradient is needed), all
+// recurrence launches read (row-major, W_hh transposed too for the backward recurrence), all
 // made from the replicas `rin`.  what[l] / head say which copies exist; launch = false only
 // reports.  The head's copies are made when with_head is set.
 struct WeightCopies {
-  bool wih[16] = {false}, wihT[16] = {false}, whh[16] = {false}, whhT[16] = {false};
+  bool wih[16] = {false}, whh[16] = {false}, whhT[16] = {false};
   bool head = false;
 };
 
@@ -590,22 +592,18 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
     const float* Whh = rin + c->eoff(c->lidx[l].whh);
     if (pad) {
       const int wp = l > 0 ? H : c->Ep;
-      if (!copy_padded(Wih, bfreg(c->wihbl[l]), wp, 2 * (long)c->wihbl[l].stride, bfreg(c->wihTl[l]), 3 * H,
-                       2 * (long)c->wihTl[l].stride, 3 * H, wp, H, Hc, width) ||
+      if (!copy_padded(Wih, bfreg(c->wihbl[l]), wp, 2 * (long)c->wihbl[l].stride, nullptr, 0, 0, 3 * H, wp, H, Hc, width) ||
           !copy_padded(Whh, bfreg(c->whhb[l]), H, 2 * (long)c->whhb[l].stride, bfreg(c->whhT[l]), 3 * H,
                        2 * (long)c->whhT[l].stride, 3 * H, H, H, Hc, Hc))
         return HPSGD_EHIP;
-      wc.wih[l] = wc.wihT[l] = wc.whh[l] = wc.whhT[l] = true;
+      wc.wih[l] = wc.whh[l] = wc.whhT[l] = true;
       continue;
     }
     if (fused_b && ntc && width % 8 == 0) {
-      const bool need_T = l > 0 || lm;  // the input gradient of this layer is needed
-      __bf16* wT = need_T ? bfreg(c->wihTl[l]) : nullptr;
-      const long s_wT = 2 * (long)c->wihTl[l].stride, s_wb2 = 2 * (long)c->wihbl[l].stride;
-      if (cvt2_supported(Wih, 0, width, sR, bfreg(c->wihbl[l]), width, s_wb2, wT, 3 * H, s_wT, 3 * H, width)) {
-        if (!copy2(Wih, width, bfreg(c->wihbl[l]), width, s_wb2, wT, 3 * H, s_wT, 3 * H, width)) return HPSGD_EHIP;
+      const long s_wb2 = 2 * (long)c->wihbl[l].stride;
+      if (cvt2_supported(Wih, 0, width, sR, bfreg(c->wihbl[l]), width, s_wb2, nullptr, 0, 0, 3 * H, width)) {
+        if (!copy2(Wih, width, bfreg(c->wihbl[l]), width, s_wb2, nullptr, 0, 0, 3 * H, width)) return HPSGD_EHIP;
         wc.wih[l] = true;
-        wc.wihT[l] = need_T;
       }
     }
     if (fused_b) {
@@ -622,15 +620,13 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
   }
   if (with_head) {
     const size_t oW = c->eoff(c->i_head_w);
-    const long clp = (long)round_up(classes, 64);
-    const long s_wob = 2 * (long)c->wob.stride, s_woT = 2 * (long)c->woT.stride;
+    const long s_wob = 2 * (long)c->wob.stride;
     if (pad) {
-      if (!copy_padded(rin + oW, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, c->Vp, H, c->Vp, classes, Hc))
-        return HPSGD_EHIP;
+      if (!copy_padded(rin + oW, bfreg(c->wob), H, s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc)) return HPSGD_EHIP;
       wc.head = true;
     } else if (ntc && fused_b && classes % 8 == 0 &&
-        cvt2_supported(rin + oW, 0, H, sR, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, classes, H)) {
-      if (!copy2(rin + oW, H, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, classes, H)) return HPSGD_EHIP;
+               cvt2_supported(rin + oW, 0, H, sR, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)) {
+      if (!copy2(rin + oW, H, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)) return HPSGD_EHIP;
       wc.head = true;
     }
   }
@@ -800,9 +796,9 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const long TBp = (long)round_up(TB, 64), TB1p = (long)round_up(TB + B, 64);
     auto bfreg = [&](const Region& r) { return (__bf16*)reg(r); };
     bool xT_ready = false;  // the transposed bf16 layer-0 input was made in the forward pass
-    // per layer: the transposed bf16 W_hh / W_ih were made in the forward pass, in the same
-    // read as the row-major copies
-    bool whhT_ready[16] = {false}, wihT_ready[16] = {false};
+    // per layer: the transposed bf16 W_hh was made in the forward pass, in the same
+    // read as the row-major copy
+    bool whhT_ready[16] = {false};
     // fp32: the recurrence of a layer as one launch (a few for BPTT) with W_hh resident in LDS.
     // Its workgroups wait for each other through flag words in the workspace, zeroed here; pbase
     // follows what the flags read.  A given-up wait shows as NaN in the results (below).
@@ -833,21 +829,18 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const size_t oW = c->eoff(c->i_head_w), ob = c->eoff(c->i_head_b);
     const long nrp = (long)round_up(nrows, 64), clp = (long)round_up(classes, 64);
     const long s_dlb = 2 * (long)c->dlogb.stride, s_wob = wstride(c->wob);
-    const long s_woT = wstride(c->woT), s_dlT = 2 * (long)c->dlogT.stride;
     // bf16 precision with every head operand available as bf16: h of the top layer (written
-    // by its step kernels), head.W rounded once (row-major and transposed in one pass), the
-    // logit gradient emitted in bf16 by the loss kernel and transposed from there
+    // by its step kernels), head.W rounded once, the logit gradient emitted in bf16 by the loss kernel
     const bool headb =
         pad || (ntc && gru_fused_bf16_supported(H) && classes % 8 == 0 &&
-                cvt2_supported(rin + oW, 0, H, sRi, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, classes, H) &&
-                softmax_ce_bf16_supported(logits, ldl, s_log, bfreg(c->dlogb), clp, s_dlb, classes) &&
-                cvt2_supported(bfreg(c->dlogb), 1, clp, s_dlb, nullptr, 0, 0, bfreg(c->dlogT), nrp, s_dlT, nrows, classes));
+                cvt2_supported(rin + oW, 0, H, sRi, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H) &&
+                softmax_ce_bf16_supported(logits, ldl, s_log, bfreg(c->dlogb), clp, s_dlb, classes));
     // bf16 copies of `n` workers' head matrices (one model's when the replicas are still its clones)
     auto head_copy = [&](const float* W, long s_W, int n, hipStream_t st) -> hipError_t {
-      if (!pad || (Hc == H && cvt2_supported(W, 0, H, s_W, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, classes, H)))
-        return launch_cvt2(W, 0, H, s_W, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, classes, H, n, st);
+      if (!pad || (Hc == H && cvt2_supported(W, 0, H, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)))
+        return launch_cvt2(W, 0, H, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H, n, st);
       Cvt2Pack pk;
-      if (!cvt2_pack_push_padded(pk, W, Hc, s_W, bfreg(c->wob), H, s_wob, bfreg(c->woT), clp, s_woT, c->Vp, H, c->Vp, classes, Hc))
+      if (!cvt2_pack_push_padded(pk, W, Hc, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc))
         return hipErrorInvalidValue;
       return launch_cvt2_pack(pk, n, st);
     };
@@ -947,10 +940,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
             va = NtView{bfreg(c->xb), 1, width, s_xb};
             xT_ready = true;
           }
-          if (wc.wih[l]) {  // made at the start of the step, or before it
-            vb = NtView{bfreg(c->wihbl[l]), 1, width, wstride(c->wihbl[l])};
-            wihT_ready[l] = wc.wihT[l];
-          }
+          if (wc.wih[l]) vb = NtView{bfreg(c->wihbl[l]), 1, width, wstride(c->wihbl[l])};  // made at the start of the step, or before it
         }
         // The one copy of the head matrix that serves cloned replicas: beside the top layer's
         // input projection (between two resident-weight launches, when the synchronising stream
@@ -1088,9 +1078,10 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
                                      (long)c->rowloss.stride, nrows, Bc, B, classes, groups, s, reg(c->colpart), s_colpart, c->K));
       role = HPSGD_ROLE_GEMM_HEAD;
       const int Kv = (int)round_up(classes, 8);  // (zeros from `classes` on, in both operands)
-      const NtView vdl{bfreg(c->dlogb), 1, clp, s_dlb}, vwT{bfreg(c->woT), 1, clp, s_woT};
-      const NtView vdT{bfreg(c->dlogT), 1, nrp, s_dlT};
-      const NtView vhT{bfreg(c->hsT[L - 1]) + (lm ? B : T * B), 1, TB1p, 2 * (long)c->hsT[L - 1].stride};
+      // (the contractions over the classes, of the input gradient, and over the rows, of the weight gradient, run over
+      // the rows of W, of the logit gradients and of h as they lie in memory)
+      const NtView vdl{bfreg(c->dlogb), 1, clp, s_dlb}, vw{bfreg(c->wob), 1, H, s_wob, 1};
+      const NtView vdo{vdl.p, 1, clp, s_dlb, 1}, vho{va.p, 1, H, s_hb, 1};
       const WgradTarget wt = wgrad_target(c->i_head_w);
       // The head's input gradient and weight gradient need the same logit gradient and nothing of
       // each other.  The former has fewer tiles than the chip has CUs (a long contraction over
@@ -1108,20 +1099,9 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         return HPSGD_OK;
       };
       if (!side_by_side) TRY0(loss_followers());
-      // The transposed logit gradient is the weight gradient's operand only: side by side it is
-      // made on that product's stream, under the start of the input gradient.
       if (side_by_side &&
           (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_fork, 0) != hipSuccess))
         return HPSGD_EHIP;
-      role = HPSGD_ROLE_OTHER;
-      if (side_by_side) {
-        if (launch_cvt2(bfreg(c->dlogb), 1, clp, s_dlb, nullptr, 0, 0, bfreg(c->dlogT), nrp, s_dlT, nrows, Kv,
-                        groups, c->aux) != hipSuccess)
-          return HPSGD_EHIP;
-      } else {
-        HIP_TRY(launch_cvt2(bfreg(c->dlogb), 1, clp, s_dlb, nullptr, 0, 0, bfreg(c->dlogT), nrp, s_dlT, nrows,
-                            Kv, groups, s));
-      }
       role = HPSGD_ROLE_GEMM_HEAD;
       {
         TimerScope pair(c, role, s, 2);
@@ -1135,15 +1115,15 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         if (ns > 1 && n_parts > 1 && c->dxp.stride >= (size_t)n_parts * nrows * H) {
           const size_t n = (size_t)nrows * H;
           float* parts = reg(c->dxp);
-          HIP_TRY(launch_gemm_bf16_nt(vdl.p, 1, vdl.ld, vdl.stride, vwT.p, 1, vwT.ld, vwT.stride, parts, H, (long)n, nullptr, 0,
-                                      nullptr, 0, 0.f, nrows, H, part, groups, s, 0, 0, 0, n_parts, Kv));
+          HIP_TRY(launch_gemm_bf16_nt(vdl.p, 1, vdl.ld, vdl.stride, vw.p, 1, vw.ld, vw.stride, parts, H, (long)n, nullptr, 0,
+                                      nullptr, 0, 0.f, nrows, H, part, groups, s, 0, 0, 0, n_parts, Kv, vw.outer << 1));
           HIP_TRY(launch_reduce_parts(parts, n_parts, n, nullptr, 0, lm ? dx : D, (size_t)(lm ? s_dx : s_D), 0.f, 0, groups, s));
         } else {
           TRY(gemm2(s, groups, bf, nrows, H, Kv, logits, ldl, s_log, 0, rin + oW, H, sRi, 0, lm ? dx : D, H,
-                    lm ? s_dx : s_D, EPI_STORE, nullptr, 0, vdl, vwT, 0.f, true));
+                    lm ? s_dx : s_D, EPI_STORE, nullptr, 0, vdl, vw, 0.f, true));
         }
         TRY(gemm2(side_by_side ? c->aux : s, groups, bf, classes, Hc, nrows, logits, ldl, s_log, 1, feats, H, s_top,
-                  0, wt.C, Hc, wt.sC, wt.epi, wt.aux, sRi, vdT, vhT, lr, pad));
+                  0, wt.C, Hc, wt.sC, wt.epi, wt.aux, sRi, vdo, vho, lr, true));
         if (side_by_side) {
           const int saved_role = role;
           role = HPSGD_ROLE_OTHER;
@@ -1450,7 +1430,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       }
       const float* Wih = rin + c->eoff(c->lidx[l].wih);
       const bool need_dx = l > 0 || lm;
-      NtView v_dgxT, v_dghT, v_xT, v_hsT, v_wihT;
+      NtView v_dgxT, v_dghT, v_xT, v_hsT, v_wih;
       if (ntc && win % 8 == 0) {
         role = HPSGD_ROLE_OTHER;
         if (!stepT) {
@@ -1470,12 +1450,12 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
                                     win, true, groups, s));
           v_xT = NtView{bfreg(c->xT), 1, TBp, 2 * (long)c->xT.stride};
         }
-        if (need_dx && wihT_ready[l]) {
-          v_wihT = NtView{bfreg(c->wihTl[l]), 1, 3 * H, wstride(c->wihTl[l])};
+        if (need_dx && wc.wih[l] && stepT) {  // (the row-major copy: the contraction runs over its rows)
+          v_wih = NtView{bfreg(c->wihbl[l]), 1, win, wstride(c->wihbl[l]), 1};
         } else if (need_dx) {
           HIP_TRY(launch_cvt_bf16(Wih, win, sRi, bfreg(c->wihT), 3 * H, 2 * (long)c->wihT.stride, 3 * H, win, true,
                                   groups, s));
-          v_wihT = NtView{bfreg(c->wihT), 1, 3 * H, 2 * (long)c->wihT.stride};
+          v_wih = NtView{bfreg(c->wihT), 1, 3 * H, 2 * (long)c->wihT.stride};
         }
       }
       role = HPSGD_ROLE_GEMM_DX;
@@ -1487,7 +1467,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         const NtView v_dgx = use_solo_b ? NtView{bfreg(c->dghx), 1, 4 * H, 2 * (long)c->dghx.stride}
                              : stepT    ? NtView{dgxb, 1, 3 * H, s_dgb}
                                         : NtView{dgx, 0, 3 * H, s_gx};
-        dx_beside = persist_b && stepT && v_wihT.bf16 && c->aux && c->ev_fork && c->ev_join && NC == 1;
+        dx_beside = persist_b && stepT && v_wih.bf16 && c->aux && c->ev_fork && c->ev_join && NC == 1;
         // Above the first layer the input gradient is the product with the long tiles (a contraction
         // over 3H, fewer tiles than CUs): it goes first, on this stream, and the first weight
         // gradient beside it on the auxiliary one, whose many short tiles fill in around it (issued
@@ -1499,12 +1479,12 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
           if (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_fork, 0) != hipSuccess)
             return HPSGD_EHIP;
           TRY(gemm2(s, groups, bf, TB, win, 3 * H, dgx, 3 * H, s_gx, 0, Wih, win, sRi, 0, dx, win, s_dx, EPI_STORE,
-                    nullptr, 0, v_dgx, v_wihT, 0.f, persist_b));
+                    nullptr, 0, v_dgx, v_wih, 0.f, persist_b));
         } else if (dx_beside) {
           if (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_fork, 0) != hipSuccess)
             return HPSGD_EHIP;
           TRY0(gemm2(c->aux, groups, bf, TB, win, 3 * H, dgx, 3 * H, s_gx, 0, Wih, win, sRi, 0, dx, win, s_dx,
-                     EPI_STORE, nullptr, 0, v_dgx, v_wihT, 0.f, persist_b));
+                     EPI_STORE, nullptr, 0, v_dgx, v_wih, 0.f, persist_b));
           // the embedding rows need this product and nothing of the weight gradients beside it
           if (l == 0 && lm) {
             TRY0(embed_grad(c->aux));
@@ -1516,7 +1496,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
                                nullptr, 0)));
         } else {
           TRY(gemm2(s, groups, bf, TB, win, 3 * H, dgx, 3 * H, s_gx, 0, Wih, win, sRi, 0, dx, win, s_dx, EPI_STORE,
-                    nullptr, 0, v_dgx, v_wihT, 0.f, persist_b));
+                    nullptr, 0, v_dgx, v_wih, 0.f, persist_b));
         }
         above = dx;
       }

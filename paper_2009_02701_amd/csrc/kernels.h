@@ -49,7 +49,7 @@ enum KernelId : int {
   KID_GEMM_BF16_NT = 13,          // gemm_bf16_nt_kernel (an fp32 operand rounded while staged)
   KID_GEMM_F32_FAST = 14,         // gemm_f32_fast_kernel (all tile forms)
   KID_GEMM_F32 = 15,              // gemm_f32_kernel / gemm_bf16_kernel (generic fallbacks)
-  KID_CVT2 = 16,                  // cvt2_kernel (bf16 copy + transposed copy)
+  KID_CVT2 = 16,                  // cvt2_kernel, embed_bf16_kernel (bf16 copy, transposed copy or both)
   KID_SOFTMAX_CE_BF16 = 17,       // softmax_ce_bf16_rows_kernel / softmax_ce_bf16_kernel
   KID_GRU_STEP = 18,              // gru_{fwd,bwd}_step(_bf16)_kernel: one launch per time step
   KID_COMMIT_ACC = 19,            // commit_acc4_kernel / commit_acc_kernel (update + accumulate, 20 B/param)
@@ -418,10 +418,12 @@ hipError_t launch_gemm_bf16_nt(const void* A, int a_bf16, long lda, long sA, con
                                long ldb, long sB, float* C, long ldc, long sC, const float* bias,
                                long sBias, const float* win, long sWin, float lr, int M, int N, int Kd,
                                int groups, hipStream_t s, int form = 0, int gp = 0, int gh = 0, int splits = 1,
-                               int Kall = 0);
+                               int Kall = 0, int outer = 0);
 // (splits > 1, two bf16 operands, no bias and no update: the contraction of Kall in parts of Kd, a multiple
 // of 64; part p of group g writes its own C at C + (g splits + p) sC)
 // (gp != 0: the operands' rows come in up to three gate blocks of gp, C and win have gh rows per block)
+// (outer: 2 for a B that is stored [Kd][N], without an update; 3 for such a B and an A that is stored [Kd][M]; both
+// bf16, gp == 0, a pitch that covers the row rounded up to 8)
 // Two products with bf16 operands and the update epilogue (C = win - lr * A B^T) in ONE launch of
 // the 192 x 256 form: for two that neither need each other nor fill the chip alone.  Strides in
 // elements of each buffer's own type; the same conditions as launch_gemm_bf16_nt per product.
