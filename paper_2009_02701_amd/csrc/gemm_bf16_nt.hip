@@ -681,6 +681,21 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
     __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the reads issued for the tile after the last
+  // (their registers stay theirs up to here: written by a value of the epilogue before the wait, a read that is still on
+  // its way would overwrite it)
+  {
+    const Frag& f = fr[0];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if constexpr (AO) asm volatile("" ::"v"(f.ah[i][0]), "v"(f.ah[i][1]));
+      else asm volatile("" ::"v"(f.a[i]));
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if constexpr (BO) asm volatile("" ::"v"(f.bh[j][0]), "v"(f.bh[j][1]));
+      else asm volatile("" ::"v"(f.b[j]));
+    }
+  }
   // the zero loads of the tiles beyond the contraction must have landed before the operand
   // buffers become the epilogue tile
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
