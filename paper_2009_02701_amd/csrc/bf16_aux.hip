@@ -312,7 +312,7 @@ hipError_t launch_embed_bf16(const float* E, long s_E, const int32_t* tok, long 
 // partial sums of the head's bias gradient, added up by a second small kernel.  The next row's
 // loads are issued before the current row is reduced.  Columns from C up to Cw (C rounded up to 8) are
 // written as zeros; rows of the batch's padding (b >= B in row t Bp + b) have a zero gradient.
-constexpr int SMR = 8;  // the fewest rows per workgroup
+constexpr int SMR = 2;  // the fewest rows per workgroup (a row is a chain of 3 us: 72 rows x 6 workers of 6736 words 27 us in blocks of 8)
 
 template <int V4, int NT>
 __global__ void __launch_bounds__(NT)

@@ -296,14 +296,16 @@ int build_layout(hpsgd_ctx* c) {
         c->wihbl.push_back(c->alloc(((l == 0 ? win0 : H) * 3 * H + 1) / 2));
       }
       const size_t nr = lm ? TB : Bi, Vi = c->Vp;
-      c->dlogT = c->alloc(Vi * round_up(nr, 64) / 2);
+      // the transposed logit gradients, or (the head of bf16 operands) the loss kernel's column sums
+      const size_t n_dlogT = Vi * round_up(nr, 64) / 2, n_colpart = softmax_ce_bf16_row_blocks((int)nr) * round_up(Vi, 8);
+      c->dlogT = c->alloc(n_dlogT > n_colpart ? n_dlogT : n_colpart);
+      c->colpart = c->dlogT;
       c->wihT = c->alloc(wmax * 3 * H / 2);
       c->woT = c->alloc(H * round_up(classes, 64) / 2);
       c->xb = c->alloc((TB * win0 + 1) / 2);
       c->wihb = c->alloc((wmax * 3 * H + 1) / 2);
       c->wob = c->alloc((round_up(Vi, 8) * H + 1) / 2);
       c->dlogb = c->alloc((nr * round_up(classes, 64) + 1) / 2);
-      c->colpart = c->alloc(round_up((size_t)softmax_ce_bf16_row_blocks((int)nr) * round_up(Vi, 8), 4));
     }
     size_t wmax = H;
     if (lm && (size_t)c->Ep > wmax) wmax = c->Ep;
