@@ -349,7 +349,8 @@ size_t hpsgd_commit_kernel_params(const hpsgd_ctx *ctx);
  * is added up: flops (2 M N Kd per group; a recurrence launch 2 B 3H H per time step, plus the
  * products it fuses) for the contractions, bytes (each operand once) for the streaming kernels.
  * hpsgd_kernel_timer_read waits for the recorded events, returns the number of timed launches of
- * `kernel`, their summed duration in milliseconds and their summed work, and clears that kernel.
+ * `kernel` (one that holds several products counts as that many), their summed duration in milliseconds
+ * and their summed work, and clears that kernel.
  * Names are those a kernel trace shows (template arguments included where they tell forms apart). */
 enum hpsgd_kernel {
   HPSGD_KERNEL_NONE = 0,

@@ -363,15 +363,12 @@ __device__ __forceinline__ bf16x8 nt_join(u32x2n lo, u32x2n hi) {
 #define HPSGD_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // AO, BO: the operand is of the outer kind.
-template <bool COMMIT, bool GATED = false, bool AO = false, bool BO = false>
-__global__ void __launch_bounds__(NTHREADS, 2)
-gemm_bf16_dl_kernel(GemmNtDesc d) {
+template <bool COMMIT, bool GATED, bool AO, bool BO>
+__device__ __forceinline__ void dl_body(GemmNtDesc d, int g, int tile_m, int tile_n) {
   extern __shared__ __attribute__((aligned(16))) unsigned char nt_smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave & 1, wn = wave >> 1;
   const int lrow = lane & 31, lk = lane >> 5;
-  int g, tile_m, tile_n;
-  if (!nt_tile(d, g, tile_m, tile_n)) return;
   const int m0 = tile_m * NBM, n0 = tile_n * NBN;
   const __bf16 *A, *B;
   nt_part<AO, BO>(d, g, A, B);
@@ -453,6 +450,14 @@ gemm_bf16_dl_kernel(GemmNtDesc d) {
   }
   __syncthreads();  // the operand buffers become the epilogue tile
   nt_epilogue<COMMIT, GATED>(d, acc, nt_smem, g, m0, n0);
+}
+
+template <bool COMMIT, bool GATED = false, bool AO = false, bool BO = false>
+__global__ void __launch_bounds__(NTHREADS, 2)
+gemm_bf16_dl_kernel(GemmNtDesc d) {
+  int g, tile_m, tile_n;
+  if (!nt_tile(d, g, tile_m, tile_n)) return;
+  dl_body<COMMIT, GATED, AO, BO>(d, g, tile_m, tile_n);
 }
 
 // ---------------------------------------------------------------------------- one workgroup per CU
@@ -787,6 +792,29 @@ gemm_bf16_dlx_pair_kernel(GemmNtDesc d0, GemmNtDesc d1, unsigned blocks0) {
   dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED>(first ? d0 : d1, first ? blockIdx.x : blockIdx.x - blocks0);
 }
 
+// Up to three products that need nothing of each other in one launch of 128 x 128 tiles, of any of the kinds that a
+// layer's backward pass has: product i owns the workgroups blk0[i] .. blk0[i + 1] - 1.
+struct GemmNtPack {
+  GemmNtDesc d[3];
+  unsigned blk0[4];
+  int kind[3], n;
+};
+__global__ void __launch_bounds__(NTHREADS, 2)
+gemm_bf16_multi_kernel(GemmNtPack pk) {
+  int i = 0;
+  while (i + 1 < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
+  const GemmNtDesc& d = pk.d[i];
+  int g, tile_m, tile_n;
+  if (!dlx_tile<NBM, NBN>(d, blockIdx.x - pk.blk0[i], g, tile_m, tile_n)) return;
+  switch (pk.kind[i]) {
+    case 0: dl_body<false, false, false, true>(d, g, tile_m, tile_n); break;
+    case 1: dl_body<false, true, false, false>(d, g, tile_m, tile_n); break;
+    case 2: dl_body<true, true, false, false>(d, g, tile_m, tile_n); break;
+    case 3: dl_body<false, false, true, true>(d, g, tile_m, tile_n); break;
+    default: dl_body<true, false, true, true>(d, g, tile_m, tile_n); break;
+  }
+}
+
 template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO, bool BO>
 hipError_t launch_dlx_form(const GemmNtDesc& d, hipStream_t s) {
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
@@ -810,9 +838,15 @@ hipError_t launch_dlx(const GemmNtDesc& d, int outer, hipStream_t s) {
               : launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, false, false, false>(d, s);
 }
 
-static bool pair_desc(const GemmBf16Args& a, GemmNtDesc& d) {
-  if (a.M <= 0 || a.N <= 0 || a.groups <= 0 || !a.win || !a.C) return false;
-  if (!gemm_bf16_nt_supported(a.A, 1, a.lda, a.sA, a.Kd) || !gemm_bf16_nt_supported(a.B, 1, a.ldb, a.sB, a.Kd)) return false;
+static bool args_desc(const GemmBf16Args& a, GemmNtDesc& d) {
+  const int kd8 = a.outer == 3 ? 8 : a.Kd;
+  if (a.M <= 0 || a.N <= 0 || a.groups <= 0 || !a.C || a.Kd < 1) return false;
+  if (!gemm_bf16_nt_supported(a.A, 1, a.lda, a.sA, kd8) || !gemm_bf16_nt_supported(a.B, 1, a.ldb, a.sB, kd8)) return false;
+  if (a.outer && (a.gp || (a.outer != 2 && a.outer != 3) || (a.outer == 2 && a.win) || a.ldb < ((a.N + 7) & ~7) ||
+                  (a.outer == 3 && a.lda < ((a.M + 7) & ~7))))
+    return false;
+  if (a.splits > 1 && (a.win || a.Kd % 64 != 0 || a.Kall <= (a.splits - 1) * a.Kd || a.Kall % 8 != 0)) return false;
+  if (a.gp && (a.gh < 1 || a.gh > a.gp || a.M > 3 * a.gp)) return false;
   d.A = a.A; d.lda = a.lda; d.strideA = a.sA;
   d.B = a.B; d.ldb = a.ldb; d.strideB = a.sB;
   d.C = a.C; d.ldc = a.ldc; d.strideC = a.sC;
@@ -820,13 +854,57 @@ static bool pair_desc(const GemmBf16Args& a, GemmNtDesc& d) {
   d.win = a.win; d.strideWin = a.sWin; d.lr = a.lr;
   d.M = a.M; d.N = a.N; d.Kd = a.Kd; d.groups = a.groups;
   d.gp = a.gp; d.gh = a.gh;
-  d.splits = 1; d.Kall = 0;
+  d.splits = a.splits; d.Kall = a.Kall;
   return true;
 }
+static bool pair_desc(const GemmBf16Args& a, GemmNtDesc& d) { return a.win && !a.outer && a.splits <= 1 && args_desc(a, d); }
 
 bool gemm_bf16_update_pair_supported(const GemmBf16Args& p0, const GemmBf16Args& p1) {
   GemmNtDesc d;
   return pair_desc(p0, d) && pair_desc(p1, d);
+}
+
+static long args_tiles(const GemmBf16Args& a) {
+  return (long)((a.M + NBM - 1) / NBM) * ((a.N + NBN - 1) / NBN) * a.groups * (a.splits > 1 ? a.splits : 1);
+}
+
+// A layer's products together up to 2048 tiles of 128 x 128 (four rounds of the chip): apart, on two streams, each costs
+// a launch and the streams an event in each direction, and each leaves its last round's CUs idle, which is more than
+// the larger tiles of the launches by themselves save.  A round or local step, together up to none / 512 / 2048 / 4096:
+// 6736 words, H = 104, 72 rows, 6 workers 336 / 201 / 201 / 201 us; 9999 words, H = 200, 480 rows, 4 workers
+// 567 / 501 / 467 / 467; H = 650, 700 rows, 4 workers 1441 / 1427 / 1365 / 1359; 10 000 words, H = 1024, 1120 rows,
+// 8 workers 2294 / 2268 / 2266 / 2485; 5840 words, H = 352, 1728 rows, 3 workers - / 812 / 826 / 826.
+bool gemm_bf16_multi_pays(const GemmBf16Args* a, int n) {
+  GemmNtDesc d;
+  long t = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!args_desc(a[i], d)) return false;
+    t += args_tiles(a[i]);
+  }
+  return n >= 1 && n <= 3 && t <= 2048;
+}
+
+hipError_t launch_gemm_bf16_multi(const GemmBf16Args* a, int n, hipStream_t s) {
+  if (n < 1 || n > 3) return hipErrorInvalidValue;
+  GemmNtPack pk;
+  pk.n = n;
+  pk.blk0[0] = 0;
+  double flops = 0.;
+  bool commit = false;
+  for (int i = 0; i < n; ++i) {
+    if (!args_desc(a[i], pk.d[i])) return hipErrorInvalidValue;
+    if (!a[i].outer && !a[i].gp) pk.d[i].gp = pk.d[i].gh = a[i].M;  // (one block of all rows: rows as they are)
+    pk.kind[i] = a[i].outer == 2 ? 0 : a[i].outer == 3 ? (a[i].win ? 4 : 3) : (a[i].win ? 2 : 1);
+    pk.blk0[i + 1] = pk.blk0[i] + (unsigned)(8 * ((args_tiles(a[i]) + 7) / 8));
+    flops += 2.0 * a[i].M * a[i].N * (double)(a[i].splits > 1 ? a[i].Kall : a[i].Kd) * a[i].groups;
+    commit = commit || a[i].win;
+  }
+  constexpr size_t smem = (size_t)NBM * (NBN + 4) * sizeof(float);
+  static std::atomic<size_t> allowed{0};
+  if (const hipError_t e = allow_lds((const void*)gemm_bf16_multi_kernel, smem, allowed)) return e;
+  KernelTimer kt(commit ? KID_GEMM_BF16_DL_COMMIT : KID_GEMM_BF16_DL, flops, s, n);
+  hipLaunchKernelGGL(gemm_bf16_multi_kernel, dim3(pk.blk0[n]), dim3(NTHREADS), smem, s, pk);
+  return hipGetLastError();
 }
 
 template <bool GATED>

@@ -144,7 +144,7 @@ struct hpsgd_ctx {
   long role_launches[HPSGD_ROLE_COUNT] = {0};
   // per-kernel timing: event pairs recorded by the launchers themselves (KernelTimer)
   unsigned kernel_mask = 0;
-  struct KStamp { int kid; double work; hipEvent_t a, b; };
+  struct KStamp { int kid; double work; hipEvent_t a, b; int launches; };
   std::vector<KStamp> kstamps;
   double kernel_ms[HPSGD_KERNEL_COUNT] = {0}, kernel_work[HPSGD_KERNEL_COUNT] = {0};
   long kernel_launches[HPSGD_KERNEL_COUNT] = {0};
@@ -850,7 +850,12 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // unless they were made before the step
     WeightCopies wc;
     role = HPSGD_ROLE_OTHER;
-    TRY(weight_copies(c, rin, sRi, k0, own_set ? 1 : groups, ws, s, !prepared, false, wc));
+    // (clones with a small head: that copy too.  By itself it goes to the second stream, with an event in each direction,
+    // which costs more than its bytes.  1.4 M elements: 10 us either way, in the pack without the events; 92 M: 31 us, in
+    // the shade of the top layer's input projection.)
+    const bool head_with = headb && own_set && (double)classes * Hc <= 4e6;
+    TRY(weight_copies(c, rin, sRi, k0, own_set ? 1 : groups, ws, s, !prepared, head_with, wc));
+    const bool head_made = head_done || (head_with && wc.head);
     // ---- forward
     const float* lin = (const float*)x;
     long s_lin = (long)TB * d.input;
@@ -947,7 +952,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         // The one copy of the head matrix that serves cloned replicas: beside the top layer's
         // input projection (between two resident-weight launches, when the synchronising stream
         // has finished), joined before the recurrence starts.
-        const bool early = l == L - 1 && l > 0 && headb && !head_done && head_src && c->aux && c->ev_fork && c->ev_join;
+        const bool early = l == L - 1 && l > 0 && headb && !head_made && head_src && c->aux && c->ev_fork && c->ev_join;
         if (early) {
           if (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_fork, 0) != hipSuccess ||
               head_copy(head_src + oW, 0, 1, c->aux) != hipSuccess ||
@@ -1056,7 +1061,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       // the copy has the memory system to itself (beside a resident-weight launch it takes 2.3
       // times as long and slows that launch by more than it takes alone; at the start of the step it
       // shares the bandwidth with the merge and the clone)
-      if (head_done || head_early) {
+      if (head_made || head_early) {
         // made with the layers' copies, before the step, or beside the top layer's input projection
       } else if (head_src) {  // the replicas are clones of one model: one copy of its head matrix serves all workers
         HIP_TRY(head_copy(head_src + oW, 0, 1, s));
@@ -1090,49 +1095,63 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       // the classes): with an auxiliary stream the two run side by side and the tiles of the
       // weight gradient fill the CUs the other leaves idle.  One event pair brackets both.
       const bool side_by_side = c->aux && c->ev_fork && c->ev_join;
-      // What needs the loss kernel's results only (the mean loss, the bias gradient from its
-      // partial column sums): side by side, the weight gradient outlasts the input gradient, and
-      // these follow the latter on this stream while the other stream is still busy.
-      auto loss_followers = [&]() -> int {
-        if (loss_out)
-          HIP_TRY(launch_loss_mean(rowloss, (long)c->rowloss.stride, loss_out, nrows, groups, s, lm ? TBc : Bc));
-        HIP_TRY(launch_reduce_parts(reg(c->colpart), n_colparts, (size_t)classes, nullptr, 0,
-                                    grad + ob, (size_t)sG, 0.f, 0, groups, s, (size_t)colpitch));
-        return HPSGD_OK;
-      };
-      if (!side_by_side) TRY0(loss_followers());
-      if (side_by_side &&
+      // in parts where the product's tiles leave the chip idle (M = 480, N = 224, 10 000 classes, K = 4:
+      // 32 tiles, 124 us in one piece)
+      const int ns = dx_splits(nrows, H, Kv, c->K, 128, 512), part = (Kv / 64 + ns) / ns * 64;
+      const int n_parts = (Kv + part - 1) / part;
+      const size_t n_dx = (size_t)nrows * H;
+      const bool in_parts = ns > 1 && n_parts > 1 && c->dxp.stride >= (size_t)n_parts * n_dx;
+      float* dfeat = lm ? dx : D;
+      const long s_dfeat = lm ? s_dx : s_D;
+      // (bf16 operands only: the fp32 head matrix may be updated in place beside the input gradient)
+      const GemmBf16Args jobs[2] = {
+          {vdl.p, vdl.ld, vdl.stride, vw.p, vw.ld, vw.stride, in_parts ? reg(c->dxp) : dfeat, H, in_parts ? (long)n_dx : s_dfeat,
+           nullptr, 0, 0.f, nrows, H, in_parts ? part : Kv, groups, 0, 0, 2, in_parts ? n_parts : 1, in_parts ? Kv : 0},
+          {vdo.p, vdo.ld, vdo.stride, vho.p, vho.ld, vho.stride, wt.C, Hc, wt.sC, wt.aux, sRi, lr, classes, Hc, nrows, groups, 0, 0, 3}};
+      const bool together = gemm_bf16_multi_pays(jobs, 2);
+      const bool fork = side_by_side && !together;
+      if (fork &&
           (hipEventRecord(c->ev_fork, s) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_fork, 0) != hipSuccess))
         return HPSGD_EHIP;
-      role = HPSGD_ROLE_GEMM_HEAD;
       {
-        TimerScope pair(c, role, s, 2);
+        TimerScope pair(c, role, s, together ? 1 : 2);
         const bool nested = c->timer_nested;
         c->timer_nested = c->timer_nested || pair.active();
-        // (bf16 views only: the fp32 head matrix may be updated in place by the GEMM beside this one)
-        // in parts where the product's tiles leave the chip idle (M = 480, N = 224, 10 000 classes, K = 4:
-        // 32 tiles, 124 us in one piece)
-        const int ns = dx_splits(nrows, H, Kv, c->K, 128, 512), part = (Kv / 64 + ns) / ns * 64;
-        const int n_parts = (Kv + part - 1) / part;
-        if (ns > 1 && n_parts > 1 && c->dxp.stride >= (size_t)n_parts * nrows * H) {
-          const size_t n = (size_t)nrows * H;
-          float* parts = reg(c->dxp);
-          HIP_TRY(launch_gemm_bf16_nt(vdl.p, 1, vdl.ld, vdl.stride, vw.p, 1, vw.ld, vw.stride, parts, H, (long)n, nullptr, 0,
+        if (together) {
+          HIP_TRY(launch_gemm_bf16_multi(jobs, 2, s));
+        } else if (in_parts) {
+          HIP_TRY(launch_gemm_bf16_nt(vdl.p, 1, vdl.ld, vdl.stride, vw.p, 1, vw.ld, vw.stride, reg(c->dxp), H, (long)n_dx, nullptr, 0,
                                       nullptr, 0, 0.f, nrows, H, part, groups, s, 0, 0, 0, n_parts, Kv, vw.outer << 1));
-          HIP_TRY(launch_reduce_parts(parts, n_parts, n, nullptr, 0, lm ? dx : D, (size_t)(lm ? s_dx : s_D), 0.f, 0, groups, s));
         } else {
-          TRY(gemm2(s, groups, bf, nrows, H, Kv, logits, ldl, s_log, 0, rin + oW, H, sRi, 0, lm ? dx : D, H,
-                    lm ? s_dx : s_D, EPI_STORE, nullptr, 0, vdl, vw, 0.f, true));
+          TRY(gemm2(s, groups, bf, nrows, H, Kv, logits, ldl, s_log, 0, rin + oW, H, sRi, 0, dfeat, H, s_dfeat, EPI_STORE,
+                    nullptr, 0, vdl, vw, 0.f, true));
         }
-        TRY(gemm2(side_by_side ? c->aux : s, groups, bf, classes, Hc, nrows, logits, ldl, s_log, 1, feats, H, s_top,
-                  0, wt.C, Hc, wt.sC, wt.epi, wt.aux, sRi, vdo, vho, lr, true));
-        if (side_by_side) {
+        if (!together)
+          TRY(gemm2(fork ? c->aux : s, groups, bf, classes, Hc, nrows, logits, ldl, s_log, 1, feats, H, s_top,
+                    0, wt.C, Hc, wt.sC, wt.epi, wt.aux, sRi, vdo, vho, lr, true));
+        // What is added up from parts, and the mean loss, in one launch: the input gradient, and the bias gradient
+        // from the loss kernel's column sums, with its update unless the gradients are accumulated as well.
+        // (Side by side the weight gradient outlasts the input gradient: this runs beside it.)
+        {
           const int saved_role = role;
           role = HPSGD_ROLE_OTHER;
-          TRY0(loss_followers());
+          ReducePack rp;
+          rp.n = 0;
+          rp.blk0[0] = 0;
+          rp.lr = lr;
+          if (loss_out) {
+            rp.rowloss = rowloss; rp.s_rowloss = (long)c->rowloss.stride;
+            rp.loss = loss_out; rp.rows = nrows; rp.count = lm ? TBc : Bc;
+          }
+          if (!acc) fused_commit[c->i_head_b] = 1;
+          if ((in_parts && !reduce_pack_push(rp, reg(c->dxp), n_parts, n_dx, nullptr, 0, dfeat, (size_t)s_dfeat, 0)) ||
+              !reduce_pack_push(rp, reg(c->colpart), n_colparts, (size_t)classes, acc ? nullptr : rin + ob, (size_t)sRi,
+                                acc ? grad + ob : rout + ob, (size_t)(acc ? sG : sR), acc ? 0 : 1, (size_t)colpitch))
+            return HPSGD_ESHAPE;
+          HIP_TRY(launch_reduce_pack(rp, groups, s));
           role = saved_role;
         }
-        if (side_by_side &&
+        if (fork &&
             (hipEventRecord(c->ev_join, c->aux) != hipSuccess || hipStreamWaitEvent(s, c->ev_join, 0) != hipSuccess))
           return HPSGD_EHIP;
         c->timer_nested = nested;
@@ -1460,12 +1479,32 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
           v_wih = NtView{bfreg(c->wihT), 1, 3 * H, 2 * (long)c->wihT.stride};
         }
       }
+      // bf16 operands and few tiles: the input gradient (from bf16 copies, not from the weights that the others update in
+      // place) and both weight gradients in one launch
+      bool together = false;
+      if (persist_b && stepT && NC == 1 && v_dgxT.bf16 && v_dghT.bf16 && v_xT.bf16 && v_hsT.bf16 && (!need_dx || v_wih.outer)) {
+        const WgradTarget wi = wgrad_target(c->lidx[l].wih), wh = wgrad_target(c->lidx[l].whh);
+        const GemmBf16Args jobs[3] = {
+            {v_dghT.p, v_dghT.ld, v_dghT.stride, v_hsT.p, v_hsT.ld, v_hsT.stride, wh.C, Hc, wh.sC, wh.aux, sRi, lr, 3 * H, Hc, TB, groups,
+             gp, gh},
+            {v_dgxT.p, v_dgxT.ld, v_dgxT.stride, v_xT.p, v_xT.ld, v_xT.stride, wi.C, winc, wi.sC, wi.aux, sRi, lr, 3 * H, winc, TB, groups,
+             gp, gh},
+            {use_solo_b ? (const void*)bfreg(c->dghx) : dgxb, use_solo_b ? 4L * H : 3L * H, use_solo_b ? 2 * (long)c->dghx.stride : s_dgb,
+             v_wih.p, v_wih.ld, v_wih.stride, dx, win, s_dx, nullptr, 0, 0.f, TB, win, 3 * H, groups, 0, 0, 2}};
+        const int n_jobs = need_dx ? 3 : 2;
+        if (gemm_bf16_multi_pays(jobs, n_jobs)) {
+          role = HPSGD_ROLE_GEMM_WGRAD;
+          HIP_TRY(launch_gemm_bf16_multi(jobs, n_jobs, s));
+          together = true;
+          if (need_dx) above = dx;
+        }
+      }
       role = HPSGD_ROLE_GEMM_DX;
       // bf16 operands: the input gradient reads only bf16 copies (not the weights the gradient
       // GEMMs below update in place) and has fewer tiles than the chip has CUs: with an auxiliary
       // stream it runs beside the layer's weight-gradient GEMMs (its launch is then not timed)
       bool dx_beside = false, swap = false;
-      if (need_dx) {  // reads W_ih: before its update
+      if (need_dx && !together) {  // reads W_ih: before its update
         const NtView v_dgx = use_solo_b ? NtView{bfreg(c->dghx), 1, 4 * H, 2 * (long)c->dghx.stride}
                              : stepT    ? NtView{dgxb, 1, 3 * H, s_dgb}
                                         : NtView{dgx, 0, 3 * H, s_gx};
@@ -1503,7 +1542,9 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         above = dx;
       }
       role = HPSGD_ROLE_GEMM_WGRAD;
-      if (NC > 1) {
+      if (together) {
+        // issued above
+      } else if (NC > 1) {
         TRY(gb.flush());
         // join, then the first chunk's share on top of what the aux stream accumulated
         if (hipEventRecord(c->ev_join, c->aux) != hipSuccess || hipStreamWaitEvent(s, c->ev_join, 0) != hipSuccess)
@@ -1698,12 +1739,12 @@ int check_step_args(const hpsgd_ctx* c, const float* rin, float* rout, size_t rs
 namespace hpsgd {
 static_assert((int)KID_COUNT == (int)HPSGD_KERNEL_COUNT, "kernel ids of kernels.h and hpsgd.h differ");
 
-KernelTimer::KernelTimer(int kid, double work, hipStream_t s) : ctx_(nullptr), idx_(-1), s_(s) {
+KernelTimer::KernelTimer(int kid, double work, hipStream_t s, int launches) : ctx_(nullptr), idx_(-1), s_(s) {
   hpsgd_ctx* c = t_step_ctx;
   if (!c || kid <= 0 || kid >= KID_COUNT || !(c->kernel_mask & (1u << kid))) return;
   hipEvent_t a = TimerScope::get(c), b = TimerScope::get(c);
   if (!a || !b) return;
-  c->kstamps.push_back({kid, work, a, b});
+  c->kstamps.push_back({kid, work, a, b, launches});
   ctx_ = c;
   idx_ = (int)c->kstamps.size() - 1;
   (void)hipEventRecord(a, s);
@@ -2139,7 +2180,7 @@ int hpsgd_kernel_timer_read(hpsgd_ctx* ctx, int kernel, long* launches, double* 
     if (hipEventElapsedTime(&ms, st.a, st.b) != hipSuccess) return HPSGD_EHIP;
     ctx->kernel_ms[st.kid] += ms;
     ctx->kernel_work[st.kid] += st.work;
-    ctx->kernel_launches[st.kid] += 1;
+    ctx->kernel_launches[st.kid] += st.launches;
     ctx->free_events.push_back(st.a);
     ctx->free_events.push_back(st.b);
   }

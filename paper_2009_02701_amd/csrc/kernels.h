@@ -58,7 +58,8 @@ enum KernelId : int {
   KID_COUNT = 22
 };
 struct KernelTimer {
-  KernelTimer(int kid, double work, hipStream_t s);
+  // launches: what the launch counts as (the products it holds, where it holds several)
+  KernelTimer(int kid, double work, hipStream_t s, int launches = 1);
   ~KernelTimer();
   KernelTimer(const KernelTimer&) = delete;
   KernelTimer& operator=(const KernelTimer&) = delete;
@@ -301,6 +302,11 @@ struct ReducePack {
   unsigned blk0[MAXSEG + 1];
   int n;
   float lr;
+  // beside the sums (nullptr: none): loss[g] = the sum of group g's `rows` row losses over `count`
+  const float* rowloss = nullptr;
+  long s_rowloss = 0;
+  float* loss = nullptr;
+  int rows = 0, count = 0;
 };
 bool reduce_pack_push(ReducePack& pk, const float* parts, int n_parts, size_t n, const float* in, size_t s_in,
                       float* out, size_t s_out, int commit, size_t pitch = 0);
@@ -435,7 +441,11 @@ struct GemmBf16Args {
   float lr;
   int M, N, Kd, groups;
   int gp, gh;
+  int outer = 0, splits = 1, Kall = 0;  // (the pair: as they are here)
 };
+// Up to three products with bf16 operands, as updates (win) or plain, in one launch of 128 x 128 tiles
+bool gemm_bf16_multi_pays(const GemmBf16Args* p, int n);
+hipError_t launch_gemm_bf16_multi(const GemmBf16Args* p, int n, hipStream_t s);
 bool gemm_bf16_update_pair_supported(const GemmBf16Args& p0, const GemmBf16Args& p1);
 hipError_t launch_gemm_bf16_update_pair(const GemmBf16Args& p0, const GemmBf16Args& p1, hipStream_t s);
 

@@ -386,6 +386,20 @@ reduce_parts_kernel(const float* __restrict__ parts, int n_parts, size_t n4, con
 // a launch): segment i owns the grid columns blk0[i] .. blk0[i+1]-1.  A segment whose length or buffers
 // are not in whole 16-byte words is added one element per thread.
 __global__ void __launch_bounds__(kThreads) reduce_parts_multi_kernel(ReducePack pk) {
+  if (pk.rowloss && blockIdx.x == gridDim.x - 1) {  // the mean loss, in a fixed order
+    __shared__ float red[kThreads];
+    const int tid = threadIdx.x;
+    float v = 0.f;
+    for (int i = tid; i < pk.rows; i += kThreads) v += pk.rowloss[blockIdx.y * pk.s_rowloss + i];
+    red[tid] = v;
+    __syncthreads();
+    for (int o = kThreads / 2; o > 0; o >>= 1) {
+      if (tid < o) red[tid] += red[tid + o];
+      __syncthreads();
+    }
+    if (tid == 0) pk.loss[blockIdx.y] = red[0] / (float)pk.count;
+    return;
+  }
   int sgi = 0;
 #pragma unroll
   for (int i = 1; i < ReducePack::MAXSEG; ++i)
@@ -433,8 +447,9 @@ bool reduce_pack_push(ReducePack& pk, const float* parts, int n_parts, size_t n,
 }
 
 hipError_t launch_reduce_pack(const ReducePack& pk, int groups, hipStream_t s) {
-  if (pk.n == 0 || groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_parts_multi_kernel, dim3(pk.blk0[pk.n], groups), dim3(kThreads), 0, s, pk);
+  const unsigned blocks = pk.blk0[pk.n] + (pk.rowloss ? 1u : 0u);
+  if (blocks == 0 || groups <= 0) return hipSuccess;
+  hipLaunchKernelGGL(reduce_parts_multi_kernel, dim3(blocks, groups), dim3(kThreads), 0, s, pk);
   return hipGetLastError();
 }
 
