@@ -65,33 +65,51 @@ __device__ __forceinline__ void cvt2_tile(const TIN* __restrict__ src, long ld_i
 }
 
 // The same for a source of any alignment whose rows come in blocks of gh (gp in the copies) and whose Cs
-// columns are padded to C: 4-byte loads, and zeros where the source has nothing.
+// columns are padded to C (C % 4 == 0): zeros where the source has nothing.  16-byte loads at 4-byte boundaries, the last
+// of a row from its last four values, shifted into place.  (H = 650, K = 4, the layers' weights and the head's: 49 and
+// 53 us in 4-byte loads and 2-byte stores, 38 and 37 now, 31 and 36 at the rate of a large copy.)
 __device__ __forceinline__ void cvt2_tile_padded(const float* __restrict__ src, long ld_in, __bf16* __restrict__ dst_p, long ld_p,
                                                  __bf16* __restrict__ dst_t, long ld_t, int R, int C, int gp, int gh, int Cs,
                                                  int c0, int r0, __bf16 (&tile)[64][72]) {
+  typedef float f4u_a __attribute__((ext_vector_type(4), aligned(4)));
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float v[4][4];
+  const int c = c0 + 4 * tx, cl = max(min(c, Cs - 4), 0), sh = c - cl;
+  const float* p[4];
+  bool rok[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = r0 + ty + 16 * i, q = r / gp, j = r - q * gp;
-    const float* p = src + (long)(q * gh + min(j, gh - 1)) * ld_in;
-    const bool rok = r < R && j < gh;
+    rok[i] = r < R && j < gh;
+    p[i] = src + (rok[i] ? (long)(q * gh + j) * ld_in : 0) + cl;
+  }
+  float v[4][4];
+  if (Cs >= 4) {  // (uniform)
+    f4u_a w[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      // (a column 16 lanes further per element: a load instruction reads 64 contiguous bytes of 4 rows)
-      const int c = c0 + tx + 16 * e;
-      v[i][e] = rok && c < Cs ? p[c] : 0.f;
+    for (int i = 0; i < 4; ++i) w[i] = __builtin_nontemporal_load(reinterpret_cast<const f4u_a*>(p[i]));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i][0] = sh == 0 ? w[i].x : sh == 1 ? w[i].y : sh == 2 ? w[i].z : w[i].w;
+      v[i][1] = sh == 0 ? w[i].y : sh == 1 ? w[i].z : w[i].w;
+      v[i][2] = sh == 0 ? w[i].z : w[i].w;
+      v[i][3] = w[i].w;
     }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i][e] = p[i][min(c + e, Cs - 1) - cl];
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int rl = ty + 16 * i, r = r0 + rl;
+    bf16x4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int c = c0 + tx + 16 * e;
-      const __bf16 b = (__bf16)v[i][e];
-      if (dst_p && r < R && c < C) dst_p[(long)r * ld_p + c] = b;
-      if (dst_t) tile[tx + 16 * e][rl] = b;
+    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(rok[i] && c + e < Cs ? v[i][e] : 0.f);
+    if (dst_p && r < R && c < C) __builtin_nontemporal_store(o, reinterpret_cast<bf16x4*>(dst_p + (long)r * ld_p + c));
+    if (dst_t) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tile[4 * tx + e][rl] = o[e];
     }
   }
   if (!dst_t) return;
@@ -170,7 +188,8 @@ bool cvt2_pack_push(Cvt2Pack& p, const float* in, long ld_in, long s_in, void* o
 bool cvt2_pack_push_padded(Cvt2Pack& p, const float* in, long ld_in, long s_in, void* out_p, long ld_p, long s_p,
                            void* out_t, long ld_t, long s_t, int R, int C, int gp, int gh, int Cs) {
   if (p.n >= Cvt2Pack::MAX || R <= 0 || C <= 0) return false;
-  if (gp && (gh < 1 || gh > gp || Cs < 1 || Cs > C || R % 8 != 0 ||
+  if (gp && (gh < 1 || gh > gp || Cs < 1 || Cs > C || R % 8 != 0 || C % 4 != 0 ||
+             (out_p && (((uintptr_t)out_p & 7) != 0 || ld_p % 4 != 0 || s_p % 4 != 0)) ||
              (out_t && (((uintptr_t)out_t & 15) != 0 || ld_t % 8 != 0 || s_t % 8 != 0))))
     return false;
   Cvt2Job& q = p.job[p.n];
