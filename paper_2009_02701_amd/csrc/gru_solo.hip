@@ -464,29 +464,31 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
 
 // ---------------------------------------------------------------------------- bf16 operands, H <= 256
 // The same idea on bf16 copies of W_hh and h (fp32 accumulation, cell math and saved values): a workgroup owns
-// 8 batch rows and all units (HP = 16 HB, a multiple of 32), v_mfma_f32_16x16x32_bf16.  W_hh of 256 units is
+// 4 or 8 batch rows and all units (HP = 16 HB, a multiple of 32), v_mfma_f32_16x16x32_bf16.  W_hh of 256 units is
 // 393 KB: a wave holds UB = 1 (HP <= 128) or 2 blocks of 16 units, and for two blocks the third gate
-// (backward: the last chunks) lives in LDS, each wave reading back only its own fragments.  Half of an
-// instruction's 16 rows are unused: the matrix work of a step is 0.6 us at 256 units all the same, and 8 rows
-// halve the cell math, which is as long (two outputs per lane and block).
-// Row 4*lg + v of a product, v < 2, is batch row r0 + 2*lg + v: a lane's two values are neighbours in the
-// transposed copies and leave as one 4-byte store.  Rows with v >= 2 repeat row v = 1 and are ignored.
+// (backward: the last chunks) lives in LDS, each wave reading back only its own fragments.  Most of an
+// instruction's 16 rows are unused: the matrix work of a step is 0.6 us at 256 units all the same, while the cell
+// math, which is longer, goes by the rows (V = 1 or 2 outputs per lane and block).
+// Row 4*lg + v of a product, v < V, is batch row r0 + V*lg + v: a lane's two values of 8 rows are neighbours in the
+// transposed copies and leave as one 4-byte store.  Rows with v >= V repeat another and are ignored.
 // The forward launch writes h in bf16, row-major and transposed, h_0 = 0 included; saved gates and h_{t-1} are
 // kept in lane order.  The backward launch writes the gate gradients row-major only, through the LDS tile of the
 // next step's operand: 16 bytes per (unit, step) of a transposed copy is a cache line per lane group, and six of
 // those per output made the launch 2.5 times as long as its chain (H = 224: 4.5 us per step); a launch
 // behind it transposes all steps at once.
-// Bound by the chain of a step: product, cell math, barrier.  Per step, with B = 32 and four workers:
-//   H           64    96   128   160   192   224   256
-//   forward   0.61  0.78  1.01  1.55  1.77  2.28  2.40 us
-//   backward  0.63  0.99  1.09  1.33  1.79  2.12  2.51 us
-// (gates of the hardware's exp2 and reciprocal; a forward step with those of the fp32 launches, EX, takes 0.4 us
+// Bound by the chain of a step: product, cell math, barrier.  Per step of 40, launch included, B = 32 and four workers:
+//   H                   64    96   128   160   192   224   256
+//   forward   8 rows  0.71  0.81  1.15  1.71  2.00  2.36  2.67 us
+//             4 rows  0.65  0.68  0.86  1.20  1.50  1.61  1.91 us
+//   backward  8 rows  0.58  0.99  1.05  1.34  1.79  2.10  2.53 us
+//             4 rows  0.52  0.58  0.88  0.96  1.16  1.66  2.03 us
+// (gates of the hardware's exp2 and reciprocal; a forward step with those of the fp32 launches, EX, takes 0.2 us
 // more at 224 units)
 // against 3.3 and 3.5 us of the resident-weight launches, whose workgroups exchange h through L2, at all of
 // these widths; 256 is as far as one CU's registers and LDS hold the weights.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 namespace {
-constexpr int kSoloBRows = 8, kSoloBMaxH = 256;
+constexpr int kSoloBMaxH = 256;
 __device__ __forceinline__ unsigned pack2(float a, float b) {
   const __bf16 x = (__bf16)a, y = (__bf16)b;
   return (unsigned)__builtin_bit_cast(unsigned short, x) | ((unsigned)__builtin_bit_cast(unsigned short, y) << 16);
@@ -497,31 +499,32 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_b(const void* base, long 
 }
 }  // namespace
 
-template <int HB, int UB>
+// V: outputs per lane and block, 4 V rows per workgroup
+template <int HB, int UB, int V>
 struct SoloB {
-  static constexpr int NW = HB / UB, NT = 64 * NW, HP = 16 * HB, NC = HB / 2;
+  static constexpr int RO = 4 * V, NW = HB / UB, NT = 64 * NW, HP = 16 * HB, NC = HB / 2;
   static constexpr bool WL = UB == 2;                     // the n gate's weights in LDS (forward)
   static constexpr int LP = HP + 8;                       // pitch (bf16) of a row of h
-  static constexpr size_t FWD_LDS = (size_t)2 * 8 * LP * 2 + (WL ? (size_t)HB * NC * 1024 : 0);
+  static constexpr size_t FWD_LDS = (size_t)2 * RO * LP * 2 + (WL ? (size_t)HB * NC * 1024 : 0);
   static constexpr int NC3 = 3 * NC, NCR = NC3 < 18 ? NC3 : 18, NCL = NC3 - NCR;  // chunks in registers / in LDS (backward)
   static constexpr int LP4 = 4 * HP + 8;                  // a row of gate gradients: r | z | q | n
-  static constexpr size_t BWD_LDS = (size_t)2 * 8 * LP4 * 2 + (size_t)HB * NCL * 1024;
+  static constexpr size_t BWD_LDS = (size_t)2 * RO * LP4 * 2 + (size_t)HB * NCL * 1024;
 };
 
-template <int HB, int UB, bool EX>
+template <int HB, int UB, int V, bool EX>
 __global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih, const float* __restrict__ b_hh,
                          long s_rep, int Hc, const float* __restrict__ gx, long s_gx, __bf16* __restrict__ hb, long s_hb,
                          float* __restrict__ hs, long s_hs, float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT,
                          long s_hT, int Bc, int B, int T, int RT) {
-  using S = SoloB<HB, UB>;
+  using S = SoloB<HB, UB, V>;
   constexpr int HP = S::HP, LP = S::LP, NC = S::NC;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
-  __bf16* hl = reinterpret_cast<__bf16*>(solo_lds);                       // [2][8][LP]
-  u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * 8 * LP * 2);      // [HB][NC][64]: the n gate
+  __bf16* hl = reinterpret_cast<__bf16*>(solo_lds);                       // [2][RO][LP]
+  u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * S::RO * LP * 2);      // [HB][NC][64]: the n gate
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * kSoloBRows;
+  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * S::RO;
   bf16x8 wf[S::WL ? 2 : 3][UB][NC];
   {
     const __amdgpu_buffer_rsrc_t rw = rsrc_b(Wb + g * s_wb, 3L * HP * HP * 2);
@@ -553,42 +556,42 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
     }
   }
   const float* gxg = gx + g * s_gx;
-  const unsigned ox = (unsigned)(((r0 + 2 * lg) * 3 * HP + w * UB * 16 + lr) * 4);
+  const unsigned ox = (unsigned)(((r0 + V * lg) * 3 * HP + w * UB * 16 + lr) * 4);
   __bf16* hbg = hb + g * s_hb;
   __bf16* hTg = hT + g * s_hT;
-  const unsigned oT = (unsigned)((w * UB * 16 + lr) * ld_hT + r0 + 2 * lg) * 2u;
-  const long blk = (long)HB * 2 * 64;  // outputs of a tile and step, in lane order
+  const unsigned oT = (unsigned)((w * UB * 16 + lr) * ld_hT + r0 + V * lg) * 2u;
+  const long blk = (long)HB * V * 64;  // outputs of a tile and step, in lane order
   float* svg = sv + g * s_sv + (long)ty * blk * 4;
   float* hsg = hs + g * s_hs + (long)ty * blk;
   const long step_out = (long)RT * blk;
-  for (int i = tid; i < 2 * 8 * LP / 2; i += S::NT) reinterpret_cast<unsigned*>(hl)[i] = 0u;
+  for (int i = tid; i < S::RO * LP; i += S::NT) reinterpret_cast<unsigned*>(hl)[i] = 0u;
   // h_0 = 0: the first B rows of hb, the first B columns of hT
-  for (int i = tid; i < 8 * HP / 8; i += S::NT)
+  for (int i = tid; i < S::RO * HP / 8; i += S::NT)
     *reinterpret_cast<u32x4s*>(hbg + (long)(r0 + i / (HP / 8)) * HP + (i % (HP / 8)) * 8) = (u32x4s){0u, 0u, 0u, 0u};
 #pragma unroll
   for (int u = 0; u < UB; ++u)
-    *reinterpret_cast<unsigned*>(hTg + (long)((w * UB + u) * 16 + lr) * ld_hT + r0 + 2 * lg) = 0u;
-  auto load_gx = [&](int t, float (&G)[UB][3][2]) {
+    for (int v = 0; v < V; ++v) hTg[(long)((w * UB + u) * 16 + lr) * ld_hT + r0 + V * lg + v] = (__bf16)0.f;
+  auto load_gx = [&](int t, float (&G)[UB][3][V]) {
     const __amdgpu_buffer_rsrc_t rs = rsrc_b(gxg + (long)min(t, T - 1) * B * 3 * HP, 12L * B * HP);
 #pragma unroll
     for (int u = 0; u < UB; ++u)
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int v = 0; v < 2; ++v)
+        for (int v = 0; v < V; ++v)
           G[u][q][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)ox, ((v * 3 + q) * HP + u * 16) * 4, 0));
   };
   // (two blocks per wave: the input projections are requested one step ahead instead of two, the registers of
   // the second set being the ones that would spill)
   constexpr int PD = UB == 2 ? 1 : 2;
-  float ga[UB][3][2], gb[PD == 2 ? UB : 1][3][2], hp[UB][2];
+  float ga[UB][3][V], gb[PD == 2 ? UB : 1][3][V], hp[UB][V];
 #pragma unroll
-  for (int u = 0; u < UB; ++u) hp[u][0] = hp[u][1] = 0.f;
+  for (int u = 0; u < UB; ++u) for (int v = 0; v < V; ++v) hp[u][v] = 0.f;
   load_gx(0, ga);
   if constexpr (PD == 2) load_gx(1, gb);
   __syncthreads();
-  const int arow = 2 * (lr >> 2) + ((lr & 3) ? 1 : 0);  // the batch row of product row lr (see above)
-  auto step = [&](int t, const __bf16* hin, __bf16* hout, float (&G)[UB][3][2]) {
+  const int arow = V == 2 ? 2 * (lr >> 2) + ((lr & 3) ? 1 : 0) : lr >> 2;  // the batch row of product row lr (see above)
+  auto step = [&](int t, const __bf16* hin, __bf16* hout, float (&G)[UB][3][V]) {
     bf16x8 a[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) a[c] = *reinterpret_cast<const bf16x8*>(hin + arow * LP + 32 * c + 8 * lg);
@@ -607,48 +610,51 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
         const bf16x8 wn = S::WL ? __builtin_bit_cast(bf16x8, wl[((w * UB + u) * NC + c) * 64 + lane]) : wf[S::WL ? 0 : 2][u][c];
         acc[u][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], wn, acc[u][2], 0, 0, 0);
       }
-    float rr[UB][2], zz[UB][2], nn[UB][2];
+    float rr[UB][V], zz[UB][V], nn[UB][V];
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
+      for (int v = 0; v < V; ++v) {
         rr[u][v] = sigm_of<EX>(G[u][0][v] + acc[u][0][v]);
         zz[u][v] = sigm_of<EX>(G[u][1][v] + acc[u][1][v]);
         nn[u][v] = tanh_of<EX>((G[u][2][v] + bx[u]) + rr[u][v] * acc[u][2][v]);
         // Rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model
         // times their zero operands is NaN, which their h and gate gradients would hand to everyone.
-        if (r0 + 2 * lg + v >= Bc || (w * UB + u) * 16 + lr >= Hc) rr[u][v] = zz[u][v] = nn[u][v] = acc[u][2][v] = 0.f;
+        if (r0 + V * lg + v >= Bc || (w * UB + u) * 16 + lr >= Hc) rr[u][v] = zz[u][v] = nn[u][v] = acc[u][2][v] = 0.f;
       }
     }
     const __amdgpu_buffer_rsrc_t rh = rsrc_b(hsg + (long)t * step_out, blk * 4), rv = rsrc_b(svg + (long)t * step_out * 4, blk * 16);
 #pragma unroll
     for (int u = 0; u < UB; ++u)
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {  // what the backward launch wants of this step: h_{t-1} and the gates
-        const int o = ((w * UB + u) * 2 + v) * 64 + lane;
+      for (int v = 0; v < V; ++v) {  // what the backward launch wants of this step: h_{t-1} and the gates
+        const int o = ((w * UB + u) * V + v) * 64 + lane;
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, hp[u][v]), rh, o * 4, 0, 0);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4s, (floatx4){rr[u][v], zz[u][v], nn[u][v], acc[u][2][v]}), rv,
                                                o * 16, 0, 0);
         hp[u][v] = (1.0f - zz[u][v]) * nn[u][v] + zz[u][v] * hp[u][v];
-        hout[(2 * lg + v) * LP + (w * UB + u) * 16 + lr] = (__bf16)hp[u][v];
+        hout[(V * lg + v) * LP + (w * UB + u) * 16 + lr] = (__bf16)hp[u][v];
       }
     load_gx(t + PD, G);
     const __amdgpu_buffer_rsrc_t rT = rsrc_b(hTg + (long)(t + 1) * B, ((long)HP * ld_hT - (long)(t + 1) * B) * 2);
 #pragma unroll
     for (int u = 0; u < UB; ++u)
-      __builtin_amdgcn_raw_buffer_store_b32(pack2(hp[u][0], hp[u][1]), rT, (int)oT, (int)(u * 16 * ld_hT * 2), 0);
+      if constexpr (V == 2)
+        __builtin_amdgcn_raw_buffer_store_b32(pack2(hp[u][0], hp[u][1]), rT, (int)oT, (int)(u * 16 * ld_hT * 2), 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (__bf16)hp[u][0]), rT, (int)oT, (int)(u * 16 * ld_hT * 2), 0);
     __syncthreads();
     // the row-major copy of h, 16 bytes per piece, from the tile the next step multiplies
     const __amdgpu_buffer_rsrc_t rb = rsrc_b(hbg + (long)(t + 1) * B * HP, 2L * B * HP);
 #pragma unroll
-    for (int i = 0; i < (HP + S::NT - 1) / S::NT; ++i)
-      if (tid + i * S::NT < HP)
+    for (int i = 0; i < (V * HP / 2 + S::NT - 1) / S::NT; ++i)
+      if (tid + i * S::NT < V * HP / 2)
         __builtin_amdgcn_raw_buffer_store_b128(
             *reinterpret_cast<const u32x4s*>(hout + ((tid + i * S::NT) / (HP / 8)) * LP + ((tid + i * S::NT) % (HP / 8)) * 8), rb,
             (r0 * HP + (tid + i * S::NT) * 8) * 2, 0, 0);
   };
   __bf16* h0 = hl;
-  __bf16* h1 = hl + 8 * LP;
+  __bf16* h1 = hl + S::RO * LP;
   int t = 0;
   for (; t + 1 < T; t += 2) {
     step(t, h0, h1, ga);
@@ -658,19 +664,19 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
   if (t < T) step(t, h0, h1, ga);
 }
 
-template <int HB, int UB>
+template <int HB, int UB, int V>
 __global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* __restrict__ above, long s_above,
                          const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, __bf16* __restrict__ dg4,
                          long s_dg4, float* __restrict__ dbp, int Hc, int B, int T, int RT) {
-  using S = SoloB<HB, UB>;
+  using S = SoloB<HB, UB, V>;
   constexpr int HP = S::HP, LP = S::LP4, NC3 = S::NC3, NCR = S::NCR, NCL = S::NCL;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
-  __bf16* dl = reinterpret_cast<__bf16*>(solo_lds);                       // [2][8][LP]: r | z | q | n
-  u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * 8 * LP * 2);      // [HB][NCL][64]
+  __bf16* dl = reinterpret_cast<__bf16*>(solo_lds);                       // [2][RO][LP]: r | z | q | n
+  u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * S::RO * LP * 2);      // [HB][NCL][64]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * kSoloBRows;
+  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * S::RO;
   // W_hh^T rows of this wave's units: [unit][3 HP]
   bf16x8 wf[UB][NCR];
   {
@@ -684,13 +690,13 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
         else wl[((w * UB + u) * NCL + (c - NCR)) * 64 + lane] = v;
       }
   }
-  const long blk = (long)HB * 2 * 64;
+  const long blk = (long)HB * V * 64;
   const float* svg = sv + g * s_sv + (long)ty * blk * 4;
   const float* hsg = hs + g * s_hs + (long)ty * blk;
   const long step_out = (long)RT * blk;
   const float* abg = above + g * s_above;
-  const unsigned oa = (unsigned)(((r0 + 2 * lg) * HP + w * UB * 16 + lr) * 4);
-  struct In { floatx4 s[UB][2]; float hp[UB][2], ab[UB][2]; };
+  const unsigned oa = (unsigned)(((r0 + V * lg) * HP + w * UB * 16 + lr) * 4);
+  struct In { floatx4 s[UB][V]; float hp[UB][V], ab[UB][V]; };
   auto load_in = [&](int t, In& I) {
     const int tc = max(t, 0);
     const __amdgpu_buffer_rsrc_t rv = rsrc_b(svg + (long)tc * step_out * 4, blk * 16), rh = rsrc_b(hsg + (long)tc * step_out, blk * 4),
@@ -698,8 +704,8 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
 #pragma unroll
     for (int u = 0; u < UB; ++u)
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        const int o = ((w * UB + u) * 2 + v) * 64 + lane;
+      for (int v = 0; v < V; ++v) {
+        const int o = ((w * UB + u) * V + v) * 64 + lane;
         I.s[u][v] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rv, o * 16, 0, 0));
         I.hp[u][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rh, o * 4, 0, 0));
         I.ab[u][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, (int)oa, (v * HP + u * 16) * 4, 0));
@@ -707,17 +713,18 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
   };
   In ia;
   load_in(T - 1, ia);
-  float dc[UB][2], bs[UB][4];
+  float dc[UB][V], bs[UB][4];
 #pragma unroll
   for (int u = 0; u < UB; ++u) {
-    dc[u][0] = dc[u][1] = 0.f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) dc[u][v] = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) bs[u][i] = 0.f;
   }
-  for (int i = tid; i < 2 * 8 * LP / 2; i += S::NT) reinterpret_cast<unsigned*>(dl)[i] = 0u;
+  for (int i = tid; i < S::RO * LP; i += S::NT) reinterpret_cast<unsigned*>(dl)[i] = 0u;
   __syncthreads();
   __bf16* dgb = dg4 + g * s_dg4;
-  const int arow = 2 * (lr >> 2) + ((lr & 3) ? 1 : 0);
+  const int arow = V == 2 ? 2 * (lr >> 2) + ((lr & 3) ? 1 : 0) : lr >> 2;
   auto step = [&](int t, const __bf16* din, __bf16* dout) {
     floatx4 acc[UB][2];
 #pragma unroll
@@ -734,10 +741,10 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
     }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      float da_r[2], da_z[2], da_n[2], dq[2];
+      float da_r[V], da_z[V], da_n[V], dq[V];
       const int j = (w * UB + u) * 16 + lr;
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
+      for (int v = 0; v < V; ++v) {
         const float r = ia.s[u][v][0], z = ia.s[u][v][1], n = ia.s[u][v][2], q = ia.s[u][v][3];
         const float dh = (dc[u][v] + ia.ab[u][v]) + (acc[u][0][v] + acc[u][1][v]);
         const float dn = dh * (1.0f - z);
@@ -747,7 +754,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
         da_r[v] = da_n[v] * q * r * (1.0f - r);
         da_z[v] = dz * z * (1.0f - z);
         dc[u][v] = dh * z;
-        __bf16* o = dout + (2 * lg + v) * LP + j;
+        __bf16* o = dout + (V * lg + v) * LP + j;
         o[0] = (__bf16)da_r[v];
         o[HP] = (__bf16)da_z[v];
         o[2 * HP] = (__bf16)dq[v];
@@ -763,16 +770,16 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
     // the gate gradients row-major (r | z | n | q), 16 bytes per piece
     const __amdgpu_buffer_rsrc_t rb = rsrc_b(dgb + (long)t * B * 4 * HP, 8L * B * HP);
 #pragma unroll
-    for (int i = 0; i < (4 * HP + S::NT - 1) / S::NT; ++i) {
+    for (int i = 0; i < (2 * V * HP + S::NT - 1) / S::NT; ++i) {
       const int p = tid + i * S::NT, row = p / (HP / 2), c = (p % (HP / 2)) * 8;
       const int src = c < 2 * HP ? c : c < 3 * HP ? c + HP : c - HP;  // (in LDS q comes before n)
-      if (p < 4 * HP)
+      if (p < 2 * V * HP)
         __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4s*>(dout + row * LP + src), rb,
                                                ((r0 + row) * 4 * HP + c) * 2, 0, 0);
     }
   };
   __bf16* d0 = dl;
-  __bf16* d1 = dl + 8 * LP;
+  __bf16* d1 = dl + S::RO * LP;
   int t = T - 1;
   for (; t >= 1; t -= 2) {
     step(t, d0, d1);
@@ -800,7 +807,11 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
 bool gru_solo_bf16_supported(int B, int H) {
   return H % 32 == 0 && H >= 32 && H <= kSoloBMaxH && B % 8 == 0 && B >= 8 && 12L * B * H < 0x7fffffe0L;
 }
-int gru_solo_bf16_row_tiles(int B) { return B / kSoloBRows; }
+// Rows of a workgroup: 4 up to a workgroup per CU, 8 beyond (a local step of 20 time steps, 4 / 8 rows: H = 256, 256 tiles
+// of 4 rows 406 / 427 us, 512 tiles 737 / 688; H = 128, 384 tiles 412 / 400).  By the context's workers, not by how many are
+// stepped: the sums of the bias gradients are the same then.
+static int solo_b_rows(int B, int workers) { return (long)workers * (B / 4) <= 256 ? 4 : 8; }
+int gru_solo_bf16_row_tiles(int B, int workers) { return B / solo_b_rows(B, workers); }
 
 #define HPSGD_SOLOB_CASES(LAUNCH)         \
   switch (H / 32) {                       \
@@ -817,27 +828,30 @@ int gru_solo_bf16_row_tiles(int B) { return B / kSoloBRows; }
 
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, bool exact,
-                                    hipStream_t s) {
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, int workers,
+                                    bool exact, hipStream_t s) {
   if (!gru_solo_bf16_supported(B, H) || T < 1 || Hc < 1 || Hc > H || Bc < 1 || Bc > B || (ld_hT & 1) != 0 || (s_hT & 1) != 0 ||
       (long)H * ld_hT * 2 >= 0x7fffffe0L)
     return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
-  const int RT = gru_solo_bf16_row_tiles(B);
+  const int RT = gru_solo_bf16_row_tiles(B, workers);
+  const bool four = B / RT == 4;
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_SOLOB_FWD_EX(HB, UB, EX)                                                                                \
+#define HPSGD_SOLOB_FWD_EX(HB, UB, V, EX)                                                                               \
   do {                                                                                                                \
-    using S = SoloB<HB, UB>;                                                                                          \
+    using S = SoloB<HB, UB, V>;                                                                                       \
     static std::atomic<size_t> allowed{0};                                                                            \
-    if (const hipError_t e = allow_lds((const void*)gru_solo_fwd_bf16_kernel<HB, UB, EX>, S::FWD_LDS, allowed)) return e;\
-    hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB, EX>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s,         \
+    if (const hipError_t e = allow_lds((const void*)gru_solo_fwd_bf16_kernel<HB, UB, V, EX>, S::FWD_LDS, allowed)) return e;\
+    hipLaunchKernelGGL((gru_solo_fwd_bf16_kernel<HB, UB, V, EX>), dim3(groups * RT), dim3(S::NT), S::FWD_LDS, s,         \
                        (const __bf16*)Wb, s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, (__bf16*)hb, s_hb, hs, s_hs, sv, s_sv, \
                        (__bf16*)hT, ld_hT, s_hT, Bc, B, T, RT);                                                       \
   } while (0)
 #define HPSGD_SOLOB_FWD(HB, UB)                    \
   do {                                             \
-    if (exact) HPSGD_SOLOB_FWD_EX(HB, UB, true);   \
-    else HPSGD_SOLOB_FWD_EX(HB, UB, false);        \
+    if (exact && four) HPSGD_SOLOB_FWD_EX(HB, UB, 1, true);   \
+    else if (exact) HPSGD_SOLOB_FWD_EX(HB, UB, 2, true);      \
+    else if (four) HPSGD_SOLOB_FWD_EX(HB, UB, 1, false);      \
+    else HPSGD_SOLOB_FWD_EX(HB, UB, 2, false);                \
   } while (0)
   HPSGD_SOLOB_CASES(HPSGD_SOLOB_FWD)
 #undef HPSGD_SOLOB_FWD_EX
@@ -847,22 +861,29 @@ hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih
 
 hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* above, long s_above, const float* sv, long s_sv,
                                     const float* hs, long s_hs, void* dg4, long s_dg4, float* dbp, int Hc, int B, int H, int T,
-                                    int groups, hipStream_t s) {
+                                    int groups, int workers, hipStream_t s) {
   if (!gru_solo_bf16_supported(B, H) || T < 1 || Hc < 1 || Hc > H || !above || ((uintptr_t)dg4 & 15) != 0 || (s_dg4 & 7) != 0)
     return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
-  const int RT = gru_solo_bf16_row_tiles(B);
+  const int RT = gru_solo_bf16_row_tiles(B, workers);
+  const bool four = B / RT == 4;
   KernelTimer kt(KID_GRU_BWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_SOLOB_BWD(HB, UB)                                                                                       \
+#define HPSGD_SOLOB_BWD1(HB, UB, V)                                                                                   \
   do {                                                                                                                \
-    using S = SoloB<HB, UB>;                                                                                          \
+    using S = SoloB<HB, UB, V>;                                                                                       \
     static std::atomic<size_t> allowed{0};                                                                            \
-    if (const hipError_t e = allow_lds((const void*)gru_solo_bwd_bf16_kernel<HB, UB>, S::BWD_LDS, allowed)) return e; \
-    hipLaunchKernelGGL((gru_solo_bwd_bf16_kernel<HB, UB>), dim3(groups * RT), dim3(S::NT), S::BWD_LDS, s, (const __bf16*)WT, \
+    if (const hipError_t e = allow_lds((const void*)gru_solo_bwd_bf16_kernel<HB, UB, V>, S::BWD_LDS, allowed)) return e; \
+    hipLaunchKernelGGL((gru_solo_bwd_bf16_kernel<HB, UB, V>), dim3(groups * RT), dim3(S::NT), S::BWD_LDS, s, (const __bf16*)WT, \
                        s_wt, above, s_above, sv, s_sv, hs, s_hs, (__bf16*)dg4, s_dg4, dbp, Hc, B, T, RT);             \
+  } while (0)
+#define HPSGD_SOLOB_BWD(HB, UB)            \
+  do {                                     \
+    if (four) HPSGD_SOLOB_BWD1(HB, UB, 1); \
+    else HPSGD_SOLOB_BWD1(HB, UB, 2);      \
   } while (0)
   HPSGD_SOLOB_CASES(HPSGD_SOLOB_BWD)
 #undef HPSGD_SOLOB_BWD
+#undef HPSGD_SOLOB_BWD1
   return hipGetLastError();
 }
 

@@ -244,7 +244,9 @@ int build_layout(hpsgd_ctx* c) {
     }
     c->gx = c->alloc(TB * 3 * H);
     c->dgh = c->alloc(TB * 3 * H);
-    const size_t dbp_solo = c->solo ? (size_t)gru_solo_row_tiles(d.batch) * 6 * H : 0;
+    const size_t dbp_solo = c->solo     ? (size_t)gru_solo_row_tiles(d.batch) * 6 * H
+                            : c->solo_b ? (size_t)gru_solo_bf16_row_tiles((int)Bi, c->K) * 6 * H
+                                        : 0;
     c->gh = c->alloc(dbp_solo > Bi * 3 * H ? dbp_solo : Bi * 3 * H);
     c->D = c->alloc(Bi * H);
     c->wt = c->alloc(3 * H * H);
@@ -254,11 +256,10 @@ int build_layout(hpsgd_ctx* c) {
                   : gru_persist_rows(d.batch, d.hidden, c->K);
     // (no step of a narrow model waits for another workgroup)
     if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : 32));
-    if (c->solo) {  // (in the place of `gh`, which a step of such launches does not use)
+    if (dbp_solo) {  // (in the place of `gh`, which a step of such launches does not use)
       c->dbp.offset = c->gh.offset;
       c->dbp.stride = dbp_solo;
     } else if (c->prow) c->dbp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 6 * H);
-    else if (c->solo_b) c->dbp = c->alloc_packed((size_t)gru_solo_bf16_row_tiles((int)Bi) * 6 * H);
     else if (d.prec == HPSGD_BF16_MFMA && gru_fused_bf16_supported((int)H)) c->dbp = c->alloc_packed(((Bi + 31) / 32) * 6 * H);
     if (c->prow && gru_persist_dw_supported((int)H)) c->dwp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 3 * H * H);
     if (d.prec != HPSGD_BF16_MFMA) {
@@ -1010,7 +1011,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_solo_fwd_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx,
-                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, exact_gates, s));
+                                         hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, c->K, exact_gates, s));
         ++c->last_resident;
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
@@ -1396,7 +1397,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_BWD;
         // (gate gradients r | z | n | q, in the place of the exchange buffer)
         HIP_TRY(launch_gru_solo_bwd_bf16(wtb, s_wtb, above, s_dx, sv, s_sv, hs, s_hs, bfreg(c->dghx), 2 * (long)c->dghx.stride, dbp, Hc,
-                                         B, H, T, groups, s));
+                                         B, H, T, groups, c->K, s));
         HIP_TRY(launch_transpose_dg4(bfreg(c->dghx), 2 * (long)c->dghx.stride, bfreg(c->dgxT), bfreg(c->dghT), TBp, s_T, TB, H, groups, s));
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
@@ -1639,7 +1640,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         // the kernel that adds the partial sums applies the update too, when it can write the
         // replica with 16-byte accesses and the gradients are not accumulated as well
         const size_t ob_ih = c->eoff(c->lidx[l].bih);
-        const int n_dbp = use_solo ? gru_solo_row_tiles(B) : use_solo_b ? gru_solo_bf16_row_tiles(B) : (B + prow - 1) / prow;
+        const int n_dbp = use_solo ? gru_solo_row_tiles(B) : use_solo_b ? gru_solo_bf16_row_tiles(B, c->K) : (B + prow - 1) / prow;
         // (a width off the 16-unit blocks leaves the update to the commit launch, which takes all such
         // ranges of the step together)
         if (!acc && (bf || H % 16 == 0)) {

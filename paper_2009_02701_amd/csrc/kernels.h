@@ -233,14 +233,14 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
 // resident-weight launches below do, and the gate gradients row-major as dg4 [T B][4H] = r | z | n | q; hs
 // and sv hold h_{t-1} and the gates in lane order (T B H and 4 T B H floats), for the backward launch only
 bool gru_solo_bf16_supported(int B, int H);
-int gru_solo_bf16_row_tiles(int B);
+int gru_solo_bf16_row_tiles(int B, int workers);
 hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc,
                                     const float* gx, long s_gx, void* hb, long s_hb, float* hs, long s_hs, float* sv, long s_sv,
-                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, bool exact,
+                                    void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T, int groups, int workers, bool exact,
                                     hipStream_t s);
 hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* above, long s_above, const float* sv, long s_sv,
                                     const float* hs, long s_hs, void* dg4, long s_dg4, float* dbp, int Hc, int B, int H, int T,
-                                    int groups, hipStream_t s);
+                                    int groups, int workers, hipStream_t s);
 // its transposes: dgxT [3H][ld_T] = (r | z | n)^T, dghT = (r | z | q)^T over R = T B rows, in one launch
 hipError_t launch_transpose_dg4(const void* dg4, long s_dg4, void* dgxT, void* dghT, long ld_T, long s_T, int R, int H, int groups,
                                 hipStream_t s);
