@@ -1635,21 +1635,26 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         }
       }
       role = HPSGD_ROLE_GEMM_WGRAD;
-      TRY(gb.flush());
+      // Bias gradients from the recurrence's partial sums, with their update unless the gradients are accumulated as
+      // well (a width off the 16-unit blocks leaves it to the commit launch, which takes all such ranges of the step
+      // together): in the layer's adding launch or, where the layer has nothing else to add up, as column sums in the
+      // launch of its weight gradients.
+      bool bias_rides = false;
       if (dbp) {
-        // the kernel that adds the partial sums applies the update too, when it can write the
-        // replica with 16-byte accesses and the gradients are not accumulated as well
         const size_t ob_ih = c->eoff(c->lidx[l].bih);
         const int n_dbp = use_solo ? gru_solo_row_tiles(B) : use_solo_b ? gru_solo_bf16_row_tiles(B, c->K) : (B + prow - 1) / prow;
-        // (a width off the 16-unit blocks leaves the update to the commit launch, which takes all such
-        // ranges of the step together)
-        if (!acc && (bf || H % 16 == 0)) {
-          fused_commit[c->lidx[l].bih] = 1;
-          fused_commit[c->lidx[l].bhh] = 1;
-          TRY0(queue_reduce(dbp, n_dbp, (size_t)6 * Hc, rin + ob_ih, (size_t)sRi, rout + ob_ih, (size_t)sR, 1));
-        } else {
-          TRY0(queue_reduce(dbp, n_dbp, (size_t)6 * Hc, nullptr, 0, grad + ob_ih, (size_t)sG, 0));
-        }
+        const bool update = !acc && (bf || H % 16 == 0);
+        const float* b_in = update ? rin + ob_ih : nullptr;
+        float* b_out = update ? rout + ob_ih : grad + ob_ih;
+        const size_t s_bout = (size_t)(update ? sR : sG);
+        if (update) fused_commit[c->lidx[l].bih] = fused_commit[c->lidx[l].bhh] = 1;
+        bias_rides = !bf && rp.n == 0 && gb.pk.n > 0 &&
+                     colsum_pack_push(gb.cs, dbp, 6L * Hc, (long)n_dbp * 6 * Hc, b_out, (long)s_bout, b_in, sRi, n_dbp, 6 * Hc);
+        if (!bias_rides) TRY0(queue_reduce(dbp, n_dbp, (size_t)6 * Hc, b_in, (size_t)sRi, b_out, s_bout, update ? 1 : 0));
+      }
+      TRY(gb.flush());
+      if (dbp) {
+        // (above)
       } else {
         HIP_TRY(launch_colsum(dgx, 3 * H, s_gx, grad + c->eoff(c->lidx[l].bih), sG, TB, 3 * H, groups, s));
         HIP_TRY(launch_colsum(dgh, 3 * H, s_gx, grad + c->eoff(c->lidx[l].bhh), sG, TB, 3 * H, groups, s));
