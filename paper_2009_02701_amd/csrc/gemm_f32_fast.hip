@@ -530,18 +530,19 @@ static int fast_kind(const GemmDesc& d) {
   if (ua < 4 || ub < 4) return 0;
   return !aligned(d.A, d.lda, d.strideA) || !aligned(d.B, d.ldb, d.strideB) || ((ua | ub) & 3) != 0 ? 2 : 1;
 }
-static bool fast_large(const GemmDesc& d) {
+static bool fast_large(const GemmDesc& d, int groups) {
   // 128 x 128 tiles from two full rounds of workgroups on: below that the smaller tiles' better
   // balance over the CUs outweighs their extra LDS traffic (the fp32 matrix rate is low enough).
   // A contraction of a few k-tiles (a weight gradient over one batch) is mostly first loads and
   // epilogue: four small workgroups per SIMD cover those better than two large ones (matrix
   // pipes busy 52 % of the time with the large tile at Kd = 128)
-  const long t = (long)((d.M + 127) / 128) * ((d.N + 127) / 128) * d.groups;
+  const long t = (long)((d.M + 127) / 128) * ((d.N + 127) / 128) * groups;
   return d.M > 64 && d.N > 64 && t >= 512 && d.Kd > 256;
 }
 
 // The form for few tiles: up to 64 tiles of 64 x 64, up to 256 with a contraction that makes a long chain, and
-// up to 128 where the launch holds nothing else.  (Beyond, the chip is busy either way and the larger tile reads its
+// up to 128 where the launch holds nothing else (`shared`: it does, or would with all workers' tiles: the form decides
+// the order of a sum).  (Beyond, the chip is busy either way and the larger tile reads its
 // operands fewer times.)  Measured, one / the other form of every product of at most that many tiles:
 //   to  64: MLP 30-64-896-8, batch 224, K = 2     90 /  52 us a round; 28-832-672-32-13, batch 16, K = 3   94 /  72
 //   to 256: MLP 596-928-140-7, batch 145, K = 3   83 /  74;  two GRU layers of H = 544, batch 4, K = 4  1148 / 1134
@@ -552,13 +553,13 @@ static bool fast_slim(const GemmDesc& d, bool shared) {
   const long t = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
   return !(d.transA && d.transB) && (t <= 64 || (t <= 256 && d.Kd >= 512) || (t <= 128 && !shared));
 }
-static long slim_blocks(const GemmDesc& d) {
-  const long t = (long)((d.N + 31) / 32) * ((d.M + 31) / 32) * d.groups * (d.splits > 1 ? d.splits : 1);
-  return 8 * ((t + 7) / 8);
+static unsigned tile_blocks(const GemmDesc& d, int tile) {
+  const long t = (long)((d.N + tile - 1) / tile) * ((d.M + tile - 1) / tile) * d.groups * (d.splits > 1 ? d.splits : 1);
+  return (unsigned)(8 * ((t + 7) / 8));
 }
 template <bool RAG>
 static hipError_t launch_slim(const GemmDesc& d, hipStream_t s) {
-  const dim3 grid((unsigned)slim_blocks(d));
+  const dim3 grid(tile_blocks(d, 32));
   KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
   if (d.transA) hipLaunchKernelGGL((gemm_f32_slim_kernel<true, false, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
   else if (d.transB) hipLaunchKernelGGL((gemm_f32_slim_kernel<false, true, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
@@ -567,26 +568,29 @@ static hipError_t launch_slim(const GemmDesc& d, hipStream_t s) {
 }
 
 bool gemm_pack_push(GemmPack& pk, const GemmDesc& d) {
-  if (pk.n >= GemmPack::MAX || d.bf16 || d.background || (d.transA && d.transB) || !fast_kind(d) || fast_large(d)) return false;
+  if (pk.n >= GemmPack::MAX || d.bf16 || d.background || (d.transA && d.transB) || !fast_kind(d) || fast_large(d, d.groups)) return false;
   if (d.M <= 0 || d.N <= 0 || d.groups <= 0) return false;
-  const long t = (long)((d.N + 63) / 64) * ((d.M + 63) / 64) * d.groups * (d.splits > 1 ? d.splits : 1);
-  pk.d[pk.n] = d;
-  pk.blk0[pk.n + 1] = pk.blk0[pk.n] + (unsigned)(fast_slim(d, true) ? slim_blocks(d) : 8 * ((t + 7) / 8));
-  ++pk.n;
+  pk.d[pk.n++] = d;
+  // (fewer workers than all: a product that all of them launch by itself is a guest here, which changes no other's form)
+  if (!fast_large(d, d.workers ? d.workers : d.groups)) ++pk.n_all;
   return true;
 }
 
-hipError_t launch_gemm_pack(const GemmPack& pk, const ColsumPack& cs, int groups, hipStream_t s) {
+hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipStream_t s) {
   if (pk.n == 0 && cs.n == 0) return hipSuccess;
   if (pk.n == 0) return launch_colsum_pack(cs, groups, s);
   if (pk.n == 1 && cs.n == 0) return launch_gemm_f32_fast(pk.d[0], s);
   bool rag = false;
   unsigned slim = 0;
   double flops = 0.;
+  const bool shared = pk.n_all > 1 || cs.n > 0;
+  pk.blk0[0] = 0;
   for (int i = 0; i < pk.n; ++i) {
     const GemmDesc& d = pk.d[i];
+    const bool few = fast_slim(d, shared);
     rag = rag || fast_kind(d) == 2;
-    slim |= fast_slim(d, true) ? 1u << i : 0u;
+    slim |= few ? 1u << i : 0u;
+    pk.blk0[i + 1] = pk.blk0[i] + tile_blocks(d, few ? 32 : 64);
     flops += 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups;
   }
   using OpC = FastOperand<64, true, false>;
@@ -610,7 +614,7 @@ hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s) {
   if (!kind) return hipErrorNotSupported;
   const bool rag = kind == 2;
   if (fast_slim(d, false)) return rag ? launch_slim<true>(d, s) : launch_slim<false>(d, s);
-  if (fast_large(d)) return rag ? launch_fast_layout<128, 128, true>(d, s) : launch_fast_layout<128, 128, false>(d, s);
+  if (fast_large(d, d.groups)) return rag ? launch_fast_layout<128, 128, true>(d, s) : launch_fast_layout<128, 128, false>(d, s);
   return rag ? launch_fast_layout<64, 64, true>(d, s) : launch_fast_layout<64, 64, false>(d, s);
 }
 
