@@ -635,6 +635,20 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
       for (int j = 0; j < TN; ++j) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[j]) : "v"(ab), "n"(j * 4096));
     }
   };
+  // Behind a wait: the values pass through here, so that no use of them, and no copy that a use asks for, is placed before it.
+  // (What the compiler adds by itself is looked for in the listing of every build that the tests make.)
+  auto landed = [&](Frag& f) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if constexpr (AO) asm volatile("" : "+v"(f.ah[i][0]), "+v"(f.ah[i][1]));
+      else asm volatile("" : "+v"(f.a[i]));
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if constexpr (BO) asm volatile("" : "+v"(f.bh[j][0]), "+v"(f.bh[j][1]));
+      else asm volatile("" : "+v"(f.b[j]));
+    }
+  };
   auto mfmas = [&](const Frag& f) {
     bf16x8 a[TM], b[TN];
 #pragma unroll
@@ -668,6 +682,7 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
       constexpr int ks = ks_;
       fragments(sb, std::integral_constant<int, ks + 1>{}, fr[(ks + 1) & 1]);
       asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(READS) : "memory");  // step ks has landed
+      landed(fr[ks & 1]);
       __builtin_amdgcn_sched_barrier(0);
       mfmas(fr[ks & 1]);
       __builtin_amdgcn_sched_barrier(0);
@@ -677,6 +692,7 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
     quarter(std::integral_constant<int, 2>{});
     // this wave's reads of tile kt are complete, its loads of tile kt+1 have landed ...
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * IPW) : "memory");
+    landed(fr[1]);
     __builtin_amdgcn_s_barrier();  // ... and so are and have everyone's
     issue(stage, kt + S);          // into the buffer tile kt has left
     stage = stage + 1 == S ? 0 : stage + 1;
@@ -688,19 +704,7 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the reads issued for the tile after the last
   // (their registers stay theirs up to here: written by a value of the epilogue before the wait, a read that is still on
   // its way would overwrite it)
-  {
-    const Frag& f = fr[0];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      if constexpr (AO) asm volatile("" ::"v"(f.ah[i][0]), "v"(f.ah[i][1]));
-      else asm volatile("" ::"v"(f.a[i]));
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      if constexpr (BO) asm volatile("" ::"v"(f.bh[j][0]), "v"(f.bh[j][1]));
-      else asm volatile("" ::"v"(f.b[j]));
-    }
-  }
+  landed(fr[0]);
   // the zero loads of the tiles beyond the contraction must have landed before the operand
   // buffers become the epilogue tile
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
