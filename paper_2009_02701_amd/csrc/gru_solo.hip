@@ -4,8 +4,8 @@
 // then hand each other h_t (backward: the gate gradients) through memory at every step: 4 to 9 us per
 // step, whatever the width.  A layer of up to 128 units needs none of that: W_hh (196 KB at H = 128)
 // fits the registers of ONE compute unit, and batch rows are independent of each other.  So here a
-// workgroup owns 4 batch rows of one worker (or 8: solo_two_tiles) and ALL hidden units, and runs all
-// T steps by itself.  There is no flag, no residency requirement and no ordering against other streams:
+// workgroup owns 4 batch rows of one worker (or 8: solo_two_tiles; of very many rows 16, in a form of its own: solo_16_rows)
+// and ALL hidden units, and runs all T steps by itself.  There is no flag, no residency requirement and no ordering against other streams:
 // any number of workgroups may be launched.
 //
 // The products are v_mfma_f32_4x4x1_16b_f32 with the first operand broadcast: one instruction of 8 cycles
@@ -388,12 +388,314 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
   }
 }
 
+// ---------------------------------------------------------------------------- many rows: 16 per workgroup
+// Where every CU has several tiles of 4 rows anyway, the extra waves and partial sums of the form above are no help:
+// here a workgroup owns up to 16 rows and wave w the weights of units 16w .. 16w+15 (3 gates x H, at most 96 registers per
+// lane), all of the contraction, so that a step is one trip through LDS and one barrier, and a SIMD's second wave
+// multiplies while the first has its cell math.
+//
+// v_mfma_f32_16x16x4_f32 lane layout: A lane l holds A[m = l%16][k = l/16], B lane l holds
+// B[k = l/16][n = l%16], accumulator register v holds C[4*(l/16) + v][l%16].  The contraction index is
+// taken in the order k = 16c + 4*(l/16) + e (c-th chunk, e-th instruction), so that a lane reads its
+// A values of four instructions as one 16-byte LDS word.  All three gates of a unit are accumulated by
+// the same lane: the cell math needs nothing of another lane.  Matrix row m = 4*lg + v is batch row
+// r0 + 4*v + lg: a tile of n rows fills ceil(n/4) of the four registers in every lane group, and
+// the cell math of the others is skipped.
+namespace {
+
+inline int solo16_tiles(int B) { return (B + 15) / 16; }
+
+// Saved gates: (r, z, n, q) of one output as one 16-byte word, in the order the backward launch's lanes
+// read them: [step][row tile][unit block][register v][lane].
+template <int HB>
+__device__ __forceinline__ long sv_block() { return (long)HB * 4 * 64 * 4; }
+
+}  // namespace
+
+// grid: groups * RT workgroups of HB waves (HB = ceil(H / 16)).  gx: input projections, b_ih included.
+// hs: h_0 .. h_T ((T+1) blocks of B x H; h_0 = 0 is written here).
+template <int HB>
+__global__ void __launch_bounds__(64 * HB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo16_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
+                    const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs, float* __restrict__ sv,
+                    long s_sv, int B, int H, int T, int RT) {
+  constexpr int HP = 16 * HB, LP = HP + 4;  // LDS pitch: an odd number of 16-byte words, no bank conflicts
+  __shared__ __attribute__((aligned(16))) float hb[2][16 * LP];
+  // (the wave's number in a scalar register: buffer descriptors derived from it stay scalar)
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT;
+  const int r0 = 16 * ty, nrow = min(16, B - r0), nv = (nrow + 3) >> 2;
+  const int j = 16 * w + lr;
+  const bool jok = j < H;
+  float wt[3][4 * HB];
+  {
+    const __amdgpu_buffer_rsrc_t rw = rsrc_of(W_hh + g * s_rep, 3L * H * H);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int c = 0; c < HB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 16 * c + 4 * lg + e;
+          wt[q][4 * c + e] = ld_b32(rw, jok && k < H ? (unsigned)((q * H + j) * H + k) * 4u : kOut);
+        }
+  }
+  float bias[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) bias[q] = jok ? (b_hh + g * s_rep)[q * H + j] : 0.f;
+  // byte offsets of this lane's four outputs inside a step's block of gx and of hs
+  unsigned ox[4], oh[4];
+  float hp[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = r0 + 4 * v + lg;
+    const bool ok = jok && 4 * v + lg < nrow;
+    ox[v] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
+    oh[v] = ok ? (unsigned)(row * H + j) * 4u : kOut;
+    hp[v] = 0.f;
+  }
+  const float* gxg = gx + g * s_gx;
+  float* hsg = hs + g * s_hs;
+  float* svg = sv + g * s_sv + ((long)ty * HB + w) * 1024 + lane * 4;
+  const long sv_step = (long)RT * sv_block<HB>();
+  const long BH = (long)B * H;
+  {
+    const __amdgpu_buffer_rsrc_t rs = rsrc_of(hsg, BH);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) st_b32(rs, oh[v], 0.f);
+  }
+  for (int i = tid; i < 16 * LP; i += 64 * HB) hb[0][i] = 0.f;
+  auto load_gx = [&](int t, float (&G)[3][4]) {
+    const __amdgpu_buffer_rsrc_t rs = rsrc_of(gxg + (long)min(t, T - 1) * 3 * BH, 3 * BH);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) G[q][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)ox[v], q * H * 4, 0));
+  };
+  float ga[3][4], gb[3][4];
+  load_gx(0, ga);
+  load_gx(1, gb);
+  __syncthreads();
+  // one step; G holds its input projection and receives the one of step t + 2
+  auto step = [&](int t, const float* hin, float* hout, float (&G)[3][4]) {
+    floatx4 acc[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) acc[q] = (floatx4){bias[q], bias[q], bias[q], bias[q]};
+    floatx4 a[HB];
+#pragma unroll
+    for (int c = 0; c < HB; ++c) a[c] = *reinterpret_cast<const floatx4*>(&hin[lr * LP + 16 * c + 4 * lg]);
+    __builtin_amdgcn_sched_barrier(0);  // every LDS read is issued before the first product waits for one
+#pragma unroll
+    for (int c = 0; c < HB; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][e], wt[q][4 * c + e], acc[q], 0, 0, 0);
+    float rr[4], zz[4], nn[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      rr[v] = zz[v] = nn[v] = 0.f;
+      if (v < nv) {  // uniform
+        rr[v] = sigm_f32(G[0][v] + acc[0][v]);
+        zz[v] = sigm_f32(G[1][v] + acc[1][v]);
+        nn[v] = tanh_f32(G[2][v] + rr[v] * acc[2][v]);
+        hp[v] = (1.0f - zz[v]) * nn[v] + zz[v] * hp[v];
+        hout[(4 * lg + v) * LP + j] = hp[v];
+      }
+    }
+    load_gx(t + 2, G);
+    const __amdgpu_buffer_rsrc_t ro = rsrc_of(hsg + (long)(t + 1) * BH, BH);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) st_b32(ro, oh[v], hp[v]);
+    const __amdgpu_buffer_rsrc_t rv = rsrc_of(svg + (long)t * sv_step - lane * 4, 1024);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      st_b128(rv, v < nv ? (unsigned)(v * 64 + lane) * 16u : kOut, (floatx4){rr[v], zz[v], nn[v], acc[2][v]});
+    __syncthreads();
+  };
+  // (rows of hb[1] that no output lane writes are multiplied into outputs nobody stores; they must
+  // only be finite)
+  for (int i = tid; i < 16 * LP; i += 64 * HB) hb[1][i] = 0.f;
+  __syncthreads();
+  // the first of a SIMD's two waves goes ahead: its cell math then runs under the other's products
+  if (HB > 4 && w < 4) __builtin_amdgcn_s_setprio(2);
+  int t = 0;
+  for (; t + 1 < T; t += 2) {
+    step(t, hb[0], hb[1], ga);
+    step(t + 1, hb[1], hb[0], gb);
+  }
+  if (t < T) step(t, hb[0], hb[1], ga);
+}
+
+// (arguments as of the 4-row launch)
+template <int HB>
+__global__ void __launch_bounds__(64 * HB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo16_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx, float* __restrict__ dgh, long s_dg,
+                    const float* __restrict__ D, long s_D, const float* __restrict__ above, long s_above,
+                    const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
+                    int B, int H, int T, int RT) {
+  constexpr int HP = 16 * HB, LP = 3 * HP + 4;
+  __shared__ __attribute__((aligned(16))) float db[2][16 * LP];
+  // (the wave's number in a scalar register: buffer descriptors derived from it stay scalar)
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT;
+  const int r0 = 16 * ty, nrow = min(16, B - r0);
+  const int j = 16 * w + lr;
+  const bool jok = j < H;
+  // B[k][n] = W_hh[q*H + k][j]: the transposed weights, 64-byte pieces of rows
+  float wt[3][4 * HB];
+  {
+    const __amdgpu_buffer_rsrc_t rw = rsrc_of(W_hh + g * s_rep, 3L * H * H);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int c = 0; c < HB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 16 * c + 4 * lg + e;
+          wt[q][4 * c + e] = ld_b32(rw, jok && k < H ? (unsigned)((q * H + k) * H + j) * 4u : kOut);
+        }
+  }
+  unsigned ox[4], oh[4], ov[4];
+  float dc[4], bs[4] = {0.f, 0.f, 0.f, 0.f};
+  const long BH = (long)B * H;
+  const __amdgpu_buffer_rsrc_t rD = rsrc_of(D ? D + g * s_D : hs, D ? BH : 0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = r0 + 4 * v + lg;
+    const bool ok = jok && 4 * v + lg < nrow;
+    ox[v] = ok ? (unsigned)(row * 3 * H + j) * 4u : kOut;
+    oh[v] = ok ? (unsigned)(row * H + j) * 4u : kOut;
+    ov[v] = ok ? (unsigned)(v * 64 + lane) * 16u : kOut;
+    dc[v] = ld_b32(rD, oh[v]);
+  }
+  const float* hsg = hs + g * s_hs;
+  const float* abg = above ? above + g * s_above : hs;
+  const float* svg = sv + g * s_sv + ((long)ty * HB + w) * 1024;
+  const long sv_step = (long)RT * sv_block<HB>();
+  struct In { floatx4 s[4]; float hp[4], ab[4]; };
+  auto load_in = [&](int t, In& I) {
+    const int tc = max(t, 0);
+    const __amdgpu_buffer_rsrc_t rv = rsrc_of(svg + (long)tc * sv_step, 1024), rh = rsrc_of(hsg + (long)tc * BH, BH),
+                                 ra = rsrc_of(abg + (long)tc * BH, above ? BH : 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      I.s[v] = ld_b128(rv, ov[v]);
+      I.hp[v] = ld_b32(rh, oh[v]);
+      I.ab[v] = ld_b32(ra, oh[v]);
+    }
+  };
+  In ia, ib;
+  load_in(T - 1, ia);
+  load_in(T - 2, ib);
+  for (int i = tid; i < 2 * 16 * LP; i += 64 * HB) db[0][i] = 0.f;  // (both buffers)
+  __syncthreads();
+  auto step = [&](int t, const float* din, float* dout, In& I) {
+    floatx4 acc[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) acc[q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < HB; ++c) {
+      floatx4 a[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const floatx4*>(&din[lr * LP + q * HP + 16 * c + 4 * lg]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][e], wt[q][4 * c + e], acc[q], 0, 0, 0);
+    }
+    const __amdgpu_buffer_rsrc_t rx = rsrc_of(dgx + g * s_dg + (long)t * 3 * BH, 3 * BH),
+                                 rh = rsrc_of(dgh + g * s_dg + (long)t * 3 * BH, 3 * BH);
+    float da_r[4], da_z[4], da_n[4], dq[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      // (outside the batch or beyond H every input is zero, and so is every gradient)
+      const float r = I.s[v][0], z = I.s[v][1], n = I.s[v][2], q = I.s[v][3];
+      const float dh = (dc[v] + I.ab[v]) + (acc[0][v] + acc[1][v] + acc[2][v]);
+      const float dn = dh * (1.0f - z);
+      const float dz = dh * (I.hp[v] - n);
+      da_n[v] = dn * (1.0f - n * n);
+      dq[v] = da_n[v] * r;
+      da_r[v] = da_n[v] * q * r * (1.0f - r);
+      da_z[v] = dz * z * (1.0f - z);
+      dc[v] = dh * z;
+      float* o = &dout[(4 * lg + v) * LP + j];
+      o[0] = da_r[v];
+      o[HP] = da_z[v];
+      o[2 * HP] = dq[v];
+      bs[0] += da_r[v];
+      bs[1] += da_z[v];
+      bs[2] += da_n[v];
+      bs[3] += dq[v];
+    }
+    load_in(t - 2, I);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      st_b32(rx, ox[v], da_r[v]);
+      st_b32(rx, ox[v], da_z[v], H * 4);
+      st_b32(rx, ox[v], da_n[v], H * 8);
+      st_b32(rh, ox[v], da_r[v]);
+      st_b32(rh, ox[v], da_z[v], H * 4);
+      st_b32(rh, ox[v], dq[v], H * 8);
+    }
+    __syncthreads();
+  };
+  if (HB > 4 && w < 4) __builtin_amdgcn_s_setprio(2);
+  int t = T - 1;
+  for (; t >= 1; t -= 2) {
+    step(t, db[0], db[1], ia);
+    step(t - 1, db[1], db[0], ib);
+  }
+  if (t >= 0) step(t, db[0], db[1], ia);
+  // bias gradients: the four lane groups hold disjoint rows
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bs[i] += __shfl_xor(bs[i], 16);
+    bs[i] += __shfl_xor(bs[i], 32);
+  }
+  if (lg == 0 && jok) {
+    float* out = dbp + (long)(g * RT + ty) * 6 * H;
+    out[j] = out[3 * H + j] = bs[0];
+    out[H + j] = out[4 * H + j] = bs[1];
+    out[2 * H + j] = bs[2];
+    out[5 * H + j] = bs[3];
+  }
+}
+
 bool gru_solo_supported(int B, int H) {
   // (one step's block of gate gradients is addressed with 31-bit byte offsets)
   return H >= 1 && H <= kSoloMaxH && (long)B * 3 * H * 4 < 0x7fffffe0L;
 }
-int gru_solo_row_tiles(int B) { return solo_tiles(B); }
-size_t gru_solo_saved_words(int B, int H, int T) { return (size_t)T * solo_tiles(B) * 16 * H; }
+// 16 rows per workgroup in place of 4: where the chip is busy for more than one round either way.  `rounds`: of its workgroups
+// over the CUs (a workgroup of more than 64 units has a CU to itself).  By the context's workers, not by how many are stepped:
+// the sums have another order, and the bias gradients a quarter of the parts to add up, which is what decides for a few workers of very many rows.
+// Local steps of 12 time steps, 4 / 16 rows, us (B rows on K workers):
+//   H                      16          32          48          64          72          96          104         128
+//   B = 128,  K = 16    58 / 62     64 / 72     78 / 91     87 / 102    113 / 140   139 / 167   143 / 186   162 / 208
+//   B = 192,  K = 16    83 / 79     100 / 96    124 / 121   129 / 129   164 / 175   232 / 210   236 / 230   270 / 251
+//   B = 256,  K = 16    85 / 79     108 / 105   134 / 131   138 / 137   200 / 196   261 / 237   265 / 258   321 / 307
+//   B = 384,  K = 16    117 / 96    148 / 137   185 / 181   190 / 191   279 / 312   388 / 405   394 / 446   463 / 495
+//   B = 512,  K = 16    135 / 107   173 / 155   220 / 207   253 / 238   373 / 381   502 / 475   510 / 523   605 / 582
+//   B = 1024, K = 4     90 / 81     105 / 97    131 / 123   145 / 137   202 / 194   256 / 229   260 / 249   333 / 309
+//   B = 2048, K = 1     88 / 80     94 / 91     105 / 104   119 / 122   136 / 151   162 / 179   179 / 208   199 / 230
+//   B = 4096, K = 1     137 / 106   152 / 123   170 / 139   196 / 167   228 / 195   288 / 239   317 / 282   382 / 329
+static bool solo_16_rows(int B, int H, int workers) {
+  const long n = (long)workers * solo_tiles(B), rounds = ((long)workers * solo16_tiles(B) + 255) / 256;
+  if (n <= 512) return H <= 32 && B >= 2048;
+  if (H <= 32) return true;
+  if (H <= 64) return n > 1536 || B >= 1024;
+  if (H <= 80) return rounds == 1 && (n > 768 || B >= 2048);
+  // (4 rows: two tiles per workgroup; 97 to 104 units are 7 blocks of 16, but 13 steps of 8)
+  return 9 * rounds < 5 * ((n + 511) / 512) && (rounds == 1 || H <= 96 || H > 104);
+}
+int gru_solo_row_tiles(int B, int H, int workers) { return solo_16_rows(B, H, workers) ? solo16_tiles(B) : solo_tiles(B); }
+size_t gru_solo_saved_words(int B, int H, int T, int workers) {
+  return solo_16_rows(B, H, workers) ? (size_t)T * solo16_tiles(B) * ((H + 15) / 16) * 1024 : (size_t)T * solo_tiles(B) * 16 * H;
+}
 
 #define HPSGD_SOLO_CASES(LAUNCH) \
   switch ((H + 7) / 8) {         \
@@ -415,6 +717,18 @@ size_t gru_solo_saved_words(int B, int H, int T) { return (size_t)T * solo_tiles
     case 16: LAUNCH(16); break;  \
     default: return hipErrorInvalidValue; \
   }
+#define HPSGD_SOLO16_CASES(LAUNCH) \
+  switch ((H + 15) / 16) {         \
+    case 1: LAUNCH(1); break;      \
+    case 2: LAUNCH(2); break;      \
+    case 3: LAUNCH(3); break;      \
+    case 4: LAUNCH(4); break;      \
+    case 5: LAUNCH(5); break;      \
+    case 6: LAUNCH(6); break;      \
+    case 7: LAUNCH(7); break;      \
+    case 8: LAUNCH(8); break;      \
+    default: return hipErrorInvalidValue; \
+  }
 
 // Two tiles per workgroup where single ones are more than run at once: two share a step's LDS round trips and
 // barriers.  Up to 80 units a CU holds two workgroups or more, whose steps cover each other's waits.  A local step
@@ -426,11 +740,20 @@ static bool solo_two_tiles(int B, int H, int groups) {
 }
 
 hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep, const float* gx, long s_gx, float* hs,
-                               long s_hs, float* sv, long s_sv, int B, int H, int T, int groups, hipStream_t s) {
+                               long s_hs, float* sv, long s_sv, int B, int H, int T, int groups, int workers, hipStream_t s) {
   if (!gru_solo_supported(B, H) || T < 1) return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
   const int RT = solo_tiles(B);
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups, s);
+  if (solo_16_rows(B, H, workers)) {
+    const int tiles = solo16_tiles(B);
+#define HPSGD_SOLO16_FWD(HB)                                                                                            \
+  hipLaunchKernelGGL(gru_solo16_fwd_kernel<HB>, dim3(groups * tiles), dim3(64 * HB), 0, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
+                     s_hs, sv, s_sv, B, H, T, tiles)
+    HPSGD_SOLO16_CASES(HPSGD_SOLO16_FWD)
+#undef HPSGD_SOLO16_FWD
+    return hipGetLastError();
+  }
 #define HPSGD_SOLO_FWD(H8)                                                                                                  \
   if (solo_two_tiles(B, H, groups))                                                                                          \
     hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, b_hh, s_rep, \
@@ -445,11 +768,20 @@ hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep,
 
 hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float* dgh, long s_dg, const float* D, long s_D,
                                const float* above, long s_above, const float* sv, long s_sv, const float* hs, long s_hs,
-                               float* dbp, int B, int H, int T, int groups, hipStream_t s) {
+                               float* dbp, int B, int H, int T, int groups, int workers, hipStream_t s) {
   if (!gru_solo_supported(B, H) || T < 1) return hipErrorInvalidValue;
   if (groups <= 0) return hipSuccess;
   const int RT = solo_tiles(B);
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups, s);
+  if (solo_16_rows(B, H, workers)) {
+    const int tiles = solo16_tiles(B);
+#define HPSGD_SOLO16_BWD(HB)                                                                                                   \
+  hipLaunchKernelGGL(gru_solo16_bwd_kernel<HB>, dim3(groups * tiles), dim3(64 * HB), 0, s, W_hh, s_rep, dgx, dgh, s_dg, D, s_D, \
+                     above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, tiles)
+    HPSGD_SOLO16_CASES(HPSGD_SOLO16_BWD)
+#undef HPSGD_SOLO16_BWD
+    return hipGetLastError();
+  }
 #define HPSGD_SOLO_BWD(H8)                                                                                                     \
   if (solo_two_tiles(B, H, groups))                                                                                             \
     hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, s_rep, dgx, dgh, \

@@ -239,12 +239,12 @@ int build_layout(hpsgd_ctx* c) {
     if (lm) c->xe = c->alloc(TB * c->Ep);
     for (int l = 0; l < d.layers; ++l) {
       c->hs.push_back(c->alloc((TB + Bi) * H));
-      const size_t sv_solo = c->solo ? gru_solo_saved_words(d.batch, d.hidden, d.seq_len) : 0;
+      const size_t sv_solo = c->solo ? gru_solo_saved_words(d.batch, d.hidden, d.seq_len, c->K) : 0;
       c->sv.push_back(c->alloc(sv_solo > TB * 4 * H ? sv_solo : TB * 4 * H));
     }
     c->gx = c->alloc(TB * 3 * H);
     c->dgh = c->alloc(TB * 3 * H);
-    const size_t dbp_solo = c->solo     ? (size_t)gru_solo_row_tiles(d.batch) * 6 * H
+    const size_t dbp_solo = c->solo     ? (size_t)gru_solo_row_tiles(d.batch, d.hidden, c->K) * 6 * H
                             : c->solo_b ? (size_t)gru_solo_bf16_row_tiles((int)Bi, c->K) * 6 * H
                                         : 0;
     c->gh = c->alloc(dbp_solo > Bi * 3 * H ? dbp_solo : Bi * 3 * H);
@@ -994,7 +994,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       c->timer_nested = loop_fwd.active() && (fused || fused_b || use_solo || persist);
       if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
-        HIP_TRY(launch_gru_solo_fwd(Whh, rin + c->eoff(c->lidx[l].bhh), sRi, gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, groups, s));
+        HIP_TRY(launch_gru_solo_fwd(Whh, rin + c->eoff(c->lidx[l].bhh), sRi, gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, groups, c->K, s));
         ++c->last_resident;
       }
       if (persist) {
@@ -1377,7 +1377,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
         HIP_TRY(launch_gru_solo_bwd(Whh, sRi, dgx, dgh, s_gx, d_zero ? nullptr : D, s_D, above, s_dx, sv, s_sv, hs, s_hs, dbp,
-                                    B, H, T, groups, s));
+                                    B, H, T, groups, c->K, s));
       }
       int next_chunk = NC - 1;  // the chunk BPTT is walking through
       // resident weights: all of BPTT is one launch; its weight-gradient GEMMs follow it (work
@@ -1642,7 +1642,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       bool bias_rides = false;
       if (dbp) {
         const size_t ob_ih = c->eoff(c->lidx[l].bih);
-        const int n_dbp = use_solo ? gru_solo_row_tiles(B) : use_solo_b ? gru_solo_bf16_row_tiles(B, c->K) : (B + prow - 1) / prow;
+        const int n_dbp = use_solo ? gru_solo_row_tiles(B, H, c->K) : use_solo_b ? gru_solo_bf16_row_tiles(B, c->K) : (B + prow - 1) / prow;
         const bool update = !acc && (bf || H % 16 == 0);
         const float* b_in = update ? rin + ob_ih : nullptr;
         float* b_out = update ? rout + ob_ih : grad + ob_ih;

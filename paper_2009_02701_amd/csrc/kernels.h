@@ -220,16 +220,17 @@ hipError_t launch_gru_bwd_step(const float* WT, long s_wt, const float* dgh_next
                                long s_sv, const float* h_prev, long s_hs, float* dgx_t, float* dgh_t,
                                int B, int H, int groups, hipStream_t s);
 // ---- all time steps of a narrow layer in one launch without any exchange between workgroups (fp32), see gru_solo.hip ----
+// (workers: all of the context's, of which `groups` are stepped)
 bool gru_solo_supported(int B, int H);
-int gru_solo_row_tiles(int B);                        // partial sums of the bias gradients per worker
-size_t gru_solo_saved_words(int B, int H, int T);     // floats of `sv` per worker (a layout of its own)
+int gru_solo_row_tiles(int B, int H, int workers);                    // partial sums of the bias gradients per worker
+size_t gru_solo_saved_words(int B, int H, int T, int workers);        // floats of `sv` per worker (a layout of its own)
 hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep, const float* gx, long s_gx, float* hs,
-                               long s_hs, float* sv, long s_sv, int B, int H, int T, int groups, hipStream_t s);
+                               long s_hs, float* sv, long s_sv, int B, int H, int T, int groups, int workers, hipStream_t s);
 // D == nullptr: no gradient is carried into the last step; dbp[(g * row tiles + tile)][6H] receives the
 // partial bias-gradient sums (b_ih: r z n, then b_hh: r z q)
 hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float* dgh, long s_dg, const float* D, long s_D,
                                const float* above, long s_above, const float* sv, long s_sv, const float* hs, long s_hs,
-                               float* dbp, int B, int H, int T, int groups, hipStream_t s);
+                               float* dbp, int B, int H, int T, int groups, int workers, hipStream_t s);
 // the same with bf16 operands (H a multiple of 32 up to 256, B of 8): writes hb, hT (h_0 = 0 included) and dbp as the
 // resident-weight launches below do, and the gate gradients row-major as dg4 [T B][4H] = r | z | n | q; hs
 // and sv hold h_{t-1} and the gates in lane order (T B H and 4 T B H floats), for the backward launch only
