@@ -388,7 +388,13 @@ hipError_t launch_cls_head(const float* feats, long s_feats, const float* W_in, 
                            float* dfeat, long s_dfeat, float* W_out, float* b_out, long s_out, float lr, int commit,
                            float* loss, int N, int C, int H, int groups, hipStream_t s, int relu_mask) {
   if (!cls_head_supported(N, C, H)) return hipErrorInvalidValue;
-  if (N <= 32 && (H <= 128 || !commit || W_out != W_in)) {
+  // One launch up to the width where its logits, which every workgroup makes for itself over all features, cost more than a
+  // launch.  A whole local step (an MLP of two layers), time in two launches over time in one, with 1, 4 and 16 workers:
+  //   16 rows, 10 classes   H = 512  1.01 1.06 1.11   1024  0.96 1.05 1.00   2048  0.89 0.90 0.94
+  //   32 rows, 10 classes   H = 256  1.01 1.02 1.09   384   0.98 0.97 1.00   512   0.96 0.98 0.96   1024  0.84 0.84 0.87
+  //   32 rows, 32 classes   H = 640  1.05 1.03 1.05   768   0.98 1.02 1.02   1024  0.99 0.94 0.95
+  const int one_to = N <= 16 ? 1024 : C <= 16 ? 384 : 768;
+  if (N <= 32 && H <= one_to && (H <= 128 || !commit || W_out != W_in)) {
     auto one = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3((H + 127) / 128, groups), dim3(512), 0, s, feats, s_feats, W_in, b_in, s_in, y, s_y, dfeat, s_dfeat,
                          W_out, b_out, s_out, lr, commit, loss, N, C, H, relu_mask);
