@@ -15,6 +15,7 @@
 // per CU, so one's barrier wait is covered by the other's MFMAs.
 // LDS rows are [i][k] with a pitch of 72 halves (144 B): the 16-byte operand reads of 16
 // consecutive rows then fall on 64 distinct banks.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -874,10 +875,14 @@ static long args_tiles(const GemmBf16Args& a) {
 
 // A layer's products together up to 2048 tiles of 128 x 128 (four rounds of the chip): apart, on two streams, each costs
 // a launch and the streams an event in each direction, and each leaves its last round's CUs idle, which is more than
-// the larger tiles of the launches by themselves save.  A round or local step, together up to none / 512 / 2048 / 4096:
-// 6736 words, H = 104, 72 rows, 6 workers 336 / 201 / 201 / 201 us; 9999 words, H = 200, 480 rows, 4 workers
-// 567 / 501 / 467 / 467; H = 650, 700 rows, 4 workers 1441 / 1427 / 1365 / 1359; 10 000 words, H = 1024, 1120 rows,
-// 8 workers 2294 / 2268 / 2266 / 2485; 5840 words, H = 352, 1728 rows, 3 workers - / 812 / 826 / 826.
+// the larger tiles of the launches by themselves save.  Local steps, together up to none / 512 / 2048 / 4096:
+//   6736 words, H = 104, 72 rows, 6 workers      226 /  159 /  158 /  159 us
+//   9999 words, H = 200, 480 rows, 4 workers     478 /  446 /  437 /  437     400 rows  463 / 432 / 396 / 396
+//   10 000 words, H = 650, 700 rows, 4 workers  1292 / 1291 / 1284 / 1299
+//   10 000 words, H = 1024, 1120 rows, 8 workers 2306 / 2308 / 2307 / 2389
+//   5840 words, H = 352, 1728 rows, 3 workers    580 /  574 /  573 /  573
+//   768 words, H = 700, 80 rows, 8 workers       471 /  466 /  423 /  423
+//   4820 words, H = 992, 544 rows, 8 workers     731 /  732 /  732 /  743
 bool gemm_bf16_multi_pays(const GemmBf16Args* a, int n) {
   GemmNtDesc d;
   long t = 0;
@@ -895,13 +900,18 @@ hipError_t launch_gemm_bf16_multi(const GemmBf16Args* a, int n, hipStream_t s) {
   pk.blk0[0] = 0;
   double flops = 0.;
   bool commit = false;
+  // The longest tiles first: begun last they would run on alone.  (A layer's input gradient, with its contraction over 3H, behind the weight
+  // gradients: the sixth of the table above 467 us, the last 769, and up to 5 % more than the launches apart for H >= 576.)
+  int order[3] = {0, 1, 2};
+  std::stable_sort(order, order + n, [&](int x, int y) { return a[x].Kd > a[y].Kd; });
   for (int i = 0; i < n; ++i) {
-    if (!args_desc(a[i], pk.d[i])) return hipErrorInvalidValue;
-    if (!a[i].outer && !a[i].gp) pk.d[i].gp = pk.d[i].gh = a[i].M;  // (one block of all rows: rows as they are)
-    pk.kind[i] = a[i].outer == 2 ? 0 : a[i].outer == 3 ? (a[i].win ? 4 : 3) : (a[i].win ? 2 : 1);
-    pk.blk0[i + 1] = pk.blk0[i] + (unsigned)(8 * ((args_tiles(a[i]) + 7) / 8));
-    flops += 2.0 * a[i].M * a[i].N * (double)(a[i].splits > 1 ? a[i].Kall : a[i].Kd) * a[i].groups;
-    commit = commit || a[i].win;
+    const GemmBf16Args& p = a[order[i]];
+    if (!args_desc(p, pk.d[i])) return hipErrorInvalidValue;
+    if (!p.outer && !p.gp) pk.d[i].gp = pk.d[i].gh = p.M;  // (one block of all rows: rows as they are)
+    pk.kind[i] = p.outer == 2 ? 0 : p.outer == 3 ? (p.win ? 4 : 3) : (p.win ? 2 : 1);
+    pk.blk0[i + 1] = pk.blk0[i] + (unsigned)(8 * ((args_tiles(p) + 7) / 8));
+    flops += 2.0 * p.M * p.N * (double)(p.splits > 1 ? p.Kall : p.Kd) * p.groups;
+    commit = commit || p.win;
   }
   constexpr size_t smem = (size_t)NBM * (NBN + 4) * sizeof(float);
   static std::atomic<size_t> allowed{0};
