@@ -313,10 +313,13 @@ int hpsgd_merge_snapshot(float *global, const float *const *replicas, float *sna
  * hpsgd_local_step(_all) records a HIP event pair on the caller's stream around every launch
  * group of that role (hpsgd_destroy frees the events).  hpsgd_timer_read waits for the recorded events, returns the number of timed
  * launch groups of `role` and their summed duration in milliseconds, and clears that role.
- * With an auxiliary stream set (hpsgd_set_aux_stream) some launches run beside others: the
- * bf16 head's two backward GEMMs share one pair (counted as two launches), and a launch
- * that the library issues on the auxiliary stream alone (a layer's input-gradient GEMM beside
- * its weight-gradient GEMMs) is not timed. */
+ * Where products that need nothing of each other share a launch, the launch counts once: the bf16
+ * head's input and weight gradient under HPSGD_ROLE_GEMM_HEAD, a layer's weight gradients and the
+ * input gradient beside them under HPSGD_ROLE_GEMM_WGRAD, an fp32 step's products under the role that
+ * is current when they are issued.  With an auxiliary stream set (hpsgd_set_aux_stream) products that
+ * are launches of their own run beside others: the bf16 head's two then share one pair (counted as two
+ * launches), and a launch that the library issues on the auxiliary stream alone (a layer's
+ * input-gradient GEMM beside its weight-gradient GEMMs) is not timed. */
 enum hpsgd_role {
   HPSGD_ROLE_OTHER = 0,        /* zero fills */
   HPSGD_ROLE_GEMM_INPUT = 1,   /* time-batched input projection  X W_ih^T */
@@ -349,9 +352,18 @@ size_t hpsgd_commit_kernel_params(const hpsgd_ctx *ctx);
  * is added up: flops (2 M N Kd per group; a recurrence launch 2 B 3H H per time step, plus the
  * products it fuses) for the contractions, bytes (each operand once) for the streaming kernels.
  * hpsgd_kernel_timer_read waits for the recorded events, returns the number of timed launches of
- * `kernel` (one that holds several products counts as that many), their summed duration in milliseconds
- * and their summed work, and clears that kernel.
- * Names are those a kernel trace shows (template arguments included where they tell forms apart). */
+ * `kernel` (one that holds several bf16 products of a layer or of the head counts as that many), their
+ * summed duration in milliseconds and their summed work, and clears that kernel.
+ * hpsgd_kernel_name gives the name a kernel trace shows (template arguments included where they tell
+ * forms apart) of the kernel an id is named after.  Counted under the same id are
+ *   GRU_FWD_PERSIST, GRU_BWD_PERSIST (_BF16)  the recurrences without an exchange, gru_solo*_kernel
+ *   GEMM_BF16_DL, _DL_COMMIT     gemm_bf16_multi_kernel, under the latter as soon as one of its products
+ *                                is an update, the input gradient beside it included
+ *   GEMM_BF16_DLX192_COMMIT      gemm_bf16_dlx_pair_kernel (two updates; one launch)
+ *   GEMM_F32_FAST                gemm_f32_slim_kernel and gemm_f32_multi_kernel (one launch)
+ *   GEMM_F32                     gemm_bf16_kernel
+ *   CVT2                         embed_bf16_kernel
+ *   GRU_STEP                     gru_fwd_step*_kernel and gru_bwd_step*_kernel. */
 enum hpsgd_kernel {
   HPSGD_KERNEL_NONE = 0,
   HPSGD_KERNEL_GRU_FWD_PERSIST = 1,
