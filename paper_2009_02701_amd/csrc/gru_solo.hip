@@ -731,9 +731,10 @@ size_t gru_solo_saved_words(int B, int H, int T, int workers) {
   }
 
 // Two tiles per workgroup where single ones are more than run at once: two share a step's LDS round trips and
-// barriers.  Up to 80 units a CU holds two workgroups or more, whose steps cover each other's waits.  A local step
-// of 20 time steps with 512 tiles, one / two per workgroup: H = 128 294 / 276 us, H = 100 246 / 236, H = 64 153 / 160;
-// 384 tiles: H = 80 172 / 180, H = 40 114 / 122; 1024 tiles: H = 80 339 / 348, H = 64 225 / 218, H = 32 175 / 165.
+// barriers.  Up to 80 units a CU holds two workgroups or more, whose steps cover each other's waits, and up to 32 so many tiles
+// go to workgroups of 16 rows.  A local step of 20 time steps with 512 tiles, one / two per workgroup: H = 128 294 / 276 us,
+// H = 100 246 / 236, H = 64 153 / 160; 384 tiles: H = 80 172 / 180, H = 40 114 / 122; 1024 tiles: H = 80 339 / 348, H = 64 225 / 218.
+constexpr bool solo_pairs(int H8) { return (H8 > 4 && H8 <= 8) || H8 > 10; }
 static bool solo_two_tiles(int B, int H, int groups) {
   const long n = (long)groups * solo_tiles(B);
   return H <= 64 ? n > 512 : H > 80 && n > 256;
@@ -755,9 +756,9 @@ hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep,
     return hipGetLastError();
   }
 #define HPSGD_SOLO_FWD(H8)                                                                                                  \
-  if (solo_two_tiles(B, H, groups))                                                                                          \
-    hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, b_hh, s_rep, \
-                       gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, RT);                                                           \
+  if (solo_pairs(H8) && solo_two_tiles(B, H, groups))                                                                        \
+    hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, solo_pairs(H8) ? 2 : 1>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, \
+                       b_hh, s_rep, gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, RT);                                              \
   else                                                                                                                      \
     hipLaunchKernelGGL((gru_solo_fwd_kernel<H8, 1>), dim3(groups * RT), dim3(Solo<H8>::NT), 0, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
                        s_hs, sv, s_sv, B, H, T, RT)
@@ -783,9 +784,9 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
     return hipGetLastError();
   }
 #define HPSGD_SOLO_BWD(H8)                                                                                                     \
-  if (solo_two_tiles(B, H, groups))                                                                                             \
-    hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, 2>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, s_rep, dgx, dgh, \
-                       s_dg, D, s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT);                                    \
+  if (solo_pairs(H8) && solo_two_tiles(B, H, groups))                                                                           \
+    hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, solo_pairs(H8) ? 2 : 1>), dim3(groups * ((RT + 1) / 2)), dim3(Solo<H8>::NT), 0, s, W_hh, \
+                       s_rep, dgx, dgh, s_dg, D, s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT);                   \
   else                                                                                                                         \
     hipLaunchKernelGGL((gru_solo_bwd_kernel<H8, 1>), dim3(groups * RT), dim3(Solo<H8>::NT), 0, s, W_hh, s_rep, dgx, dgh, s_dg, D,  \
                        s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT)
