@@ -3,9 +3,9 @@
 // One launch per time step pays, at every step, a launch gap, a cold L2 and the transfer of
 // the workgroup's slice of W_hh (the larger part of what a step reads).  Here a workgroup
 // keeps its slice of W_hh (forward: the 3 x 16 gate rows of its 16 hidden units; backward:
-// 16 rows of W_hh^T) in LDS for all the steps of the launch; the activations of the step
+// 16 rows of W_hh^T) in registers for all the steps of the launch, split into bf16 parts; the activations of the step
 // (h_{t-1}, or the gate gradients of step t+1) go from memory straight into MFMA operand
-// registers, every wave fetching exactly the fragments it multiplies, so that the matrix
+// registers, every wave fetching and splitting exactly the fragments it multiplies, so that the matrix
 // work of a step needs no barrier until the partial sums are combined.
 //
 // The steps of one launch depend on each other across workgroups: h_t of a 32-row batch tile
@@ -43,20 +43,31 @@
 // out, or another workgroup has given up, the workgroup sets the abort word and the whole
 // workgroup leaves the kernel, so every wave reaches its end whatever happens.
 //
-// Tiling: 8 waves, 32 batch rows x 16 hidden units per workgroup, v_mfma_f32_16x16x4_f32.
-// The contraction is cut into 32-wide chunks, chunk c belongs to waves with (wave & 3) == c % 4,
-// the two 16-row blocks to the wave halves (wave >> 2); partial sums are combined through LDS.
-// MFMA 16x16x4 lane layout: A lane l holds A[m = l%16][k = l/16], B lane l holds
-// B[k = l/16][n = l%16], accumulator register v holds C[4*(l/16) + v][l%16].  The order of the
-// contraction index is free as long as both operands agree: for the chunk's MFMA number
-// e = 0..7 lane group lg = l/16 takes k = 32c + 16*(e/4) + 4*lg + e%4, i.e. two 16-byte pieces
+// Matrix work: 8 waves, 16 or 32 batch rows x 16 hidden units per workgroup.  The fp32 instruction (v_mfma_f32_16x16x4_f32)
+// with the weights in LDS took 40 to 50 % of a step; the products are those of split_f32.h instead, a 2.7th of its cycles,
+// the conversions beside them.  Where registers run out the smallest parts of the weights lie in LDS (persist_fwd_lw,
+// persist_bwd_nl: a launch that spills is slower than the fp32 instruction, its reloads queue up with the operands).
+// us per launch, before / now (forward, backward with its share of dW_hh):
+//   35 steps, H = 512, 4 workers of 64 rows, input of 128     239 / 197    392 / 338
+//   35 steps, H = 256, 4 workers of 16 rows, input of 128     146 /  89    182 / 134
+//    9 steps, H = 320, 4 workers of 40 rows, input of 32       48 /  38     57 /  50
+// The contraction is cut into 32-wide chunks, chunk c belongs to the waves with wave % KW == c % KW; partial sums are combined
+// through LDS.
+// MFMA 16x16x32 lane layout: A lane l holds A[m = l%16][8 values of k], B lane l the same of B[..][n = l%16],
+// accumulator register v holds C[4*(l/16) + v][l%16].  The order of the contraction index is free as long as both
+// operands agree: lane group lg = l/16 takes k = 32c + 4 lg .. + 3 and 16 further on, i.e. two 16-byte pieces
 // of its row per chunk, and one load instruction reads 64 contiguous bytes of each of 16 rows.
+#include <algorithm>
+#include <type_traits>
+
 #include "cell_math.h"
 #include "kernels.h"
+#include "split_f32.h"
 
 namespace hpsgd {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -64,7 +75,6 @@ constexpr int PNT = 512;     // threads per workgroup
 constexpr int PR = 32;       // batch rows per workgroup (bf16; fp32: 16 or 32, a template argument)
 constexpr int PJ = 16;       // hidden units per workgroup
 constexpr int PC = 32;       // contraction chunk
-constexpr int SP = 80;       // pitch of the staged dgh tile: 4 batch rows x 16 gate rows hit 64 banks
 
 // A synchronisation group owns PF flag words, one per member: a member stores the number of
 // steps it has completed into its own word (plain device-scope stores to distinct words: no
@@ -170,18 +180,16 @@ __device__ __forceinline__ bool persist_place(unsigned* tickets, unsigned ticket
     }
   }
   __syncthreads();
-  sg = lds_word[0];
-  tx = lds_word[1];
+  // (uniform, and known as such: addresses then take scalar registers)
+  sg = __builtin_amdgcn_readfirstlane(lds_word[0]);
+  tx = __builtin_amdgcn_readfirstlane(lds_word[1]);
   __syncthreads();  // (the words are used again by the first wait)
   return sg >= 0;
 }
 
-constexpr int kBeyond = 0x7ffffff0;  // a byte offset outside every tile's buffer: such a load gives zeros
-
-// 16 bytes at byte offset `off` of the buffer, as a device-scope load
-__device__ __forceinline__ float4 ld16_dev(__amdgpu_buffer_rsrc_t rs, int off) {
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 16 /* sc1 */);
+// 16 bytes at byte offset `off` (the lane's) + `from` (uniform) of the buffer, as a device-scope load
+__device__ __forceinline__ float4 ld16_dev(__amdgpu_buffer_rsrc_t rs, int off, int from) {
+  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, from, 16 /* sc1 */);
   return __builtin_bit_cast(float4, v);
 }
 // store of an exchanged value: device-scope (write-through), or ordinary when the group shares one L2
@@ -190,85 +198,61 @@ __device__ __forceinline__ void st_dev(float* p, float v, bool l2x) {
   else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Copies the 48 weight rows of units j0 .. j0+15 (gate q's row of unit j at src + (q H + j) KD, KD words
-// each, at any alignment) into LDS at pitch wp; rows of units beyond H and the columns from KD up to the
-// next multiple of the chunk are zero.
-__device__ __forceinline__ void load_resident(float* wres, int wp, const float* src, int H, int j0, int KD) {
-  const int KDp = (KD + PC - 1) / PC * PC, ur = KDp >> 2;
-  const bool vec = (KD & 3) == 0 && ((uintptr_t)src & 15) == 0;
-  for (int u = threadIdx.x; u < 48 * ur; u += PNT) {
-    const int row = u / ur, c4 = 4 * (u - row * ur);
-    const int j = j0 + (row & 15);
-    const float* p = src + ((long)(row >> 4) * H + min(j, H - 1)) * KD;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j < H) {
-      if (vec) {
-        if (c4 < KD) v = *reinterpret_cast<const float4*>(p + c4);
-      } else {
-        if (c4 < KD) v.x = p[c4];
-        if (c4 + 1 < KD) v.y = p[c4 + 1];
-        if (c4 + 2 < KD) v.z = p[c4 + 2];
-        if (c4 + 3 < KD) v.w = p[c4 + 3];
-      }
+// A fragment of eight fp32 values per lane as three bf16 ones (split_f32.h)
+struct SplitFrag { bf16x8s p[3]; };
+__device__ __forceinline__ SplitFrag split_frag(const float4& lo, const float4& hi) {
+  uint4 p0, p1, p2;
+  split8({lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, p0, p1, p2);
+  return {{__builtin_bit_cast(bf16x8s, p0), __builtin_bit_cast(bf16x8s, p1), __builtin_bit_cast(bf16x8s, p2)}};
+}
+// big[q] += a0 w0, small[q] += the other five products, for NQ blocks of 16 columns (consecutive instructions
+// update different accumulators)
+template <int NQ>
+__device__ __forceinline__ void split_mfmas(const SplitFrag& a, const SplitFrag (&w)[NQ], floatx4 (&big)[NQ], floatx4 (&small)[NQ]) {
+  auto mul = [&](int pa, int pw, floatx4 (&to)[NQ]) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) to[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[pa], w[q].p[pw], to[q], 0, 0, 0);
+  };
+  mul(0, 0, big);
+  mul(1, 0, small);
+  mul(2, 0, small);
+  mul(0, 1, small);
+  mul(1, 1, small);
+  mul(0, 2, small);
+}
+// not finite, or rounded to an infinity by the split
+__device__ __forceinline__ bool split_beyond(float v) { return !(fabsf(v) < 3.38e38f); }
+__device__ __forceinline__ bool split_beyond(const float4& v) {
+  return split_beyond(v.x) || split_beyond(v.y) || split_beyond(v.z) || split_beyond(v.w);
+}
+
+// The fragment of 32-chunk c of a weight row (KD words at src, at any alignment; ok: the row exists) in the order in which
+// the activations come: words 32c + 4 lg .. + 3 and 16 further on; zeros beyond KD and for a row that does not exist.
+__device__ __forceinline__ void weight_row_frag(const float* __restrict__ src, bool ok, bool vec, int KD, int c, float4 (&v)[2]) {
+  const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int k = PC * c + 16 * h + 4 * lg;
+    v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!ok) continue;
+    if (vec) {
+      if (k < KD) v[h] = *reinterpret_cast<const float4*>(src + k);
+    } else {
+      if (k < KD) v[h].x = src[k];
+      if (k + 1 < KD) v[h].y = src[k + 1];
+      if (k + 2 < KD) v[h].z = src[k + 2];
+      if (k + 3 < KD) v[h].w = src[k + 3];
     }
-    *reinterpret_cast<float4*>(&wres[row * wp + c4]) = v;
   }
 }
 
-// The loads of NB chunks of this wave, first chunk c0, + KW per chunk.  rs: buffer
-// over the workgroup's activation tile (row pitch KD words); rows >= rows_valid are read from
-// row 0 (their results are never stored), columns beyond KD are loaded as zeros (they meet a zero weight, which
-// an infinite input of another column would turn into NaN).
-template <int NB, int KW>
-__device__ __forceinline__ void fragment_loads(__amdgpu_buffer_rsrc_t rs, int KD, int rows_valid, int rsel, int c0,
-                                               float4 (&a)[NB][2]) {
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int row = rsel * 16 + lr;
-  const int rowoff = (row < rows_valid ? row : 0) * KD;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int k0 = PC * (c0 + KW * i) + 4 * lg;
-    // (KD is a multiple of 16: each piece is all in or all out)
-    a[i][0] = ld16_dev(rs, k0 < KD ? (rowoff + k0) * 4 : kBeyond);
-    a[i][1] = ld16_dev(rs, k0 + 16 < KD ? (rowoff + k0 + 16) * 4 : kBeyond);
-  }
-}
-
-// ... and their products with the resident rows
-template <int NQ, int NB, int KW>
-__device__ __forceinline__ void fragment_mfmas(const float* wres, int wp, int KD, int c0, const float4 (&a)[NB][2],
-                                               floatx4 (&acc)[2][NQ]) {
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int nch = (KD + PC - 1) / PC;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    // branch-free (a branch would pull the loads of its chunk in behind it): a chunk slot
-    // beyond the contraction reads weight column 0 and gets zeros instead
-    const int c = c0 + KW * i;
-    const bool cv = c < nch;  // uniform over the wave
-    const int cc = cv ? c : 0;
-    float4 w[NQ][2];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const float* wr = &wres[(q * 16 + lr) * wp + PC * cc + 4 * lg];
-      const float4 w0 = *reinterpret_cast<const float4*>(wr);
-      const float4 w1 = *reinterpret_cast<const float4*>(wr + 16);
-      w[q][0] = make_float4(cv ? w0.x : 0.f, cv ? w0.y : 0.f, cv ? w0.z : 0.f, cv ? w0.w : 0.f);
-      w[q][1] = make_float4(cv ? w1.x : 0.f, cv ? w1.y : 0.f, cv ? w1.z : 0.f, cv ? w1.w : 0.f);
-    }
-    // consecutive MFMAs update different accumulators
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const float4 av = a[i][e >> 2], wv = w[q][e >> 2];
-        const float as = (e & 3) == 0 ? av.x : (e & 3) == 1 ? av.y : (e & 3) == 2 ? av.z : av.w;
-        const float ws = (e & 3) == 0 ? wv.x : (e & 3) == 1 ? wv.y : (e & 3) == 2 ? wv.z : wv.w;
-        acc[e & 1][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(as, ws, acc[e & 1][q], 0, 0, 0);
-      }
-  }
+// The two pieces of this lane's fragment of chunk c of a row-major tile of the layer input (row pitch KD words, a multiple
+// of 16: each piece is all in or all out): rows >= rows_valid are read from row 0 (their results are never stored), columns beyond
+// KD are zeros (they meet a zero weight, which an infinite input of another column would turn into NaN).
+__device__ __forceinline__ void input_frag(__amdgpu_buffer_rsrc_t rs, int KD, int rows_valid, int row, int c, float4 (&a)[2]) {
+  const int off = ((row < rows_valid ? row : 0) * KD + 4 * (int)((threadIdx.x & 63) >> 4)) * 4;
+  a[0] = ld16_dev(rs, off, PC * 4 * c);
+  a[1] = PC * c + 16 < KD ? ld16_dev(rs, off, PC * 4 * c + 64) : make_float4(0.f, 0.f, 0.f, 0.f);  // (uniform)
 }
 
 // The exchanged operands (h_t, the gate gradients) are not read from a row-major matrix: there a
@@ -276,54 +260,43 @@ __device__ __forceinline__ void fragment_mfmas(const float* wres, int wp, int KD
 // does 2.8 times slower than whole lines (see the bf16 part below).  They are kept
 // fragment-major: per step a block of ceil(B/16) row blocks x ceil(KD/32) chunks x 2 halves,
 // each the 1 KB one load instruction reads, lane l's 16 bytes at byte 16 l (lane l: row l % 16,
-// contraction indices 16 half + 4 (l / 16) .. + 3 of the chunk).  xoff: word offset of (row, k)
-// inside a step's block; halves beyond KD are never written and never read.  KD is HP = 16 ceil(H / 16)
+// contraction indices 16 half + 4 (l / 16) .. + 3 of the chunk): row r's index k lies at word
+// (((r / 16) chunks + k / 32) 2 + (k / 16) % 2) 256 + (16 ((k % 16) / 4) + r % 16) 4 + k % 4.  Halves beyond KD are never written and never read.  KD is HP = 16 ceil(H / 16)
 // for h_t and 3 HP for the gate gradients (gate q's unit j at index q HP + j): whole halves for every H.
-__device__ __forceinline__ long xoff(int row, int nch, int k) {
-  return ((((long)(row >> 4) * nch + (k >> 5)) * 2 + ((k >> 4) & 1)) * 64 + (((k & 15) >> 2) << 4) + (row & 15)) * 4 + (k & 3);
-}
 // words of a step's block
 __host__ __device__ __forceinline__ long xblock_words(int B, int KD) {
   return (long)((B + 15) / 16) * 16 * ((KD + PC - 1) / PC) * PC;
 }
-// fragment_loads from a step's fragment-major block (rs), row block rbx of it
-template <int NB, int KW>
-__device__ __forceinline__ void fragment_loads_x(__amdgpu_buffer_rsrc_t rs, int KD, int rbx, int c0, float4 (&a)[NB][2]) {
-  const int lane = threadIdx.x & 63;
-  const int nch = (KD + PC - 1) / PC;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int c = c0 + KW * i;
-    // (KD is a multiple of 16: a half is all in or all out; one that is out meets zero weights and
-    // is read from the block's first fragment)
-    const bool v0 = PC * c < KD, v1 = PC * c + 16 < KD;
-    a[i][0] = ld16_dev(rs, ((rbx * nch + (v0 ? c : 0)) * 2) * 1024 + lane * 16);
-    a[i][1] = ld16_dev(rs, ((rbx * nch + (v1 ? c : 0)) * 2 + (v1 ? 1 : 0)) * 1024 + lane * 16);
-  }
+// the two pieces of chunk c of row block rbx of a step's block (rs); a half beyond KD: zeros
+__device__ __forceinline__ void exchange_frag(__amdgpu_buffer_rsrc_t rs, int nch, int KD, int rbx, int c, float4 (&a)[2]) {
+  const int off = (int)(threadIdx.x & 63) * 16, from = (rbx * nch + c) * 2048;
+  a[0] = ld16_dev(rs, off, from);
+  a[1] = PC * c + 16 < KD ? ld16_dev(rs, off, from + 1024) : make_float4(0.f, 0.f, 0.f, 0.f);  // (uniform)
 }
 
-// acc[i][q] (i = 0, 1: two accumulators per gate block, summed by the caller) +=
-// sum over this wave's chunks (kw, kw + KW, ..) of A[16 rbx + ..][k] * Wres[q*16 + ..][k].
-// wres: the resident weight rows (pitch wp words, zero beyond KD).  NB: chunks per wave whose
-// loads are in flight together.
-// behind(): called once, behind the first trip's loads - where a step requests what it needs one
-// step later from memory (requested in front of the flag wait, such loads would sit between the
-// polling wave and its view of the flags: a wave's loads return in order).
-template <int NQ, int NB, int KW, typename Behind>
-__device__ __forceinline__ void resident_contraction_x(const float* wres, int wp, __amdgpu_buffer_rsrc_t rs, int KD,
-                                                       int rbx, int kw, floatx4 (&acc)[2][NQ], Behind behind) {
-  const int nch = (KD + PC - 1) / PC;
-  bool first = true;
-  for (int c0 = kw; c0 < nch; c0 += KW * NB) {
-    float4 a[NB][2];
-    fragment_loads_x<NB, KW>(rs, KD, rbx, c0, a);
-    __builtin_amdgcn_sched_barrier(0);
-    if (first) behind();
-    first = false;
-    __builtin_amdgcn_sched_barrier(0);  // every load is issued before anything waits for one
-    fragment_mfmas<NQ, NB, KW>(wres, wp, KD, c0, a, acc);
+// A copy of a value that the compiler computes with only here: what a rare path derives from it is not hoisted out of the time loop,
+// where it would hold registers
+template <typename V>
+__device__ __forceinline__ V rarely(V v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// acc += the products of one fragment's fp32 values with the fp32 instruction (W: the fragment of 16 columns): where the split
+// gives no number
+__device__ __forceinline__ void plain_mfmas(const float4 (&a)[2], const float4 (&w)[2], bool second, floatx4& acc) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && !second) continue;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].x, w[h].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].y, w[h].y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].z, w[h].z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].w, w[h].w, acc, 0, 0, 0);
   }
-  if (first) behind();
+}
+__device__ __forceinline__ bool any_beyond(const floatx4& v) {
+  const float s = __builtin_fmaf(v[0], 0.f, __builtin_fmaf(v[1], 0.f, __builtin_fmaf(v[2], 0.f, v[3] * 0.f)));
+  return __any(!(s == 0.f)) != 0;
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const float* base) {
@@ -338,24 +311,20 @@ __device__ __forceinline__ float sum_planes(const float* red, int o, int PL) {
   return v;
 }
 
-// Rows of a workgroup's tile, and how the 8 waves share its products.  32 rows: the two 16-row blocks
-// to the wave halves, the contraction to four waves each.  16 rows: the contraction to all eight, and half
-// the matrix work and half the operand per workgroup - for launches whose workgroups then still fit the
-// chip (the first four waves take the cell math of the 16 x 16 outputs).
-template <int PRT>
-struct PersistShape {
-  static constexpr int KW = PRT == 32 ? 4 : 8, RB = PRT / 16;
-};
+// Whether the forward kernel keeps the smallest parts of its slice of W_hh in LDS: with them in registers it would spill.
+__host__ __device__ constexpr bool persist_fwd_lw(int ncw, int xnb, int rbw) { return ncw >= 4 || rbw == 2 || (ncw == 3 && xnb == 2); }
 
 // Forward: steps t = 0 .. T-1.  hs holds h_0 .. h_T ((T+1) blocks of B x H per worker, h_0
 // given), gx the input projections of all steps, sv receives r|z|n|q of every step.
 // sync: the abort word, then 64 flag words per synchronisation group; `base` is what the
 // flags read when the kernel starts.
-// XP: the kernel computes the input projection itself, gx_t = x_t W_ih^T + b_ih, from the
-// layer input xin (blocks of B x width per step) with its 48 rows of W_ih resident in LDS too;
+// XNB > 0: the kernel computes the input projection itself, gx_t = x_t W_ih^T + b_ih, from the
+// layer input xin (blocks of B x width per step) with its 48 rows of W_ih resident in LDS;
 // that part of a step does not depend on the other workgroups and is done before the wait.
 // The r and z gates then take one sum over both contractions; gx is not used.
-template <int XNB, int PRT>  // XNB: chunks of the layer input per wave (width <= 32 KW XNB); 0: gx is given
+// PRT batch rows per workgroup.  KW waves share the contraction, NCW chunks each (H <= 32 KW NCW; the layer input's width
+// <= 32 KW XNB); with KW = 4 the other four have the second 16 rows, with KW = 8 a wave has all rows.
+template <int NCW, int XNB, int PRT, int KW>
 __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
                        const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs, float* hx, long s_hx,
@@ -364,19 +333,20 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
                        const float* __restrict__ xin, long s_x, int width,
                        const float* __restrict__ W_ih, const float* __restrict__ b_ih) {
   extern __shared__ __attribute__((aligned(16))) float persist_lds[];
-  constexpr int KW = PersistShape<PRT>::KW, RB = PersistShape<PRT>::RB;
+  constexpr int RB = PRT / 16, RBW = RB * KW / 8;  // row blocks of the tile, of a wave
+  static_assert(RBW >= 1, "8 waves");
   constexpr bool XP = XNB > 0;
   constexpr int XB = XP ? XNB : 1;
+  constexpr bool LW = persist_fwd_lw(NCW, XNB, RBW);  // the smallest parts of W_hh lie in LDS
   constexpr int NP = XP ? 4 : 3;             // planes of partial sums: r, z, q (+ the x part of n)
   const int NJ = (H + PJ - 1) / PJ, HP = NJ * PJ, RT = (B + PRT - 1) / PRT;
-  const int wp = (HP + PC - 1) / PC * PC + 4;
-  const int wp2 = XP ? (width + PC - 1) / PC * PC + 4 : 0;
-  float* wres = persist_lds;                 // [48][wp]
-  float* red = wres + 48 * wp;               // [KW][RB][NP][4][64]: 8 waves' partial sums
-  float* wres2 = red + 8 * NP * 4 * 64;      // [48][wp2]
-  int* lds_flag = reinterpret_cast<int*>(wres2 + 48 * wp2);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kw = wave & (KW - 1), rsel = RB == 2 ? wave >> 2 : 0;
+  const int nch = (HP + PC - 1) / PC, nchw = XP ? (width + PC - 1) / PC : 0;
+  float* red = persist_lds;                                       // [KW][RB][NP][4][64] partial sums
+  u32x4_t* wx = reinterpret_cast<u32x4_t*>(red + KW * RB * NP * 256);   // [nchw][3 gates][3 parts][64 lanes]: W_ih
+  u32x4_t* wl = wx + nchw * 9 * 64;                               // [KW][NCW][3][64]
+  int* lds_flag = reinterpret_cast<int*>(wl + (LW ? KW * NCW * 3 * 64 : 0));
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = wave & (KW - 1), rsel = RBW == RB ? 0 : wave / KW;   // first row block of this wave
   const int lr = lane & 15, lg = lane >> 4;
   unsigned* abort_w = sync;
   int tx, sg;
@@ -387,14 +357,41 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   const int j0 = tx * PJ, r0 = ty * PRT;
   unsigned* flags = sync + 1 + sg * PF;
   __builtin_amdgcn_s_setprio(3);
-  // the resident slices: rows q*16 + r = W_hh[q*H + j0 + r][:] (and the same rows of W_ih)
-  load_resident(wres, wp, W_hh + g * s_rep, H, j0, H);
-  if (XP) load_resident(wres2, wp2, W_ih + g * s_rep, H, j0, width);
   const int j = j0 + lr, jc = min(j, H - 1);
   const bool jok = j < H;
+  // the resident slices: gate q's fragment of chunk c holds W_hh[q H + j][32 c ..], this wave's chunks kw + KW i
+  const float* Wj = W_hh + g * s_rep + (long)jc * H;
+  const float* Xj = XP ? W_ih + g * s_rep + (long)jc * width : nullptr;
+  const bool wvec = (H & 3) == 0 && ((uintptr_t)(W_hh + g * s_rep) & 15) == 0;
+  const bool xvec = XP && ((uintptr_t)(W_ih + g * s_rep) & 15) == 0;
+  bf16x8s w[NCW][3][LW ? 2 : 3];
+  bool beyond = false;
+#pragma unroll
+  for (int i = 0; i < NCW; ++i)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      float4 v[2];
+      weight_row_frag(Wj + (long)q * H * H, jok && kw + KW * i < nch, wvec, H, kw + KW * i, v);
+      beyond = beyond || split_beyond(v[0]) || split_beyond(v[1]);
+      const SplitFrag f = split_frag(v[0], v[1]);
+      w[i][q][0] = f.p[0];
+      w[i][q][1] = f.p[1];
+      if (LW) wl[((kw * NCW + i) * 3 + q) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[2]);  // (KW = 4: by two waves, the same)
+      else w[i][q][LW ? 0 : 2] = f.p[2];
+      if (NCW > 2) __builtin_amdgcn_sched_barrier(0);  // (or the pieces of all chunks take registers at once)
+    }
+  beyond = __any(beyond);
+  if (XP)
+    for (int u = wave; u < 3 * nchw; u += 8) {
+      float4 v[2];
+      weight_row_frag(Xj + (long)(u % 3) * H * width, jok, xvec, width, u / 3, v);
+      const SplitFrag f = split_frag(v[0], v[1]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) wx[(u * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[p]);
+    }
   const bool act = RB == 2 || wave < 4;             // this wave has outputs (uniform)
-  const int qv = wave & 3;
-  const int row = r0 + rsel * 16 + 4 * lg + qv;     // this thread's element of the tile
+  const int qv = wave & 3, rbo = RB == 2 ? wave >> 2 : 0;
+  const int row = r0 + rbo * 16 + 4 * lg + qv;      // this thread's element of the tile
   const int rowc = min(row, B - 1);                 // loads are clamped, stores guarded
   const bool ok = row < B && jok;
   const float* bh = b_hh + g * s_rep;
@@ -408,62 +405,136 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   float* hsg = hs + g * s_hs;
   float* hxg = hx + g * s_hx;                 // h_0 .. h_T as the workgroups exchange them
   const long xblk = xblock_words(B, HP);
-  const int nchx = (HP + PC - 1) / PC;
-  const int rbx = (r0 + rsel * 16 < B ? r0 + rsel * 16 : r0) >> 4;  // this wave's row block (one beyond the batch: the tile's first)
-  float hpv = jok ? hsg[(long)rowc * H + jc] : 0.f;
-  float4 xa[XB][2];  // this step's fragments of the layer input, loaded one step ahead
-  float gxn[3] = {0.f, 0.f, 0.f};  // ... or its input projection
-  if (XP) {
-    fragment_loads<XB, KW>(tile_rsrc(xin + g * s_x + (long)r0 * width), width, B - r0, rsel, kw, xa);
-  } else if (act) {
-    const float* gxr = gx + g * s_gx + (long)rowc * 3 * H;
+  int rbx[RBW];  // this wave's row blocks (one beyond the batch: the tile's first)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) gxn[q] = gxr[q * H + jc];
-  }
+  for (int rb = 0; rb < RBW; ++rb) rbx[rb] = (r0 + (rsel + rb) * 16 < B ? r0 + (rsel + rb) * 16 : r0) >> 4;
+  float hpv = jok ? hsg[(long)rowc * H + jc] : 0.f;
+  float4 xa[RBW][XB][2];  // this step's fragments of the layer input, loaded one step ahead
+  float gxn[3] = {0.f, 0.f, 0.f};  // ... or its input projection
+  // (uniform addresses and 32-bit offsets of the lane)
+  const unsigned ogx = rowc * 3 * H + jc, osv = row * 4 * H + j, oh = row * H + j;
+  // where the lane's unit goes in a step's block 
+  const unsigned xb = ((r0 / 16 + rbo) * nch * 2 + j0 / 16) * 256, xl = (((lr >> 2) << 4) + (row & 15)) * 4 + (lr & 3);
+  auto load_x = [&](int t) {
+    if (XP) {
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(xin + g * s_x + ((long)t * B + r0) * width);
+#pragma unroll
+      for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+        for (int i = 0; i < XB; ++i)
+          if (kw + KW * i < nchw) input_frag(rs, width, B - r0, (rsel + rb) * 16 + lr, kw + KW * i, xa[rb][i]);
+    } else if (act) {
+      const float* gxt = gx + g * s_gx + (long)t * B * 3 * H;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) gxn[q] = (gxt + q * H)[ogx];
+    }
+  };
+  load_x(0);
   __syncthreads();
   for (int t = 0; t < T; ++t) {
     // what does not depend on the recurrence is computed in front of the wait
     const float gxv[3] = {gxn[0], gxn[1], gxn[2]};
-    floatx4 acc[2][3], accx[2];
+    floatx4 big[RBW][3], small[RBW][3], accx[RBW];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int rb = 0; rb < RBW; ++rb) {
 #pragma unroll
-      for (int q = 0; q < 3; ++q) acc[i][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
-      accx[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < 3; ++q) big[rb][q] = small[rb][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      accx[rb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     }
     if (XP) {
-      fragment_mfmas<3, XB, KW>(wres2, wp2, width, kw, xa, acc);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        accx[i] = acc[i][2];  // n keeps its two parts apart: n = tanh(x part + r * (h part))
-        acc[i][2] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < XB; ++i) {
+        const int c = kw + KW * i;
+        if (c >= nchw) continue;  // (uniform)
+        SplitFrag wq[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+          for (int p = 0; p < 3; ++p) wq[q].p[p] = __builtin_bit_cast(bf16x8s, wx[((c * 3 + q) * 3 + p) * 64 + lane]);
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb) split_mfmas(split_frag(xa[rb][i][0], xa[rb][i][1]), wq, big[rb], small[rb]);
+      }
+#pragma unroll
+      for (int rb = 0; rb < RBW; ++rb) {
+        bool redo = false;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) redo = any_beyond(big[rb][q] + small[rb][q]) || redo;
+        if (__builtin_expect(redo, 0)) {
+          const int wd = rarely(width);
+          const __amdgpu_buffer_rsrc_t rs = tile_rsrc(xin + g * s_x + ((long)t * B + r0) * wd);
+          const float* Xr = rarely(W_ih) + g * s_rep + (long)jc * wd;
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            big[rb][q] = small[rb][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int c = kw; c < nchw; c += KW) {
+              float4 v[2], x[2];
+              input_frag(rs, wd, B - r0, (rsel + rb) * 16 + lr, c, x);
+              weight_row_frag(Xr + (long)q * H * wd, jok, false, wd, c, v);
+              plain_mfmas(x, v, PC * c + 16 < wd, big[rb][q]);
+            }
+          }
+        }
+        // n keeps its two parts apart: n = tanh(x part + r * (h part))
+        accx[rb] = big[rb][2] + small[rb][2];
+        big[rb][2] = small[rb][2] = (floatx4){0.f, 0.f, 0.f, 0.f};
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     if (t > 0 && !group_wait(flags, NJ, base + (unsigned)t, abort_w, spin_limit, lds_flag)) return;
-    resident_contraction_x<3, RB == 2 ? 4 : 2, KW>(wres, wp, tile_rsrc(hxg + (long)t * xblk), HP, rbx, kw, acc, [&]() {
-      // step t+1's layer input (or input projection) travels during this step's product
-      if (XP) {
-        fragment_loads<XB, KW>(tile_rsrc(xin + g * s_x + ((long)min(t + 1, T - 1) * B + r0) * width), width, B - r0, rsel, kw, xa);
-      } else if (act) {
-        const float* gxr = gx + g * s_gx + ((long)min(t + 1, T - 1) * B + rowc) * 3 * H;
+    {
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(hxg + (long)t * xblk);
+      float4 a[RBW][NCW][2];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) gxn[q] = gxr[q * H + jc];
+      for (int i = 0; i < NCW; ++i)
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb)
+          if (kw + KW * i < nch) exchange_frag(rs, nch, HP, rbx[rb], kw + KW * i, a[rb][i]);  // (uniform)
+      __builtin_amdgcn_sched_barrier(0);
+      load_x(min(t + 1, T - 1));  // step t+1's layer input (or input projection) travels during this step's product
+      __builtin_amdgcn_sched_barrier(0);  // every load is issued before anything waits for one
+      if (__builtin_expect(beyond, 0)) {
+        const int Hr = rarely(H);
+        const float* Wr = rarely(W_hh) + g * s_rep + (long)jc * Hr;
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+          for (int rb = 0; rb < RBW; ++rb) {
+#pragma unroll 1
+            for (int c = kw; c < nch; c += KW) {
+              float4 v[2], x[2];
+              exchange_frag(rs, nch, HP, rbx[rb], c, x);
+              weight_row_frag(Wr + (long)q * Hr * Hr, jok, false, Hr, c, v);
+              plain_mfmas(x, v, PC * c + 16 < HP, big[rb][q]);
+            }
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < NCW; ++i) {
+          if (kw + KW * i >= nch) continue;
+          SplitFrag wi[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            wi[q] = {{w[i][q][0], w[i][q][1], LW ? __builtin_bit_cast(bf16x8s, wl[((kw * NCW + i) * 3 + q) * 64 + lane]) : w[i][q][LW ? 0 : 2]}};
+#pragma unroll
+          for (int rb = 0; rb < RBW; ++rb) split_mfmas(split_frag(a[rb][i][0], a[rb][i][1]), wi, big[rb], small[rb]);
+        }
       }
-    });
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        red[(((kw * RB + rsel) * NP + q) * 4 + v) * 64 + lane] = acc[0][q][v] + acc[1][q][v];
-      if (XP) red[(((kw * RB + rsel) * NP + 3) * 4 + v) * 64 + lane] = accx[0][v] + accx[1][v];
     }
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) red[(((kw * RB + rsel + rb) * NP + q) * 4 + v) * 64 + lane] = big[rb][q][v] + small[rb][q][v];
+        if (XP) red[(((kw * RB + rsel + rb) * NP + 3) * 4 + v) * 64 + lane] = accx[rb][v];
+      }
     __syncthreads();
     if (act) {
       float gh[NP];
 #pragma unroll
       for (int q = 0; q < NP; ++q)
-        gh[q] = sum_planes<KW>(red, ((rsel * NP + q) * 4 + qv) * 64 + lane, RB * NP * 256);
+        gh[q] = sum_planes<KW>(red, ((rbo * NP + q) * 4 + qv) * 64 + lane, RB * NP * 256);
       const float r = sigm_f32(gxv[0] + biasx[0] + (gh[0] + bias[0]));
       const float z = sigm_f32(gxv[1] + biasx[1] + (gh[1] + bias[1]));
       const float q2 = gh[2] + bias[2];
@@ -471,14 +542,14 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       // (the lanes beyond H compute with unit H-1's projection, or an infinite input times a zero weight: whatever
       // that is - a NaN too, which a zero factor would keep - the h that the others multiply is zero)
       const float hn = jok ? (1.0f - z) * n + z * hpv : 0.f;
-      if (row < B) st_dev(hxg + (long)(t + 1) * xblk + xoff(row, nchx, j), hn, l2x);
+      if (row < B) st_dev(hxg + (long)(t + 1) * xblk + xb + xl, hn, l2x);
       if (ok) {
-        hsg[((long)(t + 1) * B + row) * H + j] = hn;
-        float* svr = sv + g * s_sv + ((long)t * B + row) * 4 * H;
-        svr[j] = r;
-        svr[H + j] = z;
-        svr[2 * H + j] = n;
-        svr[3 * H + j] = q2;
+        (hsg + (long)(t + 1) * B * H)[oh] = hn;
+        float* svt = sv + g * s_sv + (long)t * B * 4 * H;
+        svt[osv] = r;
+        (svt + H)[osv] = z;
+        (svt + 2 * H)[osv] = n;
+        (svt + 3 * H)[osv] = q2;
       }
       hpv = hn;
     }
@@ -487,7 +558,7 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
 }
 
 // Backward: steps t = T-1 down to 0.  The workgroup's resident slice is 16 columns of
-// W_hh (3H x H), kept transposed in LDS (16 rows of 3 HP, unit stride along the contraction).  dgh and
+// W_hh (3H x H).  dgh and
 // dgx hold the gate gradients of all steps (blocks of B x 3H); block t+1 of the exchanged copy is the
 // contraction operand of step t (none at t = T-1).  D holds the gradient carried into the last step (the
 // head's; d_zero: it is zero and D is not read).
@@ -507,10 +578,41 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
 // its whole register file, so that no wave of any other kernel (the merge of the other stream,
 // a short kernel queued behind) could start on a CU before this launch has ended.  The
 // attribute counts in halves of the unified VGPR/AGPR file on this target: 124 caps the wave at
-// 248 registers (2 dwords per lane are spilled), which leaves 16 per SIMD for a co-tenant.
+// 248 registers, which leaves 16 per SIMD for a co-tenant.
 typedef float f4ua __attribute__((ext_vector_type(4), aligned(4)));  // four floats at any 4-byte boundary
 
-template <int PRT>
+// The workgroup's share of dW_hh takes its operands in the order of the batch rows: a stage of the step's gate gradients,
+// transposed and split, [part][gate row][batch row].
+constexpr int SPT = 40;  // its pitch in values: 16-byte pieces of 16 gate rows in different banks
+
+// The batch rows of a lane's operand: 8 of the 32 with v_mfma_f32_16x16x32_bf16, 4 of the 16 with v_mfma_f32_16x16x16_bf16.
+typedef short bf16x4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ floatx4 dw_mfma(const bf16x8s& a, const bf16x8s& b, const floatx4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 dw_mfma(const bf16x4s& a, const bf16x4s& b, const floatx4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+// column jt of the rows v, split
+__device__ __forceinline__ void split_rows(const f4ua (&v)[8], int jt, bf16x8s (&h)[3]) {
+  const SplitFrag f = split_frag(make_float4(v[0][jt], v[1][jt], v[2][jt], v[3][jt]), make_float4(v[4][jt], v[5][jt], v[6][jt], v[7][jt]));
+#pragma unroll
+  for (int p = 0; p < 3; ++p) h[p] = f.p[p];
+}
+__device__ __forceinline__ void split_rows(const f4ua (&v)[4], int jt, bf16x4s (&h)[3]) {
+  uint2 p[3];
+  split2(v[0][jt], v[1][jt], p[0].x, p[1].x, p[2].x);
+  split2(v[2][jt], v[3][jt], p[0].y, p[1].y, p[2].y);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) h[i] = __builtin_bit_cast(bf16x4s, p[i]);
+}
+
+// How many of the three parts of the resident weights lie in LDS, the smallest first (each wave reads back only its own): with
+// them in registers the kernel would spill.
+__host__ __device__ constexpr int persist_bwd_nl(int ncw, int prt) { return ncw > 6 ? 0 : prt == 32 ? (ncw >= 3 ? 2 : 1) : ncw >= 6 ? 2 : ncw >= 4 ? 1 : 0; }
+
+// NCW: chunks of the contraction per wave (3 HP <= 256 NCW)
+template <int NCW, int PRT>
 __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_num_vgpr(124)))
 gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgh, float* dghx, long s_dghx,
                        float* __restrict__ dgx, long s_dg,
@@ -520,16 +622,20 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
                        unsigned spin_limit, unsigned* tickets, unsigned ticket_base, unsigned per_xcd,
                        float* __restrict__ dWp, float* __restrict__ dbp) {
   extern __shared__ __attribute__((aligned(16))) float persist_lds[];
-  constexpr int KW = PersistShape<PRT>::KW, RB = PersistShape<PRT>::RB;
+  constexpr int RB = PRT / 16;
+  constexpr int DR = PRT / 4;                                       // batch rows per lane of the dW_hh products
+  using DwFrag = std::conditional_t<PRT == 32, bf16x8s, bf16x4s>;
+  constexpr int JN = PRT == 32 ? 2 : 4;                             // columns split at a time (registers)
+  constexpr bool DW = NCW <= 6;                                     // (8 waves x 64 columns cover H)
+  constexpr int NL = persist_bwd_nl(NCW, PRT), NR = 3 - NL;         // parts of the weights in LDS, in registers
   const int NJ = (H + PJ - 1) / PJ, HP = NJ * PJ, RT = (B + PRT - 1) / PRT;
   const int H3 = 3 * H, HP3 = 3 * HP;
-  const int wp = (HP3 + PC - 1) / PC * PC + 4;
-  float* wres = persist_lds;                 // [16][wp]
-  float* red = wres + 16 * wp;               // [KW][RB][4][64]
-  float* stage = red + 8 * 4 * 64;           // [PRT][SP]: the step's dgh tile, batch row x gate row
-  int* lds_flag = reinterpret_cast<int*>(stage + PRT * SP);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kw = wave & (KW - 1), rsel = RB == 2 ? wave >> 2 : 0;
+  const int nch = (HP3 + PC - 1) / PC;
+  float* red = persist_lds;                                         // [8][RB][4][64]
+  __bf16* stage = reinterpret_cast<__bf16*>(red + 8 * RB * 256);    // [3 parts][48][SPT]
+  u32x4_t* wl = reinterpret_cast<u32x4_t*>(stage + 3 * 48 * SPT);   // [8 waves][NCW][NL][64 lanes]
+  int* lds_flag = reinterpret_cast<int*>(wl + 8 * NCW * NL * 64);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   unsigned* abort_w = sync;
   int tx, sg;
@@ -542,49 +648,61 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
   __builtin_amdgcn_s_setprio(3);
   // weight-gradient share: this lane's 4 columns (clamped: results outside H are not stored)
   const int wn = 64 * wave + 4 * lr;
-  const bool wn_ok = dWp != nullptr && wn < H;
+  const bool dw_wave = DW && dWp != nullptr && 64 * wave < H;  // (uniform)
+  const bool wn_ok = dw_wave && wn < H;
   const int wnc = wn < H ? wn : 0;
   floatx4 dw[3][4];
 #pragma unroll
   for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
     for (int jt = 0; jt < 4; ++jt) dw[mt][jt] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  {
-    // wres[m][q HP + k] = W_hh[q H + k][j0 + m]: 64-byte pieces of 3H rows, transposed on the way into LDS
-    const float* Wg = W_hh + g * s_rep + j0;
-    if (j0 + PJ <= H && H == HP && ((uintptr_t)Wg & 15) == 0) {
-      for (int u = tid; u < H3 * 4; u += PNT) {
-        const int k = u >> 2, c4 = u & 3;
-        const float4 v = *reinterpret_cast<const float4*>(Wg + (long)k * H + 4 * c4);
-        wres[(4 * c4 + 0) * wp + k] = v.x;
-        wres[(4 * c4 + 1) * wp + k] = v.y;
-        wres[(4 * c4 + 2) * wp + k] = v.z;
-        wres[(4 * c4 + 3) * wp + k] = v.w;
-      }
-    } else {
-#pragma unroll 8
-      for (int u = tid; u < HP3 * PJ; u += PNT) {
-        const int k = u >> 4, m = u & 15, q = (k >= HP ? 1 : 0) + (k >= 2 * HP ? 1 : 0), kk = k - q * HP;
-        const float v = Wg[((long)q * H + min(kk, H - 1)) * H + min(m, H - 1 - j0)];
-        wres[m * wp + k] = kk < H && j0 + m < H ? v : 0.f;
-      }
+  // resident fragments: W_hh[q H + k][j0 + lr] for the contraction indices q HP + k of chunk wave + 8 i
+  auto weight_frag = [&](int c, const float* Wh, int H, float4 (&v)[2]) {
+    const float* Wj = Wh + g * s_rep + min(j0 + lr, H - 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kk = PC * c + 16 * h, q = (kk >= HP ? 1 : 0) + (kk >= 2 * HP ? 1 : 0), k = kk - q * HP + 4 * lg;
+      const bool in = kk < HP3 && j0 + lr < H;
+      const float* p = Wj + (long)q * H * H;
+      v[h] = make_float4(in && k < H ? p[(long)k * H] : 0.f, in && k + 1 < H ? p[(long)(k + 1) * H] : 0.f,
+                         in && k + 2 < H ? p[(long)(k + 2) * H] : 0.f, in && k + 3 < H ? p[(long)(k + 3) * H] : 0.f);
     }
-    const int padk = wp - 4 - HP3;  // zero columns up to the next multiple of the chunk
-    for (int u = tid; u < 16 * padk; u += PNT) wres[(u / padk) * wp + HP3 + u % padk] = 0.f;
+  };
+  bf16x8s w[NCW][NR];
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    float4 v[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+    if (wave + 8 * i < nch) weight_frag(wave + 8 * i, W_hh, H, v);
+    const SplitFrag f = split_frag(v[0], v[1]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if (p < NR) w[i][p < NR ? p : 0] = f.p[p];
+      else wl[((wave * NCW + i) * NL + p - NR) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[p]);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // (or the pieces of all chunks take registers at once)
   }
   float bsum[4] = {0.f, 0.f, 0.f, 0.f};  // this thread's da_r, da_z, da_n, dq summed over the steps
   const int j = j0 + lr, jc = min(j, H - 1);
   const bool act = RB == 2 || wave < 4;
-  const int qv = wave & 3;
-  const int row = r0 + rsel * 16 + 4 * lg + qv;
+  const int qv = wave & 3, rbo = RB == 2 ? wave >> 2 : 0;
+  const int rt = rbo * 16 + 4 * lg + qv;  // this thread's row of the tile
+  const int row = r0 + rt;
   const int rowc = min(row, B - 1);
   const bool ok = row < B && j < H;
+  const int ohv = ((r0 + DR * lg) * H + wnc) * 4;
+  const unsigned osv = rowc * 4 * H + jc, oh = rowc * H + jc, og = row * H3 + j;
+  // where the lane's gate q goes in a step's block: word xb[q] + xl
+  const unsigned xl = (((lr >> 2) << 4) + (row & 15)) * 4 + (lr & 3);
+  unsigned xb[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) xb[q] = ((r0 / 16 + rbo) * nch * 2 + (q * HP + j0) / 16) * 256;
   float dcar = d_zero || !ok || !act ? 0.f : D[g * s_D + (long)rowc * H + jc];  // dh_{t+1} * z_{t+1}, carried in a register
-  float* dghg = dgh ? dgh + g * s_dg : nullptr;  // row-major, for later launches (nullptr: nobody reads it)
+  // (dgh: row-major, for later launches; nullptr: nobody reads it)
   float* dgxg = dghx + g * s_dghx;               // the gate gradients as the workgroups exchange them
   const long xblk = xblock_words(B, HP3);
-  const int nchx = (HP3 + PC - 1) / PC;
-  const int rbx = (r0 + rsel * 16 < B ? r0 + rsel * 16 : r0) >> 4;
+  int rbx[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) rbx[rb] = (r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4;
   __syncthreads();
   int it = 0;
   for (int t = T - 1; t >= 0; --t, ++it) {
@@ -592,24 +710,65 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
     // registers, spills - measured, 400 -> 620 us)
     float r = 0.f, z = 0.f, n = 0.f, q = 0.f, hp = 0.f, ab = 0.f;
     if (act) {
-      const long e = ((long)t * B + rowc) * H + jc;
-      const float* svr = sv + g * s_sv + ((long)t * B + rowc) * 4 * H;
-      r = svr[jc], z = svr[H + jc], n = svr[2 * H + jc], q = svr[3 * H + jc];
-      hp = hs[g * s_hs + e];
-      ab = above ? above[g * s_above + e] : 0.f;
+      // (uniform addresses and 32-bit offsets of the lane: a lane's own addresses would take registers this kernel has not got)
+      const float* svt = sv + g * s_sv + (long)t * B * 4 * H;
+      r = svt[osv], z = (svt + H)[osv], n = (svt + 2 * H)[osv], q = (svt + 3 * H)[osv];
+      hp = (hs + g * s_hs + (long)t * B * H)[oh];
+      ab = above ? (above + g * s_above + (long)t * B * H)[oh] : 0.f;
     }
     if (it > 0 && !group_wait(flags, NJ, base + (unsigned)it, abort_w, spin_limit, lds_flag)) return;
-    floatx4 acc[2][1];
-    acc[0][0] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    acc[1][0] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    if (t + 1 < T)  // uniform over the grid
-      resident_contraction_x<1, RB == 2 ? 12 : 6, KW>(wres, wp, tile_rsrc(dgxg + (long)(t + 1) * xblk), HP3, rbx, kw, acc, []() {});
+    floatx4 big[RB][1], small[RB][1];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) red[((kw * RB + rsel) * 4 + v) * 64 + lane] = acc[0][0][v] + acc[1][0][v];
+    for (int rb = 0; rb < RB; ++rb) big[rb][0] = small[rb][0] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    if (t + 1 < T) {  // uniform over the grid
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(dgxg + (long)(t + 1) * xblk);
+      constexpr int AHEAD = RB == 1 ? 6 : NCW == 6 ? 2 : 3, NA = NCW < AHEAD ? NCW : AHEAD;  // chunks in flight
+      float4 a[NA][RB][2];
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          if (wave + 8 * i < nch) exchange_frag(rs, nch, HP3, rbx[rb], wave + 8 * i, a[i][rb]);  // (uniform)
+      __builtin_amdgcn_sched_barrier(0);  // these loads are issued before anything waits for one
+#pragma unroll
+      for (int i = 0; i < NCW; ++i) {
+        if (wave + 8 * i < nch) {
+          SplitFrag wi[1];
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            wi[0].p[p] = p < NR ? w[i][p < NR ? p : 0] : __builtin_bit_cast(bf16x8s, wl[((wave * NCW + i) * NL + p - NR) * 64 + lane]);
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            const SplitFrag f = split_frag(a[i % NA][rb][0], a[i % NA][rb][1]);
+            if (i + NA < NCW && wave + 8 * (i + NA) < nch) exchange_frag(rs, nch, HP3, rbx[rb], wave + 8 * (i + NA), a[i % NA][rb]);
+            split_mfmas(f, wi, big[rb], small[rb]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        big[rb][0] += small[rb][0];
+        if (__builtin_expect(any_beyond(big[rb][0]), 0)) {
+          big[rb][0] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int c = wave; c < nch; c += 8) {
+            float4 v[2], x[2];
+            exchange_frag(rs, nch, HP3, rbx[rb], c, x);
+            weight_frag(c, rarely(W_hh), rarely(H), v);
+            plain_mfmas(x, v, PC * c + 16 < HP3, big[rb][0]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[((wave * RB + rb) * 4 + v) * 64 + lane] = big[rb][0][v];
     __syncthreads();
     float da_r = 0.f, da_z = 0.f, dq = 0.f;
     if (act) {
-      const float rec = sum_planes<KW>(red, (rsel * 4 + qv) * 64 + lane, RB * 256);
+      const float rec = sum_planes<8>(red, (rbo * 4 + qv) * 64 + lane, RB * 256);
       // (a unit beyond H reads another unit's gates; its gradient is forced to zero)
       const float dh = ok ? (dcar + ab) + rec : 0.f;
       const float dn = dh * (1.0f - z);
@@ -620,20 +779,20 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
       da_z = dz * z * (1.0f - z);
       if (row < B) {
         float* oe = dgxg + (long)t * xblk;
-        st_dev(oe + xoff(row, nchx, j), da_r, l2x);
-        st_dev(oe + xoff(row, nchx, HP + j), da_z, l2x);
-        st_dev(oe + xoff(row, nchx, 2 * HP + j), dq, l2x);
+        st_dev(oe + xb[0] + xl, da_r, l2x);
+        st_dev(oe + xb[1] + xl, da_z, l2x);
+        st_dev(oe + xb[2] + xl, dq, l2x);
       }
       if (ok) {
-        float* ox = dgx + g * s_dg + ((long)t * B + row) * H3;
-        ox[j] = da_r;
-        ox[H + j] = da_z;
-        ox[2 * H + j] = da_n;
-        if (dghg) {
-          float* oh = dghg + ((long)t * B + row) * H3;
-          oh[j] = da_r;
-          oh[H + j] = da_z;
-          oh[2 * H + j] = dq;
+        float* ox = dgx + g * s_dg + (long)t * B * H3;
+        ox[og] = da_r;
+        (ox + H)[og] = da_z;
+        (ox + 2 * H)[og] = da_n;
+        if (dgh) {
+          float* ohg = dgh + g * s_dg + (long)t * B * H3;
+          ohg[og] = da_r;
+          (ohg + H)[og] = da_z;
+          (ohg + 2 * H)[og] = dq;
         }
       }
       dcar = dh * z;
@@ -642,38 +801,62 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
       bsum[2] += da_n;
       bsum[3] += dq;
     }
-    constexpr int S4 = PRT / 4;
-    float4 hv[S4];
-    if (dWp) {  // uniform
+    f4ua hv[DR];
+    if (DW && dWp) {  // uniform
       // rows beyond the batch contribute nothing: their staged gradients are zero, their h is
       // read from a valid row
       if (act) {
-        float* st = stage + (rsel * 16 + 4 * lg + qv) * SP + lr;
-        st[0] = da_r;
-        st[16] = da_z;
-        st[32] = dq;
-      }
-      const float* hrow = hs + g * s_hs + (long)t * B * H + wnc;
+        const float d3[3] = {da_r, da_z, dq};
 #pragma unroll
-      for (int s8 = 0; s8 < S4; ++s8) {
-        const f4ua v = *reinterpret_cast<const f4ua*>(hrow + (long)min(r0 + 4 * s8 + lg, B - 1) * H);
-        hv[s8] = make_float4(v.x, v.y, v.z, v.w);
+        for (int i = 0; i < 3; ++i) {
+          uint32_t p0, p1, p2;
+          split2(d3[i], 0.f, p0, p1, p2);
+          __bf16* st = stage + (i * 16 + lr) * SPT + rt;
+          st[0] = __builtin_bit_cast(bf16x2, p0)[0];
+          st[48 * SPT] = __builtin_bit_cast(bf16x2, p1)[0];
+          st[2 * 48 * SPT] = __builtin_bit_cast(bf16x2, p2)[0];
+        }
+      }
+      if (dw_wave) {
+        // (rows beyond the batch are zeros but for the first, which the block behind it holds)
+        const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hs + g * s_hs + (long)t * B * H), 0,
+                                                                            (B * H + 4) * 4, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < DR; ++e)
+          hv[e] = __builtin_bit_cast(f4ua, __builtin_amdgcn_raw_buffer_load_b128(rh, ohv, e * H * 4, 0));
       }
     }
     group_signal(flags + tx, base + (unsigned)it + 1u, l2x);  // (its barrier also publishes the staged tile to the workgroup)
-    if (dWp) {
+    if (dw_wave) {
+      // The sum over the step's rows by itself, then added: the running sum is rounded once a step.  (A gate gradient that is
+      // not finite makes NaN of it, as it does in any case: it reaches every unit one step earlier in time, and h_0 is zero.)
 #pragma unroll
-      for (int s8 = 0; s8 < S4; ++s8) {
-        float am[3];
+      for (int jp = 0; jp < 4; jp += JN) {
+        DwFrag h[JN][3];
 #pragma unroll
-        for (int mt = 0; mt < 3; ++mt) am[mt] = stage[(4 * s8 + lg) * SP + mt * 16 + lr];
+        for (int i = 0; i < JN; ++i) split_rows(hv, jp + i, h[i]);
 #pragma unroll
         for (int mt = 0; mt < 3; ++mt) {
-          dw[mt][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(am[mt], hv[s8].x, dw[mt][0], 0, 0, 0);
-          dw[mt][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(am[mt], hv[s8].y, dw[mt][1], 0, 0, 0);
-          dw[mt][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(am[mt], hv[s8].z, dw[mt][2], 0, 0, 0);
-          dw[mt][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(am[mt], hv[s8].w, dw[mt][3], 0, 0, 0);
+          DwFrag am[3];
+#pragma unroll
+          for (int p = 0; p < 3; ++p) am[p] = *reinterpret_cast<const DwFrag*>(stage + (p * 48 + mt * 16 + lr) * SPT + DR * lg);
+          floatx4 sm[JN];
+#pragma unroll
+          for (int i = 0; i < JN; ++i) sm[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+          auto mul = [&](int pa, int ph) {
+#pragma unroll
+            for (int i = 0; i < JN; ++i) sm[i] = dw_mfma(am[pa], h[i][ph], sm[i]);
+          };
+          mul(1, 1);
+          mul(2, 0);
+          mul(0, 2);
+          mul(1, 0);
+          mul(0, 1);
+          mul(0, 0);
+#pragma unroll
+          for (int i = 0; i < JN; ++i) dw[mt][jp + i] += sm[i];
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -681,10 +864,10 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
     // bias gradients: sums over the tile's batch rows, in row order; one partial sum per
     // batch-row tile: [b_ih: r | z | n][b_hh: r | z | q], 6H floats
     __syncthreads();
-    float* bs = stage;  // [PRT][64]: row, then 4 sums x 16 units
+    float* bs = reinterpret_cast<float*>(stage);  // [PRT][64]: row, then 4 sums x 16 units
     if (act) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bs[(rsel * 16 + 4 * lg + qv) * 64 + i * 16 + lr] = bsum[i];
+      for (int i = 0; i < 4; ++i) bs[rt * 64 + i * 16 + lr] = bsum[i];
     }
     __syncthreads();
     if (tid < 64) {
@@ -747,7 +930,6 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
 // Rows of the last row block beyond the batch are never written: what a consumer reads there goes
 // into output rows that are never stored.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int QJ = 32;       // hidden units per workgroup
 constexpr int TP = 40;       // pitch (bf16) of a staged transposed row of 32 batch rows
@@ -1191,19 +1373,22 @@ int groups_per_launch(int NJ, int SG) {
   return most >= 8 ? most / 8 * 8 : most;  // (whole rounds over the XCDs)
 }
 
-// forward: 48 rows of H (rounded up to the chunk) + 4 words, the partial sums, the flag words;
-// backward: 16 rows of 3H (rounded up) + 4 words, fewer partial sums, the staged tile
-size_t persist_lds_bytes(int H) {
-  const int HP = (H + PJ - 1) / PJ * PJ;
-  const size_t fwd = (size_t)48 * ((HP + PC - 1) / PC * PC + 4) + 8 * 3 * 4 * 64 + 4;
-  const size_t bwd = (size_t)16 * ((3 * HP + PC - 1) / PC * PC + 4) + 8 * 4 * 64 + PR * SP + 4;
-  return (fwd > bwd ? fwd : bwd) * sizeof(float);
+// Widths the fp32 launches take: a group's members' flags fit its words, the weight parts a wave's registers.
+constexpr int kPersistMaxH = 704;
+// forward: the waves that share a contraction (and the batch rows per wave that follow from it), see the kernel
+int persist_fwd_kw(int H, int rows) { return rows == 32 && H <= 512 ? 4 : 8; }
+size_t persist_fwd_lds(int rows, int width, int kw, int ncw, int xnb) {
+  return (size_t)kw * (rows / 16) * (width ? 4 : 3) * 1024 + (size_t)((width + PC - 1) / PC) * 9 * 1024 +
+         (persist_fwd_lw(ncw, xnb, rows / 16 * kw / 8) ? (size_t)kw * ncw * 3 * 1024 : 0) + 16;
 }
-// forward with the input projection: a fourth plane of partial sums and 48 rows of W_ih
-size_t persist_xp_lds_bytes(int H, int width) {
-  const int HP = (H + PJ - 1) / PJ * PJ;
-  return ((size_t)48 * ((HP + PC - 1) / PC * PC + 4) + 8 * 4 * 4 * 64 + (size_t)48 * ((width + PC - 1) / PC * PC + 4) + 4) *
-         sizeof(float);
+// backward: chunks per wave
+int persist_bwd_ncw(int H) {
+  const int n = (3 * ((H + PJ - 1) / PJ * PJ) + 8 * PC - 1) / (8 * PC);
+  return n <= 4 ? (n < 2 ? 2 : n) : n <= 6 ? 6 : 9;
+}
+size_t persist_bwd_lds(int H, int rows) {
+  const int n = persist_bwd_ncw(H);
+  return (size_t)8 * (rows / 16) * 1024 + (size_t)3 * 48 * SPT * 2 + (size_t)8 * n * persist_bwd_nl(n, rows) * 1024 + 16;
 }
 
 }  // namespace
@@ -1213,7 +1398,7 @@ size_t persist_xp_lds_bytes(int H, int width) {
 // workers' workgroups then still fit the chip; more workgroups than CUs go out as several launches of
 // whole synchronisation groups, of 32 rows each where a batch has more than 16.
 int gru_persist_rows(int B, int H, int K) {
-  if (H < 16 || B < 1 || K < 1 || persist_lds_bytes(H) > kLdsLimit) return 0;
+  if (H < 16 || B < 1 || K < 1 || H > kPersistMaxH) return 0;
   const long NJ = (H + PJ - 1) / PJ;
   return B <= 16 || NJ * ((B + 15) / 16) * K <= kPlanCus ? 16 : 32;
 }
@@ -1246,10 +1431,10 @@ size_t gru_persist_sync_words(int B, int groups, int rows) { return (size_t)grou
 // How much every flag advances per time step of a launch.
 unsigned gru_persist_count_per_step(int) { return 1u; }
 
-// The forward kernel can do the input projection itself when the layer input is narrow enough
-// for the 48 rows of W_ih to fit the LDS beside those of W_hh (at most 2 x 4 chunks of 32).
+// The forward kernel can do the input projection itself when the layer input is narrow (at most 2 chunks of 32 per
+// wave; beside a wide layer a product of its own is no slower).
 bool gru_persist_xproj_supported(int H, int width) {
-  return width >= 16 && width % 16 == 0 && width <= 256 && persist_xp_lds_bytes(H, width) <= kLdsLimit;
+  return width >= 16 && width % 16 == 0 && width <= 256 && (H + PC - 1) / PC + (width + PC - 1) / PC <= 21;
 }
 
 size_t gru_persist_exchange_words(int B, int H, int gates) { return (size_t)xblock_words(B, gates * ((H + PJ - 1) / PJ * PJ)); }
@@ -1260,36 +1445,46 @@ hipError_t launch_gru_fwd_persist(const float* W_hh, const float* b_hh, long s_r
                                   unsigned* sync, unsigned base, unsigned spin_limit, const float* xin, long s_x,
                                   int width, const float* W_ih, const float* b_ih, bool device_scope, unsigned* ticket_launches, hipStream_t s) {
   const int NJ = (H + PJ - 1) / PJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
-  if ((rows != 16 && rows != 32) || T < 1 || persist_lds_bytes(H) > kLdsLimit || NJ > device_cus()) return hipErrorInvalidValue;
+  if ((rows != 16 && rows != 32) || T < 1 || H > kPersistMaxH || NJ > device_cus()) return hipErrorInvalidValue;
   if (!hx || ((uintptr_t)hx & 15) != 0 || (s_hx & 3) != 0) return hipErrorInvalidValue;
   if (xin && (!gru_persist_xproj_supported(H, width) || !W_ih || !b_ih || ((uintptr_t)xin & 15) != 0 || (s_x & 3) != 0))
     return hipErrorInvalidValue;
   if (!xin && !gx) return hipErrorInvalidValue;
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * ((double)H + (xin ? width : 0)) * T * groups, s);
-#define HPSGD_FWD_PERSIST(N, R)                                                                                   \
+#define HPSGD_FWD_PERSIST(C, N, R, KW)                                                                            \
   do {                                                                                                            \
-    static std::atomic<size_t> allowed{0};                                                                                    \
-    const hipError_t e = allow_lds((const void*)gru_fwd_persist_kernel<N, R>, pl.lds, allowed);                   \
+    static std::atomic<size_t> allowed{0};                                                                        \
+    const hipError_t e = allow_lds((const void*)gru_fwd_persist_kernel<C, N, R, KW>, pl.lds, allowed);            \
     if (e != hipSuccess) return e;                                                                                \
-    hipLaunchKernelGGL((gru_fwd_persist_kernel<N, R>), dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
+    hipLaunchKernelGGL((gru_fwd_persist_kernel<C, N, R, KW>), dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, b_hh, s_rep, gx, s_gx, hs, \
                        s_hs, hx, s_hx, sv, s_sv, B, H, T, sg0, n_sg, sync, base, spin_limit, pl.tickets, pl.ticket_base, \
                        pl.per_xcd, xin, s_x, width, W_ih, b_ih);                                                  \
   } while (0)
-  const int per_wave = 32 * (rows == 32 ? 4 : 8);  // columns of the layer input the waves cover with one chunk each
-  const int xnb = !xin ? 0 : (width + per_wave - 1) / per_wave;
+#define HPSGD_FWD_PERSIST_X(C, R, KW, XMAX)                \
+  do {                                                     \
+    if (xnb == 0) HPSGD_FWD_PERSIST(C, 0, R, KW);          \
+    else if (xnb == 1) HPSGD_FWD_PERSIST(C, 1, R, KW);     \
+    else HPSGD_FWD_PERSIST(C, XMAX, R, KW);                \
+  } while (0)
+  const int kw = persist_fwd_kw(H, rows);
+  const int xnb = !xin ? 0 : (width + 32 * kw - 1) / (32 * kw);  // chunks of the layer input per wave
+  const int least = rows == 16 ? 1 : kw == 4 ? 2 : 3, ncw = std::max(least, ((NJ * PJ + PC - 1) / PC + kw - 1) / kw);
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
-    const Placement pl = placement(sync, SG, n_sg, NJ, xin ? persist_xp_lds_bytes(H, width) : persist_lds_bytes(H), device_scope,
-                                   ticket_launches);
+    const Placement pl = placement(sync, SG, n_sg, NJ, persist_fwd_lds(rows, xin ? width : 0, kw, ncw, xnb), device_scope, ticket_launches);
     if (rows == 16) {
-      if (xnb == 0) HPSGD_FWD_PERSIST(0, 16);
-      else HPSGD_FWD_PERSIST(1, 16);
+      if (ncw == 1) HPSGD_FWD_PERSIST_X(1, 16, 8, 1);
+      else if (ncw == 2) HPSGD_FWD_PERSIST_X(2, 16, 8, 1);
+      else HPSGD_FWD_PERSIST_X(3, 16, 8, 1);
+    } else if (kw == 4) {
+      if (ncw == 2) HPSGD_FWD_PERSIST_X(2, 32, 4, 2);
+      else if (ncw == 3) HPSGD_FWD_PERSIST_X(3, 32, 4, 2);
+      else HPSGD_FWD_PERSIST_X(4, 32, 4, 2);
     } else {
-      if (xnb == 0) HPSGD_FWD_PERSIST(0, 32);
-      else if (xnb == 1) HPSGD_FWD_PERSIST(1, 32);
-      else HPSGD_FWD_PERSIST(2, 32);
+      HPSGD_FWD_PERSIST_X(3, 32, 8, 1);
     }
   }
+#undef HPSGD_FWD_PERSIST_X
 #undef HPSGD_FWD_PERSIST
   return hipGetLastError();
 }
@@ -1301,25 +1496,36 @@ hipError_t launch_gru_bwd_persist(const float* W_hh, long s_rep, float* dgh, flo
                                   int groups, int rows, unsigned* sync, unsigned base, unsigned spin_limit, float* dWp,
                                   float* dbp, bool device_scope, unsigned* ticket_launches, hipStream_t s) {
   const int NJ = (H + PJ - 1) / PJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
-  if ((rows != 16 && rows != 32) || T < 1 || persist_lds_bytes(H) > kLdsLimit || NJ > device_cus()) return hipErrorInvalidValue;
+  if ((rows != 16 && rows != 32) || T < 1 || H > kPersistMaxH || NJ > device_cus()) return hipErrorInvalidValue;
   if ((dWp && !gru_persist_dw_supported(H)) || !dghx || ((uintptr_t)dghx & 15) != 0 || (s_dghx & 3) != 0)
     return hipErrorInvalidValue;
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * (dWp ? 2 : 1), s);
-#define HPSGD_BWD_PERSIST(R)                                                                                        \
+#define HPSGD_BWD_PERSIST(C, R)                                                                                     \
   do {                                                                                                              \
-    static std::atomic<size_t> allowed{0};                                                                                      \
-    const hipError_t e = allow_lds((const void*)gru_bwd_persist_kernel<R>, pl.lds, allowed);                        \
+    static std::atomic<size_t> allowed{0};                                                                          \
+    const hipError_t e = allow_lds((const void*)gru_bwd_persist_kernel<C, R>, pl.lds, allowed);                     \
     if (e != hipSuccess) return e;                                                                                  \
-    hipLaunchKernelGGL(gru_bwd_persist_kernel<R>, dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, s_rep, dgh, dghx, s_dghx, dgx, \
+    hipLaunchKernelGGL((gru_bwd_persist_kernel<C, R>), dim3(pl.grid), dim3(PNT), pl.lds, s, W_hh, s_rep, dgh, dghx, s_dghx, dgx, \
                        s_dg, D, s_D, d_zero ? 1 : 0, above, s_above, sv, s_sv, hs, s_hs, B, H, T, sg0, n_sg, sync, base, \
                        spin_limit, pl.tickets, pl.ticket_base, pl.per_xcd, dWp, dbp);                               \
   } while (0)
+#define HPSGD_BWD_PERSIST_C(C)           \
+  do {                                   \
+    if (rows == 16) HPSGD_BWD_PERSIST(C, 16); \
+    else HPSGD_BWD_PERSIST(C, 32);       \
+  } while (0)
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
-    const Placement pl = placement(sync, SG, n_sg, NJ, persist_lds_bytes(H), device_scope, ticket_launches);
-    if (rows == 16) HPSGD_BWD_PERSIST(16);
-    else HPSGD_BWD_PERSIST(32);
+    const Placement pl = placement(sync, SG, n_sg, NJ, persist_bwd_lds(H, rows), device_scope, ticket_launches);
+    switch (persist_bwd_ncw(H)) {
+      case 2: HPSGD_BWD_PERSIST_C(2); break;
+      case 3: HPSGD_BWD_PERSIST_C(3); break;
+      case 4: HPSGD_BWD_PERSIST_C(4); break;
+      case 6: HPSGD_BWD_PERSIST_C(6); break;
+      default: HPSGD_BWD_PERSIST_C(9); break;
+    }
   }
+#undef HPSGD_BWD_PERSIST_C
 #undef HPSGD_BWD_PERSIST
   return hipGetLastError();
 }

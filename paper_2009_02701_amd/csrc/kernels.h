@@ -246,11 +246,11 @@ hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* abov
 // its transposes: dgxT [3H][ld_T] = (r | z | n)^T, dghT = (r | z | q)^T over R = T B rows, in one launch
 hipError_t launch_transpose_dg4(const void* dg4, long s_dg4, void* dgxT, void* dghT, long ld_T, long s_T, int R, int H, int groups,
                                 hipStream_t s);
-// ---- whole runs of time steps in one launch, W_hh resident in LDS (fp32), see gru_persist.hip ----
+// ---- whole runs of time steps in one launch, W_hh resident on the chip (fp32), see gru_persist.hip ----
 // sync: gru_persist_sync_words() words of device memory (the abort word, the flag words of the
 // synchronisation groups, 8 ticket counters); base: what the flags read when the launch starts; every launch
 // advances them by steps * gru_persist_count_per_step().  spin_limit bounds every wait.
-// any H from 16 up to what the LDS holds; rows: batch rows per workgroup, as gru_persist_rows gives them
+// any H from 16 to 704; rows: batch rows per workgroup, as gru_persist_rows gives them
 // for the context's K workers, however many of them a call steps (0: does not fit).  More workgroups than the chip
 // has CUs run as several launches where that pays, which goes by the workers of the call (gru_persist_pays): stepping
 // one worker and stepping all of them may take different forms, whose sums differ in their order.

@@ -1,0 +1,53 @@
+// fp32 products on the bf16 matrix cores.
+//
+// An fp32 value is exactly the sum of three bf16 values: h0 = bf16(x), h1 = bf16(x - h0), h2 = x - h0 - h1 (24 bits of
+// significand in 8 + 8 + 8; both differences are exact).  A product of two such sums is nine products of bf16 values, each
+// exact in fp32; the six largest are kept,
+//     a0 b0   |   a1 b0 + a0 b1 + a1 b1 + a2 b0 + a0 b2,
+// and what is dropped (a1 b2, a2 b1, a2 b2) is below 2^-23 of the product, mostly below 2^-25, of either sign.  The bf16 instruction does sixteen
+// times the multiply-adds of the fp32 one per cycle, so six of them are 2.7 times as fast.  Two sums are kept, one of a0 b0
+// and one of the rest: the instruction adds 16 products at a time to its accumulator, so the large sum is rounded an eighth as
+// often as with v_mfma_f32_32x32x2_f32, and the small sum's roundings are 2^-8 smaller.  Error against 64 bits
+// (2-norm, N(0,1) operands), fp32 instruction / six bf16 products in one sum / in two sums:
+//     contraction 16  7.4e-8 / 3.4e-8 / 3.2e-8,  128  2.0e-7 / 1.6e-7 / 6.6e-8,  1024  5.7e-7 / 4.9e-7 / 1.8e-7,  2240  8.5e-7 / 7.4e-7 / 2.9e-7.
+//
+// The ends of the range: an infinity, a NaN and a value that rounds to a bf16 infinity (above 3.39e38) make a NaN of what they reach
+// (h1 = inf - inf), so a caller computes the outputs that are not finite again with the fp32 instruction.
+// Values below 2^-110 = 7.7e-34 lose low bits of h1 and h2 to the end of the exponent's range.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace hpsgd {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8s __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ uint32_t split_round2(float x, float y) {
+  bf16x2 v;
+  v[0] = (__bf16)x;
+  v[1] = (__bf16)y;
+  uint32_t p = __builtin_bit_cast(uint32_t, v);
+  asm("" : "+v"(p));  // (or x is rounded once more by itself where its half is widened)
+  return p;
+}
+// (The differences as v_dot2_f32_bf16 would save the two instructions that widen a pair, but that instruction waits for the matrix
+// unit, which the ones below run beside: a 32-cycle MFMA with four of them 56 cycles, with four of these 34.)
+__device__ __forceinline__ float split_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float split_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+// the three parts of x (low halves) and y (high halves)
+__device__ __forceinline__ void split2(float x, float y, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
+  p0 = split_round2(x, y);
+  const float rx = x - split_lo(p0), ry = y - split_hi(p0);
+  p1 = split_round2(rx, ry);
+  p2 = split_round2(rx - split_lo(p1), ry - split_hi(p1));
+}
+// ... of eight values, as the operands of a matrix instruction
+__device__ __forceinline__ void split8(const float (&v)[8], uint4& p0, uint4& p1, uint4& p2) {
+  split2(v[0], v[1], p0.x, p1.x, p2.x);
+  split2(v[2], v[3], p0.y, p1.y, p2.y);
+  split2(v[4], v[5], p0.z, p1.z, p2.z);
+  split2(v[6], v[7], p0.w, p1.w, p2.w);
+}
+
+}  // namespace hpsgd
