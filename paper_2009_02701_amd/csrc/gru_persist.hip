@@ -48,8 +48,8 @@
 // the conversions beside them.  Where registers run out the smallest parts of the weights lie in LDS (persist_fwd_lw,
 // persist_bwd_nl: a launch that spills is slower than the fp32 instruction, its reloads queue up with the operands).
 // us per launch, before / now (forward, backward with its share of dW_hh):
-//   35 steps, H = 512, 4 workers of 64 rows, input of 128     239 / 197    392 / 338
-//   35 steps, H = 256, 4 workers of 16 rows, input of 128     146 /  89    182 / 134
+//   35 steps, H = 512, 4 workers of 64 rows, input of 128     239 / 197    392 / 338   (168, 280 since two blocks take turns, below)
+//   35 steps, H = 256, 4 workers of 16 rows, input of 128     146 /  89    182 / 134   ( 84, 114)
 //    9 steps, H = 320, 4 workers of 40 rows, input of 32       48 /  38     57 /  50
 // The contraction is cut into 32-wide chunks, chunk c belongs to the waves with wave % KW == c % KW; partial sums are combined
 // through LDS.
@@ -186,6 +186,15 @@ __device__ __forceinline__ bool persist_place(unsigned* tickets, unsigned ticket
   __syncthreads();  // (the words are used again by the first wait)
   return sg >= 0;
 }
+
+// The block of the exchange buffer that holds h_t, and that of the gate gradients of step t.  Where the group shares one L2
+// two blocks take turns (block 0 keeps h_0): a workgroup that writes h_t has seen every member finish step t - 1, which
+// is behind the member's reads of h_{t-2}; likewise backward.  Their lines then stay in the L2, where a block per step
+// would be written into new lines that push others out: the operands of a backward step of 32 rows x 1024 units (bf16)
+// arrive in 4100 cycles instead of 6100 to 6900, and its launch of 35 steps takes 180 us instead of 216 (forward 128, before 152).  At device scope every step has its own block: another XCD's L2 must not
+// hold its lines from an earlier step.
+__device__ __forceinline__ long fwd_block(int t, bool l2x) { return l2x && t > 0 ? 2 - (t & 1) : t; }
+__device__ __forceinline__ long bwd_block(int t, bool l2x) { return l2x ? t & 1 : t; }
 
 // 16 bytes at byte offset `off` (the lane's) + `from` (uniform) of the buffer, as a device-scope load
 __device__ __forceinline__ float4 ld16_dev(__amdgpu_buffer_rsrc_t rs, int off, int from) {
@@ -483,15 +492,13 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
     }
     if (t > 0 && !group_wait(flags, NJ, base + (unsigned)t, abort_w, spin_limit, lds_flag)) return;
     {
-      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(hxg + (long)t * xblk);
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(hxg + fwd_block(t, l2x) * xblk);
       float4 a[RBW][NCW][2];
 #pragma unroll
       for (int i = 0; i < NCW; ++i)
 #pragma unroll
         for (int rb = 0; rb < RBW; ++rb)
           if (kw + KW * i < nch) exchange_frag(rs, nch, HP, rbx[rb], kw + KW * i, a[rb][i]);  // (uniform)
-      __builtin_amdgcn_sched_barrier(0);
-      load_x(min(t + 1, T - 1));  // step t+1's layer input (or input projection) travels during this step's product
       __builtin_amdgcn_sched_barrier(0);  // every load is issued before anything waits for one
       if (__builtin_expect(beyond, 0)) {
         const int Hr = rarely(H);
@@ -520,6 +527,11 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
           for (int rb = 0; rb < RBW; ++rb) split_mfmas(split_frag(a[rb][i][0], a[rb][i][1]), wi, big[rb], small[rb]);
         }
       }
+      // Step t+1's layer input (or input projection).  Not in front of the products: a CU's loads return in the order of their
+      // issue, whichever wave's they are, and the second four waves' operands would wait for these to come from memory.
+      __builtin_amdgcn_sched_barrier(0);
+      load_x(min(t + 1, T - 1));
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb)
@@ -542,7 +554,7 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       // (the lanes beyond H compute with unit H-1's projection, or an infinite input times a zero weight: whatever
       // that is - a NaN too, which a zero factor would keep - the h that the others multiply is zero)
       const float hn = jok ? (1.0f - z) * n + z * hpv : 0.f;
-      if (row < B) st_dev(hxg + (long)(t + 1) * xblk + xb + xl, hn, l2x);
+      if (row < B) st_dev(hxg + fwd_block(t + 1, l2x) * xblk + xb + xl, hn, l2x);
       if (ok) {
         (hsg + (long)(t + 1) * B * H)[oh] = hn;
         float* svt = sv + g * s_sv + (long)t * B * 4 * H;
@@ -703,25 +715,29 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
   int rbx[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) rbx[rb] = (r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4;
+  // The step's saved gates, h and the gradient from above are loaded one step ahead, and the rows of h that the step's share
+  // of dW_hh multiplies, behind the products: a CU's loads return in the order of their issue, whichever wave's they are, and
+  // operands (or the polling wave's flags) would wait for these to come from memory.
+  // (uniform addresses and 32-bit offsets of the lane: a lane's own addresses would take registers this kernel has not got)
+  float nr = 0.f, nz = 0.f, nn = 0.f, nq = 0.f, nhp = 0.f, nab = 0.f;
+  auto prefetch = [&](int tn) {
+    if (!act) return;
+    const float* svt = sv + g * s_sv + (long)tn * B * 4 * H;
+    nr = svt[osv], nz = (svt + H)[osv], nn = (svt + 2 * H)[osv], nq = (svt + 3 * H)[osv];
+    nhp = (hs + g * s_hs + (long)tn * B * H)[oh];
+    nab = above ? (above + g * s_above + (long)tn * B * H)[oh] : 0.f;
+  };
+  prefetch(T - 1);
   __syncthreads();
   int it = 0;
   for (int t = T - 1; t >= 0; --t, ++it) {
-    // (loaded in front of the wait: one step ahead they would cost this kernel, which is held at 248
-    // registers, spills - measured, 400 -> 620 us)
-    float r = 0.f, z = 0.f, n = 0.f, q = 0.f, hp = 0.f, ab = 0.f;
-    if (act) {
-      // (uniform addresses and 32-bit offsets of the lane: a lane's own addresses would take registers this kernel has not got)
-      const float* svt = sv + g * s_sv + (long)t * B * 4 * H;
-      r = svt[osv], z = (svt + H)[osv], n = (svt + 2 * H)[osv], q = (svt + 3 * H)[osv];
-      hp = (hs + g * s_hs + (long)t * B * H)[oh];
-      ab = above ? (above + g * s_above + (long)t * B * H)[oh] : 0.f;
-    }
+    const float r = nr, z = nz, n = nn, q = nq, hp = nhp, ab = nab;
     if (it > 0 && !group_wait(flags, NJ, base + (unsigned)it, abort_w, spin_limit, lds_flag)) return;
     floatx4 big[RB][1], small[RB][1];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) big[rb][0] = small[rb][0] = (floatx4){0.f, 0.f, 0.f, 0.f};
     if (t + 1 < T) {  // uniform over the grid
-      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(dgxg + (long)(t + 1) * xblk);
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(dgxg + bwd_block(t + 1, l2x) * xblk);
       constexpr int AHEAD = RB == 1 ? 6 : NCW == 6 ? 2 : 3, NA = NCW < AHEAD ? NCW : AHEAD;  // chunks in flight
       float4 a[NA][RB][2];
 #pragma unroll
@@ -761,6 +777,18 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
         }
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
+    f4ua hv[DR];
+    if (dw_wave) {
+      // (rows beyond the batch are zeros but for the first, which the block behind it holds)
+      const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hs + g * s_hs + (long)t * B * H), 0,
+                                                                          (B * H + 4) * 4, 0x00020000);
+#pragma unroll
+      for (int e = 0; e < DR; ++e)
+        hv[e] = __builtin_bit_cast(f4ua, __builtin_amdgcn_raw_buffer_load_b128(rh, ohv, e * H * 4, 0));
+    }
+    prefetch(max(t - 1, 0));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -778,7 +806,7 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
       da_r = da_n * q * r * (1.0f - r);
       da_z = dz * z * (1.0f - z);
       if (row < B) {
-        float* oe = dgxg + (long)t * xblk;
+        float* oe = dgxg + bwd_block(t, l2x) * xblk;
         st_dev(oe + xb[0] + xl, da_r, l2x);
         st_dev(oe + xb[1] + xl, da_z, l2x);
         st_dev(oe + xb[2] + xl, dq, l2x);
@@ -801,7 +829,6 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
       bsum[2] += da_n;
       bsum[3] += dq;
     }
-    f4ua hv[DR];
     if (DW && dWp) {  // uniform
       // rows beyond the batch contribute nothing: their staged gradients are zero, their h is
       // read from a valid row
@@ -816,14 +843,6 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
           st[48 * SPT] = __builtin_bit_cast(bf16x2, p1)[0];
           st[2 * 48 * SPT] = __builtin_bit_cast(bf16x2, p2)[0];
         }
-      }
-      if (dw_wave) {
-        // (rows beyond the batch are zeros but for the first, which the block behind it holds)
-        const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hs + g * s_hs + (long)t * B * H), 0,
-                                                                            (B * H + 4) * 4, 0x00020000);
-#pragma unroll
-        for (int e = 0; e < DR; ++e)
-          hv[e] = __builtin_bit_cast(f4ua, __builtin_amdgcn_raw_buffer_load_b128(rh, ohv, e * H * 4, 0));
       }
     }
     group_signal(flags + tx, base + (unsigned)it + 1u, l2x);  // (its barrier also publishes the staged tile to the workgroup)
@@ -988,7 +1007,7 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
   float* red = persist_lds;                                     // [8][2][6][4][64]
   __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * 12 * 256);   // [32 units][TP]
   int* lds_flag = reinterpret_cast<int*>(tt + QJ * TP);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const int NJ = H / QJ, RT = (B + PR - 1) / PR;
   unsigned* abort_w = sync;
@@ -1039,21 +1058,23 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
   int aoff[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
-  // The step's input projection is loaded one step ahead, behind the operand loads of the step
-  // before: requested in front of the wait, it would sit between the polling wave and its view
-  // of the flags (a wave's loads return in order, and these come from memory, not from the L2).
+  // The step's input projection is loaded one step ahead, behind the products of the step before: a CU's loads return in
+  // the order of their issue, whichever wave's they are, and these come from memory, not from the L2.  Requested in front of
+  // the wait, they would sit between the polling wave and its view of the flags; in front of the products, between the
+  // second four waves and their operands (144 us a launch against 128).
   float2 gxn[3];
-  {
-    const float* gxr = gx + g * s_gx + (long)rowc * 3 * H + j;
+  auto prefetch = [&](int tn) {
+    const float* gxr = gx + g * s_gx + ((long)tn * B + rowc) * 3 * H + j;
 #pragma unroll
     for (int q = 0; q < 3; ++q) gxn[q] = ld2_nt(gxr + q * H);
-  }
+  };
+  prefetch(0);
   for (int t = 0; t < T; ++t) {
     float2 gxv[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) gxv[q] = make_float2(gxn[q].x + biasx[q].x, gxn[q].y + biasx[q].y);
     if (t > 0 && !group_wait(flags, NJ, base + (unsigned)t, abort_w, spin_limit, lds_flag)) return;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(hxg + (long)t * xblk, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(hxg + fwd_block(t, l2x) * xblk, 0, 0x7fffffff, 0x00020000);
     bf16x8 a[NCF][2];
 #pragma unroll
     for (int i = 0; i < NCF; ++i) {
@@ -1061,12 +1082,6 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
       const int co = (c < nch ? c : 0) * 1024;
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) a[i][rb] = ld_frag_dev(rs, aoff[rb] + co);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    {
-      const float* gxr = gx + g * s_gx + ((long)min(t + 1, T - 1) * B + rowc) * 3 * H + j;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) gxn[q] = ld2_nt(gxr + q * H);
     }
     floatx4 acc[2][6];
 #pragma unroll
@@ -1081,6 +1096,9 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
 #pragma unroll
         for (int cb = 0; cb < 6; ++cb)
           acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][rb], wf[i][cb], acc[rb][cb], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    prefetch(min(t + 1, T - 1));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -1109,7 +1127,7 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
     if (row < B) {
       const long e = ((long)(t + 1) * B + row) * H + j;
       const unsigned hp2 = pack_bf16(hn.x, hn.y);
-      st_dev_u32(hxg + (long)(t + 1) * xblk + xfrag(row, nch, tx, u0), hp2, l2x);
+      st_dev_u32(hxg + fwd_block(t + 1, l2x) * xblk + xfrag(row, nch, tx, u0), hp2, l2x);
       st2_nt(hsg + e, hn);
       st_u32_nt(hbg + e, hp2);
       float* svr = sv + g * s_sv + ((long)t * B + row) * 4 * H + j;
@@ -1157,7 +1175,7 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
   __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * 4 * 256);    // [da_r | da_z | da_n | dq][32 units][TP]
   u32x4_t* wl = reinterpret_cast<u32x4_t*>(tt + 4 * QJ * TP);   // [8 waves][NCL][2][64 lanes] fragments
   int* lds_flag = reinterpret_cast<int*>(wl + 8 * NCL * 2 * 64);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const int NJ = H / QJ, RT = (B + PR - 1) / PR;
   unsigned* abort_w = sync;
@@ -1200,9 +1218,9 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
   int aoff[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
-  // The step's saved gates, h and the gradient from above are loaded one step ahead, behind the
-  // operand loads of the step before (see the forward kernel: in front of the wait they would
-  // delay the polling wave's view of the flags by a trip to memory).
+  // The step's saved gates, h and the gradient from above are loaded one step ahead, behind the operand loads of the step
+  // before (see the forward kernel: in front of the wait they would delay the polling wave's view of the flags by a trip to
+  // memory; further back there is too little of the step left to cover them, 179 us a launch against 184 to 195).
   float2 nr, nz, nn, nq, nhp, nab;
   auto prefetch = [&](int tn) {
     const long e = ((long)tn * B + rowc) * H + j;
@@ -1223,7 +1241,7 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     if (t + 1 < T) {  // uniform over the grid
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dghg + (long)(t + 1) * xblk, 0, 0x7fffffff,
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dghg + bwd_block(t + 1, l2x) * xblk, 0, 0x7fffffff,
                                                                           0x00020000);
       bf16x8 a[NCB][2];
 #pragma unroll
@@ -1274,7 +1292,7 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
     if (row < B) {
       const long o = ((long)t * B + row) * H3 + j;
       const unsigned pr = pack_bf16(da_r.x, da_r.y), pz = pack_bf16(da_z.x, da_z.y);
-      const long ox3 = (long)t * xblk + xfrag(row, nch, tx, u0);  // gate q: chunk q H/32 + tx
+      const long ox3 = bwd_block(t, l2x) * xblk + xfrag(row, nch, tx, u0);  // gate q: chunk q H/32 + tx
       st_dev_u32(dghg + ox3, pr, l2x);
       st_dev_u32(dghg + ox3 + (long)(H / PC) * 512, pz, l2x);
       st_dev_u32(dghg + ox3 + (long)(2 * H / PC) * 512, pack_bf16(dq.x, dq.y), l2x);
