@@ -1,44 +1,29 @@
-// Grouped fp32 GEMM on the fp32 matrix cores: pipelined kernel for operands of any alignment.
+// Grouped fp32 GEMM for operands of any alignment: pipelined kernels.
 //
 //   C[g] (M x N) = op(A[g]) (M x Kd) * op(B[g]) (Kd x N)      (same contract as gemm_f32.hip)
 //
-// Differences from the generic kernel: k-tiles of 32 with two LDS buffers and one barrier per
-// k-tile, two register prefetch stages, and a main loop without branches (rows and columns
-// are clamped into the matrix, which only changes values that feed outputs never stored; the
-// contraction tail is zeroed by a select when a tile is written to LDS).  Operand tiles keep
-// their natural layout in LDS, so no store is transposing:
-//   * an operand that is unit-stride along k is stored [i][k]; an MFMA lane then reads a
-//     float4 = 4 consecutive k of its row and feeds component s to MFMA number s (the order of
-//     the contraction index is free as long as both operands agree): lane half lk covers
-//     k = 8c + 4*lk + s;
-//   * an operand that is unit-stride along i is stored [k][i] and read one float per MFMA at
-//     the same k = 8c + 4*lk + s.
+// Products of many tiles are computed on the bf16 matrix cores from operands split into three parts, products of few tiles on
+// the fp32 ones.
 // v_mfma_f32_32x32x2_f32 lane layout: A lane l holds A[m = l%32][k = l/32], B lane l holds
-// B[k = l/32][n = l%32], accumulator register v holds C[8*(v/4) + 4*(l/32) + v%4][l%32].
+// B[k = l/32][n = l%32], accumulator register v holds C[8*(v/4) + 4*(l/32) + v%4][l%32];
+// v_mfma_f32_32x32x16_bf16 the same with 8 values of k per lane.
+#include <type_traits>
+
 #include "kernels.h"
+#include "split_f32.h"
 
 namespace hpsgd {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-static constexpr int FBK = 32;
-static constexpr int FTHREADS = 256;
+static constexpr int FTHREADS = 256;  // of a product of few tiles, of column sums
 
 // 16 bytes at a 4-byte boundary: one load or store instruction like the aligned kind (this target
 // splits what crosses a cache line)
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-template <bool RAG>
 __device__ __forceinline__ float4 ld16(const float* p) {
-  if (RAG) {
-    const f4u v = *reinterpret_cast<const f4u*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-  }
-  return *reinterpret_cast<const float4*>(p);
-}
-template <bool RAG>
-__device__ __forceinline__ void st16(float* p, const float4& v) {
-  if (RAG) *reinterpret_cast<f4u*>(p) = (f4u){v.x, v.y, v.z, v.w};
-  else *reinterpret_cast<float4*>(p) = v;
+  const f4u v = *reinterpret_cast<const f4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
 }
 // components sh .. 3 of v moved to the front, zeros behind them
 __device__ __forceinline__ float4 shift_down(const float4& v, int sh) {
@@ -46,82 +31,112 @@ __device__ __forceinline__ float4 shift_down(const float4& v, int sh) {
                      sh == 0 ? v.z : sh == 1 ? v.w : 0.f, sh == 0 ? v.w : 0.f);
 }
 
-// One operand tile: BI rows/columns x FBK.  CK: unit-stride along k in memory.
-// RAG: any base alignment, row pitch and extent (>= 4 along the unit-stride index): the vectors are
-// loaded at 4-byte boundaries, and one that would reach past the end of its row is loaded from the
-// row's last four values and shifted into place when it is written to LDS.
-template <int BI, bool CK, bool RAG>
-struct FastOperand {
-  static constexpr int PITCH = CK ? FBK + 4 : BI + 4;          // floats
-  static constexpr int LDS_FLOATS = CK ? BI * PITCH : FBK * PITCH;
-  static constexpr int UPT = BI * FBK / 4 / FTHREADS;          // float4 units per thread
-  const float* ptr[UPT];   // each unit's row (CK) or column (not CK) base, clamped into the matrix
-  float4 r[2][UPT];
-  int shi = 0;             // RAG, not CK: how far this thread's column base was clamped (the same for all units)
+// ---------------------------------------------------------------------------- split operands
+// The product as six products of bf16 parts (split_f32.h).  A workgroup has a 64 x 64 tile and k-tiles of 32; 2 x 2 waves share the
+// tile, and every other group of 8 along k has four waves of its own, whose sums meet in the epilogue: with four waves for all
+// of them, half as many waves were there to cover each other's loads, splits and barriers.
+// An operand tile is split once, on its way to LDS, where its parts lie in the order in which the lanes of an MFMA
+// read them: 16 bytes are the 8 values of k-group g (k = 8g ..) of one row, 32 rows of a group are consecutive,
+// REGION keeps a row's four groups in different banks for the writes.
+// Any alignment, pitch and size: rows and columns are clamped into the matrix (what that changes is never stored); along k a
+// thread has half a group of 4, clamped to the last 4 of the contraction, and those that another half group has already are
+// zeroed in A.  Operands of up to 2 GB per group (32-bit offsets; every address a load of its own took more instructions than
+// its products).
+// us, the fp32 instruction's pipelined kernel of 64 x 64 or 128 x 128 tiles before / this (GRU language model, classifier and
+// MLP, operands of every worker's own):
+//   128 x 1024 x 784, 16 workers  39.4 / 29.1      560 x 2000 x 256, 4  32.4 / 26.0        560 x 256 x 2000, 4  48.5 / 35.3
+//   1536 x 128 x 560, 16          46.6 / 35.7      2000 x 256 x 560, 4, in place  34.1 / 25.3     1000 x 300 x 40, 4  6.9 / 7.1
+//   1024 x 784 x 128, 16, in place  51.2 / 51.9 (its bytes)     4096 x 4096 x 4096  1099 / 876
+// 1.4 to 2.0 us per k-tile of 256 workgroups: the LDS writes (6 bytes a value at 75 bytes a cycle) and the conversions take
+// as long as the matrix work.
+static constexpr int SBM = 64, SBK = 32, STHREADS = 512;
+typedef float f4v __attribute__((ext_vector_type(4)));
+template <bool CK>
+struct SplitTile {
+  static constexpr int REGION = 512 + 32, PLANE = SBM / 32 * 4 * REGION, LDS_BYTES = 3 * PLANE;
+  __amdgpu_buffer_rsrc_t rs;
+  int off, ld4;  // the thread's row (CK) or column, in bytes; the pitch
+  float r[2][4];  // a half group each: 64 x 8 of them are one per thread
 
-  __device__ __forceinline__ void init(const float* __restrict__ base, long ld, int i0, int imax, int tid) {
+  __device__ __forceinline__ static int half(int tid) { return CK ? tid & 7 : __builtin_amdgcn_readfirstlane(tid / SBM); }
+  __device__ __forceinline__ static int row(int tid) { return CK ? tid >> 3 : tid % SBM; }
+  // first k of half group k4 as it is read
+  __device__ __forceinline__ static int base(int k4, int Kd) { return max(min(k4, Kd - 4), 0); }
+  __device__ __forceinline__ void init(const float* __restrict__ p, long ld, int i0, int imax, int Kd, int tid) {
+    const long floats = CK ? (imax - 1) * ld + Kd : (Kd - 1) * ld + imax;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(floats * 4), 0x00020000);
+    ld4 = (int)ld * 4;
+    off = min(i0 + row(tid), imax - 1) * (CK ? ld4 : 4);
+  }
+  __device__ __forceinline__ void load(int st, int kt, int Kd, int tid) {
+    const int k4 = kt * SBK + 4 * half(tid);
+    const bool tail = (kt + 1) * SBK > Kd;  // (uniform; beyond the last tile everything is read from the end)
+    if (CK) {
+      const f4v v = __builtin_bit_cast(f4v, tail ? __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * base(k4, Kd), 0, 0)
+                                                 : __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * half(tid), kt * SBK * 4, 0));
 #pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      const int unit = tid + u * FTHREADS;
-      if (CK) {
-        ptr[u] = base + (long)min(i0 + (unit >> 3), imax - 1) * ld;
-      } else {
-        const int i = i0 + ((unit % (BI / 4)) << 2), ic = min(i, imax - 4);
-        ptr[u] = base + ic;
-        if (RAG) shi = min(i - ic, 3);
-      }
+      for (int j = 0; j < 4; ++j) r[st][j] = v[j];
+    } else {
+      int from = (tail ? base(k4, Kd) : k4) * ld4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j, from += ld4) r[st][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, from, 0));
     }
   }
-  // k index of unit u inside a k-tile
-  __device__ __forceinline__ static int kofs(int u, int tid) {
-    const int unit = tid + u * FTHREADS;
-    return CK ? ((unit & 7) << 2) : unit / (BI / 4);
-  }
-  __device__ __forceinline__ void load(int st, int kt, int Kd, long ld, int tid) {
+  __device__ __forceinline__ void mask(int st, int kt, int Kd, int tid) {
+    const int k4 = kt * SBK + 4 * half(tid), kb = base(k4, Kd);
 #pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      // a unit past the end of the contraction re-reads k = 0 (always in bounds) and is zeroed
-      // when it is stored
-      const int k = kt * FBK + kofs(u, tid);
-      const int kc = k >= Kd ? 0 : (RAG && CK) ? min(k, Kd - 4) : k;
-      r[st][u] = ld16<RAG>(ptr[u] + (CK ? (long)kc : (long)kc * ld));
-    }
+    for (int j = 0; j < 4; ++j) r[st][j] = kb + j >= k4 && kb + j < Kd ? r[st][j] : 0.f;
   }
-  __device__ __forceinline__ void store(int st, int kt, int Kd, float* __restrict__ lds, int tid) const {
+  __device__ __forceinline__ void store(int st, char* __restrict__ lds, int tid) const {
+    uint2 p0, p1, p2;
+    split2(r[st][0], r[st][1], p0.x, p1.x, p2.x);
+    split2(r[st][2], r[st][3], p0.y, p1.y, p2.y);
+    const int i = row(tid), h = half(tid);
+    char* q = lds + ((i >> 5) * 4 + (h >> 1)) * REGION + (i & 31) * 16 + (h & 1) * 8;
+    *reinterpret_cast<uint2*>(q) = p0;
+    *reinterpret_cast<uint2*>(q + PLANE) = p1;
+    *reinterpret_cast<uint2*>(q + 2 * PLANE) = p2;
+  }
+  // the parts of the values of 32-row block b, k-group g, lane row `lrow`
+  __device__ __forceinline__ static void frag(const char* __restrict__ lds, int b, int g, int lrow, bf16x8s (&f)[3]) {
 #pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      const int unit = tid + u * FTHREADS;
-      const int k = kt * FBK + kofs(u, tid);
-      const bool in = k < Kd;  // not RAG: Kd % 4 == 0 for CK, a float4 is all in or out
-      float4 v = in ? r[st][u] : make_float4(0.f, 0.f, 0.f, 0.f);
-      if (RAG && CK && (kt + 1) * FBK > Kd && in) v = shift_down(v, k - min(k, Kd - 4));
-      if (RAG && !CK) v = shift_down(v, shi);
-      if (CK)
-        *reinterpret_cast<float4*>(&lds[(unit >> 3) * PITCH + ((unit & 7) << 2)]) = v;
-      else
-        *reinterpret_cast<float4*>(&lds[(unit / (BI / 4)) * PITCH + ((unit % (BI / 4)) << 2)]) = v;
-    }
-  }
-  // the 4 values k = 8c + 4*lk + {0..3} of row/column `i` of the tile
-  __device__ __forceinline__ static float4 frag(const float* __restrict__ lds, int i, int c, int lk) {
-    if (CK) return *reinterpret_cast<const float4*>(&lds[i * PITCH + 8 * c + 4 * lk]);
-    const float* p = &lds[(8 * c + 4 * lk) * PITCH + i];
-    return make_float4(p[0], p[PITCH], p[2 * PITCH], p[3 * PITCH]);
+    for (int p = 0; p < 3; ++p) f[p] = *reinterpret_cast<const bf16x8s*>(lds + p * PLANE + (b * 4 + g) * REGION + lrow * 16);
   }
 };
 
-// bid: the workgroup's index among those of this product
-template <int BM, int BN, bool TA, bool TB, bool RAG>
-__device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
-  using OpA = FastOperand<BM, !TA, RAG>;   // A is unit-stride along k when stored [M][Kd]
-  using OpB = FastOperand<BN, TB, RAG>;    // B is unit-stride along k when stored [N][Kd]
-  constexpr int TM = BM / 64, TN = BN / 64;  // 2 x 2 waves, each (BM/2) x (BN/2) in 32 x 32 blocks
-  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
-  float* sA[2] = {fast_lds, fast_lds + OpA::LDS_FLOATS};
-  float* sB[2] = {fast_lds + 2 * OpA::LDS_FLOATS, fast_lds + 2 * OpA::LDS_FLOATS + OpB::LDS_FLOATS};
+// The sums of a 32 x 32 block that are not finite, again with the fp32 instruction (rare: nothing is staged):
+// the k-groups g0, g0 + dg, .. of 8
+template <bool TA, bool TB>
+__device__ __forceinline__ floatx16 split_redo(const float* __restrict__ A, long lda, const float* __restrict__ B, long ldb,
+                                               int m, int n, int Kd, int g0, int dg, floatx16 have) {
+  const int lk = (threadIdx.x & 63) >> 5;
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 1
+  for (int k8 = 8 * g0; k8 < Kd; k8 += 8 * dg)
+#pragma unroll 1
+    for (int kk = k8; kk < min(k8 + 8, Kd); kk += 2) {
+      const int k = min(kk + lk, Kd - 1);
+      const float a = TA ? A[(long)k * lda + m] : A[(long)m * lda + k], b = TB ? B[(long)n * ldb + k] : B[(long)k * ldb + n];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kk + lk < Kd ? a : 0.f, kk + lk < Kd ? b : 0.f, acc, 0, 0, 0);
+    }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) have[v] = have[v] - have[v] == 0.f ? have[v] : acc[v];
+  return have;
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
+template <bool TA, bool TB>
+__device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
+  constexpr int NT = STHREADS, BM = SBM, BN = SBM;
+  using OpA = SplitTile<!TA>;
+  using OpB = SplitTile<TB>;
+  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
+  char* const lds = reinterpret_cast<char*>(fast_lds);
+  constexpr int BUF = OpA::LDS_BYTES + OpB::LDS_BYTES;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave & 1, wm = (wave >> 1) & 1, ks = wave >> 2;
   const int lrow = lane & 31, lk = lane >> 5;
   // Tile order.  Workgroup i runs on XCD i % 8 and every XCD has its own L2: the tiles, in
   // (group, row tile, column tile) order, are cut into 8 contiguous runs, one per XCD, so that
@@ -137,57 +152,18 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
 
   OpA a;
   OpB b;
-  const long ka = (long)part * d.Kd * (TA ? d.lda : 1), kb = (long)part * d.Kd * (TB ? 1 : d.ldb);
+  const float* Ag = d.A + (long)g * d.strideA + (long)part * d.Kd * (TA ? d.lda : 1);
+  const float* Bg = d.B + (long)g * d.strideB + (long)part * d.Kd * (TB ? 1 : d.ldb);
   // a part of a split contraction starts part * Kd further along k; the last one may be shorter
   if (splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
-  a.init(d.A + (long)g * d.strideA + ka, d.lda, m0, d.M, tid);
-  b.init(d.B + (long)g * d.strideB + kb, d.ldb, n0, d.N, tid);
+  a.init(Ag, d.lda, m0, d.M, d.Kd, tid);
+  b.init(Bg, d.ldb, n0, d.N, d.Kd, tid);
 
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < FBK / 8; ++c) {
-      float4 fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = OpA::frag(sA[buf], wm * (BM / 2) + i * 32 + lrow, c, lk);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[j] = OpB::frag(sB[buf], wn * (BN / 2) + j * 32 + lrow, c, lk);
-      // contraction steps outermost: consecutive MFMAs update different accumulator tiles
-      // (a dependent MFMA waits for the previous one to leave the pipeline)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i].x, fb[j].x, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i].y, fb[j].y, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i].z, fb[j].z, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i].w, fb[j].w, acc[i][j], 0, 0, 0);
-    }
-  };
-
-  const int nk = (d.Kd + FBK - 1) / FBK;
-  a.load(0, 0, d.Kd, d.lda, tid);
-  b.load(0, 0, d.Kd, d.ldb, tid);
-  a.store(0, 0, d.Kd, sA[0], tid);
-  b.store(0, 0, d.Kd, sB[0], tid);
-  a.load(0, 1, d.Kd, d.lda, tid);
-  b.load(0, 1, d.Kd, d.ldb, tid);
-  a.load(1, 2, d.Kd, d.lda, tid);
-  b.load(1, 2, d.Kd, d.ldb, tid);
+  const int nk = (d.Kd + SBK - 1) / SBK;
+  a.load(0, 0, d.Kd, tid);
+  b.load(0, 0, d.Kd, tid);
+  a.load(1, 1, d.Kd, tid);
+  b.load(1, 1, d.Kd, tid);
   // The epilogue's extra matrix operand in C's layout (the old C, the ReLU mask or the weights
   // to update) is requested here, behind the first operand tiles: it arrives during the
   // contraction instead of holding up the epilogue (a weight gradient over one batch is a few
@@ -195,81 +171,106 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
   float* C = d.C + (long)(splits > 1 ? gp : g) * d.strideC;
   const float* aux = d.aux ? d.aux + (long)g * d.strideAux : nullptr;
   constexpr int CP = BN + 4;                       // pitch in floats
-  constexpr int RPP = FTHREADS / (BN / 4);         // rows per pass
+  constexpr int RPP = NT / (BN / 4);               // rows per pass
   constexpr int PASSES = BM / RPP;
   const int c4 = (tid % (BN / 4)) << 2, rbase = tid / (BN / 4);
   const int col = n0 + c4;
   const int epi = d.epilogue;
   const float* X = epi == EPI_ACCUM ? C : (epi == EPI_RELU_MASK || epi == EPI_COMMIT) ? aux : nullptr;
-  const long xs = epi == EPI_ACCUM ? d.strideC : d.strideAux;
-  const bool vec = RAG || (((d.ldc | d.strideC) & 3) == 0 && ((uintptr_t)d.C & 15) == 0 &&
-                           (!X || (((uintptr_t)(epi == EPI_ACCUM ? d.C : d.aux) & 15) == 0 && (xs & 3) == 0)));
-  float4 x[PASSES];
-  if (X && vec && col + 3 < d.N) {
+  f4u x[PASSES];
+  if (X && col + 3 < d.N) {
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int row = min(m0 + rbase + RPP * p, d.M - 1);  // clamped: not stored when outside
-      x[p] = ld16<RAG>(X + (long)row * d.ldc + col);
+      x[p] = *reinterpret_cast<const f4u*>(X + (long)row * d.ldc + col);
     }
   }
+  if (nk == 1) a.mask(0, 0, d.Kd, tid);
+  a.store(0, lds, tid);
+  b.store(0, lds + OpA::LDS_BYTES, tid);
+  a.load(0, 2, d.Kd, tid);
+  b.load(0, 2, d.Kd, tid);
+
+  floatx16 acc, acs;  // the sum of a0 b0 and the sum of the other products
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = acs[v] = 0.f;
+  // fragments of two tiles (this wave's groups of each): the one that is multiplied and the next one, on its way from LDS
+  bf16x8s fa[2][3], fb[2][3];
+  auto frags = [&](int s, int buf) {
+    OpA::frag(lds + buf * BUF, wm, 2 * lk + ks, lrow, fa[s]);
+    OpB::frag(lds + buf * BUF + OpA::LDS_BYTES, wn, 2 * lk + ks, lrow, fb[s]);
+  };
+  auto mul = [&](int s, int pa, int pb, floatx16& to) { to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][pa], fb[s][pb], to, 0, 0, 0); };
   __syncthreads();
+  frags(0, 0);
+  // Tile kt's fragments are in registers, tile kt + 1 in register stage (kt + 1) & 1, tile kt + 2 on its way to the other.
+  // Half of the tile's products cover the splitting of the next one, the other half the first reads of it.
+  auto step = [&](auto P_, int kt) {
+    constexpr int P = decltype(P_)::value, Q = 1 - P;
+    if (kt + 2 >= nk) a.mask(Q, kt + 1, d.Kd, tid);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(P, 0, 0, acc);
+    mul(P, 1, 0, acs);
+    mul(P, 2, 0, acs);
+    a.store(Q, lds + Q * BUF, tid);
+    b.store(Q, lds + Q * BUF + OpA::LDS_BYTES, tid);
+    a.load(Q, kt + 3, d.Kd, tid);
+    b.load(Q, kt + 3, d.Kd, tid);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {  // (interleaved: an MFMA, 12 vector instructions)
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+    }
+    __syncthreads();
+    frags(Q, Q);
+    mul(P, 0, 1, acs);
+    mul(P, 1, 1, acs);
+    mul(P, 0, 2, acs);
+  };
   for (int kt = 0; kt < nk; kt += 2) {
-    compute(0);                                   // tile kt
-    a.store(0, kt + 1, d.Kd, sA[1], tid);         // tile kt+1 -> buffer 1
-    b.store(0, kt + 1, d.Kd, sB[1], tid);
-    a.load(0, kt + 3, d.Kd, d.lda, tid);
-    b.load(0, kt + 3, d.Kd, d.ldb, tid);
-    __syncthreads();
-    compute(1);                                   // tile kt+1 (all zeros past the end)
-    a.store(1, kt + 2, d.Kd, sA[0], tid);         // tile kt+2 -> buffer 0
-    b.store(1, kt + 2, d.Kd, sB[0], tid);
-    a.load(1, kt + 4, d.Kd, d.lda, tid);
-    b.load(1, kt + 4, d.Kd, d.ldb, tid);
-    __syncthreads();
+    step(std::integral_constant<int, 0>(), kt);
+    if (kt + 1 < nk) step(std::integral_constant<int, 1>(), kt + 1);
   }
 
-  // Epilogue through LDS (the operand buffers are free after the last barrier): the
-  // accumulators are laid out as the BM x BN tile, then every thread moves 16-byte pieces of
+  bool redo = false;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    acc[v] += acs[v];
+    redo = redo || !(acc[v] - acc[v] == 0.f);
+  }
+  if (__builtin_expect(__any(redo), 0))
+    acc = split_redo<TA, TB>(Ag, d.lda, Bg, d.ldb, min(m0 + wm * 32 + lrow, d.M - 1), min(n0 + wn * 32 + lrow, d.N - 1), d.Kd, ks, 2, acc);
+  __syncthreads();  // (the last fragments have been read)
+
+  // Epilogue through LDS: the accumulators are laid out as the BM x BN tile, then every thread moves 16-byte pieces of
   // whole rows, so the stores and the loads of the extra operand (the old C, the ReLU mask or
   // the weights to update; all requested before the first is used) are fully coalesced.
   float* sC = fast_lds;
-  static_assert((size_t)BM * CP <= 2 * (OpA::LDS_FLOATS + OpB::LDS_FLOATS), "epilogue tile fits the operand buffers");
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        sC[(wm * (BM / 2) + i * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * CP + wn * (BN / 2) + j * 32 + lrow] =
-            acc[i][j][v];
+  for (int v = 0; v < 16; ++v) sC[(ks * BM + wm * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * CP + wn * 32 + lrow] = acc[v];
   __syncthreads();
-  if (vec && col + 3 < d.N) {
-    float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (epi == EPI_BIAS || epi == EPI_BIAS_RELU) bv = make_float4(aux[col], aux[col + 1], aux[col + 2], aux[col + 3]);
+  if (col + 3 < d.N) {
+    f4u bv = {0.f, 0.f, 0.f, 0.f};
+    if (epi == EPI_BIAS || epi == EPI_BIAS_RELU) bv = *reinterpret_cast<const f4u*>(aux + col);
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       const int rl = rbase + RPP * p, row = m0 + rl;
       if (row >= d.M) continue;
-      const float4 a = *reinterpret_cast<const float4*>(&sC[rl * CP + c4]);
-      float4 o = a;
-      switch (epi) {
-        case EPI_BIAS: o = make_float4(a.x + bv.x, a.y + bv.y, a.z + bv.z, a.w + bv.w); break;
-        case EPI_BIAS_RELU:
-          o = make_float4(fmaxf(a.x + bv.x, 0.f), fmaxf(a.y + bv.y, 0.f), fmaxf(a.z + bv.z, 0.f),
-                          fmaxf(a.w + bv.w, 0.f));
-          break;
-        case EPI_ACCUM: o = make_float4(a.x + x[p].x, a.y + x[p].y, a.z + x[p].z, a.w + x[p].w); break;
-        case EPI_RELU_MASK:
-          o = make_float4(x[p].x > 0.f ? a.x : 0.f, x[p].y > 0.f ? a.y : 0.f, x[p].z > 0.f ? a.z : 0.f,
-                          x[p].w > 0.f ? a.w : 0.f);
-          break;
-        case EPI_COMMIT:
-          o = make_float4(x[p].x - d.alpha * a.x, x[p].y - d.alpha * a.y, x[p].z - d.alpha * a.z,
-                          x[p].w - d.alpha * a.w);
-          break;
-        default: break;
+      const float4 av = *reinterpret_cast<const float4*>(&sC[rl * CP + c4]);
+      const float4 aw = *reinterpret_cast<const float4*>(&sC[(BM + rl) * CP + c4]);
+      f4u o = {av.x + aw.x, av.y + aw.y, av.z + aw.z, av.w + aw.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        switch (epi) {
+          case EPI_BIAS: o[e] = o[e] + bv[e]; break;
+          case EPI_BIAS_RELU: o[e] = fmaxf(o[e] + bv[e], 0.f); break;
+          case EPI_ACCUM: o[e] = o[e] + x[p][e]; break;
+          case EPI_RELU_MASK: o[e] = x[p][e] > 0.f ? o[e] : 0.f; break;
+          case EPI_COMMIT: o[e] = x[p][e] - d.alpha * o[e]; break;
+          default: break;
+        }
       }
-      st16<RAG>(C + (long)row * d.ldc + col, o);
+      *reinterpret_cast<f4u*>(C + (long)row * d.ldc + col) = o;
     }
   } else {
     for (int p = 0; p < PASSES; ++p) {
@@ -278,7 +279,7 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
       for (int e = 0; e < 4; ++e) {
         if (col + e >= d.N) break;
         const long off = (long)row * d.ldc + col + e;
-        float val = sC[rl * CP + c4 + e];
+        float val = sC[rl * CP + c4 + e] + sC[(BM + rl) * CP + c4 + e];
         switch (epi) {
           case EPI_BIAS: val += aux[col + e]; break;
           case EPI_BIAS_RELU: val = fmaxf(val + aux[col + e], 0.f); break;
@@ -292,6 +293,135 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
     }
   }
 }
+// ---------------------------------------------------------------------------- both operands stored along the contraction
+// C = A^T B with A stored [Kd][M] and B [Kd][N], M and N even (the weight gradients): a load of one k for 64 columns, a pair per
+// lane, is whole cache lines, so every wave takes the operands of its 64 x 64 outputs straight from memory into the MFMA
+// layout and splits them in registers: no LDS, no barrier, nobody to wait for.  Two waves a SIMD cover each other's loads,
+// conversions and epilogues.  Columns are clamped into the matrix; rows beyond the contraction lie beyond the buffers: zeros.
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+static constexpr int DBM = 128;  // 2 x 2 waves
+__device__ __forceinline__ void direct_body(GemmDesc d, unsigned bid) {
+  constexpr int BM = DBM, BN = DBM, TM = 2, TN = 2, ST = 2;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lrow = lane & 31, lk = lane >> 5;
+  const int tn = (d.N + BN - 1) / BN, tm = (d.M + BM - 1) / BM;
+  const int splits = d.splits > 1 ? d.splits : 1;
+  const long ntiles = (long)tn * tm * d.groups * splits, per = (ntiles + 7) / 8;  // (a run of tiles per XCD, as above)
+  const long tile = (long)(bid & 7) * per + (bid >> 3);
+  if ((long)(bid >> 3) >= per || tile >= ntiles) return;
+  const int gp = (int)(tile / ((long)tn * tm));
+  const int g = gp / splits, part = gp - g * splits;
+  const int m0 = (int)((tile / tn) % tm) * BM + (wave & 1) * 32 * TM, n0 = (int)(tile % tn) * BN + (wave >> 1) * 32 * TN;
+  if (m0 >= d.M || n0 >= d.N) return;  // (no barrier follows)
+  const float* Ag = d.A + (long)g * d.strideA + (long)part * d.Kd * d.lda;
+  const float* Bg = d.B + (long)g * d.strideB + (long)part * d.Kd * d.ldb;
+  if (splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
+  // the lane's neighbouring columns, one of each 32 x 32 block: 64 columns are loaded as 32 pairs
+  const int ca = m0 + 2 * lrow, cb = n0 + 2 * lrow;
+  const int oa = (min(ca, d.M - 2) + lk * (int)d.lda) * 4, ob = (min(cb, d.N - 2) + lk * (int)d.ldb) * 4;
+  auto rsrc = [](const float* p, long floats) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(floats * 4), 0x00020000); };
+  const __amdgpu_buffer_rsrc_t ba = rsrc(Ag, (long)(d.Kd - 1) * d.lda + d.M), bb = rsrc(Bg, (long)(d.Kd - 1) * d.ldb + d.N);
+  const int nc = (d.Kd + 15) / 16;
+  float ra[ST][TM][8], rb[ST][TN][8];
+  // k = 16 c + 2 j + lk: the two halves of a load are neighbouring rows
+  auto load = [&](int st, int c) {
+    int fa = c * 16 * (int)d.lda * 4, fb = c * 16 * (int)d.ldb * 4;
+#pragma unroll
+    for (int j = 0; j < 8; ++j, fa += 8 * (int)d.lda, fb += 8 * (int)d.ldb) {
+      const f2v va = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(ba, oa, fa, 0));
+      const f2v vb = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(bb, ob, fb, 0));
+      ra[st][0][j] = va.x;
+      ra[st][1][j] = va.y;
+      rb[st][0][j] = vb.x;
+      rb[st][1][j] = vb.y;
+    }
+  };
+#pragma unroll
+  for (int st = 0; st < ST; ++st) load(st, st);
+  floatx16 acc[TM][TN], acs[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = acs[i][j][v] = 0.f;
+  for (int c0 = 0; c0 < nc; c0 += ST) {
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+      const int c = c0 + st;
+      if (c >= nc) break;
+      uint4 fa[TM][3], fb[TN][3];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) split8(ra[st][i], fa[i][0], fa[i][1], fa[i][2]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) split8(rb[st][j], fb[j][0], fb[j][1], fb[j][2]);
+      load(st, c + ST);
+      auto mul = [&](int pa, int pb, floatx16 (&to)[TM][TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8s, fa[i][pa]), __builtin_bit_cast(bf16x8s, fb[j][pb]), to[i][j], 0, 0, 0);
+      };
+      mul(0, 0, acc);
+      mul(1, 0, acs);
+      mul(2, 0, acs);
+      mul(0, 1, acs);
+      mul(1, 1, acs);
+      mul(0, 2, acs);
+    }
+  }
+  float* C = d.C + (long)(splits > 1 ? gp : g) * d.strideC;
+  const float* aux = d.aux ? d.aux + (long)g * d.strideAux : nullptr;
+  const int epi = d.epilogue;
+  const float* X = epi == EPI_ACCUM ? C : (epi == EPI_RELU_MASK || epi == EPI_COMMIT) ? aux : nullptr;
+  // block (i, j) holds the rows m0 + 2 r + i and the columns n0 + 2 c + j
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    float x[16][2];
+    const int r0 = m0 + 8 * lk + i;  // + 2 (8 (v / 4) + v % 4)
+    if (X) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int r = min(r0 + 2 * (8 * (v / 4) + v % 4), d.M - 1);
+        const f2u t = *reinterpret_cast<const f2u*>(X + (long)r * d.ldc + min(cb, d.N - 2));
+        x[v][0] = t.x;
+        x[v][1] = t.y;
+      }
+    }
+    floatx16 s[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      s[j] = acc[i][j] + acs[i][j];
+      bool redo = false;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) redo = redo || !(s[j][v] - s[j][v] == 0.f);
+      if (__builtin_expect(__any(redo), 0))
+        s[j] = split_redo<true, false>(Ag, d.lda, Bg, d.ldb, min(m0 + 2 * lrow + i, d.M - 1), min(cb + j, d.N - 1), d.Kd, 0, 1, s[j]);
+    }
+    f2u bias = {0.f, 0.f};
+    if (epi == EPI_BIAS || epi == EPI_BIAS_RELU) bias = *reinterpret_cast<const f2u*>(aux + min(cb, d.N - 2));
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = r0 + 2 * (8 * (v / 4) + v % 4);
+      f2u o = {s[0][v], s[1][v]};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        switch (epi) {
+          case EPI_BIAS: o[e] = o[e] + bias[e]; break;
+          case EPI_BIAS_RELU: o[e] = fmaxf(o[e] + bias[e], 0.f); break;
+          case EPI_ACCUM: o[e] = o[e] + x[v][e]; break;
+          case EPI_RELU_MASK: o[e] = x[v][e] > 0.f ? o[e] : 0.f; break;
+          case EPI_COMMIT: o[e] = x[v][e] - d.alpha * o[e]; break;
+          default: break;
+        }
+      }
+      if (r < d.M && cb < d.N) *reinterpret_cast<f2u*>(C + (long)r * d.ldc + cb) = o;
+    }
+  }
+}
+__global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_kernel(GemmDesc d) { direct_body(d, blockIdx.x); }
 
 // ---------------------------------------------------------------------------- few tiles
 // A product of few tiles is bound by one wave's chain: in the form above a 64 x 64 tile's k-tile of 32 takes 0.8 us
@@ -299,7 +429,7 @@ __device__ __forceinline__ void fast_body(GemmDesc d, unsigned bid) {
 // Here a workgroup has a 32 x 32 tile and its four waves take a quarter of the contraction each, so that there
 // are four times the workgroups and a chain is a quarter as long.  A wave loads its operands straight into the MFMA
 // layout, four steps of 8 ahead, and waits for nobody before the sums of the four meet in LDS.
-template <bool CK, bool RAG>
+template <bool CK>
 struct SlimOperand {
   const float* p;
   long ld;
@@ -311,7 +441,7 @@ struct SlimOperand {
   // the values k .. k + 3, clamped into the contraction
   __device__ __forceinline__ void load(int u, int k, int Kd) {
     if (CK) {
-      r[u] = ld16<RAG>(p + max(min(k, Kd - 4), 0));
+      r[u] = ld16(p + max(min(k, Kd - 4), 0));
     } else {
       r[u] = make_float4(p[(long)min(k, Kd - 1) * ld], p[(long)min(k + 1, Kd - 1) * ld], p[(long)min(k + 2, Kd - 1) * ld],
                          p[(long)min(k + 3, Kd - 1) * ld]);
@@ -325,11 +455,11 @@ struct SlimOperand {
   }
 };
 
-template <bool TA, bool TB, bool RAG>
-__device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
+// bid: the four waves' index among those of this product; lds: theirs
+template <bool TA, bool TB>
+__device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid, float* lds) {
   constexpr int PITCH = 36;  // floats of a row of a wave's sums
-  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x & (FTHREADS - 1), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lrow = lane & 31, lk = lane >> 5;
   const int tn = (d.N + 31) / 32, tm = (d.M + 31) / 32;
   const int splits = d.splits > 1 ? d.splits : 1;
@@ -341,8 +471,8 @@ __device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
   const int m0 = (int)((tile / tn) % tm) * 32, n0 = (int)(tile % tn) * 32;
   const long ka = (long)part * d.Kd * (TA ? d.lda : 1), kb = (long)part * d.Kd * (TB ? 1 : d.ldb);
   if (splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
-  SlimOperand<!TA, RAG> a;
-  SlimOperand<TB, RAG> b;
+  SlimOperand<!TA> a;
+  SlimOperand<TB> b;
   a.init(d.A + (long)g * d.strideA + ka, d.lda, m0 + lrow, d.M);
   b.init(d.B + (long)g * d.strideB + kb, d.ldb, n0 + lrow, d.N);
   const int nc = (d.Kd + 7) / 8, ncw = (nc + 3) / 4, c0 = wave * ncw, c1 = min(nc, c0 + ncw);
@@ -361,7 +491,7 @@ __device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
   const long off = (long)min(row, d.M - 1) * d.ldc + col;
   float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
   if (X) {
-    if (whole) x = ld16<true>(X + off);
+    if (whole) x = ld16(X + off);
     else x = make_float4(X[off - max(col - d.N + 1, 0)], X[off - max(col + 1 - (d.N - 1), 0) + 1], X[off - max(col + 2 - (d.N - 1), 0) + 2], 0.f);
   }
   floatx16 acc[2];
@@ -388,12 +518,12 @@ __device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v)
-    fast_lds[(wave * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * PITCH + lrow] = acc[0][v] + acc[1][v];
+    lds[(wave * 32 + 8 * (v / 4) + 4 * lk + (v % 4)) * PITCH + lrow] = acc[0][v] + acc[1][v];
   __syncthreads();
   if (!in || col >= d.N) return;
   float4 o[4];
 #pragma unroll
-  for (int w = 0; w < 4; ++w) o[w] = *reinterpret_cast<const float4*>(&fast_lds[(w * 32 + (tid >> 3)) * PITCH + ((tid & 7) << 2)]);
+  for (int w = 0; w < 4; ++w) o[w] = *reinterpret_cast<const float4*>(&lds[(w * 32 + (tid >> 3)) * PITCH + ((tid & 7) << 2)]);
   const float4 s = make_float4((o[0].x + o[1].x) + (o[2].x + o[3].x), (o[0].y + o[1].y) + (o[2].y + o[3].y),
                                (o[0].z + o[1].z) + (o[2].z + o[3].z), (o[0].w + o[1].w) + (o[2].w + o[3].w));
   auto one = [&](float v, float xv, int e) -> float {
@@ -407,7 +537,7 @@ __device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
     }
   };
   if (whole) {
-    st16<true>(C + off, make_float4(one(s.x, x.x, 0), one(s.y, x.y, 1), one(s.z, x.z, 2), one(s.w, x.w, 3)));
+    *reinterpret_cast<f4u*>(C + off) = (f4u){one(s.x, x.x, 0), one(s.y, x.y, 1), one(s.z, x.z, 2), one(s.w, x.w, 3)};
   } else {
     C[off] = one(s.x, x.x, 0);
     if (col + 1 < d.N) C[off + 1] = one(s.y, x.y, 1);
@@ -416,14 +546,15 @@ __device__ __forceinline__ void slim_body(GemmDesc d, unsigned bid) {
 }
 constexpr size_t kSlimLds = 4 * 32 * 36 * sizeof(float);
 
-template <bool TA, bool TB, bool RAG>
+template <bool TA, bool TB>
 __global__ void __launch_bounds__(FTHREADS) gemm_f32_slim_kernel(GemmDesc d) {
-  slim_body<TA, TB, RAG>(d, blockIdx.x);
+  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
+  slim_body<TA, TB>(d, blockIdx.x, fast_lds);
 }
 
-template <int BM, int BN, bool TA, bool TB, bool RAG>
-__global__ void __launch_bounds__(FTHREADS) gemm_f32_fast_kernel(GemmDesc d) {
-  fast_body<BM, BN, TA, TB, RAG>(d, blockIdx.x);
+template <bool TA, bool TB>
+__global__ void __launch_bounds__(STHREADS) gemm_f32_fast_kernel(GemmDesc d) {
+  split_body<TA, TB>(d, blockIdx.x);
 }
 
 // Column sums as further workgroups of a launch of products: a workgroup covers 64 columns with 4 row slices
@@ -468,154 +599,148 @@ __device__ __forceinline__ void colsum_body(const ColsumPack& pk, unsigned bid, 
   }
 }
 
-// Several products that need nothing of each other, and column sums, in one launch (64 x 64 tiles): each of
+// Several products that need nothing of each other, and column sums, in one launch: each of
 // them leaves most of the chip idle, and a launch of its own costs 4.5 us before it does anything.
 // Product i owns the workgroups blk0[i] .. blk0[i+1]-1 (whole rounds over the XCDs), the column sums the rest.
-// SLIM: those of the bits of `slim` are products of few tiles.
-template <bool RAG, bool SLIM>
-__global__ void __launch_bounds__(FTHREADS) gemm_f32_multi_kernel(GemmPack pk, ColsumPack cs, int groups, unsigned slim) {
+// SLIM: those of the bits of `slim` are products of few tiles; a workgroup has room for two of them.
+template <bool SLIM>
+__global__ void __launch_bounds__(STHREADS) gemm_f32_multi_kernel(GemmPack pk, ColsumPack cs, int groups, unsigned slim) {
+  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
   int i = 0;
   while (i < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
   const unsigned bid = blockIdx.x - pk.blk0[i];
   if (i == pk.n) {
+    if (threadIdx.x >= FTHREADS) return;
     const unsigned per = cs.blk0[cs.n];
     colsum_body(cs, bid % per, (int)(bid / per));
     return;
   }
   const GemmDesc& d = pk.d[i];
   if (SLIM && (slim >> i & 1)) {
-    if (d.transA) slim_body<true, false, RAG>(d, bid);
-    else if (d.transB) slim_body<false, true, RAG>(d, bid);
-    else slim_body<false, false, RAG>(d, bid);
+    const unsigned half = __builtin_amdgcn_readfirstlane(threadIdx.x / FTHREADS);
+    const unsigned b32 = (bid >> 3) * 16 + half * 8 + (bid & 7);
+    float* lds = fast_lds + half * (kSlimLds / sizeof(float));
+    if (d.transA) slim_body<true, false>(d, b32, lds);
+    else if (d.transB) slim_body<false, true>(d, b32, lds);
+    else slim_body<false, false>(d, b32, lds);
     return;
   }
-  if (d.transA) fast_body<64, 64, true, false, RAG>(d, bid);
-  else if (d.transB) fast_body<64, 64, false, true, RAG>(d, bid);
-  else fast_body<64, 64, false, false, RAG>(d, bid);
+  if (d.transA) split_body<true, false>(d, bid);
+  else if (d.transB) split_body<false, true>(d, bid);
+  else split_body<false, false>(d, bid);
 }
 
-template <int BM, int BN, bool TA, bool TB, bool RAG>
-static hipError_t launch_fast_cfg(const GemmDesc& d, hipStream_t s) {
-  using OpA = FastOperand<BM, !TA, RAG>;
-  using OpB = FastOperand<BN, TB, RAG>;
-  constexpr size_t smem = (size_t)2 * (OpA::LDS_FLOATS + OpB::LDS_FLOATS) * sizeof(float);
-  static std::atomic<size_t> allowed{0};  // per instantiation: allow dynamic LDS above 64 KB
-  if (const hipError_t e = allow_lds((const void*)gemm_f32_fast_kernel<BM, BN, TA, TB, RAG>, smem, allowed)) return e;
-  const long ntiles = (long)((d.N + BN - 1) / BN) * ((d.M + BM - 1) / BM) * d.groups * (d.splits > 1 ? d.splits : 1);
-  dim3 grid((unsigned)(8 * ((ntiles + 7) / 8)));
-  KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
-  hipLaunchKernelGGL((gemm_f32_fast_kernel<BM, BN, TA, TB, RAG>), grid, dim3(FTHREADS), smem, s, d);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, bool RAG>
-static hipError_t launch_fast_layout(const GemmDesc& d, hipStream_t s) {
-  if (!d.transA && d.transB) return launch_fast_cfg<BM, BN, false, true, RAG>(d, s);
-  if (!d.transA && !d.transB) return launch_fast_cfg<BM, BN, false, false, RAG>(d, s);
-  if (d.transA && !d.transB) return launch_fast_cfg<BM, BN, true, false, RAG>(d, s);
-  return launch_fast_cfg<BM, BN, true, true, RAG>(d, s);
+// ... and of products that take their operands from memory
+__global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_multi_kernel(GemmPack pk, ColsumPack cs, int groups) {
+  int i = 0;
+  while (i < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
+  const unsigned bid = blockIdx.x - pk.blk0[i];
+  if (i < pk.n) {
+    direct_body(pk.d[i], bid);
+    return;
+  }
+  const unsigned per = cs.blk0[cs.n];
+  colsum_body(cs, bid % per, (int)(bid / per));
 }
 
 hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s);
 
-// 0: the pipelined kernel does not take the product (an extent along a unit-stride index below one vector);
-// 1: it does; 2: it does, as a product of unaligned operands
-static int fast_kind(const GemmDesc& d) {
-  auto aligned = [](const float* p, long ld, long stride) {
-    return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0 && (stride & 3) == 0;
-  };
-  // extents along the unit-stride index of the two operands (the contraction's last part included)
+// Whether these kernels take the product: a contraction of at least one half group where an operand is unit-stride along
+// it, operands within 32-bit offsets.
+static bool fast_takes(const GemmDesc& d) {
   const int klast = d.splits > 1 ? d.Kall - (d.splits - 1) * d.Kd : d.Kd;
-  const int ua = d.transA ? d.M : klast, ub = d.transB ? klast : d.N;
-  if (ua < 4 || ub < 4) return 0;
-  return !aligned(d.A, d.lda, d.strideA) || !aligned(d.B, d.ldb, d.strideB) || ((ua | ub) & 3) != 0 ? 2 : 1;
-}
-static bool fast_large(const GemmDesc& d, int groups) {
-  // 128 x 128 tiles from two full rounds of workgroups on: below that the smaller tiles' better
-  // balance over the CUs outweighs their extra LDS traffic (the fp32 matrix rate is low enough).
-  // A contraction of a few k-tiles (a weight gradient over one batch) is mostly first loads and
-  // epilogue: four small workgroups per SIMD cover those better than two large ones (matrix
-  // pipes busy 52 % of the time with the large tile at Kd = 128)
-  const long t = (long)((d.M + 127) / 128) * ((d.N + 127) / 128) * groups;
-  return d.M > 64 && d.N > 64 && t >= 512 && d.Kd > 256;
+  if (klast < 1 || (klast < 4 && (!d.transA || d.transB))) return false;
+  const long a = d.transA ? (long)(d.Kd - 1) * d.lda + d.M : (long)(d.M - 1) * d.lda + d.Kd;
+  const long b = d.transB ? (long)(d.N - 1) * d.ldb + d.Kd : (long)(d.Kd - 1) * d.ldb + d.N;
+  return a < (1L << 29) - 64 && b < (1L << 29) - 64;
 }
 
-// The form for few tiles: up to 64 tiles of 64 x 64, up to 256 with a contraction that makes a long chain, and
-// up to 128 where the launch holds nothing else (`shared`: it does, or would with all workers' tiles: the form decides
-// the order of a sum).  (Beyond, the chip is busy either way and the larger tile reads its
-// operands fewer times.)  Measured, one / the other form of every product of at most that many tiles:
-//   to  64: MLP 30-64-896-8, batch 224, K = 2     90 /  52 us a round; 28-832-672-32-13, batch 16, K = 3   94 /  72
-//   to 256: MLP 596-928-140-7, batch 145, K = 3   83 /  74;  two GRU layers of H = 544, batch 4, K = 4  1148 / 1134
-//   but     two GRU layers of H = 100, batch 20, K = 4 (128 tiles, contraction 300, beside 560 others)   311 /  315
-//           fp32 language model, 248 tiles, contraction 192   233 / 240
-//   to 512: MLP 784-1024-1024-10, batch 128, K = 16  288 / 375
+// The form for few tiles: up to 256 tiles of 32 x 32, up to 448 where the launch holds nothing else (`shared`: it does;
+// the form decides the order of a sum).  (Beyond, the chip is busy either way and the larger tile reads its
+// operands fewer times.)  us, this form / the other one:
+//   256 tiles  Kd =   64   4.9 /  5.4, 1024  11.9 / 18.3       288 tiles  Kd = 200  7.2 /  8.2      240 tiles of 960 x 32 outputs, Kd = 180  6.0 / 8.6
+//   448 tiles  Kd =  200   7.8 /  8.7,  600  13.5 / 14.6       512 tiles  Kd = 300  10.2 /  9.5, Kd = 64  7.1 / 5.9
+//   576 tiles  Kd = 2000  47.7 / 36.2                         1024 tiles  Kd = 512  23.7 / 13.0
 static bool fast_slim(const GemmDesc& d, bool shared) {
-  const long t = (long)((d.M + 63) / 64) * ((d.N + 63) / 64) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
-  return !(d.transA && d.transB) && (t <= 64 || (t <= 256 && d.Kd >= 512) || (t <= 128 && !shared));
+  const long t = (long)((d.M + 31) / 32) * ((d.N + 31) / 32) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
+  return !(d.transA && d.transB) && t <= (shared ? 256 : 448);
+}
+// Operands straight from memory: weight gradients of two rounds of workgroups and more.  us, this form / through LDS (in place,
+// 16 workers): 1024 x 784, Kd = 128 (896 tiles)  45 / 53, 1024 x 1024 (1024)  49 / 62; but 1536 x 128, Kd = 560 (192)  35 / 35,
+// 2000 x 256, Kd = 560, 4 workers (128)  36 / 25.
+static bool fast_direct(const GemmDesc& d) {
+  const long t = (long)((d.M + DBM - 1) / DBM) * ((d.N + DBM - 1) / DBM) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
+  return d.transA && !d.transB && ((d.M | d.N) & 1) == 0 && t >= 512;
 }
 static unsigned tile_blocks(const GemmDesc& d, int tile) {
   const long t = (long)((d.N + tile - 1) / tile) * ((d.M + tile - 1) / tile) * d.groups * (d.splits > 1 ? d.splits : 1);
   return (unsigned)(8 * ((t + 7) / 8));
 }
-template <bool RAG>
 static hipError_t launch_slim(const GemmDesc& d, hipStream_t s) {
   const dim3 grid(tile_blocks(d, 32));
   KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
-  if (d.transA) hipLaunchKernelGGL((gemm_f32_slim_kernel<true, false, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
-  else if (d.transB) hipLaunchKernelGGL((gemm_f32_slim_kernel<false, true, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
-  else hipLaunchKernelGGL((gemm_f32_slim_kernel<false, false, RAG>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  if (d.transA) hipLaunchKernelGGL((gemm_f32_slim_kernel<true, false>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  else if (d.transB) hipLaunchKernelGGL((gemm_f32_slim_kernel<false, true>), grid, dim3(FTHREADS), kSlimLds, s, d);
+  else hipLaunchKernelGGL((gemm_f32_slim_kernel<false, false>), grid, dim3(FTHREADS), kSlimLds, s, d);
   return hipGetLastError();
 }
 
 bool gemm_pack_push(GemmPack& pk, const GemmDesc& d) {
-  if (pk.n >= GemmPack::MAX || d.bf16 || d.background || (d.transA && d.transB) || !fast_kind(d) || fast_large(d, d.groups)) return false;
+  if (pk.n >= GemmPack::MAX || d.bf16 || d.background || (d.transA && d.transB) || !fast_takes(d)) return false;
   if (d.M <= 0 || d.N <= 0 || d.groups <= 0) return false;
   pk.d[pk.n++] = d;
-  // (fewer workers than all: a product that all of them launch by itself is a guest here, which changes no other's form)
-  if (!fast_large(d, d.workers ? d.workers : d.groups)) ++pk.n_all;
   return true;
 }
+
+// (both layouts of an operand have the same size in LDS; the epilogue tile is smaller, and so is a product of few tiles)
+static constexpr size_t kSplitLds = 4 * SplitTile<true>::LDS_BYTES;
+static_assert(2 * SBM * (SBM + 4) * sizeof(float) <= kSplitLds && 2 * kSlimLds <= kSplitLds && kSplitLds <= 64 * 1024,
+              "the operand buffers hold the rest, within the default limit of dynamic LDS");
 
 hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipStream_t s) {
   if (pk.n == 0 && cs.n == 0) return hipSuccess;
   if (pk.n == 0) return launch_colsum_pack(cs, groups, s);
   if (pk.n == 1 && cs.n == 0) return launch_gemm_f32_fast(pk.d[0], s);
-  bool rag = false;
   unsigned slim = 0;
   double flops = 0.;
-  const bool shared = pk.n_all > 1 || cs.n > 0;
+  bool direct = true;  // all of them
+  for (int i = 0; i < pk.n; ++i) direct = direct && fast_direct(pk.d[i]);
   pk.blk0[0] = 0;
   for (int i = 0; i < pk.n; ++i) {
     const GemmDesc& d = pk.d[i];
-    const bool few = fast_slim(d, shared);
-    rag = rag || fast_kind(d) == 2;
+    const bool few = !direct && fast_slim(d, true);
     slim |= few ? 1u << i : 0u;
-    pk.blk0[i + 1] = pk.blk0[i] + tile_blocks(d, few ? 32 : 64);
+    pk.blk0[i + 1] = pk.blk0[i] + (direct ? tile_blocks(d, DBM) : few ? (tile_blocks(d, 32) / 8 + 1) / 2 * 8 : tile_blocks(d, SBM));
     flops += 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups;
   }
-  using OpC = FastOperand<64, true, false>;
-  using OpN = FastOperand<64, false, false>;
-  constexpr size_t op = OpC::LDS_FLOATS > OpN::LDS_FLOATS ? OpC::LDS_FLOATS : OpN::LDS_FLOATS;
-  constexpr size_t smem = 4 * op * sizeof(float);  // two buffers of two operands, in their largest layout
-  static_assert(smem <= 64 * 1024, "within the default limit of dynamic LDS");
   dim3 grid(pk.blk0[pk.n] + (cs.n ? cs.blk0[cs.n] * (unsigned)groups : 0u));
   KernelTimer kt(KID_GEMM_F32_FAST, flops, s);
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(FTHREADS), smem, s, pk, cs, groups, slim); };
-  if (rag) slim ? launch(gemm_f32_multi_kernel<true, true>) : launch(gemm_f32_multi_kernel<true, false>);
-  else slim ? launch(gemm_f32_multi_kernel<false, true>) : launch(gemm_f32_multi_kernel<false, false>);
+  if (direct) {
+    hipLaunchKernelGGL(gemm_f32_direct_multi_kernel, grid, dim3(FTHREADS), FTHREADS * sizeof(float), s, pk, cs, groups);
+    return hipGetLastError();
+  }
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(STHREADS), kSplitLds, s, pk, cs, groups, slim); };
+  slim ? launch(gemm_f32_multi_kernel<true>) : launch(gemm_f32_multi_kernel<false>);
   return hipGetLastError();
 }
 
-// Returns hipErrorNotSupported (nothing launched) when an operand's extent along its unit-stride index
-// is below one vector; the caller then takes the generic kernel.
+// Returns hipErrorNotSupported (nothing launched) where these kernels do not take the product; the caller then takes the
+// generic one.
 hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s) {
   if (d.splits > 1 && (d.epilogue != EPI_STORE || (d.Kd & 3) != 0 || d.Kall <= (d.splits - 1) * d.Kd)) return hipErrorInvalidValue;
-  const int kind = fast_kind(d);
-  if (!kind) return hipErrorNotSupported;
-  const bool rag = kind == 2;
-  if (fast_slim(d, false)) return rag ? launch_slim<true>(d, s) : launch_slim<false>(d, s);
-  if (fast_large(d, d.groups)) return rag ? launch_fast_layout<128, 128, true>(d, s) : launch_fast_layout<128, 128, false>(d, s);
-  return rag ? launch_fast_layout<64, 64, true>(d, s) : launch_fast_layout<64, 64, false>(d, s);
+  if (!fast_takes(d)) return hipErrorNotSupported;
+  if (fast_slim(d, false)) return launch_slim(d, s);
+  const bool direct = fast_direct(d);
+  const dim3 grid(tile_blocks(d, direct ? DBM : SBM));
+  KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
+  if (direct) {
+    hipLaunchKernelGGL(gemm_f32_direct_kernel, grid, dim3(FTHREADS), 0, s, d);
+    return hipGetLastError();
+  }
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(STHREADS), kSplitLds, s, d); };
+  if (d.transA) d.transB ? launch(gemm_f32_fast_kernel<true, true>) : launch(gemm_f32_fast_kernel<true, false>);
+  else d.transB ? launch(gemm_f32_fast_kernel<false, true>) : launch(gemm_f32_fast_kernel<false, false>);
+  return hipGetLastError();
 }
 
 }  // namespace hpsgd

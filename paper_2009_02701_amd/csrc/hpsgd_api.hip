@@ -429,7 +429,7 @@ struct GemmBatch {
   hipStream_t s;
   int groups;
   GemmBatch(hipStream_t s_, int groups_, float lr) : s(s_), groups(groups_) {
-    pk.n = pk.n_all = cs.n = 0;
+    pk.n = cs.n = 0;
     cs.blk0[0] = 0;
     cs.lr = lr;
   }
@@ -443,7 +443,7 @@ struct GemmBatch {
     none.n = 0;
     none.blk0[0] = 0;
     const hipError_t e = launch_gemm_pack(pk, with_sums ? cs : none, groups, s);
-    pk.n = pk.n_all = 0;
+    pk.n = 0;
     if (with_sums) cs.n = 0;
     return e == hipSuccess ? HPSGD_OK : HPSGD_EHIP;
   }

@@ -181,13 +181,12 @@ hipError_t launch_colsum_pack(const ColsumPack& pk, int groups, hipStream_t s);
 
 // fp32 products that need nothing of each other, and column sums beside them, in one launch.
 // gemm_pack_push returns false for a product the shared launch does not take or has no room for (nothing
-// is added: launch it by itself).  pk.n = pk.n_all = 0 is set by the caller.
+// is added: launch it by itself).  pk.n = 0 is set by the caller.
 struct GemmPack {
   static constexpr int MAX = 4;
   GemmDesc d[MAX];
   unsigned blk0[MAX + 1];  // filled by the launch
   int n;
-  int n_all;  // of them, those that a launch for all of the context's workers would hold too
 };
 bool gemm_pack_push(GemmPack& pk, const GemmDesc& d);
 hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipStream_t s);
