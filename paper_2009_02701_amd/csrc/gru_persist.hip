@@ -1421,23 +1421,30 @@ int gru_persist_rows(int B, int H, int K) {
   return B <= 16 || NJ * ((B + 15) / 16) * K <= kPlanCus ? 16 : 32;
 }
 
-// Whether `groups` workers' layer is better off resident than with one launch per time step.  One launch
-// always is.  A resident step (forward and backward together) takes about 19 us at any width, which every
-// further launch adds again (31 us where a group does not fit an XCD: never worth a second launch); a step
-// of the fused per-step kernels (H a multiple of 16) some 18 us and 0.26 us per million of
-// groups * B * H * H.  The measured line lies at 40 million a launch, less 5.  Widths off 16 take several
-// launches per step instead: worth up to three.
-// us per local step of 20 time steps, resident / per step, (H, B, workers): (512, 64, 16) 1583 / 1745,
-// (512, 128, 4) 812 / 1072, (512, 72, 4) 751 / 842, (512, 40, 12) 1176 / 1258, (384, 96, 8) 1149 / 1129,
-// (256, 64, 16) 778 / 722, (144, 128, 16) 1122 / 859, (640, 32, 16) 1898 / 1704; off 16:
-// (450, 20, 16) 811 / 1904, (350, 64, 6) 764 / 1482, (130, 128, 12) 762 / 1035, (200, 40, 16) 734 / 819,
-// (300, 100, 16; 8 launches) 3025 / 1610.
-bool gru_persist_pays(int B, int H, int groups, int rows) {
+// Whether `groups` workers' layer is better off resident for its T time steps than with one launch per step.  A
+// single launch always is.  Of several, each (forward and backward together) loads and splits its weights,
+// 20 us and 1 us for every 20 units, and pays 4.5 us and 1 us for every 75 units per step, 21 us (16-row tiles: 12)
+// where a group does not fit an XCD; a step of the launches per step costs 26 us for all workers together and
+// 0.22 us per million of groups * B * H * H, with at least 16 rows for B.
+// us per local step of 20 time steps, resident / per step, (H, B, workers):
+//   2 launches  (256, 64, 16) 392 / 705, (160, 128, 8) 336 / 670, (144, 40, 16) 329 / 465, (200, 40, 16) 360 / 569,
+//               (450, 20, 16) 537 / 857, (512, 128, 4) 554 / 1030
+//   3, 4        (144, 128, 16) 492 / 919, (384, 96, 8) 670 / 1113, (300, 100, 8) 817 / 910, (512, 64, 16) 1165 / 1706
+//   8           (300, 100, 16) 1653 / 1352, (320, 128, 16) 1684 / 1741, (500, 128, 16) 2312 / 2529
+//   groups beyond an XCD  3 launches (640, 32, 16) 1338 / 1673, (700, 4, 12) 762 / 1246
+// of 3 time steps: (144, 40, 16) 104 / 87, (256, 64, 16) 127 / 119, (384, 96, 8) 198 / 185, (300, 100, 8) 233 / 161.
+// Widths off the 16-unit blocks, where the launches per step lose their wide accesses, are on par after 3 or 4 steps
+// with up to 3 launches: (300, 70, 5) 150 / 156, (530, 33, 4) 158 / 145, (500, 11, 11) 159 / 194, (690, 4, 12) 270 / 276;
+// so is work of about 40 million groups * B * H * H per launch, (512, 128, 4) 169 / 165: both are resident at any T.
+bool gru_persist_pays(int B, int H, int T, int groups, int rows) {
   const int NJ = (H + PJ - 1) / PJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
   const long launches = (SG + per - 1) / per;
-  if (launches == 1) return true;
-  if (H % 16 != 0) return launches <= 3;
-  return NJ * 8 <= kPlanCus && (double)groups * B * H * H >= 40e6 * (double)launches - 5e6;
+  const double work = (double)groups * B * H * H;
+  if (launches <= (H % 16 ? 3 : 1)) return true;
+  if (H % 16 == 0 && NJ * 8 <= kPlanCus && work >= 40e6 * (double)launches - 5e6) return true;
+  const double step = NJ * 8 <= kPlanCus ? 4.5 + H / 75.0 : rows == 16 ? 12.0 : 21.0;
+  const double steps = 26.0 + 0.22e-6 * (B < 16 ? work / B * 16 : work);
+  return (double)launches * (20.0 + H / 20.0 + T * step) <= T * steps;
 }
 
 // The backward kernel can accumulate dW_hh itself when 8 waves x 64 columns cover H.

@@ -807,7 +807,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // follows what the flags read.  A given-up wait shows as NaN in the results (below).
     // narrow fp32 layers: the whole recurrence without any exchange between workgroups
     const bool use_solo = c->solo && c->resident;
-    const bool use_persist = c->prow != 0 && c->resident && gru_persist_pays(B, H, groups, c->prow);
+    const bool use_persist = c->prow != 0 && c->resident && gru_persist_pays(B, H, T, groups, c->prow);
     const int prow = use_persist ? c->prow : 32;  // rows of a synchronisation group
     // bf16: the same with the weight slices in registers; its backward launch writes only the bf16
     // copies of the gate gradients, so every GEMM that consumes them must be able to take those

@@ -251,10 +251,10 @@ hipError_t launch_transpose_dg4(const void* dg4, long s_dg4, void* dgxT, void* d
 // advances them by steps * gru_persist_count_per_step().  spin_limit bounds every wait.
 // any H from 16 to 704; rows: batch rows per workgroup, as gru_persist_rows gives them
 // for the context's K workers, however many of them a call steps (0: does not fit).  More workgroups than the chip
-// has CUs run as several launches where that pays, which goes by the workers of the call (gru_persist_pays): stepping
+// has CUs run as several launches where that pays, which goes by the time steps and by the workers of the call (gru_persist_pays): stepping
 // one worker and stepping all of them may take different forms, whose sums differ in their order.
 int gru_persist_rows(int B, int H, int K);
-bool gru_persist_pays(int B, int H, int groups, int rows);
+bool gru_persist_pays(int B, int H, int T, int groups, int rows);
 size_t gru_persist_sync_words(int B, int groups, int rows);
 unsigned gru_persist_count_per_step(int H);
 // device_scope: the workgroups exchange through memory that every XCD sees; false lets a launch
