@@ -360,7 +360,8 @@ size_t hpsgd_commit_kernel_params(const hpsgd_ctx *ctx);
  *   GEMM_BF16_DL, _DL_COMMIT     gemm_bf16_multi_kernel, under the latter as soon as one of its products
  *                                is an update, the input gradient beside it included
  *   GEMM_BF16_DLX192_COMMIT      gemm_bf16_dlx_pair_kernel (two updates; one launch)
- *   GEMM_F32_FAST                gemm_f32_slim_kernel and gemm_f32_multi_kernel (one launch)
+ *   GEMM_F32_FAST                gemm_f32_slim_kernel, gemm_f32_direct_kernel and the launches of several products,
+ *                                gemm_f32_multi_kernel, gemm_f32_slim_multi_kernel and gemm_f32_direct_multi_kernel
  *   GEMM_F32                     gemm_bf16_kernel
  *   CVT2                         embed_bf16_kernel
  *   GRU_STEP                     gru_fwd_step*_kernel and gru_bwd_step*_kernel. */

@@ -643,6 +643,24 @@ __global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_multi_kernel(Gemm
   colsum_body(cs, bid % per, (int)(bid / per));
 }
 
+// ... and where all of them are products of few tiles: a tile a workgroup, which waits for nobody else's k-tiles
+// (two layers of H = 64 on 20 and 64 inputs, batch 80, 36 steps, one worker: weight gradients 10.9 us in the form above, 9.6 here)
+__global__ void __launch_bounds__(FTHREADS) gemm_f32_slim_multi_kernel(GemmPack pk, ColsumPack cs, int groups) {
+  extern __shared__ __attribute__((aligned(16))) float fast_lds[];
+  int i = 0;
+  while (i < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
+  const unsigned bid = blockIdx.x - pk.blk0[i];
+  if (i == pk.n) {
+    const unsigned per = cs.blk0[cs.n];
+    colsum_body(cs, bid % per, (int)(bid / per));
+    return;
+  }
+  const GemmDesc& d = pk.d[i];
+  if (d.transA) slim_body<true, false>(d, bid, fast_lds);
+  else if (d.transB) slim_body<false, true>(d, bid, fast_lds);
+  else slim_body<false, false>(d, bid, fast_lds);
+}
+
 hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s);
 
 // Whether these kernels take the product: a contraction of at least one half group where an operand is unit-stride along
@@ -703,20 +721,24 @@ hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipS
   if (pk.n == 1 && cs.n == 0) return launch_gemm_f32_fast(pk.d[0], s);
   unsigned slim = 0;
   double flops = 0.;
-  bool direct = true;  // all of them
-  for (int i = 0; i < pk.n; ++i) direct = direct && fast_direct(pk.d[i]);
+  bool direct = true, alike = true;  // all of them: operands from memory, few tiles
+  for (int i = 0; i < pk.n; ++i) direct = direct && fast_direct(pk.d[i]), alike = alike && fast_slim(pk.d[i], true);
   pk.blk0[0] = 0;
   for (int i = 0; i < pk.n; ++i) {
     const GemmDesc& d = pk.d[i];
     const bool few = !direct && fast_slim(d, true);
     slim |= few ? 1u << i : 0u;
-    pk.blk0[i + 1] = pk.blk0[i] + (direct ? tile_blocks(d, DBM) : few ? (tile_blocks(d, 32) / 8 + 1) / 2 * 8 : tile_blocks(d, SBM));
+    pk.blk0[i + 1] = pk.blk0[i] + (direct ? tile_blocks(d, DBM) : alike ? tile_blocks(d, 32) : few ? (tile_blocks(d, 32) / 8 + 1) / 2 * 8 : tile_blocks(d, SBM));
     flops += 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups;
   }
   dim3 grid(pk.blk0[pk.n] + (cs.n ? cs.blk0[cs.n] * (unsigned)groups : 0u));
   KernelTimer kt(KID_GEMM_F32_FAST, flops, s);
   if (direct) {
     hipLaunchKernelGGL(gemm_f32_direct_multi_kernel, grid, dim3(FTHREADS), FTHREADS * sizeof(float), s, pk, cs, groups);
+    return hipGetLastError();
+  }
+  if (alike) {
+    hipLaunchKernelGGL(gemm_f32_slim_multi_kernel, grid, dim3(FTHREADS), kSlimLds, s, pk, cs, groups);
     return hipGetLastError();
   }
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(STHREADS), kSplitLds, s, pk, cs, groups, slim); };

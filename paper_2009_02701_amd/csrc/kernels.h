@@ -47,7 +47,7 @@ enum KernelId : int {
   KID_GEMM_BF16_DLX256 = 11,      // gemm_bf16_dlx_kernel<false, 2, 4, 4, 2, 2>  (256 x 256)
   KID_GEMM_BF16_DLX256_COMMIT = 12,
   KID_GEMM_BF16_NT = 13,          // gemm_bf16_nt_kernel (an fp32 operand rounded while staged)
-  KID_GEMM_F32_FAST = 14,         // gemm_f32_fast_kernel (all tile forms)
+  KID_GEMM_F32_FAST = 14,         // gemm_f32_fast, _slim, _direct kernels and their joint launches
   KID_GEMM_F32 = 15,              // gemm_f32_kernel / gemm_bf16_kernel (generic fallbacks)
   KID_CVT2 = 16,                  // cvt2_kernel, embed_bf16_kernel (bf16 copy, transposed copy or both)
   KID_SOFTMAX_CE_BF16 = 17,       // softmax_ce_bf16_rows_kernel / softmax_ce_bf16_kernel
