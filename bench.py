@@ -33,17 +33,17 @@ STREAMING_KERNELS = {"cvt2_kernel", "cvt2_pack_kernel", "softmax_ce_bf16_rows_ke
 # of a round.  Summaries with the full commands: profiles/bench_*.md.  Kernels not collected: null.
 KIB = 1024.0
 MEASURED_TRAFFIC_BYTES = {
-    "gru_cls": {"gru_bwd_persist_kernel": (2.0 * 91903.0 + 150171.0) * KIB,
-                "gru_fwd_persist_kernel": (2.0 * 26935.9 + 107529.2) * KIB},
-    # the 192 x 256 form runs three products per round: the logits (679 MB) and two input gradients
+    "gru_cls": {"gru_bwd_persist_kernel": (2.0 * 59071.0 + 89440.0) * KIB,
+                "gru_fwd_persist_kernel": (2.0 * 18860.0 + 90635.0) * KIB},
+    # the 192 x 256 form runs three products per round: the logits (674 MB) and two input gradients
     # (head and top layer; both launch 192 tiles and average 262 MB)
     "gru_lm": {"gemm_bf16_dlx_kernel<false, 2, 4, 3, 2, 2>":
-                   ((2.0 * 153894.5 + 355321.4) + 2 * (2.0 * 109983.5 + 35879.3)) * KIB / 3,
-               "gru_bwd_persist_bf16_kernel": (2.0 * 161238.2 + 240383.4) * KIB,
-               "gru_fwd_persist_bf16_kernel": (2.0 * 89352.9 + 238874.5) * KIB,
-               "gemm_bf16_dlx_kernel<true, 2, 4, 4, 2, 2>": (2.0 * 296087.8 + 325485.9) * KIB,
-               "gemm_bf16_dlx_kernel<true, 2, 4, 3, 2, 2>": (2.0 * 95253.1 + 100010.3) * KIB,
-               "softmax_ce_bf16_rows_kernel": (2.0 * 177839.5 + 194819.1) * KIB},
+                   ((2.0 * 151756.0 + 355030.0) + 2 * (2.0 * 109808.0 + 35855.0)) * KIB / 3,
+               "gru_bwd_persist_bf16_kernel": (2.0 * 136515.0 + 192461.0) * KIB,
+               "gru_fwd_persist_bf16_kernel": (2.0 * 81229.0 + 223015.0) * KIB,
+               "gemm_bf16_dlx_kernel<true, 2, 4, 4, 2, 2>": (2.0 * 292633.0 + 326020.0) * KIB,
+               "gemm_bf16_dlx_kernel<true, 2, 4, 3, 2, 2>": (2.0 * 95259.0 + 100044.0) * KIB,
+               "softmax_ce_bf16_rows_kernel": (2.0 * 177719.0 + 194738.0) * KIB},
     "mlp": {},
 }
 
