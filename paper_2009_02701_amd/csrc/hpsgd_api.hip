@@ -25,16 +25,22 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // fp32 weight gradients (M x N outputs, contraction over T * B): how many parts the contraction is cut
 // into.  A narrow layer's gradient has a few dozen 64 x 64 tiles per worker and a contraction of
-// thousands: the parts run side by side, about three workgroups per CU over all K workers, and the
-// kernel that applies the update adds them in order.  A part is at least 128 long (four k-tiles: below
-// that a part is mostly first loads and epilogue), and 1 means the update stays in the epilogue.
+// thousands: the parts run side by side, about two workgroups per CU over all K workers (a launch holds two of these products
+// and more), and the kernel that applies the update adds them in order.  A part is at least 128 long (four k-tiles: below
+// that a part is mostly first loads and epilogue), of a contraction of 1000 and more 256, and 1 means the update stays
+// in the epilogue.  (Shorter contractions would leave too few workgroups: H = 96, Kd = 720, 3 workers 157.7 us a round, 159.3 with parts of 256.
+// So would products that then are few tiles, whose form is another one.)
+// us per round or local step, three workgroups per CU and parts of 128 / this: H = 48, batch 100, 30 steps, 16 workers 154.9 / 145.8;
+// H = 90, 20, 50, 16 181.5 / 175.7; H = 128, 32, 60, 2 layers, 2 workers 403 / 390; H = 110, 60, 40, 2 layers, 3 workers 337 / 329; H = 128, 40, 40, 8
+// 193.8 / 191.0; H = 256, 32, 32, 3 212.3 / 210.6; H = 100, 20, 50, 2 layers, 4 298.6 / 297.6.
 // Goes by the context's K, not by how many workers a call steps: the cuts of a context are always the same.  (Whether
 // dW_hh is cut at all may still depend on the call: where gru_persist_pays sends it to a launch per step.)
 int wgrad_splits(int M, int N, int Kd, int K) {
-  const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64) * K;
-  long n = (768 + tiles - 1) / tiles;
+  const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64) * K, tiles32 = (long)((M + 31) / 32) * ((N + 31) / 32) * K;
+  long n = (512 + tiles - 1) / tiles;
   if (n > Kd / 128) n = Kd / 128;
   if (n > 16) n = 16;
+  if (Kd >= 1000 && n > Kd / 256 && tiles32 * (Kd / 256) > 256) n = Kd / 256;
   return n < 2 ? 1 : (int)n;
 }
 // An input gradient of the head (M x N outputs, contraction over the classes: thousands, where the output
