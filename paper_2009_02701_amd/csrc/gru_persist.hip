@@ -57,7 +57,6 @@
 // accumulator register v holds C[4*(l/16) + v][l%16].  The order of the contraction index is free as long as both
 // operands agree: lane group lg = l/16 takes k = 32c + 4 lg .. + 3 and 16 further on, i.e. two 16-byte pieces
 // of its row per chunk, and one load instruction reads 64 contiguous bytes of each of 16 rows.
-#include <algorithm>
 #include <type_traits>
 
 #include "cell_math.h"
@@ -1393,26 +1392,38 @@ int groups_per_launch(int NJ, int SG) {
 
 // Widths the fp32 launches take: a group's members' flags fit its words, the weight parts a wave's registers.
 constexpr int kPersistMaxH = 704;
-// forward: the waves that share a contraction (and the batch rows per wave that follow from it), see the kernel
-int persist_fwd_kw(int H, int rows) { return rows == 32 && H <= 512 ? 4 : 8; }
-size_t persist_fwd_lds(int rows, int width, int kw, int ncw, int xnb) {
-  return (size_t)kw * (rows / 16) * (width ? 4 : 3) * 1024 + (size_t)((width + PC - 1) / PC) * 9 * 1024 +
-         (persist_fwd_lw(ncw, xnb, rows / 16 * kw / 8) ? (size_t)kw * ncw * 3 * 1024 : 0) + 16;
+// A forward launch: the waves that share a contraction (and the batch rows per wave that follow from it, see the kernel),
+// their chunks of it and of the layer input (width 0: no projection in the launch), its LDS.
+struct FwdForm { int kw, ncw, xnb; size_t lds; };
+constexpr FwdForm persist_fwd_form(int H, int rows, int width) {
+  const int kw = rows == 32 && H <= 512 ? 4 : 8, nchw = (width + PC - 1) / PC;
+  const int least = rows == 16 ? 1 : kw == 4 ? 2 : 3, need = (((H + PJ - 1) / PJ * PJ + PC - 1) / PC + kw - 1) / kw;
+  const int ncw = need > least ? need : least, xnb = (nchw + kw - 1) / kw;
+  const size_t lds = (size_t)kw * (rows / 16) * (width ? 4 : 3) * 1024 + (size_t)nchw * 9 * 1024 +
+                     (persist_fwd_lw(ncw, xnb, rows / 16 * kw / 8) ? (size_t)kw * ncw * 3 * 1024 : 0) + 16;
+  return {kw, ncw, xnb, lds};
 }
 // backward: chunks per wave
-int persist_bwd_ncw(int H) {
+constexpr int persist_bwd_ncw(int H) {
   const int n = (3 * ((H + PJ - 1) / PJ * PJ) + 8 * PC - 1) / (8 * PC);
   return n <= 4 ? (n < 2 ? 2 : n) : n <= 6 ? 6 : 9;
 }
-size_t persist_bwd_lds(int H, int rows) {
+constexpr size_t persist_bwd_lds(int H, int rows) {
   const int n = persist_bwd_ncw(H);
   return (size_t)8 * (rows / 16) * 1024 + (size_t)3 * 48 * SPT * 2 + (size_t)8 * n * persist_bwd_nl(n, rows) * 1024 + 16;
 }
+// every launch but those of a projection, which gru_persist_xproj_supported asks for by its LDS
+constexpr bool persist_fits(int rows) {
+  for (int H = 16; H <= kPersistMaxH; ++H)
+    if (persist_fwd_form(H, rows, 0).lds > kLdsLimit || persist_bwd_lds(H, rows) > kLdsLimit) return false;
+  return true;
+}
+static_assert(persist_fits(16) && persist_fits(32), "a launch of any width it takes fits a CU's LDS");
 
 }  // namespace
 
-// Batch rows per workgroup for a layer of K workers, or 0 if the resident slice plus the partial sums do
-// not fit the 160 KB of LDS.  A launch has one workgroup per CU and all of them resident: 16 rows where all
+// Batch rows per workgroup for a layer of K workers, or 0 for a width these launches do not take.  A launch has at most one
+// workgroup per CU and all of them resident: 16 rows where all
 // workers' workgroups then still fit the chip; more workgroups than CUs go out as several launches of
 // whole synchronisation groups, of 32 rows each where a batch has more than 16.
 int gru_persist_rows(int B, int H, int K) {
@@ -1457,9 +1468,11 @@ size_t gru_persist_sync_words(int B, int groups, int rows) { return (size_t)grou
 unsigned gru_persist_count_per_step(int) { return 1u; }
 
 // The forward kernel can do the input projection itself when the layer input is narrow (at most 2 chunks of 32 per
-// wave; beside a wide layer a product of its own is no slower).
-bool gru_persist_xproj_supported(int H, int width) {
-  return width >= 16 && width % 16 == 0 && width <= 256 && (H + PC - 1) / PC + (width + PC - 1) / PC <= 21;
+// wave; beside a wide layer a product of its own is no slower) and its 48 rows of W_ih fit the LDS beside the rest: with 32 rows
+// and H > 512 that is 64 KB of partial sums and 72 KB of weight parts, which leaves room for an input of 64.
+bool gru_persist_xproj_supported(int H, int width, int rows) {
+  return width >= 16 && width % 16 == 0 && width <= 256 && (H + PC - 1) / PC + (width + PC - 1) / PC <= 21 &&
+         persist_fwd_form(H, rows, width).lds <= kLdsLimit;
 }
 
 size_t gru_persist_exchange_words(int B, int H, int gates) { return (size_t)xblock_words(B, gates * ((H + PJ - 1) / PJ * PJ)); }
@@ -1472,7 +1485,7 @@ hipError_t launch_gru_fwd_persist(const float* W_hh, const float* b_hh, long s_r
   const int NJ = (H + PJ - 1) / PJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
   if ((rows != 16 && rows != 32) || T < 1 || H > kPersistMaxH || NJ > device_cus()) return hipErrorInvalidValue;
   if (!hx || ((uintptr_t)hx & 15) != 0 || (s_hx & 3) != 0) return hipErrorInvalidValue;
-  if (xin && (!gru_persist_xproj_supported(H, width) || !W_ih || !b_ih || ((uintptr_t)xin & 15) != 0 || (s_x & 3) != 0))
+  if (xin && (!gru_persist_xproj_supported(H, width, rows) || !W_ih || !b_ih || ((uintptr_t)xin & 15) != 0 || (s_x & 3) != 0))
     return hipErrorInvalidValue;
   if (!xin && !gx) return hipErrorInvalidValue;
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * ((double)H + (xin ? width : 0)) * T * groups, s);
@@ -1491,12 +1504,11 @@ hipError_t launch_gru_fwd_persist(const float* W_hh, const float* b_hh, long s_r
     else if (xnb == 1) HPSGD_FWD_PERSIST(C, 1, R, KW);     \
     else HPSGD_FWD_PERSIST(C, XMAX, R, KW);                \
   } while (0)
-  const int kw = persist_fwd_kw(H, rows);
-  const int xnb = !xin ? 0 : (width + 32 * kw - 1) / (32 * kw);  // chunks of the layer input per wave
-  const int least = rows == 16 ? 1 : kw == 4 ? 2 : 3, ncw = std::max(least, ((NJ * PJ + PC - 1) / PC + kw - 1) / kw);
+  const FwdForm f = persist_fwd_form(H, rows, xin ? width : 0);
+  const int kw = f.kw, ncw = f.ncw, xnb = f.xnb;
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
-    const Placement pl = placement(sync, SG, n_sg, NJ, persist_fwd_lds(rows, xin ? width : 0, kw, ncw, xnb), device_scope, ticket_launches);
+    const Placement pl = placement(sync, SG, n_sg, NJ, f.lds, device_scope, ticket_launches);
     if (rows == 16) {
       if (ncw == 1) HPSGD_FWD_PERSIST_X(1, 16, 8, 1);
       else if (ncw == 2) HPSGD_FWD_PERSIST_X(2, 16, 8, 1);

@@ -932,7 +932,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       const bool persist = use_persist;
       // a narrow layer input: the resident-weight kernel does the input projection itself
       const float* Wih0 = rin + c->eoff(c->lidx[l].wih);
-      const bool xproj = persist && gru_persist_xproj_supported(H, width) && ((uintptr_t)lin & 15) == 0 &&
+      const bool xproj = persist && gru_persist_xproj_supported(H, width, prow) && ((uintptr_t)lin & 15) == 0 &&
                          (s_lin & 3) == 0;
       if (!xproj) {
         const float* Wih = rin + c->eoff(c->lidx[l].wih);

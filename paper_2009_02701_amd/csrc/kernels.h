@@ -273,10 +273,10 @@ hipError_t launch_gru_fwd_persist(const float* W_hh, const float* b_hh, long s_r
                                   int groups, int rows,
                                   unsigned* sync, unsigned base, unsigned spin_limit, const float* xin, long s_x,
                                   int width, const float* W_ih, const float* b_ih, bool device_scope, unsigned* ticket_launches, hipStream_t s);
-// xin != nullptr (allowed when gru_persist_xproj_supported(H, width)): the launch computes the input
+// xin != nullptr (allowed when gru_persist_xproj_supported(H, width, rows)): the launch computes the input
 // projection itself from the layer input xin (T blocks of B x width per worker, stride s_x) and W_ih,
 // b_ih (in the replica, like W_hh); gx is then unused and may be nullptr.
-bool gru_persist_xproj_supported(int H, int width);
+bool gru_persist_xproj_supported(int H, int width, int rows);
 // d_zero: the gradient carried into the last step is zero (D is not read)
 hipError_t launch_gru_bwd_persist(const float* W_hh, long s_rep, float* dgh, float* dghx, long s_dghx, float* dgx,
                                   long s_dg, const float* D,
