@@ -711,6 +711,7 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
   // (dgh: row-major, for later launches; nullptr: nobody reads it)
   float* dgxg = dghx + g * s_dghx;               // the gate gradients as the workgroups exchange them
   const long xblk = xblock_words(B, HP3);
+  const int Bx = (B + 15) / 16 * 16;             // ... whole blocks of 16 rows
   int rbx[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) rbx[rb] = (r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4;
@@ -804,11 +805,14 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
       dq = da_n * r;
       da_r = da_n * q * r * (1.0f - r);
       da_z = dz * z * (1.0f - z);
-      if (row < B) {
+      // (rows of the last block beyond the batch as zeros: whatever the memory held, a value there that is not finite
+      // would send every step's sums to the fp32 instruction, above)
+      if (row < Bx) {
+        const bool in = row < B;
         float* oe = dgxg + bwd_block(t, l2x) * xblk;
-        st_dev(oe + xb[0] + xl, da_r, l2x);
-        st_dev(oe + xb[1] + xl, da_z, l2x);
-        st_dev(oe + xb[2] + xl, dq, l2x);
+        st_dev(oe + xb[0] + xl, in ? da_r : 0.f, l2x);
+        st_dev(oe + xb[1] + xl, in ? da_z : 0.f, l2x);
+        st_dev(oe + xb[2] + xl, in ? dq : 0.f, l2x);
       }
       if (ok) {
         float* ox = dgx + g * s_dg + (long)t * B * H3;
