@@ -840,7 +840,7 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
           uint32_t p0, p1, p2;
-          split2(d3[i], 0.f, p0, p1, p2);
+          split2<true>(d3[i], 0.f, p0, p1, p2);  // (nothing is computed again here)
           __bf16* st = stage + (i * 16 + lr) * SPT + rt;
           st[0] = __builtin_bit_cast(bf16x2, p0)[0];
           st[48 * SPT] = __builtin_bit_cast(bf16x2, p1)[0];

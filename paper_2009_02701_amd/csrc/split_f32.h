@@ -35,9 +35,12 @@ __device__ __forceinline__ uint32_t split_round2(float x, float y) {
 // unit, which the ones below run beside: a 32-cycle MFMA with four of them 56 cycles, with four of these 34.)
 __device__ __forceinline__ float split_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float split_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
-// the three parts of x (low halves) and y (high halves)
+// the three parts of x (low halves) and y (high halves).  FINITE: a value that would round to an infinity has the largest bf16
+// for its first part (the difference is a bf16 value's worth of bits still); an infinity or a NaN makes a NaN as without.
+template <bool FINITE = false>
 __device__ __forceinline__ void split2(float x, float y, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
-  p0 = split_round2(x, y);
+  constexpr float most = 0x1.fep127f;
+  p0 = FINITE ? split_round2(__builtin_amdgcn_fmed3f(x, -most, most), __builtin_amdgcn_fmed3f(y, -most, most)) : split_round2(x, y);
   const float rx = x - split_lo(p0), ry = y - split_hi(p0);
   p1 = split_round2(rx, ry);
   p2 = split_round2(rx - split_lo(p1), ry - split_hi(p1));
