@@ -40,8 +40,8 @@ __device__ __forceinline__ float4 shift_down(const float4& v, int sh) {
 // REGION keeps a row's four groups in different banks for the writes.
 // Any alignment, pitch and size: rows and columns are clamped into the matrix (what that changes is never stored); along k a
 // thread has half a group of 4, clamped to the last 4 of the contraction, and those that another half group has already are
-// zeroed in A.  Operands of up to 2 GB per group (32-bit offsets; every address a load of its own took more instructions than
-// its products).
+// zeroed in A.  Operands of any size: a lane's offset is of 32 bits (every address a load of its own took more instructions than
+// its products) from a uniform address of 64, the tile's first row or, across the contraction, the half group's.
 // us, the fp32 instruction's pipelined kernel of 64 x 64 or 128 x 128 tiles before / this (GRU language model, classifier and
 // MLP, operands of every worker's own):
 //   128 x 1024 x 784, 16 workers  39.4 / 29.1      560 x 2000 x 256, 4  32.4 / 26.0        560 x 256 x 2000, 4  48.5 / 35.3
@@ -54,32 +54,36 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 template <bool CK>
 struct SplitTile {
   static constexpr int REGION = 512 + 32, PLANE = SBM / 32 * 4 * REGION, LDS_BYTES = 3 * PLANE;
-  __amdgpu_buffer_rsrc_t rs;
-  int off, ld4;  // the thread's row (CK) or column, in bytes; the pitch
+  const float* p;  // the tile's first row (CK) or column
+  long ld;
+  int off;        // the thread's row (CK) or column from there, in bytes
   float r[2][4];  // a half group each: 64 x 8 of them are one per thread
 
   __device__ __forceinline__ static int half(int tid) { return CK ? tid & 7 : __builtin_amdgcn_readfirstlane(tid / SBM); }
   __device__ __forceinline__ static int row(int tid) { return CK ? tid >> 3 : tid % SBM; }
   // first k of half group k4 as it is read
-  __device__ __forceinline__ static int base(int k4, int Kd) { return max(min(k4, Kd - 4), 0); }
-  __device__ __forceinline__ void init(const float* __restrict__ p, long ld, int i0, int imax, int Kd, int tid) {
-    const long floats = CK ? (imax - 1) * ld + Kd : (Kd - 1) * ld + imax;
-    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(floats * 4), 0x00020000);
-    ld4 = (int)ld * 4;
-    off = min(i0 + row(tid), imax - 1) * (CK ? ld4 : 4);
+  __device__ __forceinline__ static int base(int k4, int Kd) { return CK ? min(k4, Kd - 4) : max(min(k4, Kd - 4), 0); }
+  __device__ __forceinline__ void init(const float* __restrict__ p_, long ld_, int i0, int imax, int tid) {
+    ld = ld_;
+    p = p_ + (CK ? i0 * ld : i0);
+    off = min(row(tid), imax - 1 - i0) * (CK ? (int)ld * 4 : 4);
+  }
+  // (everything that is read lies inside the operand)
+  __device__ __forceinline__ static __amdgpu_buffer_rsrc_t rsrc(const float* q) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q), 0, 0x7fffffff, 0x00020000);
   }
   __device__ __forceinline__ void load(int st, int kt, int Kd, int tid) {
     const int k4 = kt * SBK + 4 * half(tid);
     const bool tail = (kt + 1) * SBK > Kd;  // (uniform; beyond the last tile everything is read from the end)
     if (CK) {
-      const f4v v = __builtin_bit_cast(f4v, tail ? __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * base(k4, Kd), 0, 0)
-                                                 : __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * half(tid), kt * SBK * 4, 0));
+      const f4v v = __builtin_bit_cast(f4v, tail ? __builtin_amdgcn_raw_buffer_load_b128(rsrc(p), off + 4 * base(k4, Kd), 0, 0)
+                                                 : __builtin_amdgcn_raw_buffer_load_b128(rsrc(p), off + 16 * half(tid), kt * SBK * 4, 0));
 #pragma unroll
       for (int j = 0; j < 4; ++j) r[st][j] = v[j];
     } else {
-      int from = (tail ? base(k4, Kd) : k4) * ld4;
+      const __amdgpu_buffer_rsrc_t rs = rsrc(p + base(k4, Kd) * ld);
 #pragma unroll
-      for (int j = 0; j < 4; ++j, from += ld4) r[st][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, from, 0));
+      for (int j = 0; j < 4; ++j) r[st][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, min(j, Kd - 1) * (int)ld * 4, 0));
     }
   }
   __device__ __forceinline__ void mask(int st, int kt, int Kd, int tid) {
@@ -156,8 +160,8 @@ __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
   const float* Bg = d.B + (long)g * d.strideB + (long)part * d.Kd * (TB ? 1 : d.ldb);
   // a part of a split contraction starts part * Kd further along k; the last one may be shorter
   if (splits > 1) d.Kd = min(d.Kd, d.Kall - part * d.Kd);
-  a.init(Ag, d.lda, m0, d.M, d.Kd, tid);
-  b.init(Bg, d.ldb, n0, d.N, d.Kd, tid);
+  a.init(Ag, d.lda, m0, d.M, tid);
+  b.init(Bg, d.ldb, n0, d.N, tid);
 
   const int nk = (d.Kd + SBK - 1) / SBK;
   a.load(0, 0, d.Kd, tid);
@@ -185,15 +189,15 @@ __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
       x[p] = *reinterpret_cast<const f4u*>(X + (long)row * d.ldc + col);
     }
   }
+  floatx16 acc, acs;  // the sum of a0 b0 and the sum of the other products
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = acs[v] = 0.f;
   if (nk == 1) a.mask(0, 0, d.Kd, tid);
   a.store(0, lds, tid);
   b.store(0, lds + OpA::LDS_BYTES, tid);
   a.load(0, 2, d.Kd, tid);
   b.load(0, 2, d.Kd, tid);
 
-  floatx16 acc, acs;  // the sum of a0 b0 and the sum of the other products
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = acs[v] = 0.f;
   // fragments of two tiles (this wave's groups of each): the one that is multiplied and the next one, on its way from LDS
   bf16x8s fa[2][3], fb[2][3];
   auto frags = [&](int s, int buf) {
@@ -663,14 +667,13 @@ __global__ void __launch_bounds__(FTHREADS) gemm_f32_slim_multi_kernel(GemmPack 
 
 hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s);
 
-// Whether these kernels take the product: a contraction of at least one half group where an operand is unit-stride along
-// it, operands within 32-bit offsets.
+// Whether these kernels take the product: a contraction of at least one half group where an operand is unit-stride along it.
+// Rows of 2^23 floats and more, of which the 64 of a tile are beyond 32-bit offsets, take the form for few tiles, whose addresses
+// are of 64 bits.
+static int last_part(const GemmDesc& d) { return d.splits > 1 ? d.Kall - (d.splits - 1) * d.Kd : d.Kd; }
+static bool long_rows(const GemmDesc& d) { return d.lda >= 1L << 23 || d.ldb >= 1L << 23; }
 static bool fast_takes(const GemmDesc& d) {
-  const int klast = d.splits > 1 ? d.Kall - (d.splits - 1) * d.Kd : d.Kd;
-  if (klast < 1 || (klast < 4 && (!d.transA || d.transB))) return false;
-  const long a = d.transA ? (long)(d.Kd - 1) * d.lda + d.M : (long)(d.M - 1) * d.lda + d.Kd;
-  const long b = d.transB ? (long)(d.N - 1) * d.ldb + d.Kd : (long)(d.Kd - 1) * d.ldb + d.N;
-  return a < (1L << 29) - 64 && b < (1L << 29) - 64;
+  return last_part(d) >= (d.transA && !d.transB ? 1 : 4) && !(d.transA && d.transB && long_rows(d));
 }
 
 // The form for few tiles: up to 256 tiles of 32 x 32, up to 448 where the launch holds nothing else (`shared`: it does;
@@ -681,14 +684,16 @@ static bool fast_takes(const GemmDesc& d) {
 //   576 tiles  Kd = 2000  47.7 / 36.2                         1024 tiles  Kd = 512  23.7 / 13.0
 static bool fast_slim(const GemmDesc& d, bool shared) {
   const long t = (long)((d.M + 31) / 32) * ((d.N + 31) / 32) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
-  return !(d.transA && d.transB) && t <= (shared ? 256 : 448);
+  return !(d.transA && d.transB) && (t <= (shared ? 256 : 448) || long_rows(d));
 }
 // Operands straight from memory: weight gradients of two rounds of workgroups and more.  us, this form / through LDS (in place,
 // 16 workers): 1024 x 784, Kd = 128 (896 tiles)  45 / 53, 1024 x 1024 (1024)  49 / 62; but 1536 x 128, Kd = 560 (192)  35 / 35,
 // 2000 x 256, Kd = 560, 4 workers (128)  36 / 25.
 static bool fast_direct(const GemmDesc& d) {
   const long t = (long)((d.M + DBM - 1) / DBM) * ((d.N + DBM - 1) / DBM) * (d.workers ? d.workers : d.groups) * (d.splits > 1 ? d.splits : 1);
-  return d.transA && !d.transB && ((d.M | d.N) & 1) == 0 && t >= 512;
+  const long most = (1L << 29) - 64;  // floats of an operand: 32-bit offsets from its first element
+  return d.transA && !d.transB && ((d.M | d.N) & 1) == 0 && t >= 512 && (d.Kd - 1) * d.lda + d.M < most &&
+         (d.Kd - 1) * d.ldb + d.N < most;
 }
 static unsigned tile_blocks(const GemmDesc& d, int tile) {
   const long t = (long)((d.N + tile - 1) / tile) * ((d.M + tile - 1) / tile) * d.groups * (d.splits > 1 ? d.splits : 1);
