@@ -27,9 +27,13 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // into.  A narrow layer's gradient has a few dozen 64 x 64 tiles per worker and a contraction of
 // thousands: the parts run side by side, about two workgroups per CU over all K workers (a launch holds two of these products
 // and more), and the kernel that applies the update adds them in order.  A part is at least 128 long (four k-tiles: below
-// that a part is mostly first loads and epilogue), of a contraction of 1000 and more 256, and 1 means the update stays
-// in the epilogue.  (Shorter contractions would leave too few workgroups: H = 96, Kd = 720, 3 workers 157.7 us a round, 159.3 with parts of 256.
-// So would products that then are few tiles, whose form is another one.)
+// that a part is mostly first loads and epilogue), 256 from a contraction of 832 on, and 1 means the update stays
+// in the epilogue.  us per local step, parts of 128 / of 256, over Kd:
+//   H = 48, batch 20, 16 workers   520  73.7 / 75.9   720  87.5 / 91.6   800  91.6 / 93.6   840  98.8 / 96.4   900 102.5 / 100.3   1200 122.6 / 120.7
+//   H = 110, batch 20, 3 workers   520 104.7 / 106.0  720 131.1 / 131.9  800 140.3 / 140.0  840 145.8 / 144.8  900 153.4 / 152.7   1200 188.4 / 187.4
+//   H = 128, batch 20, 8 workers   520 121.5 / 120.0  720 150.4 / 149.0  800 160.0 / 157.7  840 167.0 / 163.1  900 175.3 / 171.4   1200 215.7 / 213.9
+// The longer parts want 96 workgroups of them at least (H = 128, batch 20, 2 workers, 72 workgroups: 840 150.6 / 151.6,
+// 960 165.1 / 167.0), and products that would then be few tiles, whose form is another one, keep the shorter.
 // us per round or local step, three workgroups per CU and parts of 128 / this: H = 48, batch 100, 30 steps, 16 workers 154.9 / 145.8;
 // H = 90, 20, 50, 16 181.5 / 175.7; H = 128, 32, 60, 2 layers, 2 workers 403 / 390; H = 110, 60, 40, 2 layers, 3 workers 337 / 329; H = 128, 40, 40, 8
 // 193.8 / 191.0; H = 256, 32, 32, 3 212.3 / 210.6; H = 100, 20, 50, 2 layers, 4 298.6 / 297.6.
@@ -40,7 +44,7 @@ int wgrad_splits(int M, int N, int Kd, int K) {
   long n = (512 + tiles - 1) / tiles;
   if (n > Kd / 128) n = Kd / 128;
   if (n > 16) n = 16;
-  if (Kd >= 1000 && n > Kd / 256 && tiles32 * (Kd / 256) > 256) n = Kd / 256;
+  if (Kd >= 832 && n > Kd / 256 && tiles * (Kd / 256) >= 96 && tiles32 * (Kd / 256) > 256) n = Kd / 256;
   return n < 2 ? 1 : (int)n;
 }
 // An input gradient of the head (M x N outputs, contraction over the classes: thousands, where the output
