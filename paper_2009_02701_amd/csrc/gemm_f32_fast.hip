@@ -55,6 +55,7 @@ template <bool CK>
 struct SplitTile {
   static constexpr int REGION = 512 + 32, PLANE = SBM / 32 * 4 * REGION, LDS_BYTES = 3 * PLANE;
   const float* p;  // the tile's first row (CK) or column
+  __amdgpu_buffer_rsrc_t rs;
   long ld;
   int off;        // the thread's row (CK) or column from there, in bytes
   float r[2][4];  // a half group each: 64 x 8 of them are one per thread
@@ -62,10 +63,11 @@ struct SplitTile {
   __device__ __forceinline__ static int half(int tid) { return CK ? tid & 7 : __builtin_amdgcn_readfirstlane(tid / SBM); }
   __device__ __forceinline__ static int row(int tid) { return CK ? tid >> 3 : tid % SBM; }
   // first k of half group k4 as it is read
-  __device__ __forceinline__ static int base(int k4, int Kd) { return CK ? min(k4, Kd - 4) : max(min(k4, Kd - 4), 0); }
+  __device__ __forceinline__ static int base(int k4, int Kd) { return max(min(k4, Kd - 4), 0); }
   __device__ __forceinline__ void init(const float* __restrict__ p_, long ld_, int i0, int imax, int tid) {
     ld = ld_;
     p = p_ + (CK ? i0 * ld : i0);
+    rs = rsrc(p);
     off = min(row(tid), imax - 1 - i0) * (CK ? (int)ld * 4 : 4);
   }
   // (everything that is read lies inside the operand)
@@ -76,14 +78,14 @@ struct SplitTile {
     const int k4 = kt * SBK + 4 * half(tid);
     const bool tail = (kt + 1) * SBK > Kd;  // (uniform; beyond the last tile everything is read from the end)
     if (CK) {
-      const f4v v = __builtin_bit_cast(f4v, tail ? __builtin_amdgcn_raw_buffer_load_b128(rsrc(p), off + 4 * base(k4, Kd), 0, 0)
-                                                 : __builtin_amdgcn_raw_buffer_load_b128(rsrc(p), off + 16 * half(tid), kt * SBK * 4, 0));
+      const f4v v = __builtin_bit_cast(f4v, tail ? __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * base(k4, Kd), 0, 0)
+                                                 : __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * half(tid), kt * SBK * 4, 0));
 #pragma unroll
       for (int j = 0; j < 4; ++j) r[st][j] = v[j];
     } else {
-      const __amdgpu_buffer_rsrc_t rs = rsrc(p + base(k4, Kd) * ld);
+      const __amdgpu_buffer_rsrc_t rk = rsrc(p + base(k4, Kd) * ld);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) r[st][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, min(j, Kd - 1) * (int)ld * 4, 0));
+      for (int j = 0; j < 4; ++j) r[st][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rk, off, min(j, Kd - 1) * (int)ld * 4, 0));
     }
   }
   __device__ __forceinline__ void mask(int st, int kt, int Kd, int tid) {
@@ -111,6 +113,7 @@ struct SplitTile {
 // Contractions of up to 3 (weight gradients of so small a batch) stay with the fp32 instruction: of one term it gives the rounded
 // product, the six bf16 ones an error 3 % larger in the 2-norm and up to 1.5 times as large.
 static constexpr int kShort = 3;
+__host__ __device__ static inline bool is_short(const GemmDesc& d) { return d.Kd <= kShort && d.splits <= 1 && d.transA && !d.transB; }
 
 // The sums of a 32 x 32 block that are not finite, again with the fp32 instruction (rare: nothing is staged):
 // the k-groups g0, g0 + dg, .. of 8
@@ -134,7 +137,7 @@ __device__ __forceinline__ floatx16 split_redo(const float* __restrict__ A, long
   return have;
 }
 
-template <bool TA, bool TB>
+template <bool TA, bool TB, bool SHORT>
 __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
   constexpr int NT = STHREADS, BM = SBM, BN = SBM;
   using OpA = SplitTile<!TA>;
@@ -151,12 +154,13 @@ __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
   // an XCD fetches the A rows of its run once and only the B operands of the groups it touches.
   const int tn = (d.N + BN - 1) / BN, tm = (d.M + BM - 1) / BM;
   const int splits = d.splits > 1 ? d.splits : 1;
-  const long ntiles = (long)tn * tm * d.groups * splits, per = (ntiles + 7) / 8;
-  const long tile = (long)(bid & 7) * per + (bid >> 3);
-  if ((long)(bid >> 3) >= per || tile >= ntiles) return;  // padding of the last run
-  const int gp = (int)(tile / ((long)tn * tm));   // group * splits + part of the contraction
+  // (a grid holds them: 32 bits; the divisions in 64 cost a workgroup as much as a k-tile)
+  const unsigned each = (unsigned)tn * tm, ntiles = each * d.groups * splits, per = (ntiles + 7) / 8;
+  const unsigned tile = (bid & 7) * per + (bid >> 3);
+  if ((bid >> 3) >= per || tile >= ntiles) return;  // padding of the last run
+  const int gp = (int)(tile / each), in_g = (int)(tile - gp * each);   // group * splits + part of the contraction
   const int g = gp / splits, part = gp - g * splits;
-  const int m0 = (int)((tile / tn) % tm) * BM, n0 = (int)(tile % tn) * BN;
+  const int m0 = in_g / tn * BM, n0 = in_g % tn * BN;
 
   OpA a;
   OpB b;
@@ -196,7 +200,7 @@ __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
   floatx16 acc, acs;  // the sum of a0 b0 and the sum of the other products
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = acs[v] = 0.f;
-  if (TA && !TB && d.Kd <= kShort) {  // (uniform)
+  if constexpr (SHORT) {
     float* q = fast_lds;  // [A, B][4 of k][64]: the first half groups, which wave 0 has
     if (wave == 0) {
       a.mask(0, 0, d.Kd, tid);
@@ -324,6 +328,7 @@ __device__ __forceinline__ void split_body(GemmDesc d, unsigned bid) {
 typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
 static constexpr int DBM = 128;  // 2 x 2 waves
+template <bool SHORT>
 __device__ __forceinline__ void direct_body(GemmDesc d, unsigned bid) {
   constexpr int BM = DBM, BN = DBM, TM = 2, TN = 2, ST = 2;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -369,7 +374,7 @@ __device__ __forceinline__ void direct_body(GemmDesc d, unsigned bid) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = acs[i][j][v] = 0.f;
-  if (d.Kd <= kShort) {
+  if constexpr (SHORT) {
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -377,7 +382,7 @@ __device__ __forceinline__ void direct_body(GemmDesc d, unsigned bid) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[0][i][k], rb[0][j][k], acc[i][j], 0, 0, 0);
   }
-  for (int c0 = d.Kd <= kShort ? nc : 0; c0 < nc; c0 += ST) {
+  for (int c0 = SHORT ? nc : 0; c0 < nc; c0 += ST) {
 #pragma unroll
     for (int st = 0; st < ST; ++st) {
       const int c = c0 + st;
@@ -452,7 +457,8 @@ __device__ __forceinline__ void direct_body(GemmDesc d, unsigned bid) {
     }
   }
 }
-__global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_kernel(GemmDesc d) { direct_body(d, blockIdx.x); }
+template <bool SHORT>
+__global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_kernel(GemmDesc d) { direct_body<SHORT>(d, blockIdx.x); }
 
 // ---------------------------------------------------------------------------- few tiles
 // A product of few tiles is bound by one wave's chain: in the form above a 64 x 64 tile's k-tile of 32 takes 0.8 us
@@ -583,9 +589,9 @@ __global__ void __launch_bounds__(FTHREADS) gemm_f32_slim_kernel(GemmDesc d) {
   slim_body<TA, TB>(d, blockIdx.x, fast_lds);
 }
 
-template <bool TA, bool TB>
+template <bool TA, bool TB, bool SHORT = false>
 __global__ void __launch_bounds__(STHREADS) gemm_f32_fast_kernel(GemmDesc d) {
-  split_body<TA, TB>(d, blockIdx.x);
+  split_body<TA, TB, SHORT>(d, blockIdx.x);
 }
 
 // Column sums as further workgroups of a launch of products: a workgroup covers 64 columns with 4 row slices
@@ -634,7 +640,8 @@ __device__ __forceinline__ void colsum_body(const ColsumPack& pk, unsigned bid, 
 // them leaves most of the chip idle, and a launch of its own costs 4.5 us before it does anything.
 // Product i owns the workgroups blk0[i] .. blk0[i+1]-1 (whole rounds over the XCDs), the column sums the rest.
 // SLIM: those of the bits of `slim` are products of few tiles; a workgroup has room for two of them.
-template <bool SLIM>
+// SHORT: there are contractions of up to kShort.
+template <bool SLIM, bool SHORT>
 __global__ void __launch_bounds__(STHREADS) gemm_f32_multi_kernel(GemmPack pk, ColsumPack cs, int groups, unsigned slim) {
   extern __shared__ __attribute__((aligned(16))) float fast_lds[];
   int i = 0;
@@ -656,18 +663,21 @@ __global__ void __launch_bounds__(STHREADS) gemm_f32_multi_kernel(GemmPack pk, C
     else slim_body<false, false>(d, b32, lds);
     return;
   }
-  if (d.transA) split_body<true, false>(d, bid);
-  else if (d.transB) split_body<false, true>(d, bid);
-  else split_body<false, false>(d, bid);
+  if (SHORT && is_short(d)) split_body<true, false, true>(d, bid);
+  else if (d.transA) split_body<true, false, false>(d, bid);
+  else if (d.transB) split_body<false, true, false>(d, bid);
+  else split_body<false, false, false>(d, bid);
 }
 
 // ... and of products that take their operands from memory
+template <bool SHORT>
 __global__ void __launch_bounds__(FTHREADS, 2) gemm_f32_direct_multi_kernel(GemmPack pk, ColsumPack cs, int groups) {
   int i = 0;
   while (i < pk.n && blockIdx.x >= pk.blk0[i + 1]) ++i;  // (uniform)
   const unsigned bid = blockIdx.x - pk.blk0[i];
   if (i < pk.n) {
-    direct_body(pk.d[i], bid);
+    if (SHORT && is_short(pk.d[i])) direct_body<true>(pk.d[i], bid);
+    else direct_body<false>(pk.d[i], bid);
     return;
   }
   const unsigned per = cs.blk0[cs.n];
@@ -753,8 +763,9 @@ hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipS
   if (pk.n == 1 && cs.n == 0) return launch_gemm_f32_fast(pk.d[0], s);
   unsigned slim = 0;
   double flops = 0.;
-  bool direct = true, alike = true;  // all of them: operands from memory, few tiles
-  for (int i = 0; i < pk.n; ++i) direct = direct && fast_direct(pk.d[i]), alike = alike && fast_slim(pk.d[i], true);
+  bool direct = true, alike = true, some_short = false;  // all of them: operands from memory, few tiles
+  for (int i = 0; i < pk.n; ++i)
+    direct = direct && fast_direct(pk.d[i]), alike = alike && fast_slim(pk.d[i], true), some_short = some_short || is_short(pk.d[i]);
   pk.blk0[0] = 0;
   for (int i = 0; i < pk.n; ++i) {
     const GemmDesc& d = pk.d[i];
@@ -766,7 +777,7 @@ hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipS
   dim3 grid(pk.blk0[pk.n] + (cs.n ? cs.blk0[cs.n] * (unsigned)groups : 0u));
   KernelTimer kt(KID_GEMM_F32_FAST, flops, s);
   if (direct) {
-    hipLaunchKernelGGL(gemm_f32_direct_multi_kernel, grid, dim3(FTHREADS), FTHREADS * sizeof(float), s, pk, cs, groups);
+    hipLaunchKernelGGL(some_short ? gemm_f32_direct_multi_kernel<true> : gemm_f32_direct_multi_kernel<false>, grid, dim3(FTHREADS), FTHREADS * sizeof(float), s, pk, cs, groups);
     return hipGetLastError();
   }
   if (alike) {
@@ -774,7 +785,8 @@ hipError_t launch_gemm_pack(GemmPack& pk, const ColsumPack& cs, int groups, hipS
     return hipGetLastError();
   }
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(STHREADS), kSplitLds, s, pk, cs, groups, slim); };
-  slim ? launch(gemm_f32_multi_kernel<true>) : launch(gemm_f32_multi_kernel<false>);
+  if (some_short) slim ? launch(gemm_f32_multi_kernel<true, true>) : launch(gemm_f32_multi_kernel<false, true>);
+  else slim ? launch(gemm_f32_multi_kernel<true, false>) : launch(gemm_f32_multi_kernel<false, false>);
   return hipGetLastError();
 }
 
@@ -788,11 +800,12 @@ hipError_t launch_gemm_f32_fast(const GemmDesc& d, hipStream_t s) {
   const dim3 grid(tile_blocks(d, direct ? DBM : SBM));
   KernelTimer kt(KID_GEMM_F32_FAST, 2.0 * d.M * d.N * (double)(d.splits > 1 ? d.Kall : d.Kd) * d.groups, s);
   if (direct) {
-    hipLaunchKernelGGL(gemm_f32_direct_kernel, grid, dim3(FTHREADS), 0, s, d);
+    hipLaunchKernelGGL(is_short(d) ? gemm_f32_direct_kernel<true> : gemm_f32_direct_kernel<false>, grid, dim3(FTHREADS), 0, s, d);
     return hipGetLastError();
   }
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(STHREADS), kSplitLds, s, d); };
-  if (d.transA) d.transB ? launch(gemm_f32_fast_kernel<true, true>) : launch(gemm_f32_fast_kernel<true, false>);
+  if (is_short(d)) launch(gemm_f32_fast_kernel<true, false, true>);
+  else if (d.transA) d.transB ? launch(gemm_f32_fast_kernel<true, true>) : launch(gemm_f32_fast_kernel<true, false>);
   else d.transB ? launch(gemm_f32_fast_kernel<false, true>) : launch(gemm_f32_fast_kernel<false, false>);
   return hipGetLastError();
 }
