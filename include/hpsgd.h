@@ -57,7 +57,9 @@ enum hpsgd_model_kind {
 };
 
 enum hpsgd_precision {
-  HPSGD_FP32 = 0,     /* fp32 operands on the fp32 matrix cores */
+  HPSGD_FP32 = 0,     /* fp32 operands on the fp32 matrix cores, or on the bf16 ones as three bf16 parts each (six
+                         products, fp32 accumulate): 24 bits of every operand of at least 2^-110 = 7.7e-34 in size, fewer
+                         below; infinities, NaN and values up to the largest fp32 one as with fp32 products */
   HPSGD_BF16_MFMA = 1 /* GEMM operands rounded to bf16 (nearest-even), fp32 accumulate;
                          parameters, gate math, softmax and gradients stay fp32 */
 };

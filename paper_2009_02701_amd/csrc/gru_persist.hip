@@ -36,9 +36,9 @@
 // one workgroup fills a CU) sets the abort word: the launch fails loudly.  Otherwise the tile is
 // that of the workgroup index and the exchange is at device scope as described above.
 //
-// Waiting needs every workgroup of the grid resident at the same time: the launcher refuses
-// grids with more workgroups than the device has compute units (a workgroup takes most of a
-// CU's LDS, so there is one per CU), and launches of these kernels from different streams are
+// Waiting needs every workgroup of the grid resident at the same time: the launcher's grids have at most one
+// workgroup for every compute unit of the device (a launch that places its workgroups by ticket asks for more than half of a
+// CU's LDS each, so that there is one on every CU), and launches of these kernels from different streams are
 // ordered against each other by the caller.  Every wait is bounded: when the spin limit runs
 // out, or another workgroup has given up, the workgroup sets the abort word and the whole
 // workgroup leaves the kernel, so every wave reaches its end whatever happens.
@@ -46,7 +46,9 @@
 // Matrix work: 8 waves, 16 or 32 batch rows x 16 hidden units per workgroup.  The fp32 instruction (v_mfma_f32_16x16x4_f32)
 // with the weights in LDS took 40 to 50 % of a step; the products are those of split_f32.h instead, a 2.7th of its cycles,
 // the conversions beside them.  Where registers run out the smallest parts of the weights lie in LDS (persist_fwd_lw,
-// persist_bwd_nl: a launch that spills is slower than the fp32 instruction, its reloads queue up with the operands).
+// persist_bwd_nl: a launch that spills is slower than the fp32 instruction, its reloads queue up with the operands; the one
+// that still does, by 21 registers, 32 rows beyond H = 512 with the inputs projected, is faster than without the projection and
+// with a product of its own for it, see gru_persist_xproj_supported).
 // us per launch, before / now (forward, backward with its share of dW_hh):
 //   35 steps, H = 512, 4 workers of 64 rows, input of 128     239 / 197    392 / 338   (168, 280 since two blocks take turns, below)
 //   35 steps, H = 256, 4 workers of 16 rows, input of 128     146 /  89    182 / 134   ( 84, 114)
@@ -1472,8 +1474,13 @@ size_t gru_persist_sync_words(int B, int groups, int rows) { return (size_t)grou
 unsigned gru_persist_count_per_step(int) { return 1u; }
 
 // The forward kernel can do the input projection itself when the layer input is narrow (at most 2 chunks of 32 per
-// wave; beside a wide layer a product of its own is no slower) and its 48 rows of W_ih fit the LDS beside the rest: with 32 rows
-// and H > 512 that is 64 KB of partial sums and 72 KB of weight parts, which leaves room for an input of 64.
+// wave) and its 48 rows of W_ih fit the LDS beside the rest: with 32 rows
+// and H > 512 that is 64 KB of partial sums and 72 KB of weight parts, which leaves room for an input of 64.  The line at 21 chunks of
+// both contractions together is where the fp32 form of this launch ended, with all of them in LDS; this form is the faster
+// beyond it too.  us per local step of 20 steps, 4 workers, projected in the launch / by a product of its own:
+//   16 rows, batch 16   H = 576, input 112  265.9 / 279.3,  192  267.2 / 282.4     H = 640,  48  275.2 / 290.9,  256  294.2 / 314.4
+//   32 rows, batch 64   H = 512, input 176  325.8 / 342.7,  256  325.6 / 354.5     batch 32, H = 640, 64  395.0 / 405.7
+// and on this side of it, 32 rows, batch 32   H = 528, input 16  353.6 / 357.5,  64  350.8 / 359.5
 bool gru_persist_xproj_supported(int H, int width, int rows) {
   return width >= 16 && width % 16 == 0 && width <= 256 && (H + PC - 1) / PC + (width + PC - 1) / PC <= 21 &&
          persist_fwd_form(H, rows, width).lds <= kLdsLimit;

@@ -812,7 +812,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // per layer: the transposed bf16 W_hh was made in the forward pass, in the same
     // read as the row-major copy
     bool whhT_ready[16] = {false};
-    // fp32: the recurrence of a layer as one launch (a few for BPTT) with W_hh resident in LDS.
+    // fp32: the recurrence of a layer as one launch (or a few, gru_persist_pays) with W_hh resident on the chip.
     // Its workgroups wait for each other through flag words in the workspace, zeroed here; pbase
     // follows what the flags read.  A given-up wait shows as NaN in the results (below).
     // narrow fp32 layers: the whole recurrence without any exchange between workgroups
