@@ -73,7 +73,6 @@ typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int PNT = 512;     // threads per workgroup
-constexpr int PR = 32;       // batch rows per workgroup (bf16; fp32: 16 or 32, a template argument)
 constexpr int PJ = 16;       // hidden units per workgroup
 constexpr int PC = 32;       // contraction chunk
 
@@ -931,8 +930,8 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
 // ---------------------------------------------------------------------------- bf16 operands
 // The same scheme with v_mfma_f32_16x16x32_bf16 on the bf16 copies of W_hh and of the exchanged
 // activations (every operand is the nearest-even bf16 rounding of the fp32 value; accumulation,
-// cell math and everything stored for later use stay fp32).  A workgroup owns 32 batch rows x
-// 32 hidden units.  Its slice of the weights (forward: 96 gate rows x H; backward: 32 rows of
+// cell math and everything stored for later use stay fp32).  A workgroup owns 32 batch rows (or 16,
+// gru_persist_bf16_rows) x 32 hidden units.  Its slice of the weights (forward: 96 gate rows x H; backward: 32 rows of
 // W_hh^T x 3H; 192 KB at H = 1024) stays in REGISTERS for the whole launch: the contraction is
 // cut into 32-wide chunks, wave w owns the chunks w, w + 8, .. with all the column blocks, i.e.
 // up to 24 B-operand fragments of 16 bytes per lane.  Per step a wave fetches only its own A
@@ -940,7 +939,7 @@ gru_bwd_persist_kernel(const float* __restrict__ W_hh, long s_rep, float* __rest
 // meet in LDS.  MFMA 16x16x32 lane layout: A lane l holds A[m = l%16][k = 8*(l/16) .. +7],
 // B lane l holds B[k = 8*(l/16) .. +7][n = l%16], accumulator as for 16x16x4.
 // Epilogue: thread t owns batch row t/16 and the two units 2*(t%16), +1 of the tile, so that
-// bf16 values are stored in pairs.
+// bf16 values are stored in pairs (16 rows: the first four waves).
 //
 // Layout of the exchanged operand.  A wave's A fragment is 16 rows x 32 contraction indices,
 // 16 bytes per lane.  Read from a row-major matrix that is 64 bytes of each of 16 rows, half a
@@ -1000,8 +999,8 @@ __device__ __forceinline__ void st16_nt(void* p, uint4 v) {
 // Forward.  Wb: bf16 W_hh [3H][H]; hx: bf16 h_0 .. h_T fragment-major (blocks of 16 ceil(B/16) x H,
 // h_0 given), the exchanged operand; hb: the same row-major (blocks of B x H; written, not read);
 // hs: the same in fp32; hT (nullable): bf16 transposed copy [H][ld_hT], column (t+1)*B + row.
-// NCF: chunks per wave (H <= 256 * NCF).  EX: the gates of the fp32 launches (gru_bf16_exact_gates).
-template <int NCF, bool EX>
+// NCF: chunks per wave (H <= 256 * NCF).  RB: row blocks of 16 per workgroup.  EX: the gates of the fp32 launches (gru_bf16_exact_gates).
+template <int NCF, int RB, bool EX>
 __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih,
                             const float* __restrict__ b_hh, long s_rep, int Hc, const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs,
@@ -1009,19 +1008,20 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
                             long s_hT, int Bc, int B, int H, int T, int sg0, int n_sg, unsigned* sync, unsigned base,
                             unsigned spin_limit, unsigned* tickets, unsigned ticket_base, unsigned per_xcd) {
   extern __shared__ __attribute__((aligned(16))) float persist_lds[];
-  float* red = persist_lds;                                     // [8][2][6][4][64]
-  __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * 12 * 256);   // [32 units][TP]
+  constexpr int PRB = 16 * RB;                                  // rows of the tile
+  float* red = persist_lds;                                     // [8][RB][6][4][64]
+  __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * RB * 6 * 256);  // [32 units][TP]
   int* lds_flag = reinterpret_cast<int*>(tt + QJ * TP);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int NJ = H / QJ, RT = (B + PR - 1) / PR;
+  const int NJ = H / QJ, RT = (B + PRB - 1) / PRB;
   unsigned* abort_w = sync;
   int tx, sg;
   bool l2x;
   if (!persist_place(tickets, ticket_base, per_xcd, abort_w, spin_limit, lds_flag, NJ, n_sg, tx, sg, l2x)) return;
   sg += sg0;
   const int g = sg / RT, ty = sg - g * RT;
-  const int j0 = tx * QJ, r0 = ty * PR;
+  const int j0 = tx * QJ, r0 = ty * PRB;
   unsigned* flags = sync + 1 + sg * PF;
   __builtin_amdgcn_s_setprio(3);
   const int nch = H / PC;
@@ -1039,10 +1039,11 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
     }
   }
   // epilogue element: row rl of the tile, units u0, u0 + 1
-  const int rl = tid >> 4, u0 = 2 * (tid & 15);
+  const bool epi = RB == 2 || wave < 4;  // (uniform)
+  const int rl = (tid >> 4) & (PRB - 1), u0 = 2 * (tid & 15);
   const int row = r0 + rl, rowc = min(row, B - 1);
   const int j = j0 + u0;
-  const int ro = ((rl >> 4) * 6) * 256 + (rl & 3) * 64 + ((rl >> 2) & 3) * 16 + (u0 & 15);  // + cb * 256 + w * 3072
+  const int ro = ((rl >> 4) * 6) * 256 + (rl & 3) * 64 + ((rl >> 2) & 3) * 16 + (u0 & 15);  // + cb * 256 + w * RB * 1536
   const int half = u0 >> 4;
   const bool ok0 = row < Bc && j < Hc, ok1 = row < Bc && j + 1 < Hc;  // of the model, not of its padding
   // the biases: arrays of the model's own width (units beyond it have none)
@@ -1060,9 +1061,9 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
   const long xblk = (long)((B + 15) / 16) * 16 * H;  // elements of a step's block of hx
   float2 hpv = *reinterpret_cast<const float2*>(hsg + (long)rowc * H + j);
   // A fragments: row blocks r0/16 + rb (one that lies beyond the batch is read from the tile's first)
-  int aoff[2];
+  int aoff[RB];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
+  for (int rb = 0; rb < RB; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
   // The step's input projection is loaded one step ahead, behind the products of the step before: a CU's loads return in
   // the order of their issue, whichever wave's they are, and these come from memory, not from the L2.  Requested in front of
   // the wait, they would sit between the polling wave and its view of the flags; in front of the products, between the
@@ -1073,90 +1074,96 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
 #pragma unroll
     for (int q = 0; q < 3; ++q) gxn[q] = ld2_nt(gxr + q * H);
   };
-  prefetch(0);
+  if (epi) prefetch(0);
+  else gxn[0] = gxn[1] = gxn[2] = make_float2(0.f, 0.f);
   for (int t = 0; t < T; ++t) {
     float2 gxv[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) gxv[q] = make_float2(gxn[q].x + biasx[q].x, gxn[q].y + biasx[q].y);
     if (t > 0 && !group_wait(flags, NJ, base + (unsigned)t, abort_w, spin_limit, lds_flag)) return;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(hxg + fwd_block(t, l2x) * xblk, 0, 0x7fffffff, 0x00020000);
-    bf16x8 a[NCF][2];
+    bf16x8 a[NCF][RB];
 #pragma unroll
     for (int i = 0; i < NCF; ++i) {
       const int c = wave + 8 * i;
       const int co = (c < nch ? c : 0) * 1024;
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) a[i][rb] = ld_frag_dev(rs, aoff[rb] + co);
+      for (int rb = 0; rb < RB; ++rb) a[i][rb] = ld_frag_dev(rs, aoff[rb] + co);
     }
-    floatx4 acc[2][6];
+    floatx4 acc[RB][6];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int cb = 0; cb < 6; ++cb) acc[rb][cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     __builtin_amdgcn_sched_barrier(0);  // every load is issued before anything waits for one
 #pragma unroll
     for (int i = 0; i < NCF; ++i)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
+      for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < 6; ++cb)
           acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][rb], wf[i][cb], acc[rb][cb], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    prefetch(min(t + 1, T - 1));
+    if (epi) prefetch(min(t + 1, T - 1));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int cb = 0; cb < 6; ++cb)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[(((wave * 2 + rb) * 6 + cb) * 4 + v) * 64 + lane] = acc[rb][cb][v];
+        for (int v = 0; v < 4; ++v) red[(((wave * RB + rb) * 6 + cb) * 4 + v) * 64 + lane] = acc[rb][cb][v];
     __syncthreads();
-    float2 gh[3];
+    if (epi) {
+      float2 gh[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float* rp = red + ro + (2 * q + half) * 256;
-      float2 p[8];
+      for (int q = 0; q < 3; ++q) {
+        const float* rp = red + ro + (2 * q + half) * 256;
+        float2 p[8];
 #pragma unroll
-      for (int w = 0; w < 8; ++w) p[w] = *reinterpret_cast<const float2*>(rp + w * 3072);
-      gh[q].x = (((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x))) + bias[q].x;
-      gh[q].y = (((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y))) + bias[q].y;
+        for (int w = 0; w < 8; ++w) p[w] = *reinterpret_cast<const float2*>(rp + w * RB * 1536);
+        gh[q].x = (((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x))) + bias[q].x;
+        gh[q].y = (((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y))) + bias[q].y;
+      }
+      float r0v = sigm_of<EX>(gxv[0].x + gh[0].x), r1v = sigm_of<EX>(gxv[0].y + gh[0].y);
+      float z0v = sigm_of<EX>(gxv[1].x + gh[1].x), z1v = sigm_of<EX>(gxv[1].y + gh[1].y);
+      float n0v = tanh_of<EX>(gxv[2].x + r0v * gh[2].x), n1v = tanh_of<EX>(gxv[2].y + r1v * gh[2].y);
+      // rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model times
+      // their zero operands is NaN, which their h and gate gradients would hand to everyone
+      if (!ok0) r0v = z0v = n0v = gh[2].x = 0.f;
+      if (!ok1) r1v = z1v = n1v = gh[2].y = 0.f;
+      const float2 hn = make_float2((1.0f - z0v) * n0v + z0v * hpv.x, (1.0f - z1v) * n1v + z1v * hpv.y);
+      if (row < B) {
+        const long e = ((long)(t + 1) * B + row) * H + j;
+        const unsigned hp2 = pack_bf16(hn.x, hn.y);
+        st_dev_u32(hxg + fwd_block(t + 1, l2x) * xblk + xfrag(row, nch, tx, u0), hp2, l2x);
+        st2_nt(hsg + e, hn);
+        st_u32_nt(hbg + e, hp2);
+        float* svr = sv + g * s_sv + ((long)t * B + row) * 4 * H + j;
+        st2_nt(svr, make_float2(r0v, r1v));
+        st2_nt(svr + H, make_float2(z0v, z1v));
+        st2_nt(svr + 2 * H, make_float2(n0v, n1v));
+        st2_nt(svr + 3 * H, gh[2]);
+      }
+      if (hT) {
+        tt[u0 * TP + rl] = (__bf16)hn.x;
+        tt[(u0 + 1) * TP + rl] = (__bf16)hn.y;
+      }
+      hpv = hn;
     }
-    float r0v = sigm_of<EX>(gxv[0].x + gh[0].x), r1v = sigm_of<EX>(gxv[0].y + gh[0].y);
-    float z0v = sigm_of<EX>(gxv[1].x + gh[1].x), z1v = sigm_of<EX>(gxv[1].y + gh[1].y);
-    float n0v = tanh_of<EX>(gxv[2].x + r0v * gh[2].x), n1v = tanh_of<EX>(gxv[2].y + r1v * gh[2].y);
-    // rows and units of the padding leave zeros, selected and not multiplied: an infinite value of the model times
-    // their zero operands is NaN, which their h and gate gradients would hand to everyone
-    if (!ok0) r0v = z0v = n0v = gh[2].x = 0.f;
-    if (!ok1) r1v = z1v = n1v = gh[2].y = 0.f;
-    const float2 hn = make_float2((1.0f - z0v) * n0v + z0v * hpv.x, (1.0f - z1v) * n1v + z1v * hpv.y);
-    if (row < B) {
-      const long e = ((long)(t + 1) * B + row) * H + j;
-      const unsigned hp2 = pack_bf16(hn.x, hn.y);
-      st_dev_u32(hxg + fwd_block(t + 1, l2x) * xblk + xfrag(row, nch, tx, u0), hp2, l2x);
-      st2_nt(hsg + e, hn);
-      st_u32_nt(hbg + e, hp2);
-      float* svr = sv + g * s_sv + ((long)t * B + row) * 4 * H + j;
-      st2_nt(svr, make_float2(r0v, r1v));
-      st2_nt(svr + H, make_float2(z0v, z1v));
-      st2_nt(svr + 2 * H, make_float2(n0v, n1v));
-      st2_nt(svr + 3 * H, gh[2]);
-    }
-    if (hT) {
-      tt[u0 * TP + rl] = (__bf16)hn.x;
-      tt[(u0 + 1) * TP + rl] = (__bf16)hn.y;
-    }
-    hpv = hn;
     group_signal(flags + tx, base + (unsigned)t + 1u, l2x);  // (its barrier also separates the reads of red from the next step's writes)
-    if (hT && tid >= PNT - 128) {
-      // 64-byte row segments of the transposed copy, 16 bytes per thread (the last two waves: the
+    if (hT && wave >= 8 - RB) {
+      // 64- (or 32-) byte row segments of the transposed copy, 16 bytes per thread (the last waves: the
       // first one polls the flags next, and would see them only behind its own stores)
-      const int u = (tid - (PNT - 128)) >> 2, part = tid & 3;
+      const int u = (tid - (PNT - 64 * RB)) / (2 * RB), part = tid % (2 * RB);
       if (r0 + 8 * part < B)  // B is a multiple of 8: a piece of 8 rows is all in or all out
         st16_nt(hT + g * s_hT + (long)(j0 + u) * ld_hT + (long)(t + 1) * B + r0 + 8 * part,
                 *reinterpret_cast<const uint4*>(tt + u * TP + 8 * part));
     }
   }
 }
+
+// chunks of a wave's backward weights that lie in LDS
+constexpr int persist_bwd_bf16_nl(int ncb, int rb) { return rb == 2 && ncb > 8 ? ncb - ncb / 2 : 0; }
 
 // Backward.  WT: bf16 W_hh^T [H][3H]; dghx: bf16 gate gradients of all steps, fragment-major
 // (blocks of 16 ceil(B/16) x 3H), the exchanged operand; dgxb: bf16 dgx row-major; dgxT / dghT: bf16 transposed copies
@@ -1165,8 +1172,9 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
 // (3H <= 256 * NCB).  The fragments of the first half of a wave's chunks stay in registers,
 // those of the second half in LDS (each wave reads back only its own): with all of them in
 // registers the two waves of a SIMD would fill its register file, and no wave of any other
-// kernel (a merge on the second stream) could ever share the CU.
-template <int NCB>
+// kernel (a merge on the second stream) could ever share the CU.  (Tiles of 16 rows have half the operands: all of the
+// weights in registers leave room for others.)
+template <int NCB, int RB>
 __global__ void __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dghx, long s_dgh, long s_dgb, float* __restrict__ D,
                             long s_D, int d_zero, const float* __restrict__ above, long s_above, const float* __restrict__ sv,
@@ -1175,21 +1183,22 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
                             float* __restrict__ dbp, int Hc, int B, int H, int T, int sg0, int n_sg, unsigned* sync, unsigned base,
                             unsigned spin_limit, unsigned* tickets, unsigned ticket_base, unsigned per_xcd) {
   extern __shared__ __attribute__((aligned(16))) float persist_lds[];
-  constexpr int NCR = NCB / 2, NCL = NCB - NCR;                 // chunks in registers / in LDS
-  float* red = persist_lds;                                     // [8][2][2][4][64]
-  __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * 4 * 256);    // [da_r | da_z | da_n | dq][32 units][TP]
+  constexpr int PRB = 16 * RB;                                  // rows of the tile
+  constexpr int NCL = persist_bwd_bf16_nl(NCB, RB), NCR = NCB - NCL;  // chunks in LDS / in registers
+  float* red = persist_lds;                                     // [8][RB][2][4][64]
+  __bf16* tt = reinterpret_cast<__bf16*>(red + 8 * RB * 2 * 256);    // [da_r | da_z | da_n | dq][32 units][TP]
   u32x4_t* wl = reinterpret_cast<u32x4_t*>(tt + 4 * QJ * TP);   // [8 waves][NCL][2][64 lanes] fragments
   int* lds_flag = reinterpret_cast<int*>(wl + 8 * NCL * 2 * 64);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int NJ = H / QJ, RT = (B + PR - 1) / PR;
+  const int NJ = H / QJ, RT = (B + PRB - 1) / PRB;
   unsigned* abort_w = sync;
   int tx, sg;
   bool l2x;
   if (!persist_place(tickets, ticket_base, per_xcd, abort_w, spin_limit, lds_flag, NJ, n_sg, tx, sg, l2x)) return;
   sg += sg0;
   const int g = sg / RT, ty = sg - g * RT;
-  const int j0 = tx * QJ, r0 = ty * PR;
+  const int j0 = tx * QJ, r0 = ty * PRB;
   unsigned* flags = sync + 1 + sg * PF;
   __builtin_amdgcn_s_setprio(3);
   const int H3 = 3 * H;
@@ -1210,23 +1219,24 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
         wl[((wave * NCL + (i - NCR)) * 2 + cb) * 64 + lane] = __builtin_bit_cast(u32x4_t, f);
     }
   }
-  const int rl = tid >> 4, u0 = 2 * (tid & 15);
+  const bool epi = RB == 2 || wave < 4;  // (uniform)
+  const int rl = (tid >> 4) & (PRB - 1), u0 = 2 * (tid & 15);
   const int row = r0 + rl, rowc = min(row, B - 1);
   const int j = j0 + u0;
-  const int ro = ((rl >> 4) * 2 + (u0 >> 4)) * 256 + (rl & 3) * 64 + ((rl >> 2) & 3) * 16 + (u0 & 15);  // + w * 1024
+  const int ro = ((rl >> 4) * 2 + (u0 >> 4)) * 256 + (rl & 3) * 64 + ((rl >> 2) & 3) * 16 + (u0 & 15);  // + w * RB * 512
   float* Dg = D + g * s_D;
   float2 dcar = make_float2(0.f, 0.f);
   if (!d_zero) dcar = *reinterpret_cast<const float2*>(Dg + (long)rowc * H + j);
   __bf16* dghg = dghx + g * s_dgh;
   const long xblk = (long)((B + 15) / 16) * 16 * H3;  // elements of a step's block of dghx
   float2 bsum[4] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};  // da_r, da_z, da_n, dq over the steps
-  int aoff[2];
+  int aoff[RB];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
+  for (int rb = 0; rb < RB; ++rb) aoff[rb] = (((r0 + rb * 16 < B ? r0 + rb * 16 : r0) >> 4) * nch) * 1024 + lane * 16;
   // The step's saved gates, h and the gradient from above are loaded one step ahead, behind the operand loads of the step
   // before (see the forward kernel: in front of the wait they would delay the polling wave's view of the flags by a trip to
   // memory; further back there is too little of the step left to cover them, 179 us a launch against 184 to 195).
-  float2 nr, nz, nn, nq, nhp, nab;
+  float2 nr = make_float2(0.f, 0.f), nz = nr, nn = nr, nq = nr, nhp = nr, nab = nr;
   auto prefetch = [&](int tn) {
     const long e = ((long)tn * B + rowc) * H + j;
     const float* svr = sv + g * s_sv + ((long)tn * B + rowc) * 4 * H + j;
@@ -1235,29 +1245,29 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
     nhp = ld2_nt(hs + g * s_hs + e);
     nab = above ? ld2_nt(above + g * s_above + e) : make_float2(0.f, 0.f);
   };
-  prefetch(T - 1);
+  if (epi) prefetch(T - 1);
   int it = 0;
   for (int t = T - 1; t >= 0; --t, ++it) {
     const float2 r = nr, z = nz, n = nn, q = nq, hp = nhp, ab = nab;
     if (it > 0 && !group_wait(flags, NJ, base + (unsigned)it, abort_w, spin_limit, lds_flag)) return;
-    floatx4 acc[2][2];
+    floatx4 acc[RB][2];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     if (t + 1 < T) {  // uniform over the grid
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dghg + bwd_block(t + 1, l2x) * xblk, 0, 0x7fffffff,
                                                                           0x00020000);
-      bf16x8 a[NCB][2];
+      bf16x8 a[NCB][RB];
 #pragma unroll
       for (int i = 0; i < NCB; ++i) {
         const int c = wave + 8 * i;
         const int co = (c < nch ? c : 0) * 1024;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) a[i][rb] = ld_frag_dev(rs, aoff[rb] + co);
+        for (int rb = 0; rb < RB; ++rb) a[i][rb] = ld_frag_dev(rs, aoff[rb] + co);
       }
       __builtin_amdgcn_sched_barrier(0);
-      prefetch(max(t - 1, 0));
+      if (epi) prefetch(max(t - 1, 0));
       __builtin_amdgcn_sched_barrier(0);  // every load is issued before anything waits for one
 #pragma unroll
       for (int i = 0; i < NCB; ++i) {
@@ -1267,65 +1277,67 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
           w2[cb] = i < NCR ? wf[i < NCR ? i : 0][cb]
                            : __builtin_bit_cast(bf16x8, wl[((wave * NCL + (i - NCR)) * 2 + cb) * 64 + lane]);
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
           for (int cb = 0; cb < 2; ++cb)
             acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][rb], w2[cb], acc[rb][cb], 0, 0, 0);
       }
     } else {
-      prefetch(max(t - 1, 0));
+      if (epi) prefetch(max(t - 1, 0));
     }
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[(((wave * 2 + rb) * 2 + cb) * 4 + v) * 64 + lane] = acc[rb][cb][v];
+        for (int v = 0; v < 4; ++v) red[(((wave * RB + rb) * 2 + cb) * 4 + v) * 64 + lane] = acc[rb][cb][v];
     __syncthreads();
-    float2 p[8];
+    if (epi) {
+      float2 p[8];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) p[w] = *reinterpret_cast<const float2*>(red + ro + w * 1024);
-    const float recx = ((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x));
-    const float recy = ((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y));
-    const float2 dh = make_float2((dcar.x + ab.x) + recx, (dcar.y + ab.y) + recy);
-    const float2 dn = make_float2(dh.x * (1.0f - z.x), dh.y * (1.0f - z.y));
-    const float2 dz = make_float2(dh.x * (hp.x - n.x), dh.y * (hp.y - n.y));
-    const float2 da_n = make_float2(dn.x * (1.0f - n.x * n.x), dn.y * (1.0f - n.y * n.y));
-    const float2 dq = make_float2(da_n.x * r.x, da_n.y * r.y);
-    const float2 da_r = make_float2(da_n.x * q.x * r.x * (1.0f - r.x), da_n.y * q.y * r.y * (1.0f - r.y));
-    const float2 da_z = make_float2(dz.x * z.x * (1.0f - z.x), dz.y * z.y * (1.0f - z.y));
-    if (row < B) {
-      const long o = ((long)t * B + row) * H3 + j;
-      const unsigned pr = pack_bf16(da_r.x, da_r.y), pz = pack_bf16(da_z.x, da_z.y);
-      const long ox3 = bwd_block(t, l2x) * xblk + xfrag(row, nch, tx, u0);  // gate q: chunk q H/32 + tx
-      st_dev_u32(dghg + ox3, pr, l2x);
-      st_dev_u32(dghg + ox3 + (long)(H / PC) * 512, pz, l2x);
-      st_dev_u32(dghg + ox3 + (long)(2 * H / PC) * 512, pack_bf16(dq.x, dq.y), l2x);
-      __bf16* ox = dgxb + g * s_dgb + o;
-      st_u32_nt(ox, pr);
-      st_u32_nt(ox + H, pz);
-      st_u32_nt(ox + 2 * H, pack_bf16(da_n.x, da_n.y));
-      bsum[0].x += da_r.x; bsum[0].y += da_r.y;
-      bsum[1].x += da_z.x; bsum[1].y += da_z.y;
-      bsum[2].x += da_n.x; bsum[2].y += da_n.y;
-      bsum[3].x += dq.x;   bsum[3].y += dq.y;
+      for (int w = 0; w < 8; ++w) p[w] = *reinterpret_cast<const float2*>(red + ro + w * RB * 512);
+      const float recx = ((p[0].x + p[1].x) + (p[2].x + p[3].x)) + ((p[4].x + p[5].x) + (p[6].x + p[7].x));
+      const float recy = ((p[0].y + p[1].y) + (p[2].y + p[3].y)) + ((p[4].y + p[5].y) + (p[6].y + p[7].y));
+      const float2 dh = make_float2((dcar.x + ab.x) + recx, (dcar.y + ab.y) + recy);
+      const float2 dn = make_float2(dh.x * (1.0f - z.x), dh.y * (1.0f - z.y));
+      const float2 dz = make_float2(dh.x * (hp.x - n.x), dh.y * (hp.y - n.y));
+      const float2 da_n = make_float2(dn.x * (1.0f - n.x * n.x), dn.y * (1.0f - n.y * n.y));
+      const float2 dq = make_float2(da_n.x * r.x, da_n.y * r.y);
+      const float2 da_r = make_float2(da_n.x * q.x * r.x * (1.0f - r.x), da_n.y * q.y * r.y * (1.0f - r.y));
+      const float2 da_z = make_float2(dz.x * z.x * (1.0f - z.x), dz.y * z.y * (1.0f - z.y));
+      if (row < B) {
+        const long o = ((long)t * B + row) * H3 + j;
+        const unsigned pr = pack_bf16(da_r.x, da_r.y), pz = pack_bf16(da_z.x, da_z.y);
+        const long ox3 = bwd_block(t, l2x) * xblk + xfrag(row, nch, tx, u0);  // gate q: chunk q H/32 + tx
+        st_dev_u32(dghg + ox3, pr, l2x);
+        st_dev_u32(dghg + ox3 + (long)(H / PC) * 512, pz, l2x);
+        st_dev_u32(dghg + ox3 + (long)(2 * H / PC) * 512, pack_bf16(dq.x, dq.y), l2x);
+        __bf16* ox = dgxb + g * s_dgb + o;
+        st_u32_nt(ox, pr);
+        st_u32_nt(ox + H, pz);
+        st_u32_nt(ox + 2 * H, pack_bf16(da_n.x, da_n.y));
+        bsum[0].x += da_r.x; bsum[0].y += da_r.y;
+        bsum[1].x += da_z.x; bsum[1].y += da_z.y;
+        bsum[2].x += da_n.x; bsum[2].y += da_n.y;
+        bsum[3].x += dq.x;   bsum[3].y += dq.y;
+      }
+      // the four distinct gate-gradient blocks, staged for the transposed copies
+      tt[(0 * QJ + u0) * TP + rl] = (__bf16)da_r.x;
+      tt[(0 * QJ + u0 + 1) * TP + rl] = (__bf16)da_r.y;
+      tt[(1 * QJ + u0) * TP + rl] = (__bf16)da_z.x;
+      tt[(1 * QJ + u0 + 1) * TP + rl] = (__bf16)da_z.y;
+      tt[(2 * QJ + u0) * TP + rl] = (__bf16)da_n.x;
+      tt[(2 * QJ + u0 + 1) * TP + rl] = (__bf16)da_n.y;
+      tt[(3 * QJ + u0) * TP + rl] = (__bf16)dq.x;
+      tt[(3 * QJ + u0 + 1) * TP + rl] = (__bf16)dq.y;
+      dcar = make_float2(dh.x * z.x, dh.y * z.y);
     }
-    // the four distinct gate-gradient blocks, staged for the transposed copies
-    tt[(0 * QJ + u0) * TP + rl] = (__bf16)da_r.x;
-    tt[(0 * QJ + u0 + 1) * TP + rl] = (__bf16)da_r.y;
-    tt[(1 * QJ + u0) * TP + rl] = (__bf16)da_z.x;
-    tt[(1 * QJ + u0 + 1) * TP + rl] = (__bf16)da_z.y;
-    tt[(2 * QJ + u0) * TP + rl] = (__bf16)da_n.x;
-    tt[(2 * QJ + u0 + 1) * TP + rl] = (__bf16)da_n.y;
-    tt[(3 * QJ + u0) * TP + rl] = (__bf16)dq.x;
-    tt[(3 * QJ + u0 + 1) * TP + rl] = (__bf16)dq.y;
-    dcar = make_float2(dh.x * z.x, dh.y * z.y);
     group_signal(flags + tx, base + (unsigned)it + 1u, l2x);
-    // transposed copies [gate unit][t*B + row] as 64-byte row segments, 16 bytes per piece:
-    // dgx^T = (da_r, da_z, da_n), dgh^T = (da_r, da_z, dq).  512 pieces, by the waves 1 .. 7: wave
+    // transposed copies [gate unit][t*B + row] as 64- (or 32-) byte row segments, 16 bytes per piece:
+    // dgx^T = (da_r, da_z, da_n), dgh^T = (da_r, da_z, dq).  256 RB pieces, by the waves 1 .. 7: wave
     // 0 polls the flags next, and would see them only behind its own stores
-    for (int idx = tid - 64; idx >= 0 && idx < PNT; idx += PNT - 64) {
-      const int blk = idx >> 7, u = (idx >> 2) & 31, part = idx & 3;
+    for (int idx = tid - 64; idx >= 0 && idx < 256 * RB; idx += PNT - 64) {
+      const int blk = idx / (64 * RB), u = idx / (2 * RB) & 31, part = idx % (2 * RB);
       if (r0 + 8 * part < B) {  // B is a multiple of 8
         const uint4 v = *reinterpret_cast<const uint4*>(tt + (blk * QJ + u) * TP + 8 * part);
         const int gate = blk == 3 ? 2 : blk;
@@ -1335,16 +1347,18 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
       }
     }
   }
-  if (row < B) *reinterpret_cast<float2*>(Dg + (long)row * H + j) = dcar;
-  // bias gradients: sums over the tile's 32 batch rows, in row order
+  if (epi && row < B) *reinterpret_cast<float2*>(Dg + (long)row * H + j) = dcar;
+  // bias gradients: sums over the tile's batch rows, in row order
   __syncthreads();
-  float* bs = red;  // [32 rows][4 sums][32 units]
+  float* bs = red;  // [PRB rows][4 sums][32 units]
+  if (epi) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<float2*>(bs + (rl * 4 + i) * QJ + u0) = bsum[i];
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<float2*>(bs + (rl * 4 + i) * QJ + u0) = bsum[i];
+  }
   __syncthreads();
   if (tid < 128) {
     float tot = 0.f;
-    for (int r32 = 0; r32 < PR; ++r32) tot += bs[r32 * 128 + tid];
+    for (int r = 0; r < PRB; ++r) tot += bs[r * 128 + tid];
     const int i = tid >> 5, jj = j0 + (tid & 31);
     float* out = dbp + (long)(g * RT + ty) * 6 * Hc;  // (the model's own width)
     if (jj < Hc) {
@@ -1601,11 +1615,24 @@ bool gru_persist_bf16_supported(int B, int H) {
   return H % 32 == 0 && H >= 32 && H <= 1024 && B >= 8 && B % 8 == 0 && H / QJ <= device_cus();
 }
 
+// Batch rows per workgroup.  16 where all workers' workgroups then still fit one launch, and the XCDs, where they would with 32: a step's operands, its
+// products, the partial sums that meet in LDS and the cells of a workgroup are half as many.  (A step is a chain of these; the chip has room for
+// twice the workgroups.)  us per local step, 20 time steps, 2000 words, 32 rows / 16 (with no more chunk slots per wave than the width needs):
+//   (H, batch, workers)  (1024, 32, 4) 436 / 397   (1024, 16, 8) 485 / 456   (768, 32, 2) 345 / 297   (650, 20, 4) 379 / 331
+//                        (512, 64, 4) 365 / 340    (512, 16, 16) 413 / 394   (400, 24, 8) 332 / 305   (320, 8, 1) 221 / 199
+// The slots alone, 32 rows: (672, 24, 5) 377 / 361, (672, 40, 5) 478 / 466, (768, 64, 5) 553 / 542.
+int gru_persist_bf16_rows(int B, int H, int K) {
+  if (B <= 16) return 16;
+  const long NJ = (H + QJ - 1) / QJ, xcd = NJ <= kPlanCus / 8 ? 8 * (kPlanCus / 8 / NJ) : 0;  // groups that share an L2 each
+  const long n16 = (long)((B + 15) / 16) * K, n32 = (long)((B + 31) / 32) * K;
+  return n16 * NJ <= kPlanCus && (n16 <= xcd || n32 > xcd) ? 16 : 32;
+}
+
 // The gates of a model whose sizes are the launches' own and whose K workers fit one launch are the hardware's
 // (sigm_fast, tanh_fast); every other bf16 model has those of the fp32 launches, as the step kernels that it would
 // take without these launches.  (H, B: padded; padded: they are not the model's own.)
 bool gru_bf16_exact_gates(int B, int H, int K, bool padded) {
-  return padded || (long)(H / QJ) * ((B + PR - 1) / PR) * K > kPlanCus;
+  return padded || (long)(H / QJ) * ((B + 31) / 32) * K > kPlanCus;
 }
 
 unsigned gru_persist_bf16_count_per_step(int) { return 1u; }
@@ -1616,38 +1643,46 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
                                        const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
                                        float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
-                                       int groups, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
+                                       int groups, int rows, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
                                        bool device_scope, unsigned* ticket_launches, hipStream_t s) {
-  if (!gru_persist_bf16_supported(B, H) || Hc < 1 || Hc > H || Bc < 1 || Bc > B || T < 1) return hipErrorInvalidValue;
+  if (!gru_persist_bf16_supported(B, H) || (rows != 16 && rows != 32) || Hc < 1 || Hc > H || Bc < 1 || Bc > B || T < 1) return hipErrorInvalidValue;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (!hx || !a16(hx) || (s_hx & 7) != 0) return hipErrorInvalidValue;
   if (!a16(Wb) || !a16(hb) || !a16(hs) || !a16(gx) || !a16(sv) || (hT && !a16(hT)) || (s_wb & 7) != 0 ||
       (s_hb & 7) != 0 || (s_hs & 3) != 0 || (s_gx & 3) != 0 || (s_sv & 3) != 0 ||
       (hT && ((ld_hT & 7) != 0 || (s_hT & 7) != 0)))
     return hipErrorInvalidValue;
-  const size_t lds = (size_t)8 * 12 * 256 * sizeof(float) + (size_t)QJ * TP * 2 + 16;
-  const int ncf = H <= 256 ? 1 : H <= 512 ? 2 : 4;
+  const size_t lds = (size_t)8 * rows / 16 * 6 * 256 * sizeof(float) + (size_t)QJ * TP * 2 + 16;
+  const int ncf = (H + 255) / 256;  // (a wave loads and multiplies all of its slots: those beyond the contraction are in vain)
   KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_FWD_PB(N, EX)                                                                                        \
+#define HPSGD_FWD_PB(N, RB, EX)                                                                                    \
   do {                                                                                                             \
     static std::atomic<size_t> allowed{0};                                                                                     \
-    const hipError_t e = allow_lds((const void*)gru_fwd_persist_bf16_kernel<N, EX>, pl.lds, allowed);              \
+    const hipError_t e = allow_lds((const void*)gru_fwd_persist_bf16_kernel<N, RB, EX>, pl.lds, allowed);          \
     if (e != hipSuccess) return e;                                                                                 \
-    hipLaunchKernelGGL((gru_fwd_persist_bf16_kernel<N, EX>), dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, \
+    hipLaunchKernelGGL((gru_fwd_persist_bf16_kernel<N, RB, EX>), dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)Wb, s_wb, b_ih, \
                        b_hh, s_rep, Hc, gx, s_gx, hs, s_hs, (__bf16*)hb, s_hb, (__bf16*)hx, s_hx, sv, s_sv, (__bf16*)hT, ld_hT, \
                        s_hT, Bc, B, H, T, sg0, n_sg, sync, base, spin_limit, pl.tickets, pl.ticket_base, pl.per_xcd);  \
   } while (0)
-  const int NJ = H / QJ, SG = groups * ((B + PR - 1) / PR), per = groups_per_launch(NJ, SG);
+#define HPSGD_FWD_PBN(N)                             \
+  do {                                               \
+    if (rows == 16 && exact) HPSGD_FWD_PB(N, 1, true);  \
+    else if (rows == 16) HPSGD_FWD_PB(N, 1, false);     \
+    else if (exact) HPSGD_FWD_PB(N, 2, true);           \
+    else HPSGD_FWD_PB(N, 2, false);                     \
+  } while (0)
+  const int NJ = H / QJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
     const Placement pl = placement(sync, SG, n_sg, NJ, lds, device_scope, ticket_launches);
-    if (ncf == 1 && exact) HPSGD_FWD_PB(1, true);
-    else if (ncf == 1) HPSGD_FWD_PB(1, false);
-    else if (ncf == 2 && exact) HPSGD_FWD_PB(2, true);
-    else if (ncf == 2) HPSGD_FWD_PB(2, false);
-    else if (exact) HPSGD_FWD_PB(4, true);
-    else HPSGD_FWD_PB(4, false);
+    switch (ncf) {
+      case 1: HPSGD_FWD_PBN(1); break;
+      case 2: HPSGD_FWD_PBN(2); break;
+      case 3: HPSGD_FWD_PBN(3); break;
+      default: HPSGD_FWD_PBN(4); break;
+    }
   }
+#undef HPSGD_FWD_PBN
 #undef HPSGD_FWD_PB
   return hipGetLastError();
 }
@@ -1655,9 +1690,9 @@ hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b
 hipError_t launch_gru_bwd_persist_bf16(const void* WT, long s_wt, void* dghx, long s_dgh, long s_dgb, float* D, long s_D,
                                        bool d_zero, const float* above, long s_above, const float* sv, long s_sv, const float* hs,
                                        long s_hs, void* dgxb, void* dgxT, void* dghT, long ld_T, long s_T, float* dbp,
-                                       int Hc, int B, int H, int T, int groups, unsigned* sync, unsigned base,
+                                       int Hc, int B, int H, int T, int groups, int rows, unsigned* sync, unsigned base,
                                        unsigned spin_limit, bool device_scope, unsigned* ticket_launches, hipStream_t s) {
-  if (!gru_persist_bf16_supported(B, H) || Hc < 1 || Hc > H || T < 1 || !dbp || !dgxb || !dgxT || !dghT || !dghx)
+  if (!gru_persist_bf16_supported(B, H) || (rows != 16 && rows != 32) || Hc < 1 || Hc > H || T < 1 || !dbp || !dgxb || !dgxT || !dghT || !dghx)
     return hipErrorInvalidValue;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if ((s_dgh & 7) != 0) return hipErrorInvalidValue;
@@ -1665,32 +1700,42 @@ hipError_t launch_gru_bwd_persist_bf16(const void* WT, long s_wt, void* dghx, lo
       (above && !a16(above)) || (s_wt & 7) != 0 || (s_dgb & 7) != 0 || (ld_T & 7) != 0 || (s_T & 7) != 0 ||
       (s_D & 3) != 0 || (s_above & 3) != 0 || (s_sv & 3) != 0 || (s_hs & 3) != 0)
     return hipErrorInvalidValue;
-  const int ncf = H <= 256 ? 1 : H <= 512 ? 2 : 4;
-  const int ncl = 3 * ncf - 3 * ncf / 2;
-  const size_t lds = (size_t)8 * 4 * 256 * sizeof(float) + (size_t)4 * QJ * TP * 2 + (size_t)8 * ncl * 2 * 64 * 16 + 16;
-  static std::atomic<size_t> allowed[3];
-  const int slot = ncf == 1 ? 0 : ncf == 2 ? 1 : 2;
-  const void* fn = ncf == 1   ? (const void*)gru_bwd_persist_bf16_kernel<3>
-                   : ncf == 2 ? (const void*)gru_bwd_persist_bf16_kernel<6>
-                              : (const void*)gru_bwd_persist_bf16_kernel<12>;
-  {
-    const hipError_t e = allow_lds(fn, lds > kLdsAlone ? lds : kLdsAlone, allowed[slot]);
-    if (e != hipSuccess) return e;
-  }
+  const int need = (3 * H / PC + 7) / 8;  // chunks per wave
+  const int ncb = need <= 3 ? 3 : need <= 6 ? need : need <= 8 ? 8 : need <= 10 ? need : 12;
+  const size_t lds = (size_t)8 * rows / 16 * 2 * 256 * sizeof(float) + (size_t)4 * QJ * TP * 2 +
+                     (size_t)8 * persist_bwd_bf16_nl(ncb, rows / 16) * 2 * 64 * 16 + 16;
   KernelTimer kt(KID_GRU_BWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups, s);
-#define HPSGD_BWD_PB(N)                                                                                            \
-  hipLaunchKernelGGL(gru_bwd_persist_bf16_kernel<N>, dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)WT, s_wt,              \
-                     (__bf16*)dghx, s_dgh, s_dgb, D, s_D, d_zero ? 1 : 0, above, s_above, sv, s_sv, hs, s_hs, (__bf16*)dgxb, (__bf16*)dgxT, \
-                     (__bf16*)dghT, ld_T, s_T, dbp, Hc, B, H, T, sg0, n_sg, sync, base, spin_limit,                        \
-                     pl.tickets, pl.ticket_base, pl.per_xcd)
-  const int NJ = H / QJ, SG = groups * ((B + PR - 1) / PR), per = groups_per_launch(NJ, SG);
+#define HPSGD_BWD_PB(N, RB)                                                                                        \
+  do {                                                                                                             \
+    static std::atomic<size_t> allowed{0};                                                                         \
+    const hipError_t e = allow_lds((const void*)gru_bwd_persist_bf16_kernel<N, RB>, pl.lds, allowed);              \
+    if (e != hipSuccess) return e;                                                                                 \
+    hipLaunchKernelGGL((gru_bwd_persist_bf16_kernel<N, RB>), dim3(pl.grid), dim3(PNT), pl.lds, s, (const __bf16*)WT, s_wt,      \
+                       (__bf16*)dghx, s_dgh, s_dgb, D, s_D, d_zero ? 1 : 0, above, s_above, sv, s_sv, hs, s_hs, (__bf16*)dgxb,  \
+                       (__bf16*)dgxT, (__bf16*)dghT, ld_T, s_T, dbp, Hc, B, H, T, sg0, n_sg, sync, base, spin_limit,         \
+                       pl.tickets, pl.ticket_base, pl.per_xcd);                                                    \
+  } while (0)
+#define HPSGD_BWD_PBN(N)                 \
+  do {                                   \
+    if (rows == 16) HPSGD_BWD_PB(N, 1);  \
+    else HPSGD_BWD_PB(N, 2);             \
+  } while (0)
+  const int NJ = H / QJ, SG = groups * ((B + rows - 1) / rows), per = groups_per_launch(NJ, SG);
   for (int sg0 = 0; sg0 < SG; sg0 += per) {
     const int n_sg = SG - sg0 < per ? SG - sg0 : per;
     const Placement pl = placement(sync, SG, n_sg, NJ, lds, device_scope, ticket_launches);
-    if (ncf == 1) HPSGD_BWD_PB(3);
-    else if (ncf == 2) HPSGD_BWD_PB(6);
-    else HPSGD_BWD_PB(12);
+    switch (ncb) {
+      case 3: HPSGD_BWD_PBN(3); break;
+      case 4: HPSGD_BWD_PBN(4); break;
+      case 5: HPSGD_BWD_PBN(5); break;
+      case 6: HPSGD_BWD_PBN(6); break;
+      case 8: HPSGD_BWD_PBN(8); break;
+      case 9: HPSGD_BWD_PBN(9); break;
+      case 10: HPSGD_BWD_PBN(10); break;
+      default: HPSGD_BWD_PBN(12); break;
+    }
   }
+#undef HPSGD_BWD_PBN
 #undef HPSGD_BWD_PB
   return hipGetLastError();
 }

@@ -132,7 +132,7 @@ struct hpsgd_ctx {
   int Bp = 0, Hp = 0, Ep = 0, Vp = 0;
   bool use_padded() const { return padded && resident; }
   bool solo_b = false;          // the same for the bf16 padded layout
-  int prow = 0;
+  int prow = 0, prow_b = 32;    // batch rows per workgroup of the resident-weight launches, fp32 (0: not taken) and bf16
   bool solo = false;            // fp32 and narrow: a layer's recurrence needs no exchange (gru_solo.hip)
   // 0: the layout that the fastest forms need.  1: no padding, no split contractions, none of the forms whose
   // saved state is larger than the model's own sizes.  2: no resident-weight recurrence in fp32 either.
@@ -264,13 +264,14 @@ int build_layout(hpsgd_ctx* c) {
     c->prow = c->solo || d.prec == HPSGD_BF16_MFMA || c->lean == 2 || (c->lean && d.hidden % 16 != 0)
                   ? 0
                   : gru_persist_rows(d.batch, d.hidden, c->K);
+    c->prow_b = c->lean ? 32 : gru_persist_bf16_rows((int)Bi, (int)H, c->K);
     // (no step of a narrow model waits for another workgroup)
-    if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : 32));
+    if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : c->prow_b));
     if (dbp_solo) {  // (in the place of `gh`, which a step of such launches does not use)
       c->dbp.offset = c->gh.offset;
       c->dbp.stride = dbp_solo;
     } else if (c->prow) c->dbp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 6 * H);
-    else if (d.prec == HPSGD_BF16_MFMA && gru_fused_bf16_supported((int)H)) c->dbp = c->alloc_packed(((Bi + 31) / 32) * 6 * H);
+    else if (d.prec == HPSGD_BF16_MFMA && gru_fused_bf16_supported((int)H)) c->dbp = c->alloc_packed(((Bi + c->prow_b - 1) / c->prow_b) * 6 * H);
     if (c->prow && gru_persist_dw_supported((int)H)) c->dwp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 3 * H * H);
     if (d.prec != HPSGD_BF16_MFMA) {
       size_t most = 0;  // over the layers, which follow each other: the parts of dW_ih, then those of dW_hh
@@ -818,7 +819,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // narrow fp32 layers: the whole recurrence without any exchange between workgroups
     const bool use_solo = c->solo && c->resident;
     const bool use_persist = c->prow != 0 && c->resident && gru_persist_pays(B, H, T, groups, c->prow);
-    const int prow = use_persist ? c->prow : 32;  // rows of a synchronisation group
+    const int prow = use_persist ? c->prow : c->prow_b;  // rows of a synchronisation group
     // bf16: the same with the weight slices in registers; its backward launch writes only the bf16
     // copies of the gate gradients, so every GEMM that consumes them must be able to take those
     // (contraction-contiguous bf16 views: batch, hidden size and every layer width multiples of 8)
@@ -1026,7 +1027,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_fwd_persist_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx, hs, s_hs, hb, s_hb,
-                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, exact_gates,
+                                            bfreg(c->hx), 2 * (long)c->hx.stride, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, prow, exact_gates,
                                             psync, pbase, c->spin_limit, c->device_scope, &ticket_launches, s));
         pbase += (unsigned)T * gru_persist_bf16_count_per_step(H);
         ++c->last_resident;
@@ -1413,7 +1414,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_BWD;
         HIP_TRY(launch_gru_bwd_persist_bf16(wtb, s_wtb, bfreg(c->dghx), 2 * (long)c->dghx.stride, s_dgb, D, s_D, d_zero,
                                             above, s_dx, sv, s_sv, hs, s_hs, dgxb, bfreg(c->dgxT), bfreg(c->dghT), TBp, s_T, dbp, Hc, B,
-                                            H, T, groups, psync, pbase, c->spin_limit, c->device_scope, &ticket_launches, s));
+                                            H, T, groups, prow, psync, pbase, c->spin_limit, c->device_scope, &ticket_launches, s));
         pbase += (unsigned)T * gru_persist_bf16_count_per_step(H);
         if (l == 0) TRY0(resident.mark());
         else resident.note();

@@ -326,20 +326,22 @@ hipError_t launch_reduce_parts(const float* parts, int n_parts, size_t n, const 
 // beyond Bc the forward launch leaves zeros, whatever their input projections are.  b_ih is added by the forward launch.
 // More workgroups than the chip has CUs are issued as several launches of whole synchronisation groups.
 bool gru_persist_bf16_supported(int B, int H);
+// batch rows per workgroup (16 or 32: the launches' argument `rows`) of a layer of K workers
+int gru_persist_bf16_rows(int B, int H, int K);
 // whether the bf16 forward launches compute a model's gates as the fp32 ones do (their argument `exact`)
 bool gru_bf16_exact_gates(int B, int H, int K, bool padded);
 unsigned gru_persist_bf16_count_per_step(int H);
 hipError_t launch_gru_fwd_persist_bf16(const void* Wb, long s_wb, const float* b_ih, const float* b_hh, long s_rep, int Hc, const float* gx,
                                        long s_gx, float* hs, long s_hs, void* hb, long s_hb, void* hx, long s_hx,
                                        float* sv, long s_sv, void* hT, long ld_hT, long s_hT, int Bc, int B, int H, int T,
-                                       int groups, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
+                                       int groups, int rows, bool exact, unsigned* sync, unsigned base, unsigned spin_limit,
                                        bool device_scope, unsigned* ticket_launches, hipStream_t s);
 // bf16 elements of one time step's block of an exchange buffer whose rows are `width` wide
 size_t gru_persist_bf16_exchange_elems(int B, int width);
 hipError_t launch_gru_bwd_persist_bf16(const void* WT, long s_wt, void* dghx, long s_dgh, long s_dgb, float* D, long s_D,
                                        bool d_zero, const float* above, long s_above, const float* sv, long s_sv, const float* hs,
                                        long s_hs, void* dgxb, void* dgxT, void* dghT, long ld_T, long s_T, float* dbp, int Hc,
-                                       int B, int H, int T, int groups, unsigned* sync, unsigned base,
+                                       int B, int H, int T, int groups, int rows, unsigned* sync, unsigned base,
                                        unsigned spin_limit, bool device_scope, unsigned* ticket_launches, hipStream_t s);
 // NaN into loss[0..n_loss) and into rout[g * s_rout] for every group if *abort_w != 0
 hipError_t launch_poison_on_abort(const unsigned* abort_w, float* loss, int n_loss, float* rout, long s_rout,
