@@ -167,43 +167,49 @@ __device__ __forceinline__ void nt_epilogue(const GemmNtDesc& d, floatx16 (&acc)
   __syncthreads();
   const int c4 = (tid & 31) << 2, rbase = tid >> 5;
   const int col = n0 + c4;
-  if (col + 3 < d.N) {
-    float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (!COMMIT && bias) bv = make_float4(bias[col], bias[col + 1], bias[col + 2], bias[col + 3]);
-    float4 w[COMMIT ? 16 : 1];
-    if (COMMIT) {
-      const float* W = d.win + (long)g * d.strideWin;
+  if (col >= d.N) return;
+  // (the last one to three columns as single words.  Everything is loaded before anything is stored, here too: a wait behind a
+  // store is for the store, and one element after the other these columns were 20 us of a product of 38, 2016 x 650, Kd = 840, 4 workers)
+  const bool fast = col + 3 < d.N;
+  float bv[4], w[COMMIT ? 16 : 1][4];
 #pragma unroll
-      for (int p = 0; p < 16; ++p) {
-        const int row = GATED ? max(nt_row<GATED>(d, m0 + rbase + 8 * p), 0) : min(m0 + rbase + 8 * p, d.M - 1);  // clamped: not stored when outside
-        w[COMMIT ? p : 0] = nt_load4(W + (long)row * d.ldc + col);
-      }
-    }
+  for (int e = 0; e < 4; ++e) bv[e] = !COMMIT && bias ? bias[min(col + e, d.N - 1)] : 0.f;
+  if (COMMIT) {
+    const float* W = d.win + (long)g * d.strideWin;
 #pragma unroll
     for (int p = 0; p < 16; ++p) {
-      const int rl = rbase + 8 * p, row = nt_row<GATED>(d, m0 + rl);
-      if (row < 0) continue;
-      const float4 a = *reinterpret_cast<const float4*>(&sC[rl * CP + c4]);
-      float4 o;
-      if (COMMIT) {
-        const float4 wv = w[COMMIT ? p : 0];
-        o = make_float4(wv.x - d.lr * a.x, wv.y - d.lr * a.y, wv.z - d.lr * a.z, wv.w - d.lr * a.w);
+      const int row = GATED ? max(nt_row<GATED>(d, m0 + rbase + 8 * p), 0) : min(m0 + rbase + 8 * p, d.M - 1);  // clamped: not stored when outside
+      const float* wr = W + (long)row * d.ldc;
+      float* wp = w[COMMIT ? p : 0];
+      if (fast) {
+        const float4 v = nt_load4(wr + col);
+        wp[0] = v.x, wp[1] = v.y, wp[2] = v.z, wp[3] = v.w;
       } else {
-        o = make_float4(a.x + bv.x, a.y + bv.y, a.z + bv.z, a.w + bv.w);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) wp[e] = wr[min(col + e, d.N - 1)];
+        wp[3] = 0.f;
       }
-      nt_store4(C + (long)row * d.ldc + col, o);
     }
-  } else {
-    const float* W = COMMIT ? d.win + (long)g * d.strideWin : nullptr;
-    for (int p = 0; p < 16; ++p) {
-      const int rl = rbase + 8 * p, row = nt_row<GATED>(d, m0 + rl);
-      if (row < 0) continue;
-      for (int e = 0; e < 4; ++e) {
-        if (col + e >= d.N) break;
-        const long off = (long)row * d.ldc + col + e;
-        const float a = sC[rl * CP + c4 + e];
-        C[off] = COMMIT ? W[off] - d.lr * a : a + (bias ? bias[col + e] : 0.f);
-      }
+  }
+  if (!COMMIT) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(bv[e]));
+  }
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const int rl = rbase + 8 * p, row = nt_row<GATED>(d, m0 + rl);
+    if (row < 0) continue;
+    const float4 a = *reinterpret_cast<const float4*>(&sC[rl * CP + c4]);
+    const float* wv = w[COMMIT ? p : 0];
+    const float4 o = COMMIT ? make_float4(wv[0] - d.lr * a.x, wv[1] - d.lr * a.y, wv[2] - d.lr * a.z, wv[3] - d.lr * a.w)
+                            : make_float4(a.x + bv[0], a.y + bv[1], a.z + bv[2], a.w + bv[3]);
+    float* c = C + (long)row * d.ldc + col;
+    if (fast) {
+      nt_store4(c, o);
+    } else {
+      c[0] = o.x;
+      if (col + 1 < d.N) c[1] = o.y;
+      if (col + 2 < d.N) c[2] = o.z;
     }
   }
 }
@@ -727,12 +733,20 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
     // chunk's as well, in front of this chunk's stores, needs two chunks' worth of registers and
     // gained 2 us per round more: not kept)
     float4 w[COMMIT ? PASSES : 1];
-    if (COMMIT && fast) {
+    if (COMMIT) {
       const float* W = d.win + (long)g * d.strideWin;
+      auto old_row = [&](int p) {
+        return W + (long)(GATED ? max(nt_row<GATED>(d, mh + rbase + RPP * p), 0) : min(mh + rbase + RPP * p, d.M - 1)) * d.ldc;  // clamped: not stored when outside
+      };
+      if (fast) {
 #pragma unroll
-      for (int p = 0; p < PASSES; ++p) {
-        const int row = GATED ? max(nt_row<GATED>(d, mh + rbase + RPP * p), 0) : min(mh + rbase + RPP * p, d.M - 1);  // clamped: not stored when outside
-        w[COMMIT ? p : 0] = nt_load4(W + (long)row * d.ldc + col);
+        for (int p = 0; p < PASSES; ++p) w[COMMIT ? p : 0] = nt_load4(old_row(p) + col);
+      } else if (col < d.N) {  // the last one to three columns as single words, all requested at once as well
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+          const float* wr = old_row(p);
+          w[COMMIT ? p : 0] = make_float4(wr[col], wr[min(col + 1, d.N - 1)], wr[min(col + 2, d.N - 1)], 0.f);
+        }
       }
     }
     if (h > 0) __syncthreads();  // the previous chunk has been read
@@ -765,15 +779,21 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
         nt_store4(C + (long)row * d.ldc + col, o);
       }
     } else if (col < d.N) {
-      const float* W = COMMIT ? d.win + (long)g * d.strideWin : nullptr;
+      float bv[3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) bv[e] = !COMMIT && bias ? bias[min(col + e, d.N - 1)] : 0.f;
+#pragma unroll
+      for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(bv[e]));  // (a wait behind a store would be for the store)
+#pragma unroll
       for (int p = 0; p < PASSES; ++p) {
-        const int rl = rbase + RPP * p, row = nt_row<GATED>(d, mh + rl);
+        const int row = nt_row<GATED>(d, mh + rbase + RPP * p);
         if (row < 0) continue;
-        for (int e = 0; e < 4; ++e) {
-          if (col + e >= d.N) break;
-          const long off = (long)row * d.ldc + col + e;
-          const float a = sC[rl * CP + c4 + e];
-          C[off] = COMMIT ? W[off] - d.lr * a : a + (bias ? bias[col + e] : 0.f);
+        const float4 wv = w[COMMIT ? p : 0];
+        const float wp[3] = {wv.x, wv.y, wv.z};
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const float a = sC[(rbase + RPP * p) * CP + c4 + e];
+          if (col + e < d.N) C[(long)row * d.ldc + col + e] = COMMIT ? wp[e] - d.lr * a : a + bv[e];
         }
       }
     }

@@ -1154,8 +1154,8 @@ gru_fwd_persist_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const floa
     if (hT && wave >= 8 - RB) {
       // 64- (or 32-) byte row segments of the transposed copy, 16 bytes per thread (the last waves: the
       // first one polls the flags next, and would see them only behind its own stores)
-      const int u = (tid - (PNT - 64 * RB)) / (2 * RB), part = tid % (2 * RB);
-      if (r0 + 8 * part < B)  // B is a multiple of 8: a piece of 8 rows is all in or all out
+      const unsigned u = (unsigned)(tid - (PNT - 64 * RB)) / (2 * RB), part = (unsigned)tid % (2 * RB);
+      if (r0 + 8 * (int)part < B)  // B is a multiple of 8: a piece of 8 rows is all in or all out
         st16_nt(hT + g * s_hT + (long)(j0 + u) * ld_hT + (long)(t + 1) * B + r0 + 8 * part,
                 *reinterpret_cast<const uint4*>(tt + u * TP + 8 * part));
     }
@@ -1336,11 +1336,11 @@ gru_bwd_persist_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, __bf16* dg
     // transposed copies [gate unit][t*B + row] as 64- (or 32-) byte row segments, 16 bytes per piece:
     // dgx^T = (da_r, da_z, da_n), dgh^T = (da_r, da_z, dq).  256 RB pieces, by the waves 1 .. 7: wave
     // 0 polls the flags next, and would see them only behind its own stores
-    for (int idx = tid - 64; idx >= 0 && idx < 256 * RB; idx += PNT - 64) {
-      const int blk = idx / (64 * RB), u = idx / (2 * RB) & 31, part = idx % (2 * RB);
-      if (r0 + 8 * part < B) {  // B is a multiple of 8
+    for (unsigned idx = tid - 64; idx < 256u * RB; idx += PNT - 64) {  // (wave 0's wrap beyond the end)
+      const unsigned blk = idx / (64 * RB), u = idx / (2 * RB) & 31, part = idx % (2 * RB);
+      if (r0 + 8 * (int)part < B) {  // B is a multiple of 8
         const uint4 v = *reinterpret_cast<const uint4*>(tt + (blk * QJ + u) * TP + 8 * part);
-        const int gate = blk == 3 ? 2 : blk;
+        const unsigned gate = blk == 3 ? 2 : blk;
         const long o = g * s_T + (long)(gate * H + j0 + u) * ld_T + (long)t * B + r0 + 8 * part;
         if (blk != 3) st16_nt(dgxT + o, v);
         if (blk != 2) st16_nt(dghT + o, v);

@@ -75,6 +75,14 @@ def test_every_form_matches_float64_product(shape, commit):
     assert np.array_equal(results["auto"], results["128x128"])
 
 
+# the last one to three columns of a row by themselves, in a tile of their own and beside whole pieces; one to four k-tiles (two are in
+# flight), whole and not
+@pytest.mark.parametrize("commit", [False, True], ids=["plain", "sgd"])
+@pytest.mark.parametrize("N,Kd", [(1, 64), (2, 128), (3, 136), (129, 64), (130, 192), (131, 128), (257, 256), (650, 200), (254, 8)])
+def test_last_columns_and_few_k_tiles(N, Kd, commit):
+    test_every_form_matches_float64_product((2, 133, N, Kd), commit)
+
+
 def test_seeded_random_shapes_every_form():
     """40 seeded shapes with tails against every tile size; guard rows around C catch a store
     outside the matrix."""
