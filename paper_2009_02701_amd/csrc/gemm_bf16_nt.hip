@@ -431,29 +431,46 @@ __device__ __forceinline__ void dl_body(GemmNtDesc d, int g, int tile_m, int til
     const bf16x4n hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + Out::frag_step(ks, 1)));
     return nt_join(__builtin_bit_cast(u32x2n, lo), __builtin_bit_cast(u32x2n, hi));
   };
+  // Two tiles' loads are in flight: a wave has a tile's fragments in registers after half of its products, and the loads of the
+  // tile after the next go into the buffer it leaves.  With one in flight, requested in front of the products and waited for
+  // behind them, a k-tile took the time of its loads and that of its products.  us, before / now, 4 and 8 workers:
+  //   840 x 672 x 2016 (168 tiles)  39.3 / 34.8      1120 x 1024 x 10 000 (576)  419 / 376      400 x 10 000 x 224 (1280)  35.0 / 30.8
   const int nk = (d.Kd + NBK - 1) / NBK;
   issue(0, 0);
+  if (nk > 1) issue(1, 1);
   for (int kt = 0; kt < nk; ++kt) {
-    // The tile's loads are the only ones in flight.  A bare barrier: with __syncthreads the
-    // compiler would add its own wait for every LDS-bound load, also the next tile's.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // tile kt is in LDS; everyone is done reading tile kt-1
-    if (kt + 1 < nk) issue((kt + 1) & 1, kt + 1);
+    // Bare barriers: with __syncthreads the compiler would add its own wait for every LDS-bound load, also the next tile's.
+    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // (all but the next tile's)
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // tile kt is in LDS
     const unsigned char* sb = nt_smem + (kt & 1) * 32768;
+    bf16x8 a[4][2], b[4][2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      bf16x8 a[2], b[2];
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        a[i] = AO ? outer_fragment(sb + ra[i], ks) : *reinterpret_cast<const bf16x8*>(sb + ra[i] + (((2 * ks + lk) ^ swa[i]) << 4));
-        b[i] = BO ? outer_fragment(sb + rb[i], ks) : *reinterpret_cast<const bf16x8*>(sb + rb[i] + (((2 * ks + lk) ^ swb[i]) << 4));
+        a[ks][i] = AO ? outer_fragment(sb + ra[i], ks) : *reinterpret_cast<const bf16x8*>(sb + ra[i] + (((2 * ks + lk) ^ swa[i]) << 4));
+        b[ks][i] = BO ? outer_fragment(sb + rb[i], ks) : *reinterpret_cast<const bf16x8*>(sb + rb[i] + (((2 * ks + lk) ^ swb[i]) << 4));
       }
+    __builtin_amdgcn_sched_barrier(0);
+    auto products = [&](int k0) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int ks = k0; ks < k0 + 2; ++ks)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+    };
+    products(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (kt + 2 < nk) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();  // everyone has read tile kt
+      issue(kt & 1, kt + 2);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    products(2);
   }
   __syncthreads();  // the operand buffers become the epilogue tile
   nt_epilogue<COMMIT, GATED>(d, acc, nt_smem, g, m0, n0);
