@@ -140,9 +140,10 @@ int hpsgd_local_step_all_cloned(hpsgd_ctx *ctx, const float *source, float *repl
  * (every GPU the library runs on holds one copy until the process ends); its address on the
  * current device is looked up on the first call there.  The call allocates nothing, and computes
  * exactly what hpsgd_local_step_all computes (same kernels, same bits) if hpsgd_workspace_bytes(ctx)
- * is at most HPSGD_STATIC_WORKSPACE_BYTES.  A model beyond that whose workspace without padding,
- * without cut contractions and without the forms that keep more state does fit steps in that smaller
- * layout: the same result in another order of summation, more slowly.
+ * is at most HPSGD_STATIC_WORKSPACE_BYTES.  A model beyond that steps in the first smaller layout that does fit - two narrow
+ * layers one after the other instead of together; without padding,
+ * without cut contractions and without the forms that keep more state: the same result in another order of
+ * summation, more slowly.
  * HPSGD_EWORKSPACE if the smaller layout exceeds the array too (checked first, before any device is
  * touched); otherwise errors as for hpsgd_local_step_all.
  * All calls on one GPU share that GPU's array, whatever their context: two calls that may run
@@ -224,7 +225,11 @@ int hpsgd_set_aux_stream(hpsgd_ctx *ctx, void *hip_stream);
  * Launches of this kind need the whole chip and must not run side by side.  The library orders
  * them itself, across streams, contexts and host threads: a local step holds a per-device lock
  * while it issues them, and when the previous ones went to another stream it lets its stream
- * wait (hipStreamWaitEvent, the host does not block) for the event recorded behind them. */
+ * wait (hipStreamWaitEvent, the host does not block) for the event recorded behind them.
+ * A narrow layer (fp32 up to 128 units) exchanges nothing, and its launches may run beside anything; two such layers
+ * share a launch per direction where the chip has room for both, whose workgroups wait for those of the
+ * layer before.  Those waits never depend on what else runs; they are bounded too, and one that is given up leaves NaN in loss_out and in
+ * every parameter of the workers that it reaches. */
 int hpsgd_set_recurrence(hpsgd_ctx *ctx, int resident, unsigned spin_limit);
 
 /* *gave_up = 1 if a wait of the last local step(s) that used `workspace` was given up, else 0.

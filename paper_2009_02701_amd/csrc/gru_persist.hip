@@ -207,28 +207,6 @@ __device__ __forceinline__ void st_dev(float* p, float v, bool l2x) {
   else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A fragment of eight fp32 values per lane as three bf16 ones (split_f32.h)
-struct SplitFrag { bf16x8s p[3]; };
-__device__ __forceinline__ SplitFrag split_frag(const float4& lo, const float4& hi) {
-  uint4 p0, p1, p2;
-  split8({lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, p0, p1, p2);
-  return {{__builtin_bit_cast(bf16x8s, p0), __builtin_bit_cast(bf16x8s, p1), __builtin_bit_cast(bf16x8s, p2)}};
-}
-// big[q] += a0 w0, small[q] += the other five products, for NQ blocks of 16 columns (consecutive instructions
-// update different accumulators)
-template <int NQ>
-__device__ __forceinline__ void split_mfmas(const SplitFrag& a, const SplitFrag (&w)[NQ], floatx4 (&big)[NQ], floatx4 (&small)[NQ]) {
-  auto mul = [&](int pa, int pw, floatx4 (&to)[NQ]) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) to[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[pa], w[q].p[pw], to[q], 0, 0, 0);
-  };
-  mul(0, 0, big);
-  mul(1, 0, small);
-  mul(2, 0, small);
-  mul(0, 1, small);
-  mul(1, 1, small);
-  mul(0, 2, small);
-}
 // not finite, or rounded to an infinity by the split
 __device__ __forceinline__ bool split_beyond(float v) { return !(fabsf(v) < 3.38e38f); }
 __device__ __forceinline__ bool split_beyond(const float4& v) {
@@ -281,31 +259,6 @@ __device__ __forceinline__ void exchange_frag(__amdgpu_buffer_rsrc_t rs, int nch
   const int off = (int)(threadIdx.x & 63) * 16, from = (rbx * nch + c) * 2048;
   a[0] = ld16_dev(rs, off, from);
   a[1] = PC * c + 16 < KD ? ld16_dev(rs, off, from + 1024) : make_float4(0.f, 0.f, 0.f, 0.f);  // (uniform)
-}
-
-// A copy of a value that the compiler computes with only here: what a rare path derives from it is not hoisted out of the time loop,
-// where it would hold registers
-template <typename V>
-__device__ __forceinline__ V rarely(V v) {
-  asm volatile("" : "+s"(v));
-  return v;
-}
-
-// acc += the products of one fragment's fp32 values with the fp32 instruction (W: the fragment of 16 columns): where the split
-// gives no number
-__device__ __forceinline__ void plain_mfmas(const float4 (&a)[2], const float4 (&w)[2], bool second, floatx4& acc) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (h == 1 && !second) continue;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].x, w[h].x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].y, w[h].y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].z, w[h].z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].w, w[h].w, acc, 0, 0, 0);
-  }
-}
-__device__ __forceinline__ bool any_beyond(const floatx4& v) {
-  const float s = __builtin_fmaf(v[0], 0.f, __builtin_fmaf(v[1], 0.f, __builtin_fmaf(v[2], 0.f, v[3] * 0.f)));
-  return __any(!(s == 0.f)) != 0;
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const float* base) {

@@ -32,10 +32,9 @@
 
 #include "cell_math.h"
 #include "kernels.h"
+#include "split_f32.h"
 
 namespace hpsgd {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -80,11 +79,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const float* base, lon
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(bytes < 0x7fffffe0L ? bytes : 0x7fffffe0L),
                                            0x00020000);
 }
+// (DEV: at device scope, for what another workgroup of the launch writes or reads)
+template <bool DEV = false>
 __device__ __forceinline__ float ld_b32(__amdgpu_buffer_rsrc_t rs, unsigned off, int soff = 0) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, soff, 0));
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, soff, DEV ? 16 : 0));
 }
+template <bool DEV = false>
 __device__ __forceinline__ void st_b32(__amdgpu_buffer_rsrc_t rs, unsigned off, float v, int soff = 0) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, (int)off, soff, 0);
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, (int)off, soff, DEV ? 16 : 0);
 }
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x2s __attribute__((ext_vector_type(2)));
@@ -99,16 +101,53 @@ __device__ __forceinline__ void st_b128(__amdgpu_buffer_rsrc_t rs, unsigned off,
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4s, v), rs, (int)off, 0, 0);
 }
 
-}  // namespace
+// Two layers in one launch (gru_stack_*_kernel, below): the workgroups that pass a tile's values on.
+constexpr int kChunk = 4;  // steps that are passed on together
+// out: this workgroup's words, one per wave, which its waves set to the number of steps they have written (nullptr: nobody waits
+// for it); in: the words of the workgroups that it waits for, those of even chunks, then those of odd ones.
+struct SoloLink {
+  unsigned *out, *in, *abort_w;
+  unsigned limit;
+  int n_in;
+};
+// A wave waits until the `n` words at w have reached `target`.  false: given up (limit polls, or another workgroup has given up);
+// the abort word is then set.  limit == 0: every wait is.
+// (NAP: 64 cycles each between two looks; looks of hundreds of waves are traffic that the values have to get through)
+template <int NAP>
+__device__ __forceinline__ bool link_wait(unsigned* w, int n, unsigned target, unsigned* abort_w, unsigned limit) {
+  const int l = threadIdx.x & 63;
+  bool ok = limit != 0;
+  for (unsigned i = 0; ok; ++i) {
+    const unsigned v = __hip_atomic_load(w + (l < n ? l : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__all(v >= target)) break;
+    if (i >= limit || (i % 16 == 15 && __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) ok = false;
+    else __builtin_amdgcn_s_sleep(NAP);
+  }
+  if (!ok && l == 0) __hip_atomic_store(abort_w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::: "memory");  // (what is waited for is loaded behind the wait)
+  return ok;
+}
+// This wave's stores so far, all at device scope, are where the others see them (vmcnt(0): a write-through store is counted out
+// when the level that all XCDs share has acknowledged it); then its word.
+__device__ __forceinline__ void link_publish(unsigned* w, unsigned steps) {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  asm volatile("" ::: "memory");
+  if ((threadIdx.x & 63) == 0) __hip_atomic_store(w, steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the chunk of step index `it` (its first) is there
+__device__ __forceinline__ bool link_chunk(const SoloLink& k, int it, int T) {
+  const int c = it / kChunk;
+  return link_wait<2>(k.in + (c & 1) * 8, k.n_in, (unsigned)min(it + kChunk, T), k.abort_w, k.limit);
+}
 
-// grid: groups * ceil(RT / R) workgroups; RT = ceil(B / 4) tiles of 4 rows, R of them per workgroup.
 // gx: input projections, b_ih included.  hs: h_0 .. h_T ((T+1) blocks of B x H; h_0 = 0 is written here).
 // sv: (r, z, n, q) of one output as one 16-byte word, [step][tile][row][unit].
-template <int H8, int R>
-__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
-gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
-                    const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs, float* __restrict__ sv,
-                    long s_sv, int B, int H, int T, int RT) {
+// R tiles of 4 rows, from tile ty of worker g.  LINKED: in a launch of two layers; k.in: gx is written by this launch.
+template <int H8, int R, bool LINKED>
+__device__ __forceinline__ void solo_fwd_body(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
+                                              const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs,
+                                              float* __restrict__ sv, long s_sv, int B, int H, int T, int RT, int g, int ty,
+                                              const SoloLink& k) {
   using S = Solo<H8>;
   constexpr int KW = S::KF, CB = S::CF, NC = (KW + 15) / 16;
   __shared__ float hl[R * 4 * S::LF];
@@ -116,7 +155,6 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
   // (the wave's number in a scalar register: buffer descriptors derived from it stay scalar)
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = w & 3, cg = w >> 2;  // part of the contraction, column group
-  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
   // column c = q * H + unit of the products is row c of W_hh
   float wt[CB][KW];
   {
@@ -174,9 +212,14 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) I.x[r][q] = ld_b32(rs, ox[r], q * H * 4);
+      for (int q = 0; q < 3; ++q) I.x[r][q] = ld_b32<LINKED>(rs, ox[r], q * H * 4);
+  };
+  // (a wait that was given up: every output from there on is NaN)
+  auto wait_gx = [&](int it) {
+    if (LINKED && k.in && it < T && it % kChunk == 0 && !link_chunk(k, it, T)) bias[0] = bias[1] = bias[2] = __builtin_nanf("");
   };
   In ia, ib;
+  wait_gx(0);
   load_gx(0, ia);
   load_gx(1, ib);
   wait_loads();
@@ -212,6 +255,7 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
     if (cg == 0) products(std::integral_constant<int, CB>{});
     else products(std::integral_constant<int, S::NF - CB>{});
     __syncthreads();
+    if (LINKED && k.out && t > 0 && t % kChunk == 0) link_publish(k.out + w, t);  // (the stores of step t - 1 are a while ago)
     const __amdgpu_buffer_rsrc_t ro = rsrc_of(hsg + (long)(t + 1) * BH, BH), rv = rsrc_of(svg + (long)t * sv_step, R * 16L * H);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -224,9 +268,10 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
       const float rr = sigm_f32(I.x[r][0] + y[0]), zz = sigm_f32(I.x[r][1] + y[1]), nn = tanh_f32(I.x[r][2] + rr * y[2]);
       hp[r] = (1.0f - zz) * nn + zz * hp[r];
       hl[(4 * r + m) * S::LF + j] = act ? hp[r] : 0.f;
-      st_b32(ro, oh[r], hp[r]);
+      st_b32<LINKED>(ro, oh[r], hp[r]);
       st_b128(rv, ov[r], (floatx4){rr, zz, nn, y[2]});
     }
+    wait_gx(t + 2);
     load_gx(t + 2, I);
     __syncthreads();
   };
@@ -236,24 +281,25 @@ gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_
     step(t + 1, ib);
   }
   if (t < T) step(t, ia);
+  if (LINKED && k.out) link_publish(k.out + w, T);
 }
 
 // BPTT of all steps.  dgx / dgh: gate gradients (blocks of B x 3H).  D: the gradient carried into the
 // last step (nullptr: zero); above: per-step gradient from the layer above (blocks of B x H) or
 // nullptr.  dbp[(g * RT + tile)][6H]: partial sums of the bias gradients (b_ih: r z n, b_hh: r z q).
-template <int H8, int R>
-__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
-gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx, float* __restrict__ dgh, long s_dg,
-                    const float* __restrict__ D, long s_D, const float* __restrict__ above, long s_above,
-                    const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
-                    int B, int H, int T, int RT) {
+// (LINKED: k.in: `above` is written by this launch; a wait that was given up leaves NaN in loss[g] too.)
+template <int H8, int R, bool LINKED>
+__device__ __forceinline__ void solo_bwd_body(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx,
+                                              float* __restrict__ dgh, long s_dg, const float* __restrict__ D, long s_D,
+                                              const float* __restrict__ above, long s_above, const float* __restrict__ sv,
+                                              long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
+                                              int B, int H, int T, int RT, int g, int ty, const SoloLink& k, float* loss) {
   using S = Solo<H8>;
   constexpr int KW = S::KB, NC = (KW + 15) / 16;
   __shared__ float dl[R * 4 * S::LB];
   __shared__ float part[R * 16 * S::PB];  // [tile][part][row][unit]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = w & 3, cg = w >> 2;
-  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
   // the contraction runs over the rows of W_hh, q * H + unit; column j is its column j
   float wt[KW];
   {
@@ -295,10 +341,18 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
     for (int r = 0; r < R; ++r) {
       I.s[r] = ld_b128(rv, ov[r]);
       I.hp[r] = ld_b32(rh, oh[r]);
-      I.ab[r] = ld_b32(ra, oh[r]);
+      I.ab[r] = ld_b32<LINKED>(ra, oh[r]);
+    }
+  };
+  auto wait_above = [&](int t) {
+    if (LINKED && k.in && t >= 0 && (T - 1 - t) % kChunk == 0 && !link_chunk(k, T - 1 - t, T)) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) dc[r] = __builtin_nanf("");
+      if (tid == 0 && loss) loss[g] = __builtin_nanf("");
     }
   };
   In ia, ib;
+  wait_above(T - 1);
   load_in(T - 1, ia);
   load_in(T - 2, ib);
   for (int i = tid; i < R * 4 * S::LB; i += S::NT) dl[i] = 0.f;
@@ -326,6 +380,7 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
 #pragma unroll
       for (int v = 0; v < 4; ++v) part[((4 * r + s) * 4 + v) * S::PB + cg * 64 + lane] = acc[r][0][v] + acc[r][1][v];
     __syncthreads();
+    if (LINKED && k.out && t < T - 1 && (T - 1 - t) % kChunk == 0) link_publish(k.out + w, T - 1 - t);
     const __amdgpu_buffer_rsrc_t rx = rsrc_of(dgx + g * s_dg + (long)t * 3 * BH, 3 * BH),
                                  rh = rsrc_of(dgh + g * s_dg + (long)t * 3 * BH, 3 * BH);
 #pragma unroll
@@ -349,13 +404,14 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
       bs[r][1] += da_z;
       bs[r][2] += da_n;
       bs[r][3] += dq;
-      st_b32(rx, ox[r], da_r);
-      st_b32(rx, ox[r], da_z, H * 4);
-      st_b32(rx, ox[r], da_n, H * 8);
+      st_b32<LINKED>(rx, ox[r], da_r);
+      st_b32<LINKED>(rx, ox[r], da_z, H * 4);
+      st_b32<LINKED>(rx, ox[r], da_n, H * 8);
       st_b32(rh, ox[r], da_r);
       st_b32(rh, ox[r], da_z, H * 4);
       st_b32(rh, ox[r], dq, H * 8);
     }
+    wait_above(t - 2);
     load_in(t - 2, I);
     __syncthreads();
   };
@@ -365,6 +421,7 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
     step(t - 1, ib);
   }
   if (t >= 0) step(t, ia);
+  if (LINKED && k.out) link_publish(k.out + w, T);
   // bias gradients: a tile's sums over its four rows are its own, whatever R is
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -385,6 +442,227 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
     out[H + j] = out[4 * H + j] = bs[r][1];
     out[2 * H + j] = bs[r][2];
     out[5 * H + j] = bs[r][3];
+  }
+}
+
+}  // namespace
+
+// grid: groups * ceil(RT / R) workgroups; RT = ceil(B / 4) tiles of 4 rows, R of them per workgroup.
+template <int H8, int R>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo_fwd_kernel(const float* __restrict__ W_hh, const float* __restrict__ b_hh, long s_rep,
+                    const float* __restrict__ gx, long s_gx, float* __restrict__ hs, long s_hs, float* __restrict__ sv,
+                    long s_sv, int B, int H, int T, int RT) {
+  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
+  solo_fwd_body<H8, R, false>(W_hh, b_hh, s_rep, gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, RT, g, ty, SoloLink{});
+}
+template <int H8, int R>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx, float* __restrict__ dgh, long s_dg,
+                    const float* __restrict__ D, long s_D, const float* __restrict__ above, long s_above,
+                    const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
+                    int B, int H, int T, int RT) {
+  const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
+  solo_bwd_body<H8, R, false>(W_hh, s_rep, dgx, dgh, s_dg, D, s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT, g, ty,
+                              SoloLink{}, nullptr);
+}
+
+// ---------------------------------------------------------------------------- two layers in one launch
+// Two layers one after the other are twice the chain of steps, on as few workgroups as a batch has tiles: 20 of 256 CUs at
+// batch 20 and 4 workers.  But a layer's step t needs no more of the layer below than its step t (backward: of the one above), for
+// the same rows.  So one launch has a workgroup per tile of 4 rows and layer, and between them two that multiply
+// what the first passes on - the steps' h with the upper layer's W_ih, backward its gate gradients with W_ih^T - four steps at a time, the
+// even chunks and the odd ones: the upper layer runs about ten steps behind, and the product that stood between
+// the layers' launches goes too.  What is passed on goes through memory at device scope; a wave counts the steps that it has written in
+// a word of its own (link_publish), once every four, half a step after the last one's stores; the reader polls the
+// words of all of a workgroup's waves.
+// A workgroup takes its part by ticket, in the order in which workgroups start, and waits only for those of lower tickets, which
+// run or have run: whatever else is on the chip, nothing waits for a place.  Every wait is bounded all the same: a given-up one
+// sets the abort word and makes NaN of everything behind it.
+namespace {
+
+// Extents of the product between the layers: W_ih split into bf16 parts in registers, NB blocks of 16 columns per wave, KC chunks of 32.
+template <int H8, bool BWD>
+struct LinkShape {
+  static constexpr int W = Solo<H8>::NT / 64;
+  static constexpr int NB = ((BWD ? 8 * H8 : 24 * H8) / 16 + ((BWD ? 8 * H8 : 24 * H8) % 16 ? 1 : 0) + W - 1) / W;
+  static constexpr int KC = ((BWD ? 24 * H8 : 8 * H8) + 31) / 32;
+};
+
+// The chunks c = odd, odd + 2, .. of a tile.  Forward: out[t] = in[t] W^T + bias, backward out[t] = in[t] W, over t from the end.
+// W: 3H x H, row-major.  in: blocks of B x KD, out: blocks of B x ND.  Row m = 4 s + r of a product is row r of the tile at the chunk's step s.
+template <int H8, bool BWD>
+__device__ __forceinline__ void link_body(const float* __restrict__ W, const float* __restrict__ bias, const float* in, float* out, int B,
+                                          int H, int T, int ty, int odd, unsigned* in_words, unsigned* out_words, unsigned* abort_w,
+                                          unsigned limit) {
+  using L = LinkShape<H8, BWD>;
+  constexpr int NB = L::NB, KC = L::KC;
+  __shared__ u32x4s al[KC * 3 * 64];  // the chunk's operands, split: [chunk of 32][part][lane]
+  __shared__ int go;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lg = lane >> 4;
+  const int KD = BWD ? 3 * H : H, ND = BWD ? H : 3 * H;
+  // (a piece of four at the end of `in` may reach three words beyond it)
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(W, 3L * H * H), ri = rsrc_of(in, (long)T * B * KD + 3), ro = rsrc_of(out, (long)T * B * ND);
+  auto col = [&](int b) { return (w * NB + b) * 16 + lr; };
+  auto w_frag = [&](int b, int c, int H, float4 (&v)[2]) {
+    const int n = col(b);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float e[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 32 * c + 16 * h + 4 * lg + i;
+        e[i] = ld_b32(rw, n < (BWD ? H : 3 * H) && k < (BWD ? 3 * H : H) ? (unsigned)(BWD ? k * H + n : n * H + k) * 4u : kOut);
+      }
+      v[h] = make_float4(e[0], e[1], e[2], e[3]);
+    }
+  };
+  SplitFrag wf[KC][NB];
+#pragma unroll
+  for (int c = 0; c < KC; ++c)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float4 v[2];
+      w_frag(b, c, H, v);
+      wf[c][b] = split_frag(v[0], v[1]);
+      __builtin_amdgcn_sched_barrier(0);  // (or the pieces of all chunks take registers at once)
+    }
+  float bv[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) bv[b] = !BWD && col(b) < 3 * H ? bias[col(b)] : 0.f;
+  bool ok = true;
+  for (int i0 = odd * kChunk; i0 < T; i0 += 2 * kChunk) {
+    if (w == 0) {
+      ok = ok && link_wait<8>(in_words, L::W, (unsigned)min(i0 + kChunk, T), abort_w, limit);
+      if (lane == 0) go = ok;
+    }
+    __syncthreads();  // (and everyone has read the operands of the chunk before)
+    ok = go != 0;
+    // this lane's operand row, and its first output row
+    const int ia = i0 + (lr >> 2), ra = 4 * ty + (lr & 3), io = i0 + lg;
+    const unsigned off_a = ia < T && ra < B ? (unsigned)(((BWD ? T - 1 - ia : ia) * B + ra) * KD) * 4u : kOut;
+    auto a_frag = [&](int c, int KD, float4 (&v)[2]) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 32 * c + 16 * h + 4 * lg;
+        v[h] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(ri, (int)(off_a != kOut && k < KD ? off_a + 4u * k : kOut), 0, 16));
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {  // (the next row's values)
+        const int k = 32 * c + 16 * h + 4 * lg;
+        v[h].y = k + 1 < KD ? v[h].y : 0.f;
+        v[h].z = k + 2 < KD ? v[h].z : 0.f;
+        v[h].w = k + 3 < KD ? v[h].w : 0.f;
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < (KC + L::W - 1) / L::W; ++i) {
+      const int c = w + i * L::W;
+      if (c < KC) {  // (uniform)
+        float4 v[2];
+        a_frag(c, KD, v);
+        const SplitFrag f = split_frag(v[0], v[1]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) al[(c * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4s, f.p[p]);
+      }
+    }
+    __syncthreads();
+    floatx4 big[NB], small[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) big[b] = small[b] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      SplitFrag f;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) f.p[p] = __builtin_bit_cast(bf16x8s, al[(c * 3 + p) * 64 + lane]);
+      split_mfmas(f, wf[c], big, small);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      big[b] += small[b];
+      if (__builtin_expect(any_beyond(big[b]), 0)) {  // again with the fp32 instruction
+        const int Hr = rarely(H);
+        big[b] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int c = 0; c < KC; ++c) {
+          float4 v[2], x[2];
+          a_frag(c, BWD ? 3 * Hr : Hr, x);
+          w_frag(b, c, Hr, v);
+          plain_mfmas(x, v, true, big[b]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = 4 * ty + v, n = col(b);
+        st_b32<true>(ro, io < T && row < B && n < ND ? (unsigned)(((BWD ? T - 1 - io : io) * B + row) * ND + n) * 4u : kOut,
+                     ok ? big[b][v] + bv[b] : __builtin_nanf(""));
+      }
+    }
+    link_publish(out_words + w, (unsigned)min(i0 + kChunk, T));
+  }
+}
+
+// A tile's words: its lower workgroup's waves' (8), then those of the two that multiply (8 each); the backward launch's in the second half
+// of its 64.  (Word 32, which may be the first of a worker's slice, is nobody's.)
+constexpr int kLinkWords = 64, kLinkBase = 32 * 9;
+// A workgroup's part: ticket i of class blockIdx.x % 8 (often an XCD) is role i / m of the class's tile i % m, m = ceil(n / 8), n = groups * RT:
+// the layer that goes first, the products of even and of odd chunks, the other layer.  (One counter for all: its 500 additions one after the other
+// were 13 us.)  which: 0 forward, 1 backward.  false: the class has one tile less.
+__device__ __forceinline__ bool link_part(unsigned* sync, int which, int n, int& role, int& tile) {
+  __shared__ int mine;
+  const int cls = blockIdx.x & 7, m = (n + 7) / 8;
+  if (threadIdx.x == 0)
+    mine = (int)__hip_atomic_fetch_add(sync + 32 * (1 + cls) + 8 + which, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane(mine);
+  role = ticket / m;
+  tile = cls + 8 * (ticket - role * m);
+  return tile < n;
+}
+
+}  // namespace
+
+// grid: 32 ceil(n / 8).  sync: the abort word; the counters of tickets, in lines of their own; the tiles' words from kLinkBase on.
+template <int H8>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_stack_fwd_kernel(GruStackLayer lo, GruStackLayer up, const float* W_ih, const float* b_ih, long s_rep, long s_gx, long s_hs,
+                     long s_sv, int B, int H, int T, int RT, int n, unsigned* sync, unsigned limit) {
+  constexpr int W = Solo<H8>::NT / 64;
+  int role, tile;
+  if (!link_part(sync, 0, n, role, tile)) return;
+  const int g = tile / RT, ty = tile - g * RT;
+  unsigned* words = sync + kLinkBase + (long)tile * kLinkWords;
+  if (role == 0) {
+    solo_fwd_body<H8, 1, true>(lo.W_hh, lo.b_hh, s_rep, lo.gx, s_gx, lo.hs, s_hs, lo.sv, s_sv, B, H, T, RT, g, ty,
+                               SoloLink{words, nullptr, sync, limit, 0});
+  } else if (role < 3) {
+    link_body<H8, false>(W_ih + g * s_rep, b_ih + g * s_rep, lo.hs + g * s_hs + (long)B * H, up.gx + g * s_gx, B, H, T, ty, role - 1,
+                         words, words + 8 * role, sync, limit);
+  } else {
+    solo_fwd_body<H8, 1, true>(up.W_hh, up.b_hh, s_rep, up.gx, s_gx, up.hs, s_hs, up.sv, s_sv, B, H, T, RT, g, ty,
+                               SoloLink{nullptr, words + 8, sync, limit, W});
+  }
+}
+
+// D, above: of the upper layer; dx: the gradient that it passes on (T blocks of B x H)
+template <int H8>
+__global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_stack_bwd_kernel(GruStackLayer lo, GruStackLayer up, const float* W_ih, long s_rep, const float* D, long s_D, const float* above,
+                     long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv, int B, int H, int T, int RT, int n,
+                     unsigned* sync, unsigned limit) {
+  constexpr int W = Solo<H8>::NT / 64;
+  int role, tile;
+  if (!link_part(sync, 1, n, role, tile)) return;
+  const int g = tile / RT, ty = tile - g * RT;
+  unsigned* words = sync + kLinkBase + (long)tile * kLinkWords + 36;
+  if (role == 0) {
+    solo_bwd_body<H8, 1, true>(up.W_hh, s_rep, up.gx, up.dgh, s_gx, D, s_D, above, s_above, up.sv, s_sv, up.hs, s_hs, up.dbp, B, H, T, RT,
+                               g, ty, SoloLink{words, nullptr, sync, limit, 0}, nullptr);
+  } else if (role < 3) {
+    link_body<H8, true>(W_ih + g * s_rep, nullptr, up.gx + g * s_gx, dx + g * s_dx, B, H, T, ty, role - 1, words, words + 8 * role, sync, limit);
+  } else {
+    solo_bwd_body<H8, 1, true>(lo.W_hh, s_rep, lo.gx, lo.dgh, s_gx, nullptr, 0, dx, s_dx, lo.sv, s_sv, lo.hs, s_hs, lo.dbp, B, H, T, RT,
+                               g, ty, SoloLink{nullptr, words + 8, sync, limit, W}, loss);
   }
 }
 
@@ -792,6 +1070,43 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
                        s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT)
   HPSGD_SOLO_CASES(HPSGD_SOLO_BWD)
 #undef HPSGD_SOLO_BWD
+  return hipGetLastError();
+}
+
+// Both layers in one launch, each way: where the chip has room for the four workgroups of every worker's tiles at once - one per CU beyond
+// 64 units, three up to there.  Local steps, layer by layer / this, us (H, batch, workers, steps):
+//   (100, 20, 4, 50) 298 / 195 a round   (128, 16, 4, 35) 266 / 181   (64, 20, 2, 35) 146 / 107   (32, 8, 4, 20) 88 / 65   (30, 60, 1, 60) 187 / 130
+//   few steps  (100, 20, 4, 10) 110 / 88   (100, 20, 4, 5) 87 / 75       the chip full  (110, 32, 8, 30) 261 / 180   (64, 64, 8, 30) 180 / 143   (24, 96, 8, 30) 156 / 144
+bool gru_stack_supported(int B, int H, int T, int layers, int workers) {
+  return layers == 2 && H >= 4 && gru_solo_supported(B, H) && !solo_16_rows(B, H, workers) && (long)workers * solo_tiles(B) * 4 <= (H <= 64 ? 768 : 256) &&
+         (long)(T + 1) * B * 3 * H * 4 < 0x7fffffe0L;
+}
+size_t gru_stack_sync_words(int B, int groups) { return kLinkBase + (size_t)groups * solo_tiles(B) * kLinkWords; }
+
+hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, const float* b_ih, long s_rep, long s_gx,
+                                long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
+  if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
+  const int RT = solo_tiles(B), n = groups * RT;
+  KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 3, s, 2);
+#define HPSGD_STACK_FWD(H8)                                                                                                  \
+  hipLaunchKernelGGL(gru_stack_fwd_kernel<H8>, dim3(32 * ((n + 7) / 8)), dim3(Solo<H8>::NT), 0, s, lo, up, W_ih, b_ih, s_rep, s_gx, s_hs, s_sv, \
+                     B, H, T, RT, n, sync, limit)
+  HPSGD_SOLO_CASES(HPSGD_STACK_FWD)
+#undef HPSGD_STACK_FWD
+  return hipGetLastError();
+}
+
+hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, long s_rep, const float* D, long s_D,
+                                const float* above, long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv,
+                                int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
+  if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
+  const int RT = solo_tiles(B), n = groups * RT;
+  KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 3, s, 2);
+#define HPSGD_STACK_BWD(H8)                                                                                                       \
+  hipLaunchKernelGGL(gru_stack_bwd_kernel<H8>, dim3(32 * ((n + 7) / 8)), dim3(Solo<H8>::NT), 0, s, lo, up, W_ih, s_rep, D, s_D, above, s_above, dx, s_dx, \
+                     loss, s_gx, s_hs, s_sv, B, H, T, RT, n, sync, limit)
+  HPSGD_SOLO_CASES(HPSGD_STACK_BWD)
+#undef HPSGD_STACK_BWD
   return hipGetLastError();
 }
 

@@ -134,12 +134,14 @@ struct hpsgd_ctx {
   bool solo_b = false;          // the same for the bf16 padded layout
   int prow = 0, prow_b = 32;    // batch rows per workgroup of the resident-weight launches, fp32 (0: not taken) and bf16
   bool solo = false;            // fp32 and narrow: a layer's recurrence needs no exchange (gru_solo.hip)
-  // 0: the layout that the fastest forms need.  1: no padding, no split contractions, none of the forms whose
-  // saved state is larger than the model's own sizes.  2: no resident-weight recurrence in fp32 either.
+  bool stack = false;           // ... and both layers run in one launch: the buffers of the upper one are its own
+  Region gx_up, dgh_up, dx_up, dbp_up;
+  // 0: the layout that the fastest forms need.  1: layers one after the other.  2: no padding, no split contractions, none of the forms whose
+  // saved state is larger than the model's own sizes.  3: no resident-weight recurrence in fp32 either.
   // `small`: the same model in the first such layout that fits the static array, where layout 0 does not.
   int lean = 0;
   std::unique_ptr<hpsgd_ctx> small;
-  int wgrad_parts(int M, int N, int Kd) const { return lean ? 1 : wgrad_splits(M, N, Kd, K); }
+  int wgrad_parts(int M, int N, int Kd) const { return lean > 1 ? 1 : wgrad_splits(M, N, Kd, K); }
   bool resident = true;         // fp32 recurrence: one launch per run of time steps when supported
   bool device_scope = false;    // resident-weight launches exchange at device scope even where an XCD's L2 would do
   unsigned spin_limit = 1u << 20;  // bound of every wait inside those launches
@@ -236,7 +238,7 @@ int build_layout(hpsgd_ctx* c) {
     c->i_head_b = (int)c->entries.size();
     add_entry(c, "head.b", classes, 1);
 
-    c->padded = !c->lean && lm && d.prec == HPSGD_BF16_MFMA && d.vocab >= 4 && d.vocab <= 1024 * 10 && d.hidden <= 1024 &&
+    c->padded = c->lean <= 1 && lm && d.prec == HPSGD_BF16_MFMA && d.vocab >= 4 && d.vocab <= 1024 * 10 && d.hidden <= 1024 &&
                 (long)d.seq_len * (long)round_up(d.batch, 8) * (long)round_up(4 * d.hidden > d.vocab ? 4 * (d.hidden + 31) : d.vocab, 8) < big;
     c->Bp = c->padded ? (int)round_up(d.batch, 8) : d.batch;
     c->Hp = c->padded ? (int)round_up(d.hidden, 32) : d.hidden;
@@ -244,7 +246,8 @@ int build_layout(hpsgd_ctx* c) {
     c->Vp = c->padded ? (int)round_up(classes, 8) : classes;
     const size_t Bi = c->Bp, TB = (size_t)d.seq_len * Bi, H = c->Hp;
     c->solo_b = c->padded && gru_solo_bf16_supported(c->Bp, c->Hp);
-    c->solo = !c->lean && d.prec != HPSGD_BF16_MFMA && gru_solo_supported(d.batch, d.hidden);
+    c->solo = c->lean <= 1 && d.prec != HPSGD_BF16_MFMA && gru_solo_supported(d.batch, d.hidden);
+    c->stack = !c->lean && c->solo && gru_stack_supported(d.batch, d.hidden, d.seq_len, d.layers, c->K);
     c->grad = c->alloc(c->P);
     if (lm) c->xe = c->alloc(TB * c->Ep);
     for (int l = 0; l < d.layers; ++l) {
@@ -261,11 +264,18 @@ int build_layout(hpsgd_ctx* c) {
     c->D = c->alloc(Bi * H);
     c->wt = c->alloc(3 * H * H);
     // batch rows per workgroup of the fp32 resident-weight launches (0: they do not take this layer)
-    c->prow = c->solo || d.prec == HPSGD_BF16_MFMA || c->lean == 2 || (c->lean && d.hidden % 16 != 0)
+    c->prow = c->solo || d.prec == HPSGD_BF16_MFMA || c->lean == 3 || (c->lean > 1 && d.hidden % 16 != 0)
                   ? 0
                   : gru_persist_rows(d.batch, d.hidden, c->K);
-    c->prow_b = c->lean ? 32 : gru_persist_bf16_rows((int)Bi, (int)H, c->K);
-    // (no step of a narrow model waits for another workgroup)
+    c->prow_b = c->lean > 1 ? 32 : gru_persist_bf16_rows((int)Bi, (int)H, c->K);
+    if (c->stack) {
+      c->psync = c->alloc(gru_stack_sync_words((int)Bi, 1));
+      c->gx_up = c->alloc(TB * 3 * H);
+      c->dgh_up = c->alloc(TB * 3 * H);
+      c->dx_up = c->alloc(TB * H);
+      c->dbp_up = c->alloc_packed(dbp_solo);
+    }
+    // (no other step of a narrow model waits for another workgroup)
     if (!c->solo && !c->solo_b) c->psync = c->alloc(gru_persist_sync_words((int)Bi, 1, c->prow ? c->prow : c->prow_b));
     if (dbp_solo) {  // (in the place of `gh`, which a step of such launches does not use)
       c->dbp.offset = c->gh.offset;
@@ -274,12 +284,13 @@ int build_layout(hpsgd_ctx* c) {
     else if (d.prec == HPSGD_BF16_MFMA && gru_fused_bf16_supported((int)H)) c->dbp = c->alloc_packed(((Bi + c->prow_b - 1) / c->prow_b) * 6 * H);
     if (c->prow && gru_persist_dw_supported((int)H)) c->dwp = c->alloc_packed(((Bi + c->prow - 1) / c->prow) * 3 * H * H);
     if (d.prec != HPSGD_BF16_MFMA) {
-      size_t most = 0;  // over the layers, which follow each other: the parts of dW_ih, then those of dW_hh
+      size_t most = 0;  // over the layers, which follow each other (or, in one launch, do not): the parts of dW_ih, then those of dW_hh
       for (int l = 0; l < d.layers; ++l) {
         const size_t win = l > 0 ? H : (size_t)(lm ? d.embed : d.input);
         const int si = c->wgrad_parts((int)(3 * H), (int)win, (int)TB), sh = c->wgrad_parts((int)(3 * H), (int)H, (int)TB);
         const size_t n = (si > 1 ? si * 3 * H * win : 0) + (sh > 1 ? sh * 3 * H * H : 0);
-        if (n > most) most = n;
+        if (c->stack) most += n;
+        else if (n > most) most = n;
       }
       if (most) c->dwip = c->alloc_packed(most);
     }
@@ -327,7 +338,7 @@ int build_layout(hpsgd_ctx* c) {
     {
       const bool bfp = d.prec == HPSGD_BF16_MFMA;
       const int ns = dx_splits((int)nrows, (int)H, bfp ? (int)round_up(classes, 8) : classes, c->K, bfp ? 128 : 64, bfp ? 512 : 256);
-      if (ns > 1 && !c->lean) c->dxp = c->alloc_packed((size_t)ns * nrows * H);
+      if (ns > 1 && c->lean <= 1) c->dxp = c->alloc_packed((size_t)ns * nrows * H);
     }
     c->rowloss = c->alloc(nrows);
   } else if (d.kind == HPSGD_MLP) {
@@ -795,7 +806,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const int ldl = pad ? c->Vp : classes;  // row pitch of the logits
     const int32_t* tok = (const int32_t*)x;
     float* gx = reg(c->gx);
-    float* dgh = reg(c->dgh);
+    float* dgh_lo = reg(c->dgh);
     float* gh = reg(c->gh);
     float* D = reg(c->D);
     float* dx = reg(c->dx);
@@ -818,6 +829,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // follows what the flags read.  A given-up wait shows as NaN in the results (below).
     // narrow fp32 layers: the whole recurrence without any exchange between workgroups
     const bool use_solo = c->solo && c->resident;
+    const bool use_stack = use_solo && c->stack;  // both layers in one launch
     const bool use_persist = c->prow != 0 && c->resident && gru_persist_pays(B, H, T, groups, c->prow);
     const int prow = use_persist ? c->prow : c->prow_b;  // rows of a synchronisation group
     // bf16: the same with the weight slices in registers; its backward launch writes only the bf16
@@ -828,15 +840,16 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const bool use_solo_b = pad && c->solo_b;  // (a kind of use_persist_b without the exchange)
     const bool exact_gates = gru_bf16_exact_gates(B, H, c->K, B != Bc || H != Hc || width0 != Ec);
     const bool exchange = use_persist || (use_persist_b && !use_solo_b);
-    unsigned* psync = exchange ? (unsigned*)reg(c->psync) : nullptr;
+    unsigned* psync = exchange || use_stack ? (unsigned*)reg(c->psync) : nullptr;
     // the abort words of all workers of this step, cleared whether it exchanges or not: what is reported is this
     // step, not an earlier one of another form or what the memory held
     unsigned* aborts = c->psync.stride ? (unsigned*)reg(c->psync) : nullptr;
     unsigned pbase = 0;
     unsigned ticket_launches = 0;  // launches of this step that placed their workgroups by ticket
+    const size_t psync_words = use_stack ? gru_stack_sync_words(B, groups) : exchange ? gru_persist_sync_words(B, groups, prow) : 0;
     if (exchange) {
       TRY0(resident.begin(s));
-      abort_word = psync;  // (cleared together with the first layer's h_0 below)
+      abort_word = psync;  // (cleared together with the first layer's h_0 below; the launches of two layers leave their NaN themselves)
     }
     // ---- the head's operands
     const int nrows = lm ? TB : B;
@@ -868,6 +881,11 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     const bool head_with = headb && own_set && (double)classes * Hc <= 4e6;
     TRY(weight_copies(c, rin, sRi, k0, own_set ? 1 : groups, ws, s, !prepared, head_with, wc));
     const bool head_made = head_done || (head_with && wc.head);
+    // a layer's arrays in the launches of two layers (the regions of both have the same strides)
+    auto stack_layer = [&](int l) {
+      return GruStackLayer{rin + c->eoff(c->lidx[l].whh), rin + c->eoff(c->lidx[l].bhh), l ? reg(c->gx_up) : gx, l ? reg(c->dgh_up) : dgh_lo,
+                           reg(c->hs[l]), reg(c->sv[l]), l ? reg(c->dbp_up) : reg(c->dbp)};
+    };
     // ---- forward
     const float* lin = (const float*)x;
     long s_lin = (long)TB * d.input;
@@ -899,7 +917,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       fp.blk0[0] = 0;
       fp.max_groups = 0;
       bool ok = true;
-      if (psync) ok = ok && fill_pack_push(fp, (float*)psync, 0, 1, (long)gru_persist_sync_words(B, groups, prow), 0, 1);
+      if (psync) ok = ok && fill_pack_push(fp, (float*)psync, 0, 1, (long)psync_words, 0, 1);
       if (aborts) ok = ok && fill_pack_push(fp, (float*)aborts, 0, 1, 1, c->psync.stride, groups);
       const bool solo_any = use_solo || use_solo_b;  // (those launches write h_0 themselves)
       for (int l = 0; l < L && ok && !solo_any; ++l) {
@@ -926,7 +944,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       role = HPSGD_ROLE_OTHER;
       if (!cleared) {
         HIP_TRY(launch_fill_zero(hs, (size_t)B * H, (size_t)s_hs, groups, s, l == 0 ? (float*)psync : nullptr,
-                                 l == 0 && psync ? gru_persist_sync_words(B, groups, prow) : 0));
+                                 l == 0 && psync ? psync_words : 0));
         if (aborts && l == 0) HIP_TRY(launch_fill_zero((float*)aborts, 1, c->psync.stride, groups, s));
         if (use_persist && l == 0)
           HIP_TRY(launch_fill_zero(reg(c->hx), gru_persist_exchange_words(B, H, 1), c->hx.stride, groups, s));
@@ -939,7 +957,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       const float* Wih0 = rin + c->eoff(c->lidx[l].wih);
       const bool xproj = persist && gru_persist_xproj_supported(H, width, prow) && ((uintptr_t)lin & 15) == 0 &&
                          (s_lin & 3) == 0;
-      if (!xproj) {
+      if (!xproj && !(use_stack && l > 0)) {
         const float* Wih = rin + c->eoff(c->lidx[l].wih);
         NtView va{lin, 0, width, s_lin}, vb{Wih, 0, width, sRi};
         // bf16 precision: both operands as row-major bf16 copies (the layer below wrote its
@@ -1003,7 +1021,13 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       const bool persist_b = fused_b && use_persist_b && hT != nullptr;
       TimerScope loop_fwd(c, HPSGD_ROLE_GEMM_REC_FWD, s, (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
       c->timer_nested = loop_fwd.active() && (fused || fused_b || use_solo || persist);
-      if (use_solo) {
+      if (use_stack) {
+        role = HPSGD_ROLE_GEMM_REC_FWD;
+        if (l > 0)
+          HIP_TRY(launch_gru_stack_fwd(stack_layer(0), stack_layer(1), Wih0, rin + c->eoff(c->lidx[1].bih), sRi, s_gx, s_hs, s_sv, B, H, T,
+                                       groups, psync, c->spin_limit, s));
+        ++c->last_resident;
+      } else if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_solo_fwd(Whh, rin + c->eoff(c->lidx[l].bhh), sRi, gx, s_gx, hs, s_hs, sv, s_sv, B, H, T, groups, c->K, s));
         ++c->last_resident;
@@ -1300,17 +1324,23 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       above = dx;
       d_zero = true;
     }
+    // what a layer adds up from parts (both layers of a stack, whose products go out together)
+    ReducePack rp;
+    float* parts = nullptr;  // the next free place for parts of weight gradients
     // ---- backward: GRU layers, top to bottom
     for (int l = L - 1; l >= 0; --l) {
+      const bool joined = use_stack && l > 0;  // the layer below comes with this one
       const float* hs = reg(c->hs[l]);
       const float* sv = reg(c->sv[l]);
       const long s_hs = (long)c->hs[l].stride, s_sv = (long)c->sv[l].stride;
       const int win = l > 0 ? H : width0, winc = l > 0 ? Hc : Ec;  // internal, and the model's own
       const int gp = H != Hc ? H : 0, gh = H != Hc ? Hc : 0;  // rows of the weight gradients in gate blocks
-      ReducePack rp;
-      rp.n = 0;
-      rp.blk0[0] = 0;
-      rp.lr = lr;
+      if (!use_stack || l == L - 1) {
+        rp.n = 0;
+        rp.blk0[0] = 0;
+        rp.lr = lr;
+        parts = c->dwip.stride ? reg(c->dwip) : nullptr;
+      }
       // queued for the layer's one adding launch; a segment that launch cannot take runs by itself
       auto queue_reduce = [&](const float* parts, int n_parts, size_t n, const float* in, size_t s_in, float* out,
                               size_t s_out, int commit) -> int {
@@ -1331,7 +1361,8 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         layer_in = (const float*)x;
         s_layer_in = (long)TB * d.input;
       }
-      float* dgx = gx;  // the gate pre-activation buffer is free once the layer's forward is done
+      float* dgx = joined ? reg(c->gx_up) : gx;  // the gate pre-activation buffer is free once the layer's forward is done
+      float* dgh = joined ? reg(c->dgh_up) : dgh_lo;
       const float* Whh = rin + c->eoff(c->lidx[l].whh);
       const bool fused = !bf && gru_fused_supported(H) && ((uintptr_t)Whh & 15) == 0 && (sRi & 3) == 0;
       const bool fused_b = bf && gru_fused_bf16_supported(H);
@@ -1369,7 +1400,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       // the resident-weight kernel accumulates dW_hh itself (one partial sum per batch-row tile)
       float* dwp = persist && c->dwp.stride ? reg(c->dwp) : nullptr;
       // ... and the bias gradients
-      float* dbp = persist || persist_b || use_solo ? reg(c->dbp) : nullptr;
+      float* dbp = joined ? reg(c->dbp_up) : persist || persist_b || use_solo ? reg(c->dbp) : nullptr;
       const int NC = (c->aux && fused && !persist && !use_solo && T >= 8) ? 4 : 1;
       auto chunk_lo = [&](int ch) { return (int)((long)T * ch / NC); };
       auto wgrad_rows = [&](hipStream_t st, int t0, int t1, int epi) -> int {
@@ -1385,7 +1416,14 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       {
       TimerScope loop_bwd(c, HPSGD_ROLE_GEMM_REC_BWD, s, (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
       c->timer_nested = loop_bwd.active() && (fused || fused_b || use_solo || persist);
-      if (use_solo) {
+      if (use_stack) {
+        role = HPSGD_ROLE_GEMM_REC_BWD;
+        if (joined) {
+          HIP_TRY(launch_gru_stack_bwd(stack_layer(0), stack_layer(1), rin + c->eoff(c->lidx[1].wih), sRi, d_zero ? nullptr : D, s_D, above, s_dx,
+                                       reg(c->dx_up), (long)c->dx_up.stride, loss_out, s_gx, s_hs, s_sv, B, H, T, groups, psync,
+                                       c->spin_limit, s));
+        }
+      } else if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
         HIP_TRY(launch_gru_solo_bwd(Whh, sRi, dgx, dgh, s_gx, d_zero ? nullptr : D, s_D, above, s_dx, sv, s_sv, hs, s_hs, dbp,
                                     B, H, T, groups, c->K, s));
@@ -1462,7 +1500,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       c->timer_nested = false;
       }
       const float* Wih = rin + c->eoff(c->lidx[l].wih);
-      const bool need_dx = l > 0 || lm;
+      const bool need_dx = (l > 0 || lm) && !joined;
       NtView v_dgxT, v_dghT, v_xT, v_hsT, v_wih;
       if (ntc && win % 8 == 0) {
         role = HPSGD_ROLE_OTHER;
@@ -1567,7 +1605,6 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         bool hh_first = false;
         // fp32: a gradient with few tiles has its contraction cut into parts (wgrad_splits); their sums are
         // added in order by the kernel that also applies the update
-        float* parts = c->dwip.stride ? reg(c->dwip) : nullptr;
         auto split_wgrad = [&](const float* A, const float* Bm, long sB, int N, const WgradTarget& w) -> int {
           const int ns = c->wgrad_parts(3 * H, N, TB), part = wgrad_part(TB, ns);
           const int n_parts = (TB + part - 1) / part;
@@ -1663,6 +1700,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
                      colsum_pack_push(gb.cs, dbp, 6L * Hc, (long)n_dbp * 6 * Hc, b_out, (long)s_bout, b_in, sRi, n_dbp, 6 * Hc);
         if (!bias_rides) TRY0(queue_reduce(dbp, n_dbp, (size_t)6 * Hc, b_in, (size_t)sRi, b_out, s_bout, update ? 1 : 0));
       }
+      if (joined) continue;  // (the products and sums of both layers go out together)
       TRY(gb.flush());
       if (dbp) {
         // (above)
@@ -1790,7 +1828,7 @@ int hpsgd_create(const hpsgd_model_desc* desc, int K, hpsgd_ctx** out) {
     return rc;
   }
   const size_t most = HPSGD_STATIC_WORKSPACE_BYTES / sizeof(float);
-  for (int lean = 1; lean <= 2 && c->ws_floats > most && !c->small; ++lean) {
+  for (int lean = 1; lean <= 3 && c->ws_floats > most && !c->small; ++lean) {
     std::unique_ptr<hpsgd_ctx> m(new (std::nothrow) hpsgd_ctx());
     if (!m) break;
     m->d = *desc;

@@ -230,6 +230,20 @@ hipError_t launch_gru_solo_fwd(const float* W_hh, const float* b_hh, long s_rep,
 hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float* dgh, long s_dg, const float* D, long s_D,
                                const float* above, long s_above, const float* sv, long s_sv, const float* hs, long s_hs,
                                float* dbp, int B, int H, int T, int groups, int workers, hipStream_t s);
+// Both layers of a model of two in one launch (each way), the upper one a few steps behind: gx and dgh are each layer's own (gx: the
+// upper layer's is written by the forward launch; the gate gradients replace it), dx receives the gradient that the upper layer passes on.
+// sync: gru_stack_sync_words() words, zero; sync[0] is the abort word.  A wait that was given up leaves NaN in everything behind it, and in loss.
+struct GruStackLayer {
+  const float *W_hh, *b_hh;
+  float *gx, *dgh, *hs, *sv, *dbp;
+};
+bool gru_stack_supported(int B, int H, int T, int layers, int workers);
+size_t gru_stack_sync_words(int B, int groups);
+hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, const float* b_ih, long s_rep, long s_gx,
+                                long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
+hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, long s_rep, const float* D, long s_D,
+                                const float* above, long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv,
+                                int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
 // the same with bf16 operands (H a multiple of 32 up to 256, B of 8): writes hb, hT (h_0 = 0 included) and dbp as the
 // resident-weight launches below do, and the gate gradients row-major as dg4 [T B][4H] = r | z | n | q; hs
 // and sv hold h_{t-1} and the gates in lane order (T B H and 4 T B H floats), for the backward launch only
@@ -298,7 +312,7 @@ struct ReduceSeg {
   const float* in; size_t s_in; float* out; size_t s_out; int commit;
 };
 struct ReducePack {
-  static constexpr int MAXSEG = 4;
+  static constexpr int MAXSEG = 6;  // two layers' parts of both weight gradients and of the bias gradients
   ReduceSeg seg[MAXSEG];
   unsigned blk0[MAXSEG + 1];
   int n;

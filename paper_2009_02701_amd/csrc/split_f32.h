@@ -61,4 +61,55 @@ __device__ __forceinline__ void split8(const float (&v)[8], uint4& p0, uint4& p1
   split2(v[6], v[7], p0.w, p1.w, p2.w);
 }
 
+// ---- products of 16 x 16 blocks (v_mfma_f32_16x16x32_bf16): lane group lg = l / 16 takes the words 4 lg .. + 3 of a chunk of 32
+// along the contraction and those 16 further on
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// A fragment of eight fp32 values per lane as three bf16 ones
+struct SplitFrag { bf16x8s p[3]; };
+__device__ __forceinline__ SplitFrag split_frag(const float4& lo, const float4& hi) {
+  uint4 p0, p1, p2;
+  split8({lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, p0, p1, p2);
+  return {{__builtin_bit_cast(bf16x8s, p0), __builtin_bit_cast(bf16x8s, p1), __builtin_bit_cast(bf16x8s, p2)}};
+}
+// big[q] += a0 w0, small[q] += the other five products, for NQ blocks of 16 columns (consecutive instructions
+// update different accumulators)
+template <int NQ>
+__device__ __forceinline__ void split_mfmas(const SplitFrag& a, const SplitFrag (&w)[NQ], floatx4 (&big)[NQ], floatx4 (&small)[NQ]) {
+  auto mul = [&](int pa, int pw, floatx4 (&to)[NQ]) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) to[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[pa], w[q].p[pw], to[q], 0, 0, 0);
+  };
+  mul(0, 0, big);
+  mul(1, 0, small);
+  mul(2, 0, small);
+  mul(0, 1, small);
+  mul(1, 1, small);
+  mul(0, 2, small);
+}
+// acc += the products of one fragment's fp32 values with the fp32 instruction (W: the fragment of 16 columns): where the split
+// gives no number
+__device__ __forceinline__ void plain_mfmas(const float4 (&a)[2], const float4 (&w)[2], bool second, floatx4& acc) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && !second) continue;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].x, w[h].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].y, w[h].y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].z, w[h].z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].w, w[h].w, acc, 0, 0, 0);
+  }
+}
+__device__ __forceinline__ bool any_beyond(const floatx4& v) {
+  const float s = __builtin_fmaf(v[0], 0.f, __builtin_fmaf(v[1], 0.f, __builtin_fmaf(v[2], 0.f, v[3] * 0.f)));
+  return __any(!(s == 0.f)) != 0;
+}
+
+// A copy of a value that the compiler computes with only here: what a rare path derives from it is not hoisted out of the time loop,
+// where it would hold registers
+template <typename V>
+__device__ __forceinline__ V rarely(V v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 }  // namespace hpsgd
