@@ -226,7 +226,7 @@ int hpsgd_set_aux_stream(hpsgd_ctx *ctx, void *hip_stream);
  * them itself, across streams, contexts and host threads: a local step holds a per-device lock
  * while it issues them, and when the previous ones went to another stream it lets its stream
  * wait (hipStreamWaitEvent, the host does not block) for the event recorded behind them.
- * A narrow layer (fp32 up to 128 units) exchanges nothing, and its launches may run beside anything; two such layers
+ * A narrow layer (fp32 up to 128 units, bf16 up to 256) exchanges nothing, and its launches may run beside anything; two such layers
  * share a launch per direction where the chip has room for both, whose workgroups wait for those of the
  * layer before.  Those waits never depend on what else runs; they are bounded too, and one that is given up leaves NaN in loss_out and in
  * every parameter of the workers that it reaches. */

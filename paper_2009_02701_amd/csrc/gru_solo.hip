@@ -1087,7 +1087,7 @@ hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up
                                 long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
   if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
   const int RT = solo_tiles(B), n = groups * RT;
-  KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 3, s, 2);
+  KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
 #define HPSGD_STACK_FWD(H8)                                                                                                  \
   hipLaunchKernelGGL(gru_stack_fwd_kernel<H8>, dim3(32 * ((n + 7) / 8)), dim3(Solo<H8>::NT), 0, s, lo, up, W_ih, b_ih, s_rep, s_gx, s_hs, s_sv, \
                      B, H, T, RT, n, sync, limit)
@@ -1101,7 +1101,7 @@ hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up
                                 int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
   if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
   const int RT = solo_tiles(B), n = groups * RT;
-  KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 3, s, 2);
+  KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
 #define HPSGD_STACK_BWD(H8)                                                                                                       \
   hipLaunchKernelGGL(gru_stack_bwd_kernel<H8>, dim3(32 * ((n + 7) / 8)), dim3(Solo<H8>::NT), 0, s, lo, up, W_ih, s_rep, D, s_D, above, s_above, dx, s_dx, \
                      loss, s_gx, s_hs, s_sv, B, H, T, RT, n, sync, limit)
@@ -1159,12 +1159,16 @@ struct SoloB {
   static constexpr size_t BWD_LDS = (size_t)2 * RO * LP4 * 2 + (size_t)HB * NCL * 1024;
 };
 
-template <int HB, int UB, int V, bool EX>
-__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
-gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih, const float* __restrict__ b_hh,
-                         long s_rep, int Hc, const float* __restrict__ gx, long s_gx, __bf16* __restrict__ hb, long s_hb,
-                         float* __restrict__ hs, long s_hs, float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT,
-                         long s_hT, int Bc, int B, int T, int RT) {
+namespace {
+
+// (tile ty of worker g; LINKED: in a launch of two layers, as solo_fwd_body)
+template <int HB, int UB, int V, bool EX, bool LINKED>
+__device__ __forceinline__ void solo_fwd_bf16_body(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih,
+                                                   const float* __restrict__ b_hh, long s_rep, int Hc, const float* __restrict__ gx,
+                                                   long s_gx, __bf16* __restrict__ hb, long s_hb, float* __restrict__ hs, long s_hs,
+                                                   float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT, long s_hT,
+                                                   int Bc, int B, int T, int RT, int g, int ty, const SoloLink& k) {
+  static_assert(!LINKED || 4 * V * kChunk == 16, "a product of the layers' link has the rows of a chunk");
   using S = SoloB<HB, UB, V>;
   constexpr int HP = S::HP, LP = S::LP, NC = S::NC;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
@@ -1172,7 +1176,7 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
   u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * S::RO * LP * 2);      // [HB][NC][64]: the n gate
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * S::RO;
+  const int r0 = ty * S::RO;
   bf16x8 wf[S::WL ? 2 : 3][UB][NC];
   {
     const __amdgpu_buffer_rsrc_t rw = rsrc_b(Wb + g * s_wb, 3L * HP * HP * 2);
@@ -1227,7 +1231,7 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
       for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int v = 0; v < V; ++v)
-          G[u][q][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)ox, ((v * 3 + q) * HP + u * 16) * 4, 0));
+          G[u][q][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)ox, ((v * 3 + q) * HP + u * 16) * 4, LINKED ? 16 : 0));
   };
   // (two blocks per wave: the input projections are requested one step ahead instead of two, the registers of
   // the second set being the ones that would spill)
@@ -1235,6 +1239,13 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
   float ga[UB][3][V], gb[PD == 2 ? UB : 1][3][V], hp[UB][V];
 #pragma unroll
   for (int u = 0; u < UB; ++u) for (int v = 0; v < V; ++v) hp[u][v] = 0.f;
+  auto wait_gx = [&](int it) {
+    if (LINKED && k.in && it < T && it % kChunk == 0 && !link_chunk(k, it, T)) {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) bias[u][0] = bias[u][1] = bias[u][2] = __builtin_nanf("");
+    }
+  };
+  wait_gx(0);
   load_gx(0, ga);
   if constexpr (PD == 2) load_gx(1, gb);
   __syncthreads();
@@ -1258,6 +1269,7 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
         const bf16x8 wn = S::WL ? __builtin_bit_cast(bf16x8, wl[((w * UB + u) * NC + c) * 64 + lane]) : wf[S::WL ? 0 : 2][u][c];
         acc[u][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], wn, acc[u][2], 0, 0, 0);
       }
+    if (LINKED && k.out && t > 0 && t % kChunk == 0) link_publish(k.out + w, t);
     float rr[UB][V], zz[UB][V], nn[UB][V];
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
@@ -1283,6 +1295,7 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
         hp[u][v] = (1.0f - zz[u][v]) * nn[u][v] + zz[u][v] * hp[u][v];
         hout[(V * lg + v) * LP + (w * UB + u) * 16 + lr] = (__bf16)hp[u][v];
       }
+    wait_gx(t + PD);
     load_gx(t + PD, G);
     const __amdgpu_buffer_rsrc_t rT = rsrc_b(hTg + (long)(t + 1) * B, ((long)HP * ld_hT - (long)(t + 1) * B) * 2);
 #pragma unroll
@@ -1299,7 +1312,7 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
       if (tid + i * S::NT < V * HP / 2)
         __builtin_amdgcn_raw_buffer_store_b128(
             *reinterpret_cast<const u32x4s*>(hout + ((tid + i * S::NT) / (HP / 8)) * LP + ((tid + i * S::NT) % (HP / 8)) * 8), rb,
-            (r0 * HP + (tid + i * S::NT) * 8) * 2, 0, 0);
+            (r0 * HP + (tid + i * S::NT) * 8) * 2, 0, LINKED ? 16 : 0);
   };
   __bf16* h0 = hl;
   __bf16* h1 = hl + S::RO * LP;
@@ -1310,13 +1323,14 @@ gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* 
     else step(t + 1, h1, h0, ga);
   }
   if (t < T) step(t, h0, h1, ga);
+  if (LINKED && k.out) link_publish(k.out + w, T);
 }
 
-template <int HB, int UB, int V>
-__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
-gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* __restrict__ above, long s_above,
-                         const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, __bf16* __restrict__ dg4,
-                         long s_dg4, float* __restrict__ dbp, int Hc, int B, int T, int RT) {
+template <int HB, int UB, int V, bool LINKED>
+__device__ __forceinline__ void solo_bwd_bf16_body(const __bf16* __restrict__ WT, long s_wt, const float* __restrict__ above,
+                                                   long s_above, const float* __restrict__ sv, long s_sv, const float* __restrict__ hs,
+                                                   long s_hs, __bf16* __restrict__ dg4, long s_dg4, float* __restrict__ dbp, int Hc,
+                                                   int B, int T, int RT, int g, int ty, const SoloLink& k, float* loss) {
   using S = SoloB<HB, UB, V>;
   constexpr int HP = S::HP, LP = S::LP4, NC3 = S::NC3, NCR = S::NCR, NCL = S::NCL;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
@@ -1324,7 +1338,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
   u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * S::RO * LP * 2);      // [HB][NCL][64]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int g = blockIdx.x / RT, ty = blockIdx.x - g * RT, r0 = ty * S::RO;
+  const int r0 = ty * S::RO;
   // W_hh^T rows of this wave's units: [unit][3 HP]
   bf16x8 wf[UB][NCR];
   {
@@ -1356,11 +1370,10 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
         const int o = ((w * UB + u) * V + v) * 64 + lane;
         I.s[u][v] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rv, o * 16, 0, 0));
         I.hp[u][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rh, o * 4, 0, 0));
-        I.ab[u][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, (int)oa, (v * HP + u * 16) * 4, 0));
+        I.ab[u][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, (int)oa, (v * HP + u * 16) * 4, LINKED ? 16 : 0));
       }
   };
   In ia;
-  load_in(T - 1, ia);
   float dc[UB][V], bs[UB][4];
 #pragma unroll
   for (int u = 0; u < UB; ++u) {
@@ -1369,6 +1382,16 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
 #pragma unroll
     for (int i = 0; i < 4; ++i) bs[u][i] = 0.f;
   }
+  auto wait_above = [&](int t) {
+    if (LINKED && k.in && t >= 0 && (T - 1 - t) % kChunk == 0 && !link_chunk(k, T - 1 - t, T)) {
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+        for (int v = 0; v < V; ++v) dc[u][v] = __builtin_nanf("");
+      if (tid == 0 && loss) loss[g] = __builtin_nanf("");
+    }
+  };
+  wait_above(T - 1);
+  load_in(T - 1, ia);
   for (int i = tid; i < S::RO * LP; i += S::NT) reinterpret_cast<unsigned*>(dl)[i] = 0u;
   __syncthreads();
   __bf16* dgb = dg4 + g * s_dg4;
@@ -1387,6 +1410,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
         acc[u][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wv, acc[u][c & 1], 0, 0, 0);
       }
     }
+    if (LINKED && k.out && t < T - 1 && (T - 1 - t) % kChunk == 0) link_publish(k.out + w, T - 1 - t);
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       float da_r[V], da_z[V], da_n[V], dq[V];
@@ -1413,6 +1437,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
         bs[u][3] += dq[v];
       }
     }
+    wait_above(t - 1);
     load_in(t - 1, ia);
     __syncthreads();
     // the gate gradients row-major (r | z | n | q), 16 bytes per piece
@@ -1423,7 +1448,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
       const int src = c < 2 * HP ? c : c < 3 * HP ? c + HP : c - HP;  // (in LDS q comes before n)
       if (p < 2 * V * HP)
         __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4s*>(dout + row * LP + src), rb,
-                                               ((r0 + row) * 4 * HP + c) * 2, 0, 0);
+                                               ((r0 + row) * 4 * HP + c) * 2, 0, LINKED ? 16 : 0);
     }
   };
   __bf16* d0 = dl;
@@ -1434,6 +1459,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
     step(t - 1, d1, d0);
   }
   if (t >= 0) step(t, d0, d1);
+  if (LINKED && k.out) link_publish(k.out + w, T);
 #pragma unroll
   for (int u = 0; u < UB; ++u) {
 #pragma unroll
@@ -1449,6 +1475,154 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
       out[2 * Hc + j] = bs[u][2];
       out[5 * Hc + j] = bs[u][3];
     }
+  }
+}
+
+}  // namespace
+
+template <int HB, int UB, int V, bool EX>
+__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo_fwd_bf16_kernel(const __bf16* __restrict__ Wb, long s_wb, const float* __restrict__ b_ih, const float* __restrict__ b_hh,
+                         long s_rep, int Hc, const float* __restrict__ gx, long s_gx, __bf16* __restrict__ hb, long s_hb,
+                         float* __restrict__ hs, long s_hs, float* __restrict__ sv, long s_sv, __bf16* __restrict__ hT, long ld_hT,
+                         long s_hT, int Bc, int B, int T, int RT) {
+  const int g = blockIdx.x / RT;
+  solo_fwd_bf16_body<HB, UB, V, EX, false>(Wb, s_wb, b_ih, b_hh, s_rep, Hc, gx, s_gx, hb, s_hb, hs, s_hs, sv, s_sv, hT, ld_hT, s_hT, Bc, B, T,
+                                           RT, g, blockIdx.x - g * RT, SoloLink{});
+}
+template <int HB, int UB, int V>
+__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* __restrict__ above, long s_above,
+                         const float* __restrict__ sv, long s_sv, const float* __restrict__ hs, long s_hs, __bf16* __restrict__ dg4,
+                         long s_dg4, float* __restrict__ dbp, int Hc, int B, int T, int RT) {
+  const int g = blockIdx.x / RT;
+  solo_bwd_bf16_body<HB, UB, V, false>(WT, s_wt, above, s_above, sv, s_sv, hs, s_hs, dg4, s_dg4, dbp, Hc, B, T, RT, g, blockIdx.x - g * RT,
+                                       SoloLink{}, nullptr);
+}
+
+// ---------------------------------------------------------------------------- two bf16 layers in one launch
+// As the launches of two fp32 layers above, 4 rows a tile; what is passed on are the row-major bf16 copies of h and of the gate gradients.
+// The product between the layers holds its weights as the recurrences hold theirs: forward W_ih [3 HP][HP] in the place of W_hh,
+// backward W_ih^T [HP][3 HP] in that of W_hh^T; a chunk's operands go through LDS behind them.
+namespace {
+
+template <int HB, int UB, bool BWD>
+__device__ __forceinline__ void link_bf16_body(const __bf16* __restrict__ W, const __bf16* in, float* out, int B, int T, int ty, int odd,
+                                               unsigned* in_words, unsigned* out_words, unsigned* abort_w, unsigned limit) {
+  using S = SoloB<HB, UB, 1>;
+  constexpr int HP = S::HP, NC = BWD ? S::NC3 : S::NC, NQ = BWD ? 1 : 3;
+  constexpr int QR = BWD ? 1 : S::WL ? 2 : 3, CR = BWD ? S::NCR : NC;  // gates and chunks in registers
+  constexpr int IP = BWD ? 4 * HP : HP, ND = BWD ? HP : 3 * HP;        // words of a row of `in` and `out`
+  extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
+  u32x4s* wl = reinterpret_cast<u32x4s*>(solo_lds + 2 * S::RO * (BWD ? S::LP4 : S::LP) * 2);  // [HB][NC - CR, or NC of the n gate][64]
+  u32x4s* al = reinterpret_cast<u32x4s*>(solo_lds + (BWD ? S::BWD_LDS : S::FWD_LDS));         // [NC][64]
+  __shared__ int go;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lg = lane >> 4;
+  bf16x8 wf[QR][UB][CR];
+  {
+    const __amdgpu_buffer_rsrc_t rw = rsrc_b(W, 3L * HP * HP * 2);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const u32x4s v = __builtin_amdgcn_raw_buffer_load_b128(rw, ((q * HP + (w * UB + u) * 16 + lr) * (BWD ? 3 * HP : HP) + 32 * c + 8 * lg) * 2, 0, 0);
+          if (q < QR && c < CR) wf[q < QR ? q : 0][u][c < CR ? c : 0] = __builtin_bit_cast(bf16x8, v);
+          else wl[((w * UB + u) * (BWD ? NC - CR : NC) + (BWD ? c - CR : c)) * 64 + lane] = v;
+        }
+  }
+  const __amdgpu_buffer_rsrc_t ri = rsrc_b(in, 2L * T * B * IP), ro = rsrc_b(out, 4L * T * B * ND);
+  bool ok = true;
+  for (int i0 = odd * kChunk; i0 < T; i0 += 2 * kChunk) {
+    if (w == 0) {
+      ok = ok && link_wait<8>(in_words, S::NW, (unsigned)min(i0 + kChunk, T), abort_w, limit);
+      if (lane == 0) go = ok;
+    }
+    __syncthreads();  // (and everyone has read the operands of the chunk before)
+    ok = go != 0;
+    const int ia = i0 + (lr >> 2), io = i0 + lg;
+    const unsigned off_a = ia < T ? (unsigned)(((BWD ? T - 1 - ia : ia) * B + 4 * ty + (lr & 3)) * IP + 8 * lg) * 2u : kOut;
+#pragma unroll
+    for (int i = 0; i < (NC + S::NW - 1) / S::NW; ++i) {
+      const int c = w + i * S::NW;
+      if (c < NC) al[c * 64 + lane] = __builtin_amdgcn_raw_buffer_load_b128(ri, (int)off_a, c * 64, 16);  // (uniform)
+    }
+    __syncthreads();
+    floatx4 acc[NQ][UB];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int u = 0; u < UB; ++u) acc[q][u] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, al[c * 64 + lane]);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const bf16x8 wv = q < QR && c < CR ? wf[q < QR ? q : 0][u][c < CR ? c : 0]
+                                             : __builtin_bit_cast(bf16x8, wl[((w * UB + u) * (BWD ? NC - CR : NC) + (BWD ? (c < CR ? 0 : c - CR) : c)) * 64 + lane]);
+          acc[q][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wv, acc[q][u], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          st_b32<true>(ro, io < T ? (unsigned)(((BWD ? T - 1 - io : io) * B + 4 * ty + v) * ND + q * HP + (w * UB + u) * 16 + lr) * 4u : kOut,
+                       ok ? acc[q][u][v] : __builtin_nanf(""));
+    link_publish(out_words + w, (unsigned)min(i0 + kChunk, T));
+  }
+}
+
+}  // namespace
+
+// (grid, sync: as gru_stack_fwd_kernel)
+template <int HB, int UB, bool EX>
+__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_stack_fwd_bf16_kernel(GruStackLayerB lo, GruStackLayerB up, const __bf16* W_ih, long s_wih, long s_wb, long s_rep, int Hc, long s_gx,
+                          long s_hb, long s_hs, long s_sv, long ld_hT, long s_hT, int Bc, int B, int T, int RT, int n, unsigned* sync,
+                          unsigned limit) {
+  constexpr int HP = 16 * HB, NW = HB / UB;
+  int role, tile;
+  if (!link_part(sync, 0, n, role, tile)) return;
+  const int g = tile / RT, ty = tile - g * RT;
+  unsigned* words = sync + kLinkBase + (long)tile * kLinkWords;
+  if (role == 1 || role == 2) {
+    link_bf16_body<HB, UB, false>(W_ih + g * s_wih, (const __bf16*)lo.hb + g * s_hb + (long)B * HP, up.gx + g * s_gx, B, T, ty, role - 1, words,
+                                  words + 8 * role, sync, limit);
+  } else {
+    const bool first = role == 0;
+    const GruStackLayerB& l = first ? lo : up;
+    solo_fwd_bf16_body<HB, UB, 1, EX, true>((const __bf16*)l.W, s_wb, l.b_ih, l.b_hh, s_rep, Hc, l.gx, s_gx, (__bf16*)l.hb, s_hb, l.hs, s_hs,
+                                            l.sv, s_sv, (__bf16*)l.hT, ld_hT, s_hT, Bc, B, T, RT, g, ty,
+                                            SoloLink{first ? words : nullptr, first ? nullptr : words + 8, sync, limit, NW});
+  }
+}
+
+template <int HB, int UB>
+__global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
+gru_stack_bwd_bf16_kernel(GruStackLayerB lo, GruStackLayerB up, const __bf16* WT_ih, long s_wih, long s_wt, const float* above, long s_above,
+                          float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4, int Hc, int B, int T, int RT, int n,
+                          unsigned* sync, unsigned limit) {
+  constexpr int NW = HB / UB;
+  int role, tile;
+  if (!link_part(sync, 1, n, role, tile)) return;
+  const int g = tile / RT, ty = tile - g * RT;
+  unsigned* words = sync + kLinkBase + (long)tile * kLinkWords + 36;
+  if (role == 1 || role == 2) {
+    link_bf16_body<HB, UB, true>(WT_ih + g * s_wih, (const __bf16*)up.dg4 + g * s_dg4, dx + g * s_dx, B, T, ty, role - 1, words,
+                                 words + 8 * role, sync, limit);
+  } else {
+    const bool first = role == 0;
+    const GruStackLayerB& l = first ? up : lo;
+    solo_bwd_bf16_body<HB, UB, 1, true>((const __bf16*)l.WT, s_wt, first ? above : dx, first ? s_above : s_dx, l.sv, s_sv, l.hs, s_hs,
+                                        (__bf16*)l.dg4, s_dg4, l.dbp, Hc, B, T, RT, g, ty,
+                                        SoloLink{first ? words : nullptr, first ? nullptr : words + 8, sync, limit, NW},
+                                        first ? nullptr : loss);
   }
 }
 
@@ -1532,6 +1706,63 @@ hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* abov
   HPSGD_SOLOB_CASES(HPSGD_SOLOB_BWD)
 #undef HPSGD_SOLOB_BWD
 #undef HPSGD_SOLOB_BWD1
+  return hipGetLastError();
+}
+
+// As gru_stack_supported: one workgroup per CU beyond 64 units, two up to there, where tiles have 4 rows (solo_b_rows).  Local steps, layer by layer /
+// this, us (H, batch, workers, steps; 1000 to 3000 words):
+//   (256, 16, 4, 30) 386 / 284   (128, 16, 4, 35) 246 / 210   (64, 20, 4, 35) 226 / 203   (100, 10, 2, 20) 193 / 175 a round   (150, 20, 4, 6) 165 / 158
+//   (220, 32, 8, 20), the chip full  361 / 309   (60, 64, 8, 20) 286 / 282       9999 words, (200, 20, 4, 20) 396 / 337 a round
+bool gru_stack_bf16_supported(int B, int H, int T, int layers, int workers) {
+  return layers == 2 && gru_solo_bf16_supported(B, H) && (long)workers * (B / 4) * 4 <= (H <= 64 ? 512 : 256) && 16L * T * B * H < 0x7fffffe0L;
+}
+size_t gru_stack_bf16_sync_words(int B, int groups) { return kLinkBase + (size_t)groups * (B / 4) * kLinkWords; }
+
+hipError_t launch_gru_stack_fwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* W_ih, long s_wih, long s_wb, long s_rep,
+                                     int Hc, long s_gx, long s_hb, long s_hs, long s_sv, long ld_hT, long s_hT, int Bc, int B, int H, int T,
+                                     int groups, bool exact, unsigned* sync, unsigned limit, hipStream_t s) {
+  if (!gru_stack_bf16_supported(B, H, T, 2, groups) || Hc < 1 || Hc > H || Bc < 1 || Bc > B || (ld_hT & 1) != 0 || (s_hT & 1) != 0 ||
+      (long)H * ld_hT * 2 >= 0x7fffffe0L)
+    return hipErrorInvalidValue;
+  const int RT = B / 4, n = groups * RT;
+  KernelTimer kt(KID_GRU_FWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
+#define HPSGD_STACKB_FWD_EX(HB, UB, EX)                                                                                      \
+  do {                                                                                                                       \
+    using S = SoloB<HB, UB, 1>;                                                                                              \
+    constexpr size_t lds = S::FWD_LDS + (size_t)S::NC * 1024;                                                                \
+    static std::atomic<size_t> allowed{0};                                                                                   \
+    if (const hipError_t e = allow_lds((const void*)gru_stack_fwd_bf16_kernel<HB, UB, EX>, lds, allowed)) return e;          \
+    hipLaunchKernelGGL((gru_stack_fwd_bf16_kernel<HB, UB, EX>), dim3(32 * ((n + 7) / 8)), dim3(S::NT), lds, s, lo, up,       \
+                       (const __bf16*)W_ih, s_wih, s_wb, s_rep, Hc, s_gx, s_hb, s_hs, s_sv, ld_hT, s_hT, Bc, B, T, RT, n, sync, limit); \
+  } while (0)
+#define HPSGD_STACKB_FWD(HB, UB)                      \
+  do {                                                \
+    if (exact) HPSGD_STACKB_FWD_EX(HB, UB, true);     \
+    else HPSGD_STACKB_FWD_EX(HB, UB, false);          \
+  } while (0)
+  HPSGD_SOLOB_CASES(HPSGD_STACKB_FWD)
+#undef HPSGD_STACKB_FWD_EX
+#undef HPSGD_STACKB_FWD
+  return hipGetLastError();
+}
+
+hipError_t launch_gru_stack_bwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* WT_ih, long s_wih, long s_wt,
+                                     const float* above, long s_above, float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4,
+                                     int Hc, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
+  if (!gru_stack_bf16_supported(B, H, T, 2, groups) || Hc < 1 || Hc > H || !above || (s_dg4 & 7) != 0) return hipErrorInvalidValue;
+  const int RT = B / 4, n = groups * RT;
+  KernelTimer kt(KID_GRU_BWD_PERSIST_BF16, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
+#define HPSGD_STACKB_BWD(HB, UB)                                                                                             \
+  do {                                                                                                                       \
+    using S = SoloB<HB, UB, 1>;                                                                                              \
+    constexpr size_t lds = S::BWD_LDS + (size_t)S::NC3 * 1024;                                                               \
+    static std::atomic<size_t> allowed{0};                                                                                   \
+    if (const hipError_t e = allow_lds((const void*)gru_stack_bwd_bf16_kernel<HB, UB>, lds, allowed)) return e;              \
+    hipLaunchKernelGGL((gru_stack_bwd_bf16_kernel<HB, UB>), dim3(32 * ((n + 7) / 8)), dim3(S::NT), lds, s, lo, up,           \
+                       (const __bf16*)WT_ih, s_wih, s_wt, above, s_above, dx, s_dx, loss, s_hs, s_sv, s_dg4, Hc, B, T, RT, n, sync, limit); \
+  } while (0)
+  HPSGD_SOLOB_CASES(HPSGD_STACKB_BWD)
+#undef HPSGD_STACKB_BWD
   return hipGetLastError();
 }
 

@@ -135,7 +135,8 @@ struct hpsgd_ctx {
   int prow = 0, prow_b = 32;    // batch rows per workgroup of the resident-weight launches, fp32 (0: not taken) and bf16
   bool solo = false;            // fp32 and narrow: a layer's recurrence needs no exchange (gru_solo.hip)
   bool stack = false;           // ... and both layers run in one launch: the buffers of the upper one are its own
-  Region gx_up, dgh_up, dx_up, dbp_up;
+  bool stack_b = false;         // the same for the bf16 padded layout
+  Region gx_up, dgh_up, dx_up, dbp_up, hb_lo, dg4_up;
   // 0: the layout that the fastest forms need.  1: layers one after the other.  2: no padding, no split contractions, none of the forms whose
   // saved state is larger than the model's own sizes.  3: no resident-weight recurrence in fp32 either.
   // `small`: the same model in the first such layout that fits the static array, where layout 0 does not.
@@ -246,6 +247,7 @@ int build_layout(hpsgd_ctx* c) {
     c->Vp = c->padded ? (int)round_up(classes, 8) : classes;
     const size_t Bi = c->Bp, TB = (size_t)d.seq_len * Bi, H = c->Hp;
     c->solo_b = c->padded && gru_solo_bf16_supported(c->Bp, c->Hp);
+    c->stack_b = !c->lean && c->solo_b && gru_stack_bf16_supported(c->Bp, c->Hp, d.seq_len, d.layers, c->K);
     c->solo = c->lean <= 1 && d.prec != HPSGD_BF16_MFMA && gru_solo_supported(d.batch, d.hidden);
     c->stack = !c->lean && c->solo && gru_stack_supported(d.batch, d.hidden, d.seq_len, d.layers, c->K);
     c->grad = c->alloc(c->P);
@@ -268,10 +270,10 @@ int build_layout(hpsgd_ctx* c) {
                   ? 0
                   : gru_persist_rows(d.batch, d.hidden, c->K);
     c->prow_b = c->lean > 1 ? 32 : gru_persist_bf16_rows((int)Bi, (int)H, c->K);
-    if (c->stack) {
-      c->psync = c->alloc(gru_stack_sync_words((int)Bi, 1));
+    if (c->stack || c->stack_b) {
+      c->psync = c->alloc(c->stack ? gru_stack_sync_words((int)Bi, 1) : gru_stack_bf16_sync_words((int)Bi, 1));
       c->gx_up = c->alloc(TB * 3 * H);
-      c->dgh_up = c->alloc(TB * 3 * H);
+      if (c->stack) c->dgh_up = c->alloc(TB * 3 * H);
       c->dx_up = c->alloc(TB * H);
       c->dbp_up = c->alloc_packed(dbp_solo);
     }
@@ -305,6 +307,10 @@ int build_layout(hpsgd_ctx* c) {
       // (the launches without an exchange keep their gate gradients there, r | z | n | q per row)
       const size_t dg4 = TB * 4 * H, dgx_elems = (size_t)d.seq_len * gru_persist_bf16_exchange_elems((int)Bi, (int)(3 * H));
       c->dghx = c->alloc(((c->solo_b && dg4 > dgx_elems ? dg4 : dgx_elems) + 1) / 2);
+      if (c->stack_b) {
+        c->dg4_up = c->alloc(((dg4 > dgx_elems ? dg4 : dgx_elems) + 1) / 2);
+        c->hb_lo = c->alloc(((TB + Bi) * H + 1) / 2);
+      }
       c->dgxb = c->alloc((TB * 3 * H + 1) / 2);
       const size_t TBp = round_up(TB, 64), TB1p = round_up(TB + Bi, 64);
       const size_t win0 = c->Ep;
@@ -617,7 +623,9 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
     const float* Whh = rin + c->eoff(c->lidx[l].whh);
     if (pad) {
       const int wp = l > 0 ? H : c->Ep;
-      if (!copy_padded(Wih, bfreg(c->wihbl[l]), wp, 2 * (long)c->wihbl[l].stride, nullptr, 0, 0, 3 * H, wp, H, Hc, width) ||
+      const bool up = c->stack_b && l == 1;  // (its input gradient is computed beside the recurrences, from the transposed copy)
+      if (!copy_padded(Wih, bfreg(c->wihbl[l]), wp, 2 * (long)c->wihbl[l].stride, up ? bfreg(c->wihT) : nullptr, up ? 3 * H : 0,
+                       up ? 2 * (long)c->wihT.stride : 0, 3 * H, wp, H, Hc, width) ||
           !copy_padded(Whh, bfreg(c->whhb[l]), H, 2 * (long)c->whhb[l].stride, bfreg(c->whhT[l]), 3 * H,
                        2 * (long)c->whhT[l].stride, 3 * H, H, H, Hc, Hc))
         return HPSGD_EHIP;
@@ -838,15 +846,16 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // (the padded layout of a language model has them by construction)
     const bool use_persist_b = bf && c->resident && gru_persist_bf16_supported(B, H) && ntc && width0 % 8 == 0;
     const bool use_solo_b = pad && c->solo_b;  // (a kind of use_persist_b without the exchange)
+    const bool use_stack_b = use_solo_b && c->stack_b;
     const bool exact_gates = gru_bf16_exact_gates(B, H, c->K, B != Bc || H != Hc || width0 != Ec);
     const bool exchange = use_persist || (use_persist_b && !use_solo_b);
-    unsigned* psync = exchange || use_stack ? (unsigned*)reg(c->psync) : nullptr;
+    unsigned* psync = exchange || use_stack || use_stack_b ? (unsigned*)reg(c->psync) : nullptr;
     // the abort words of all workers of this step, cleared whether it exchanges or not: what is reported is this
     // step, not an earlier one of another form or what the memory held
     unsigned* aborts = c->psync.stride ? (unsigned*)reg(c->psync) : nullptr;
     unsigned pbase = 0;
     unsigned ticket_launches = 0;  // launches of this step that placed their workgroups by ticket
-    const size_t psync_words = use_stack ? gru_stack_sync_words(B, groups) : exchange ? gru_persist_sync_words(B, groups, prow) : 0;
+    const size_t psync_words = use_stack ? gru_stack_sync_words(B, groups) : use_stack_b ? gru_stack_bf16_sync_words(B, groups) : exchange ? gru_persist_sync_words(B, groups, prow) : 0;
     if (exchange) {
       TRY0(resident.begin(s));
       abort_word = psync;  // (cleared together with the first layer's h_0 below; the launches of two layers leave their NaN themselves)
@@ -885,6 +894,11 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     auto stack_layer = [&](int l) {
       return GruStackLayer{rin + c->eoff(c->lidx[l].whh), rin + c->eoff(c->lidx[l].bhh), l ? reg(c->gx_up) : gx, l ? reg(c->dgh_up) : dgh_lo,
                            reg(c->hs[l]), reg(c->sv[l]), l ? reg(c->dbp_up) : reg(c->dbp)};
+    };
+    auto stack_layer_b = [&](int l) {
+      return GruStackLayerB{bfreg(c->whhb[l]), bfreg(c->whhT[l]), rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh),
+                            l ? reg(c->gx_up) : gx, l ? bfreg(c->hb) : bfreg(c->hb_lo), reg(c->hs[l]), reg(c->sv[l]), bfreg(c->hsT[l]),
+                            l ? bfreg(c->dg4_up) : bfreg(c->dghx), l ? reg(c->dbp_up) : reg(c->dbp)};
     };
     // ---- forward
     const float* lin = (const float*)x;
@@ -957,7 +971,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       const float* Wih0 = rin + c->eoff(c->lidx[l].wih);
       const bool xproj = persist && gru_persist_xproj_supported(H, width, prow) && ((uintptr_t)lin & 15) == 0 &&
                          (s_lin & 3) == 0;
-      if (!xproj && !(use_stack && l > 0)) {
+      if (!xproj && !((use_stack || use_stack_b) && l > 0)) {
         const float* Wih = rin + c->eoff(c->lidx[l].wih);
         NtView va{lin, 0, width, s_lin}, vb{Wih, 0, width, sRi};
         // bf16 precision: both operands as row-major bf16 copies (the layer below wrote its
@@ -1043,7 +1057,13 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         c->last_xproj += xproj ? 1 : 0;
         resident.note();
       }
-      if (persist_b && use_solo_b) {
+      if (persist_b && use_stack_b) {
+        role = HPSGD_ROLE_GEMM_REC_FWD;
+        if (l > 0)
+          HIP_TRY(launch_gru_stack_fwd_bf16(stack_layer_b(0), stack_layer_b(1), bfreg(c->wihbl[1]), wstride(c->wihbl[1]), s_wb, sRi, Hc, s_gx,
+                                            s_hb, s_hs, s_sv, TB1p, s_hT, Bc, B, H, T, groups, exact_gates, psync, c->spin_limit, s));
+        ++c->last_resident;
+      } else if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
         HIP_TRY(launch_gru_solo_fwd_bf16(wb, s_wb, rin + c->eoff(c->lidx[l].bih), rin + c->eoff(c->lidx[l].bhh), sRi, Hc, gx, s_gx,
                                          hb, s_hb, hs, s_hs, sv, s_sv, hT, TB1p, s_hT, Bc, B, H, T, groups, c->K, exact_gates, s));
@@ -1330,6 +1350,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // ---- backward: GRU layers, top to bottom
     for (int l = L - 1; l >= 0; --l) {
       const bool joined = use_stack && l > 0;  // the layer below comes with this one
+      const bool up_b = use_stack_b && l > 0;
       const float* hs = reg(c->hs[l]);
       const float* sv = reg(c->sv[l]);
       const long s_hs = (long)c->hs[l].stride, s_sv = (long)c->sv[l].stride;
@@ -1400,7 +1421,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       // the resident-weight kernel accumulates dW_hh itself (one partial sum per batch-row tile)
       float* dwp = persist && c->dwp.stride ? reg(c->dwp) : nullptr;
       // ... and the bias gradients
-      float* dbp = joined ? reg(c->dbp_up) : persist || persist_b || use_solo ? reg(c->dbp) : nullptr;
+      float* dbp = joined || up_b ? reg(c->dbp_up) : persist || persist_b || use_solo ? reg(c->dbp) : nullptr;
       const int NC = (c->aux && fused && !persist && !use_solo && T >= 8) ? 4 : 1;
       auto chunk_lo = [&](int ch) { return (int)((long)T * ch / NC); };
       auto wgrad_rows = [&](hipStream_t st, int t0, int t1, int epi) -> int {
@@ -1444,10 +1465,14 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       }
       if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
+        if (up_b)
+          HIP_TRY(launch_gru_stack_bwd_bf16(stack_layer_b(0), stack_layer_b(1), bfreg(c->wihT), wstride(c->wihT), s_wtb, above, s_dx,
+                                            reg(c->dx_up), (long)c->dx_up.stride, loss_out, s_hs, s_sv, 2 * (long)c->dghx.stride, Hc, B, H, T,
+                                            groups, psync, c->spin_limit, s));
         // (gate gradients r | z | n | q, in the place of the exchange buffer)
-        HIP_TRY(launch_gru_solo_bwd_bf16(wtb, s_wtb, above, s_dx, sv, s_sv, hs, s_hs, bfreg(c->dghx), 2 * (long)c->dghx.stride, dbp, Hc,
+        if (!use_stack_b) HIP_TRY(launch_gru_solo_bwd_bf16(wtb, s_wtb, above, s_dx, sv, s_sv, hs, s_hs, bfreg(c->dghx), 2 * (long)c->dghx.stride, dbp, Hc,
                                          B, H, T, groups, c->K, s));
-        HIP_TRY(launch_transpose_dg4(bfreg(c->dghx), 2 * (long)c->dghx.stride, bfreg(c->dgxT), bfreg(c->dghT), TBp, s_T, TB, H, groups, s));
+        HIP_TRY(launch_transpose_dg4(up_b ? bfreg(c->dg4_up) : bfreg(c->dghx), 2 * (long)c->dghx.stride, bfreg(c->dgxT), bfreg(c->dghT), TBp, s_T, TB, H, groups, s));
       } else if (persist_b) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
         HIP_TRY(launch_gru_bwd_persist_bf16(wtb, s_wtb, bfreg(c->dghx), 2 * (long)c->dghx.stride, s_dgb, D, s_D, d_zero,
@@ -1500,7 +1525,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       c->timer_nested = false;
       }
       const float* Wih = rin + c->eoff(c->lidx[l].wih);
-      const bool need_dx = (l > 0 || lm) && !joined;
+      const bool need_dx = (l > 0 || lm) && !joined && !up_b;
       NtView v_dgxT, v_dghT, v_xT, v_hsT, v_wih;
       if (ntc && win % 8 == 0) {
         role = HPSGD_ROLE_OTHER;

@@ -256,6 +256,25 @@ hipError_t launch_gru_solo_fwd_bf16(const void* Wb, long s_wb, const float* b_ih
 hipError_t launch_gru_solo_bwd_bf16(const void* WT, long s_wt, const float* above, long s_above, const float* sv, long s_sv,
                                     const float* hs, long s_hs, void* dg4, long s_dg4, float* dbp, int Hc, int B, int H, int T,
                                     int groups, int workers, hipStream_t s);
+// two such layers in one launch (each way), as launch_gru_stack_*: hb and dg4 are each layer's own; W_ih [3H][H] and WT_ih = W_ih^T [H][3H] are the
+// upper layer's
+struct GruStackLayerB {
+  const void *W, *WT;  // W_hh and W_hh^T
+  const float *b_ih, *b_hh;
+  float* gx;
+  void* hb;
+  float *hs, *sv;
+  void *hT, *dg4;
+  float* dbp;
+};
+bool gru_stack_bf16_supported(int B, int H, int T, int layers, int workers);
+size_t gru_stack_bf16_sync_words(int B, int groups);
+hipError_t launch_gru_stack_fwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* W_ih, long s_wih, long s_wb, long s_rep,
+                                     int Hc, long s_gx, long s_hb, long s_hs, long s_sv, long ld_hT, long s_hT, int Bc, int B, int H, int T,
+                                     int groups, bool exact, unsigned* sync, unsigned limit, hipStream_t s);
+hipError_t launch_gru_stack_bwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* WT_ih, long s_wih, long s_wt,
+                                     const float* above, long s_above, float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4,
+                                     int Hc, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
 // its transposes: dgxT [3H][ld_T] = (r | z | n)^T, dghT = (r | z | q)^T over R = T B rows, in one launch
 hipError_t launch_transpose_dg4(const void* dg4, long s_dg4, void* dgxT, void* dghT, long ld_T, long s_T, int R, int H, int groups,
                                 hipStream_t s);
