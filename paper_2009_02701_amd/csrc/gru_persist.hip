@@ -1442,14 +1442,18 @@ unsigned gru_persist_count_per_step(int) { return 1u; }
 
 // The forward kernel can do the input projection itself when the layer input is narrow (at most 2 chunks of 32 per
 // wave) and its 48 rows of W_ih fit the LDS beside the rest: with 32 rows
-// and H > 512 that is 64 KB of partial sums and 72 KB of weight parts, which leaves room for an input of 64.  The line at 21 chunks of
-// both contractions together is where the fp32 form of this launch ended, with all of them in LDS; this form is the faster
-// beyond it too.  us per local step of 20 steps, 4 workers, projected in the launch / by a product of its own:
-//   16 rows, batch 16   H = 576, input 112  265.9 / 279.3,  192  267.2 / 282.4     H = 640,  48  275.2 / 290.9,  256  294.2 / 314.4
-//   32 rows, batch 64   H = 512, input 176  325.8 / 342.7,  256  325.6 / 354.5     batch 32, H = 640, 64  395.0 / 405.7
-// and on this side of it, 32 rows, batch 32   H = 528, input 16  353.6 / 357.5,  64  350.8 / 359.5
+// and H > 512 that is 64 KB of partial sums and 72 KB of weight parts, which leaves room for an input of 64.  Beyond H = 512 a group
+// spans XCDs: a step waits 2 us for the hand-off, and the projection, done before the wait, costs nothing.  Up to there a step
+// waits too little to hide more than 21 chunks of both contractions.  us per local step of 20 steps, projected in the launch /
+// by a product of its own:
+//   beyond H = 512   16 rows, batch 16, 4 workers   H = 576, input 112  263 / 274,  256  279 / 294     H = 640, 256  291 / 311
+//                    12 workers, H = 610, 128  577 / 606 (several launches)          5 steps, H = 704, 16  117 / 121
+//                    32 rows, 4 workers   H = 640, 64, batch 32  397 / 409           6 workers, H = 600, 64, batch 128  1764 / 1766
+//   up to it, within 21 chunks   16 rows  H = 320, 112  176 / 178,  416, 112  200 / 201     32 rows, batch 40  H = 320, 256  218 / 236,  480, 112  289 / 296
+//             beyond them        16 rows  H = 448, 256  214 / 213,  512, 176  221 / 219     32 rows, batch 40  H = 448, 176  294 / 289,  500, 256  319 / 319,
+//             6 workers, H = 512, 256, batch 40  585 / 569; (batches of whole 32-row tiles gain: 4 workers, 512, 256, batch 64  326 / 355)
 bool gru_persist_xproj_supported(int H, int width, int rows) {
-  return width >= 16 && width % 16 == 0 && width <= 256 && (H + PC - 1) / PC + (width + PC - 1) / PC <= 21 &&
+  return width >= 16 && width % 16 == 0 && width <= 256 && (H > 512 || (H + PC - 1) / PC + (width + PC - 1) / PC <= 21) &&
          persist_fwd_form(H, rows, width).lds <= kLdsLimit;
 }
 
