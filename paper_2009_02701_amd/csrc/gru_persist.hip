@@ -215,21 +215,39 @@ __device__ __forceinline__ bool split_beyond(const float4& v) {
 
 // The fragment of 32-chunk c of a weight row (KD words at src, at any alignment; ok: the row exists) in the order in which
 // the activations come: words 32c + 4 lg .. + 3 and 16 further on; zeros beyond KD and for a row that does not exist.
-__device__ __forceinline__ void weight_row_frag(const float* __restrict__ src, bool ok, bool vec, int KD, int c, float4 (&v)[2]) {
+__device__ __forceinline__ void weight_row_frag(const float* __restrict__ src, bool ok, int KD, int c, float4 (&v)[2]) {
   const int lg = (threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int k = PC * c + 16 * h + 4 * lg;
-    v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (!ok) continue;
-    if (vec) {
-      if (k < KD) v[h] = *reinterpret_cast<const float4*>(src + k);
-    } else {
-      if (k < KD) v[h].x = src[k];
-      if (k + 1 < KD) v[h].y = src[k + 1];
-      if (k + 2 < KD) v[h].z = src[k + 2];
-      if (k + 3 < KD) v[h].w = src[k + 3];
-    }
+    v[h] = make_float4(ok && k < KD ? src[k] : 0.f, ok && k + 1 < KD ? src[k + 1] : 0.f, ok && k + 2 < KD ? src[k + 2] : 0.f,
+                       ok && k + 3 < KD ? src[k + 3] : 0.f);
+  }
+}
+// The same, row `row` of the matrix rs of at least 4 words a row, for a launch's start: no branch stands between the loads, all of
+// which are in flight at once.  What does not exist is read beyond the matrix, which the buffer's range check answers with zeros; a
+// piece that the row ends in is the row's last four words, which weight_row_tail moves up.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const float* W, int rows, int KD) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, rows * KD * 4, 0x00020000);
+}
+__device__ __forceinline__ void weight_row_load(__amdgpu_buffer_rsrc_t rs, int row, bool ok, int KD, int c, float4 (&v)[2]) {
+  constexpr int beyond = 0x7ffffff0;
+  const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int k = PC * c + 16 * h + 4 * lg;
+    v[h] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, ok && k < KD ? (row * KD + min(k, KD - 4)) * 4 : beyond, 0, 0));
+  }
+}
+__device__ __forceinline__ void weight_row_tail(int KD, int c, float4 (&v)[2]) {
+  if (PC * c + PC <= KD || (KD & 3) == 0) return;  // (uniform)
+  const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int up = PC * c + 16 * h + 4 * lg + 4 - KD;  // (beyond 3: zeros already; below 1: all of it in the row)
+    if (up == 1) v[h] = make_float4(v[h].y, v[h].z, v[h].w, 0.f);
+    if (up == 2) v[h] = make_float4(v[h].z, v[h].w, 0.f, 0.f);
+    if (up == 3) v[h] = make_float4(v[h].w, 0.f, 0.f, 0.f);
   }
 }
 
@@ -322,35 +340,21 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   const int j = j0 + lr, jc = min(j, H - 1);
   const bool jok = j < H;
   // the resident slices: gate q's fragment of chunk c holds W_hh[q H + j][32 c ..], this wave's chunks kw + KW i
-  const float* Wj = W_hh + g * s_rep + (long)jc * H;
-  const float* Xj = XP ? W_ih + g * s_rep + (long)jc * width : nullptr;
-  const bool wvec = (H & 3) == 0 && ((uintptr_t)(W_hh + g * s_rep) & 15) == 0;
-  const bool xvec = XP && ((uintptr_t)(W_ih + g * s_rep) & 15) == 0;
-  bf16x8s w[NCW][3][LW ? 2 : 3];
-  bool beyond = false;
+  // Everything that a launch reads before its first step is requested before anything waits for it (a piece at a time, each loaded and
+  // split, was a serial chain of up to 12 trips to memory).  us per launch of one step, a piece at a time / so: H = 512, 4 workers of 64
+  // rows 23.3 / 21.0,  H = 320, 4 of 40 13.3 / 11.1,  H = 256, 4 of 16 10.8 / 10.2; of 10 steps, H = 450 (rows not aligned), 6 of 40 55.6 / 48.2.
+  // (In the backward kernel the same costs more registers, and its steps more than its start gains: 20 steps of H = 500, 8 of 64 rows 165.5 / 171.2.)
+  const __amdgpu_buffer_rsrc_t rw = weight_rsrc(W_hh + g * s_rep, 3 * H, H);
+  float4 wv[NCW][3][2];
 #pragma unroll
   for (int i = 0; i < NCW; ++i)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      float4 v[2];
-      weight_row_frag(Wj + (long)q * H * H, jok && kw + KW * i < nch, wvec, H, kw + KW * i, v);
-      beyond = beyond || split_beyond(v[0]) || split_beyond(v[1]);
-      const SplitFrag f = split_frag(v[0], v[1]);
-      w[i][q][0] = f.p[0];
-      w[i][q][1] = f.p[1];
-      if (LW) wl[((kw * NCW + i) * 3 + q) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[2]);  // (KW = 4: by two waves, the same)
-      else w[i][q][LW ? 0 : 2] = f.p[2];
-      if (NCW > 2) __builtin_amdgcn_sched_barrier(0);  // (or the pieces of all chunks take registers at once)
-    }
-  beyond = __any(beyond);
-  if (XP)
-    for (int u = wave; u < 3 * nchw; u += 8) {
-      float4 v[2];
-      weight_row_frag(Xj + (long)(u % 3) * H * width, jok, xvec, width, u / 3, v);
-      const SplitFrag f = split_frag(v[0], v[1]);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) wx[(u * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[p]);
-    }
+    for (int q = 0; q < 3; ++q) weight_row_load(rw, q * H + jc, jok && kw + KW * i < nch, H, kw + KW * i, wv[i][q]);
+  float4 xv[2];  // fragment u = 3 chunk + gate of the slice of W_ih, by wave u % 8
+  auto load_wx = [&](int u) {
+    if (u < 3 * nchw) weight_row_load(weight_rsrc(W_ih + g * s_rep, 3 * H, width), (u % 3) * H + jc, jok, width, u / 3, xv);
+  };
+  if (XP) load_wx(wave);
   const bool act = RB == 2 || wave < 4;             // this wave has outputs (uniform)
   const int qv = wave & 3, rbo = RB == 2 ? wave >> 2 : 0;
   const int row = r0 + rbo * 16 + 4 * lg + qv;      // this thread's element of the tile
@@ -392,6 +396,31 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
     }
   };
   load_x(0);
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8s w[NCW][3][LW ? 2 : 3];
+  bool beyond = false;
+  const int Ht = rarely(H);
+#pragma unroll
+  for (int i = 0; i < NCW; ++i)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      weight_row_tail(Ht, kw + KW * i, wv[i][q]);
+      beyond = beyond || split_beyond(wv[i][q][0]) || split_beyond(wv[i][q][1]);
+      const SplitFrag f = split_frag(wv[i][q][0], wv[i][q][1]);
+      w[i][q][0] = f.p[0];
+      w[i][q][1] = f.p[1];
+      if (LW) wl[((kw * NCW + i) * 3 + q) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[2]);  // (KW = 4: by two waves, the same)
+      else w[i][q][LW ? 0 : 2] = f.p[2];
+      __builtin_amdgcn_sched_barrier(0);  // (in the order of the loads: each piece frees the registers it came in)
+    }
+  beyond = __any(beyond);
+  if (XP)
+    for (int u = wave; u < 3 * nchw; u += 8) {
+      const SplitFrag f = split_frag(xv[0], xv[1]);
+      load_wx(u + 8);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) wx[(u * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[p]);
+    }
   __syncthreads();
   for (int t = 0; t < T; ++t) {
     // what does not depend on the recurrence is computed in front of the wait
@@ -432,7 +461,7 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
             for (int c = kw; c < nchw; c += KW) {
               float4 v[2], x[2];
               input_frag(rs, wd, B - r0, (rsel + rb) * 16 + lr, c, x);
-              weight_row_frag(Xr + (long)q * H * wd, jok, false, wd, c, v);
+              weight_row_frag(Xr + (long)q * H * wd, jok, wd, c, v);
               plain_mfmas(x, v, PC * c + 16 < wd, big[rb][q]);
             }
           }
@@ -464,7 +493,7 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
             for (int c = kw; c < nch; c += KW) {
               float4 v[2], x[2];
               exchange_frag(rs, nch, HP, rbx[rb], c, x);
-              weight_row_frag(Wr + (long)q * Hr * Hr, jok, false, Hr, c, v);
+              weight_row_frag(Wr + (long)q * Hr * Hr, jok, Hr, c, v);
               plain_mfmas(x, v, PC * c + 16 < HP, big[rb][q]);
             }
           }
