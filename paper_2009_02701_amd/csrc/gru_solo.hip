@@ -6,7 +6,8 @@
 // fits the registers of ONE compute unit, and batch rows are independent of each other.  So here a
 // workgroup owns 4 batch rows of one worker (or 8: solo_two_tiles; of very many rows 16, in a form of its own: solo_16_rows)
 // and ALL hidden units, and runs all T steps by itself.  There is no flag, no residency requirement and no ordering against other streams:
-// any number of workgroups may be launched.
+// any number of workgroups may be launched.  (Two layers that share a launch, below, do have flags: a workgroup waits, a bounded time, for
+// such as have drawn a ticket before it, so no residency is required of them either.)
 //
 // The products are v_mfma_f32_4x4x1_16b_f32 with the first operand broadcast: one instruction of 8 cycles
 // multiplies 4 batch rows x 1 step of the contraction with 64 columns of weights, at the full fp32 matrix
