@@ -142,6 +142,14 @@ struct hpsgd_ctx {
   // `small`: the same model in the first such layout that fits the static array, where layout 0 does not.
   int lean = 0;
   std::unique_ptr<hpsgd_ctx> small;
+  // Row pitch of a bf16 copy of a weight matrix of `w` columns: whole lines of 128 bytes.  At 1344 bytes (H = 672) every second row of a k-tile
+  // lies in two lines, and a CU's loads from the L2 arrive at 82 KB/us instead of 125.  us per local step, rows close together / on lines of
+  // their own: H = 650, 4 workers 1029 / 1018 (a round 1089 / 1080), H = 800, 4 workers 747 / 739, H = 480, 8 workers 905 / 900; H = 990, 8 workers 1209 / 1209
+  // (no gain there).  Narrower than 128 a pitch would be up to twice the row.  A layout that has to be
+  // small keeps the rows together.
+  long copy_pitch(long w) const { return lean || w < 128 ? w : (w + 63) / 64 * 64; }
+  long wih_pitch(int l) const { return stack_b && l == 1 ? Hp : copy_pitch(l == 0 ? Ep : Hp); }
+  long head_pitch() const { return copy_pitch(Hp); }
   int wgrad_parts(int M, int N, int Kd) const { return lean > 1 ? 1 : wgrad_splits(M, N, Kd, K); }
   bool resident = true;         // fp32 recurrence: one launch per run of time steps when supported
   bool device_scope = false;    // resident-weight launches exchange at device scope even where an XCD's L2 would do
@@ -322,7 +330,7 @@ int build_layout(hpsgd_ctx* c) {
         c->hsT.push_back(c->alloc(H * TB1p / 2));
         c->whhT.push_back(c->alloc((3 * H * H + 1) / 2));
         c->whhb.push_back(c->alloc((3 * H * H + 1) / 2));
-        c->wihbl.push_back(c->alloc(((l == 0 ? win0 : H) * 3 * H + 1) / 2));
+        c->wihbl.push_back(c->alloc((c->wih_pitch(l) * 3 * H + 1) / 2));
       }
       const size_t nr = lm ? TB : Bi, Vi = c->Vp;
       // the transposed logit gradients, or (the head of bf16 operands) the loss kernel's column sums
@@ -333,7 +341,7 @@ int build_layout(hpsgd_ctx* c) {
       c->woT = c->alloc(H * round_up(classes, 64) / 2);
       c->xb = c->alloc((TB * win0 + 1) / 2);
       c->wihb = c->alloc((wmax * 3 * H + 1) / 2);
-      c->wob = c->alloc((round_up(Vi, 8) * H + 1) / 2);
+      c->wob = c->alloc((round_up(Vi, 8) * c->head_pitch() + 1) / 2);
       c->dlogb = c->alloc((nr * round_up(classes, 64) + 1) / 2);
     }
     size_t wmax = H;
@@ -624,7 +632,7 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
     if (pad) {
       const int wp = l > 0 ? H : c->Ep;
       const bool up = c->stack_b && l == 1;  // (its input gradient is computed beside the recurrences, from the transposed copy)
-      if (!copy_padded(Wih, bfreg(c->wihbl[l]), wp, 2 * (long)c->wihbl[l].stride, up ? bfreg(c->wihT) : nullptr, up ? 3 * H : 0,
+      if (!copy_padded(Wih, bfreg(c->wihbl[l]), c->wih_pitch(l), 2 * (long)c->wihbl[l].stride, up ? bfreg(c->wihT) : nullptr, up ? 3 * H : 0,
                        up ? 2 * (long)c->wihT.stride : 0, 3 * H, wp, H, Hc, width) ||
           !copy_padded(Whh, bfreg(c->whhb[l]), H, 2 * (long)c->whhb[l].stride, bfreg(c->whhT[l]), 3 * H,
                        2 * (long)c->whhT[l].stride, 3 * H, H, H, Hc, Hc))
@@ -634,8 +642,8 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
     }
     if (fused_b && ntc && width % 8 == 0) {
       const long s_wb2 = 2 * (long)c->wihbl[l].stride;
-      if (cvt2_supported(Wih, 0, width, sR, bfreg(c->wihbl[l]), width, s_wb2, nullptr, 0, 0, 3 * H, width)) {
-        if (!copy2(Wih, width, bfreg(c->wihbl[l]), width, s_wb2, nullptr, 0, 0, 3 * H, width)) return HPSGD_EHIP;
+      if (cvt2_supported(Wih, 0, width, sR, bfreg(c->wihbl[l]), c->wih_pitch(l), s_wb2, nullptr, 0, 0, 3 * H, width)) {
+        if (!copy2(Wih, width, bfreg(c->wihbl[l]), c->wih_pitch(l), s_wb2, nullptr, 0, 0, 3 * H, width)) return HPSGD_EHIP;
         wc.wih[l] = true;
       }
     }
@@ -655,11 +663,11 @@ int weight_copies(hpsgd_ctx* c, const float* rin, long sR, int k0, int groups, f
     const size_t oW = c->eoff(c->i_head_w);
     const long s_wob = 2 * (long)c->wob.stride;
     if (pad) {
-      if (!copy_padded(rin + oW, bfreg(c->wob), H, s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc)) return HPSGD_EHIP;
+      if (!copy_padded(rin + oW, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc)) return HPSGD_EHIP;
       wc.head = true;
     } else if (ntc && fused_b && classes % 8 == 0 &&
-               cvt2_supported(rin + oW, 0, H, sR, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)) {
-      if (!copy2(rin + oW, H, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)) return HPSGD_EHIP;
+               cvt2_supported(rin + oW, 0, H, sR, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, classes, H)) {
+      if (!copy2(rin + oW, H, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, classes, H)) return HPSGD_EHIP;
       wc.head = true;
     }
   }
@@ -869,14 +877,14 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     // by its step kernels), head.W rounded once, the logit gradient emitted in bf16 by the loss kernel
     const bool headb =
         pad || (ntc && gru_fused_bf16_supported(H) && classes % 8 == 0 &&
-                cvt2_supported(rin + oW, 0, H, sRi, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H) &&
+                cvt2_supported(rin + oW, 0, H, sRi, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, classes, H) &&
                 softmax_ce_bf16_supported(logits, ldl, s_log, bfreg(c->dlogb), clp, s_dlb, classes));
     // bf16 copies of `n` workers' head matrices (one model's when the replicas are still its clones)
     auto head_copy = [&](const float* W, long s_W, int n, hipStream_t st) -> hipError_t {
-      if (!pad || (Hc == H && cvt2_supported(W, 0, H, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H)))
-        return launch_cvt2(W, 0, H, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, classes, H, n, st);
+      if (!pad || (Hc == H && cvt2_supported(W, 0, H, s_W, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, classes, H)))
+        return launch_cvt2(W, 0, H, s_W, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, classes, H, n, st);
       Cvt2Pack pk;
-      if (!cvt2_pack_push_padded(pk, W, Hc, s_W, bfreg(c->wob), H, s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc))
+      if (!cvt2_pack_push_padded(pk, W, Hc, s_W, bfreg(c->wob), c->head_pitch(), s_wob, nullptr, 0, 0, c->Vp, H, c->Vp, classes, Hc))
         return hipErrorInvalidValue;
       return launch_cvt2_pack(pk, n, st);
     };
@@ -991,7 +999,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
             va = NtView{bfreg(c->xb), 1, width, s_xb};
             xT_ready = true;
           }
-          if (wc.wih[l]) vb = NtView{bfreg(c->wihbl[l]), 1, width, wstride(c->wihbl[l])};  // made at the start of the step, or before it
+          if (wc.wih[l]) vb = NtView{bfreg(c->wihbl[l]), 1, c->wih_pitch(l), wstride(c->wihbl[l])};  // made at the start of the step, or before it
         }
         // The one copy of the head matrix that serves cloned replicas: beside the top layer's
         // input projection (between two resident-weight launches, when the synchronising stream
@@ -1126,7 +1134,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       }
       const long s_hb = 2 * (long)c->hb.stride;
       const NtView va{(const __bf16*)reg(c->hb) + (size_t)(lm ? B : T * B) * H, 1, H, s_hb};
-      const NtView vb{bfreg(c->wob), 1, H, s_wob};
+      const NtView vb{bfreg(c->wob), 1, c->head_pitch(), s_wob};
       role = HPSGD_ROLE_GEMM_HEAD;
       TRY(gemm2(s, groups, bf, nrows, classes, H, feats, H, s_top, 0, rin + oW, H, sRi, 1, logits, ldl,
                 s_log, EPI_BIAS, rin + ob, sRi, va, vb, 0.f, pad));
@@ -1143,7 +1151,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
       const int Kv = (int)round_up(classes, 8);  // (zeros from `classes` on, in both operands)
       // (the contractions over the classes, of the input gradient, and over the rows, of the weight gradient, run over
       // the rows of W, of the logit gradients and of h as they lie in memory)
-      const NtView vdl{bfreg(c->dlogb), 1, clp, s_dlb}, vw{bfreg(c->wob), 1, H, s_wob, 1};
+      const NtView vdl{bfreg(c->dlogb), 1, clp, s_dlb}, vw{bfreg(c->wob), 1, c->head_pitch(), s_wob, 1};
       const NtView vdo{vdl.p, 1, clp, s_dlb, 1}, vho{va.p, 1, H, s_hb, 1};
       const WgradTarget wt = wgrad_target(c->i_head_w);
       // The head's input gradient and weight gradient need the same logit gradient and nothing of
@@ -1547,7 +1555,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
           v_xT = NtView{bfreg(c->xT), 1, TBp, 2 * (long)c->xT.stride};
         }
         if (need_dx && wc.wih[l] && stepT) {  // (the row-major copy: the contraction runs over its rows)
-          v_wih = NtView{bfreg(c->wihbl[l]), 1, win, wstride(c->wihbl[l]), 1};
+          v_wih = NtView{bfreg(c->wihbl[l]), 1, c->wih_pitch(l), wstride(c->wihbl[l]), 1};
         } else if (need_dx) {
           HIP_TRY(launch_cvt_bf16(Wih, win, sRi, bfreg(c->wihT), 3 * H, 2 * (long)c->wihT.stride, 3 * H, win, true,
                                   groups, s));
