@@ -288,13 +288,13 @@ __device__ __forceinline__ void solo_fwd_body(const float* __restrict__ W_hh, co
 // BPTT of all steps.  dgx / dgh: gate gradients (blocks of B x 3H).  D: the gradient carried into the
 // last step (nullptr: zero); above: per-step gradient from the layer above (blocks of B x H) or
 // nullptr.  dbp[(g * RT + tile)][6H]: partial sums of the bias gradients (b_ih: r z n, b_hh: r z q).
-// (LINKED: k.in: `above` is written by this launch; a wait that was given up leaves NaN in loss[g] too.)
+// (LINKED: k.in: `above` is written by this launch.)
 template <int H8, int R, bool LINKED>
 __device__ __forceinline__ void solo_bwd_body(const float* __restrict__ W_hh, long s_rep, float* __restrict__ dgx,
                                               float* __restrict__ dgh, long s_dg, const float* __restrict__ D, long s_D,
                                               const float* __restrict__ above, long s_above, const float* __restrict__ sv,
                                               long s_sv, const float* __restrict__ hs, long s_hs, float* __restrict__ dbp,
-                                              int B, int H, int T, int RT, int g, int ty, const SoloLink& k, float* loss) {
+                                              int B, int H, int T, int RT, int g, int ty, const SoloLink& k) {
   using S = Solo<H8>;
   constexpr int KW = S::KB, NC = (KW + 15) / 16;
   __shared__ float dl[R * 4 * S::LB];
@@ -349,7 +349,6 @@ __device__ __forceinline__ void solo_bwd_body(const float* __restrict__ W_hh, lo
     if (LINKED && k.in && t >= 0 && (T - 1 - t) % kChunk == 0 && !link_chunk(k, T - 1 - t, T)) {
 #pragma unroll
       for (int r = 0; r < R; ++r) dc[r] = __builtin_nanf("");
-      if (tid == 0 && loss) loss[g] = __builtin_nanf("");
     }
   };
   In ia, ib;
@@ -465,7 +464,7 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
                     int B, int H, int T, int RT) {
   const int n_wg = (RT + R - 1) / R, g = blockIdx.x / n_wg, ty = (blockIdx.x - g * n_wg) * R;
   solo_bwd_body<H8, R, false>(W_hh, s_rep, dgx, dgh, s_dg, D, s_D, above, s_above, sv, s_sv, hs, s_hs, dbp, B, H, T, RT, g, ty,
-                              SoloLink{}, nullptr);
+                              SoloLink{});
 }
 
 // ---------------------------------------------------------------------------- two layers in one launch
@@ -479,7 +478,8 @@ gru_solo_bwd_kernel(const float* __restrict__ W_hh, long s_rep, float* __restric
 // words of all of a workgroup's waves.
 // A workgroup takes its part by ticket, in the order in which workgroups start, and waits only for those of lower tickets, which
 // run or have run: whatever else is on the chip, nothing waits for a place.  Every wait is bounded all the same: a given-up one
-// sets the abort word and makes NaN of everything behind it.
+// sets the abort word and makes NaN of everything behind it in the chain.  What a caller sees of it, NaN in the losses and the replicas' first
+// parameters, is written behind the step where the abort word is set (launch_poison_on_abort).
 namespace {
 
 // Extents of the product between the layers: W_ih split into bf16 parts in registers, NB blocks of 16 columns per wave, KC chunks of 32.
@@ -649,7 +649,7 @@ gru_stack_fwd_kernel(GruStackLayer lo, GruStackLayer up, const float* W_ih, cons
 template <int H8>
 __global__ void __launch_bounds__(Solo<H8>::NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_stack_bwd_kernel(GruStackLayer lo, GruStackLayer up, const float* W_ih, long s_rep, const float* D, long s_D, const float* above,
-                     long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv, int B, int H, int T, int RT, int n,
+                     long s_above, float* dx, long s_dx, long s_gx, long s_hs, long s_sv, int B, int H, int T, int RT, int n,
                      unsigned* sync, unsigned limit) {
   constexpr int W = Solo<H8>::NT / 64;
   int role, tile;
@@ -658,12 +658,12 @@ gru_stack_bwd_kernel(GruStackLayer lo, GruStackLayer up, const float* W_ih, long
   unsigned* words = sync + kLinkBase + (long)tile * kLinkWords + 36;
   if (role == 0) {
     solo_bwd_body<H8, 1, true>(up.W_hh, s_rep, up.gx, up.dgh, s_gx, D, s_D, above, s_above, up.sv, s_sv, up.hs, s_hs, up.dbp, B, H, T, RT,
-                               g, ty, SoloLink{words, nullptr, sync, limit, 0}, nullptr);
+                               g, ty, SoloLink{words, nullptr, sync, limit, 0});
   } else if (role < 3) {
     link_body<H8, true>(W_ih + g * s_rep, nullptr, up.gx + g * s_gx, dx + g * s_dx, B, H, T, ty, role - 1, words, words + 8 * role, sync, limit);
   } else {
     solo_bwd_body<H8, 1, true>(lo.W_hh, s_rep, lo.gx, lo.dgh, s_gx, nullptr, 0, dx, s_dx, lo.sv, s_sv, lo.hs, s_hs, lo.dbp, B, H, T, RT,
-                               g, ty, SoloLink{nullptr, words + 8, sync, limit, W}, loss);
+                               g, ty, SoloLink{nullptr, words + 8, sync, limit, W});
   }
 }
 
@@ -1098,14 +1098,14 @@ hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up
 }
 
 hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, long s_rep, const float* D, long s_D,
-                                const float* above, long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv,
+                                const float* above, long s_above, float* dx, long s_dx, long s_gx, long s_hs, long s_sv,
                                 int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
   if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
   const int RT = solo_tiles(B), n = groups * RT;
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
 #define HPSGD_STACK_BWD(H8)                                                                                                       \
   hipLaunchKernelGGL(gru_stack_bwd_kernel<H8>, dim3(32 * ((n + 7) / 8)), dim3(Solo<H8>::NT), 0, s, lo, up, W_ih, s_rep, D, s_D, above, s_above, dx, s_dx, \
-                     loss, s_gx, s_hs, s_sv, B, H, T, RT, n, sync, limit)
+                     s_gx, s_hs, s_sv, B, H, T, RT, n, sync, limit)
   HPSGD_SOLO_CASES(HPSGD_STACK_BWD)
 #undef HPSGD_STACK_BWD
   return hipGetLastError();
@@ -1331,7 +1331,7 @@ template <int HB, int UB, int V, bool LINKED>
 __device__ __forceinline__ void solo_bwd_bf16_body(const __bf16* __restrict__ WT, long s_wt, const float* __restrict__ above,
                                                    long s_above, const float* __restrict__ sv, long s_sv, const float* __restrict__ hs,
                                                    long s_hs, __bf16* __restrict__ dg4, long s_dg4, float* __restrict__ dbp, int Hc,
-                                                   int B, int T, int RT, int g, int ty, const SoloLink& k, float* loss) {
+                                                   int B, int T, int RT, int g, int ty, const SoloLink& k) {
   using S = SoloB<HB, UB, V>;
   constexpr int HP = S::HP, LP = S::LP4, NC3 = S::NC3, NCR = S::NCR, NCL = S::NCL;
   extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
@@ -1388,7 +1388,6 @@ __device__ __forceinline__ void solo_bwd_bf16_body(const __bf16* __restrict__ WT
 #pragma unroll
       for (int u = 0; u < UB; ++u)
         for (int v = 0; v < V; ++v) dc[u][v] = __builtin_nanf("");
-      if (tid == 0 && loss) loss[g] = __builtin_nanf("");
     }
   };
   wait_above(T - 1);
@@ -1498,7 +1497,7 @@ gru_solo_bwd_bf16_kernel(const __bf16* __restrict__ WT, long s_wt, const float* 
                          long s_dg4, float* __restrict__ dbp, int Hc, int B, int T, int RT) {
   const int g = blockIdx.x / RT;
   solo_bwd_bf16_body<HB, UB, V, false>(WT, s_wt, above, s_above, sv, s_sv, hs, s_hs, dg4, s_dg4, dbp, Hc, B, T, RT, g, blockIdx.x - g * RT,
-                                       SoloLink{}, nullptr);
+                                       SoloLink{});
 }
 
 // ---------------------------------------------------------------------------- two bf16 layers in one launch
@@ -1607,7 +1606,7 @@ gru_stack_fwd_bf16_kernel(GruStackLayerB lo, GruStackLayerB up, const __bf16* W_
 template <int HB, int UB>
 __global__ void __launch_bounds__(64 * HB / UB) __attribute__((amdgpu_waves_per_eu(1, 2)))
 gru_stack_bwd_bf16_kernel(GruStackLayerB lo, GruStackLayerB up, const __bf16* WT_ih, long s_wih, long s_wt, const float* above, long s_above,
-                          float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4, int Hc, int B, int T, int RT, int n,
+                          float* dx, long s_dx, long s_hs, long s_sv, long s_dg4, int Hc, int B, int T, int RT, int n,
                           unsigned* sync, unsigned limit) {
   constexpr int NW = HB / UB;
   int role, tile;
@@ -1622,8 +1621,7 @@ gru_stack_bwd_bf16_kernel(GruStackLayerB lo, GruStackLayerB up, const __bf16* WT
     const GruStackLayerB& l = first ? up : lo;
     solo_bwd_bf16_body<HB, UB, 1, true>((const __bf16*)l.WT, s_wt, first ? above : dx, first ? s_above : s_dx, l.sv, s_sv, l.hs, s_hs,
                                         (__bf16*)l.dg4, s_dg4, l.dbp, Hc, B, T, RT, g, ty,
-                                        SoloLink{first ? words : nullptr, first ? nullptr : words + 8, sync, limit, NW},
-                                        first ? nullptr : loss);
+                                        SoloLink{first ? words : nullptr, first ? nullptr : words + 8, sync, limit, NW});
   }
 }
 
@@ -1748,7 +1746,7 @@ hipError_t launch_gru_stack_fwd_bf16(const GruStackLayerB& lo, const GruStackLay
 }
 
 hipError_t launch_gru_stack_bwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* WT_ih, long s_wih, long s_wt,
-                                     const float* above, long s_above, float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4,
+                                     const float* above, long s_above, float* dx, long s_dx, long s_hs, long s_sv, long s_dg4,
                                      int Hc, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
   if (!gru_stack_bf16_supported(B, H, T, 2, groups) || Hc < 1 || Hc > H || !above || (s_dg4 & 7) != 0) return hipErrorInvalidValue;
   const int RT = B / 4, n = groups * RT;
@@ -1760,7 +1758,7 @@ hipError_t launch_gru_stack_bwd_bf16(const GruStackLayerB& lo, const GruStackLay
     static std::atomic<size_t> allowed{0};                                                                                   \
     if (const hipError_t e = allow_lds((const void*)gru_stack_bwd_bf16_kernel<HB, UB>, lds, allowed)) return e;              \
     hipLaunchKernelGGL((gru_stack_bwd_bf16_kernel<HB, UB>), dim3(32 * ((n + 7) / 8)), dim3(S::NT), lds, s, lo, up,           \
-                       (const __bf16*)WT_ih, s_wih, s_wt, above, s_above, dx, s_dx, loss, s_hs, s_sv, s_dg4, Hc, B, T, RT, n, sync, limit); \
+                       (const __bf16*)WT_ih, s_wih, s_wt, above, s_above, dx, s_dx, s_hs, s_sv, s_dg4, Hc, B, T, RT, n, sync, limit); \
   } while (0)
   HPSGD_SOLOB_CASES(HPSGD_STACKB_BWD)
 #undef HPSGD_STACKB_BWD

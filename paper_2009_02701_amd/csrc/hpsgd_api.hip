@@ -711,7 +711,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
   // worker 0's slice of the workspace, is every worker's operand (group stride 0)
   const bool shared = head_src != nullptr;
   auto wstride = [&](const Region& r) { return shared ? 0L : 2 * (long)r.stride; };
-  const unsigned* abort_word = nullptr;  // set when resident-weight recurrence kernels were launched
+  const unsigned* abort_word = nullptr;  // set when launches were made whose workgroups wait for each other
   c->last_resident = c->last_xproj = c->last_dw = 0;
   // Weight matrices whose SGD update is applied by the epilogue of their own gradient GEMM
   // (replica_out = replica_in - lr * dW, no gradient buffer round trip); every other
@@ -864,10 +864,8 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
     unsigned pbase = 0;
     unsigned ticket_launches = 0;  // launches of this step that placed their workgroups by ticket
     const size_t psync_words = use_stack ? gru_stack_sync_words(B, groups) : use_stack_b ? gru_stack_bf16_sync_words(B, groups) : exchange ? gru_persist_sync_words(B, groups, prow) : 0;
-    if (exchange) {
-      TRY0(resident.begin(s));
-      abort_word = psync;  // (cleared together with the first layer's h_0 below; the launches of two layers leave their NaN themselves)
-    }
+    if (exchange) TRY0(resident.begin(s));
+    abort_word = psync;  // (cleared together with the first layer's h_0 below)
     // ---- the head's operands
     const int nrows = lm ? TB : B;
     const size_t oW = c->eoff(c->i_head_w), ob = c->eoff(c->i_head_b);
@@ -1449,8 +1447,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_BWD;
         if (joined) {
           HIP_TRY(launch_gru_stack_bwd(stack_layer(0), stack_layer(1), rin + c->eoff(c->lidx[1].wih), sRi, d_zero ? nullptr : D, s_D, above, s_dx,
-                                       reg(c->dx_up), (long)c->dx_up.stride, loss_out, s_gx, s_hs, s_sv, B, H, T, groups, psync,
-                                       c->spin_limit, s));
+                                       reg(c->dx_up), (long)c->dx_up.stride, s_gx, s_hs, s_sv, B, H, T, groups, psync, c->spin_limit, s));
         }
       } else if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
@@ -1475,8 +1472,8 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_BWD;
         if (up_b)
           HIP_TRY(launch_gru_stack_bwd_bf16(stack_layer_b(0), stack_layer_b(1), bfreg(c->wihT), wstride(c->wihT), s_wtb, above, s_dx,
-                                            reg(c->dx_up), (long)c->dx_up.stride, loss_out, s_hs, s_sv, 2 * (long)c->dghx.stride, Hc, B, H, T,
-                                            groups, psync, c->spin_limit, s));
+                                            reg(c->dx_up), (long)c->dx_up.stride, s_hs, s_sv, 2 * (long)c->dghx.stride, Hc, B, H, T, groups,
+                                            psync, c->spin_limit, s));
         // (gate gradients r | z | n | q, in the place of the exchange buffer)
         if (!use_stack_b) HIP_TRY(launch_gru_solo_bwd_bf16(wtb, s_wtb, above, s_dx, sv, s_sv, hs, s_hs, bfreg(c->dghx), 2 * (long)c->dghx.stride, dbp, Hc,
                                          B, H, T, groups, c->K, s));

@@ -232,7 +232,8 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
                                float* dbp, int B, int H, int T, int groups, int workers, hipStream_t s);
 // Both layers of a model of two in one launch (each way), the upper one a few steps behind: gx and dgh are each layer's own (gx: the
 // upper layer's is written by the forward launch; the gate gradients replace it), dx receives the gradient that the upper layer passes on.
-// sync: gru_stack_sync_words() words, zero; sync[0] is the abort word.  A wait that was given up leaves NaN in everything behind it, and in loss.
+// sync: gru_stack_sync_words() words, zero; sync[0] is the abort word.  A wait that was given up sets it and
+// leaves NaN in everything behind it in the chain (launch_poison_on_abort behind the step shows it in the results).
 struct GruStackLayer {
   const float *W_hh, *b_hh;
   float *gx, *dgh, *hs, *sv, *dbp;
@@ -242,7 +243,7 @@ size_t gru_stack_sync_words(int B, int groups);
 hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, const float* b_ih, long s_rep, long s_gx,
                                 long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
 hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, long s_rep, const float* D, long s_D,
-                                const float* above, long s_above, float* dx, long s_dx, float* loss, long s_gx, long s_hs, long s_sv,
+                                const float* above, long s_above, float* dx, long s_dx, long s_gx, long s_hs, long s_sv,
                                 int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
 // the same with bf16 operands (H a multiple of 32 up to 256, B of 8): writes hb, hT (h_0 = 0 included) and dbp as the
 // resident-weight launches below do, and the gate gradients row-major as dg4 [T B][4H] = r | z | n | q; hs
@@ -273,7 +274,7 @@ hipError_t launch_gru_stack_fwd_bf16(const GruStackLayerB& lo, const GruStackLay
                                      int Hc, long s_gx, long s_hb, long s_hs, long s_sv, long ld_hT, long s_hT, int Bc, int B, int H, int T,
                                      int groups, bool exact, unsigned* sync, unsigned limit, hipStream_t s);
 hipError_t launch_gru_stack_bwd_bf16(const GruStackLayerB& lo, const GruStackLayerB& up, const void* WT_ih, long s_wih, long s_wt,
-                                     const float* above, long s_above, float* dx, long s_dx, float* loss, long s_hs, long s_sv, long s_dg4,
+                                     const float* above, long s_above, float* dx, long s_dx, long s_hs, long s_sv, long s_dg4,
                                      int Hc, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);
 // its transposes: dgxT [3H][ld_T] = (r | z | n)^T, dghT = (r | z | q)^T over R = T B rows, in one launch
 hipError_t launch_transpose_dg4(const void* dg4, long s_dg4, void* dgxT, void* dghT, long ld_T, long s_T, int R, int H, int groups,
