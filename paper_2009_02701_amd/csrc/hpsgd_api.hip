@@ -3,6 +3,7 @@
 // in the kernels declared in kernels.h.
 #include "../../include/hpsgd.h"
 
+#include <algorithm>
 #include <string>
 #include <mutex>
 #include <cstring>
@@ -153,7 +154,11 @@ struct hpsgd_ctx {
   int wgrad_parts(int M, int N, int Kd) const { return lean > 1 ? 1 : wgrad_splits(M, N, Kd, K); }
   bool resident = true;         // fp32 recurrence: one launch per run of time steps when supported
   bool device_scope = false;    // resident-weight launches exchange at device scope even where an XCD's L2 would do
-  unsigned spin_limit = 1u << 20;  // bound of every wait inside those launches
+  static constexpr unsigned kSpinLimit = 1u << 20;
+  unsigned spin_limit = kSpinLimit;  // bound of every wait inside those launches
+  // ... inside the launches of two narrow layers: these wait only for workgroups that run, and a model that takes them steps with any limit
+  // as it does layer by layer, without a wait.  (0 is the test's limit: every wait fails.)
+  unsigned link_limit() const { return spin_limit ? std::max(spin_limit, kSpinLimit) : 0u; }
   size_t last_commit_params = 0;  // parameters per worker that the commit kernel handled last step
   int last_resident = 0, last_xproj = 0, last_dw = 0;  // GRU layers of the last step, see hpsgd_recurrence_info
   unsigned timer_mask = 0;
@@ -1045,7 +1050,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_FWD;
         if (l > 0)
           HIP_TRY(launch_gru_stack_fwd(stack_layer(0), stack_layer(1), Wih0, rin + c->eoff(c->lidx[1].bih), sRi, s_gx, s_hs, s_sv, B, H, T,
-                                       groups, psync, c->spin_limit, s));
+                                       groups, psync, c->link_limit(), s));
         ++c->last_resident;
       } else if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
@@ -1067,7 +1072,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_FWD;
         if (l > 0)
           HIP_TRY(launch_gru_stack_fwd_bf16(stack_layer_b(0), stack_layer_b(1), bfreg(c->wihbl[1]), wstride(c->wihbl[1]), s_wb, sRi, Hc, s_gx,
-                                            s_hb, s_hs, s_sv, TB1p, s_hT, Bc, B, H, T, groups, exact_gates, psync, c->spin_limit, s));
+                                            s_hb, s_hs, s_sv, TB1p, s_hT, Bc, B, H, T, groups, exact_gates, psync, c->link_limit(), s));
         ++c->last_resident;
       } else if (persist_b && use_solo_b) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
@@ -1447,7 +1452,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         role = HPSGD_ROLE_GEMM_REC_BWD;
         if (joined) {
           HIP_TRY(launch_gru_stack_bwd(stack_layer(0), stack_layer(1), rin + c->eoff(c->lidx[1].wih), sRi, d_zero ? nullptr : D, s_D, above, s_dx,
-                                       reg(c->dx_up), (long)c->dx_up.stride, s_gx, s_hs, s_sv, B, H, T, groups, psync, c->spin_limit, s));
+                                       reg(c->dx_up), (long)c->dx_up.stride, s_gx, s_hs, s_sv, B, H, T, groups, psync, c->link_limit(), s));
         }
       } else if (use_solo) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
@@ -1473,7 +1478,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
         if (up_b)
           HIP_TRY(launch_gru_stack_bwd_bf16(stack_layer_b(0), stack_layer_b(1), bfreg(c->wihT), wstride(c->wihT), s_wtb, above, s_dx,
                                             reg(c->dx_up), (long)c->dx_up.stride, s_hs, s_sv, 2 * (long)c->dghx.stride, Hc, B, H, T, groups,
-                                            psync, c->spin_limit, s));
+                                            psync, c->link_limit(), s));
         // (gate gradients r | z | n | q, in the place of the exchange buffer)
         if (!use_stack_b) HIP_TRY(launch_gru_solo_bwd_bf16(wtb, s_wtb, above, s_dx, sv, s_sv, hs, s_hs, bfreg(c->dghx), 2 * (long)c->dghx.stride, dbp, Hc,
                                          B, H, T, groups, c->K, s));
