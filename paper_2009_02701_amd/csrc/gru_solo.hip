@@ -492,6 +492,8 @@ struct LinkShape {
 
 // The chunks c = odd, odd + 2, .. of a tile.  Forward: out[t] = in[t] W^T + bias, backward out[t] = in[t] W, over t from the end.
 // W: 3H x H, row-major.  in: blocks of B x KD, out: blocks of B x ND.  Row m = 4 s + r of a product is row r of the tile at the chunk's step s.
+// A product of a launch of its own has the fp32 instruction at these sizes.  The split is as exact for operands of at least 2^-110; a chunk with a
+// smaller one (zero is none), and every chunk of a wave with such a weight, takes that instruction too.
 template <int H8, bool BWD>
 __device__ __forceinline__ void link_body(const float* __restrict__ W, const float* __restrict__ bias, const float* in, float* out, int B,
                                           int H, int T, int ty, int odd, unsigned* in_words, unsigned* out_words, unsigned* abort_w,
@@ -499,7 +501,7 @@ __device__ __forceinline__ void link_body(const float* __restrict__ W, const flo
   using L = LinkShape<H8, BWD>;
   constexpr int NB = L::NB, KC = L::KC;
   __shared__ u32x4s al[KC * 3 * 64];  // the chunk's operands, split: [chunk of 32][part][lane]
-  __shared__ int go;
+  __shared__ int go, low[L::W];       // low: a wave has split an operand below 2^-110
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lg = lane >> 4;
   const int KD = BWD ? 3 * H : H, ND = BWD ? H : 3 * H;
   // (a piece of four at the end of `in` may reach three words beyond it)
@@ -519,15 +521,18 @@ __device__ __forceinline__ void link_body(const float* __restrict__ W, const flo
     }
   };
   SplitFrag wf[KC][NB];
+  bool low_w = false;
 #pragma unroll
   for (int c = 0; c < KC; ++c)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       float4 v[2];
       w_frag(b, c, H, v);
+      low_w = low_w || split_below(v[0], v[1]);
       wf[c][b] = split_frag(v[0], v[1]);
       __builtin_amdgcn_sched_barrier(0);  // (or the pieces of all chunks take registers at once)
     }
+  low_w = __any(low_w) != 0;
   float bv[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) bv[b] = !BWD && col(b) < 3 * H ? bias[col(b)] : 0.f;
@@ -556,18 +561,23 @@ __device__ __forceinline__ void link_body(const float* __restrict__ W, const flo
         v[h].w = k + 3 < KD ? v[h].w : 0.f;
       }
     };
+    bool low_a = false;
 #pragma unroll
     for (int i = 0; i < (KC + L::W - 1) / L::W; ++i) {
       const int c = w + i * L::W;
       if (c < KC) {  // (uniform)
         float4 v[2];
         a_frag(c, KD, v);
+        low_a = low_a || split_below(v[0], v[1]);
         const SplitFrag f = split_frag(v[0], v[1]);
 #pragma unroll
         for (int p = 0; p < 3; ++p) al[(c * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4s, f.p[p]);
       }
     }
+    low_a = __any(low_a) != 0;
+    if (lane == 0) low[w] = low_a;
     __syncthreads();
+    const bool again = low_w || __any(low[lane & (L::W - 1)]);
     floatx4 big[NB], small[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) big[b] = small[b] = (floatx4){0.f, 0.f, 0.f, 0.f};
@@ -581,7 +591,7 @@ __device__ __forceinline__ void link_body(const float* __restrict__ W, const flo
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       big[b] += small[b];
-      if (__builtin_expect(any_beyond(big[b]), 0)) {  // again with the fp32 instruction
+      if (__builtin_expect(again || any_beyond(big[b]), 0)) {  // with the fp32 instruction
         const int Hr = rarely(H);
         big[b] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1

@@ -20,6 +20,7 @@
 // inputs N(0,1) times 1e-33 / 1e-34 / 1e-35 / 1e-36 have errors of 2.1e-7 / 5.5e-7 / 5.2e-6 / 5.0e-5, with the fp32 instruction 2.9e-7 /
 // 2.9e-7 / 2.9e-7 / 4.1e-7; a resident recurrence (H = 300, 8 steps) with head weights of up to 0.06 times 1e-28 / 1e-32 /
 // 1e-34 has 1.5e-7 / 5.0e-6 / 4.9e-4 in dW_hh, with the fp32 instruction 2.0e-7 / 2.1e-7 / 2.1e-7.
+// The product between two narrow layers in one launch, which had the fp32 instruction as a launch of its own, looks for such values and keeps it there.
 // Of one term the fp32 instruction gives the rounded product, the six bf16 ones do not: callers keep it for contractions of up to
 // three (the share of dW_hh that a recurrence accumulates takes the six of any batch).
 #pragma once
@@ -98,6 +99,12 @@ __device__ __forceinline__ void plain_mfmas(const float4 (&a)[2], const float4 (
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].z, w[h].z, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h].w, w[h].w, acc, 0, 0, 0);
   }
+}
+// whether one of a fragment's values (zero is none) is below 2^-110, where the parts lose low bits
+__device__ __forceinline__ bool split_below(const float4& lo, const float4& hi) {
+  auto size = [](float v) { return (__builtin_bit_cast(uint32_t, v) & 0x7fffffffu) - 1u; };
+  const uint32_t l = min(min(size(lo.x), size(lo.y)), min(size(lo.z), size(lo.w))), h = min(min(size(hi.x), size(hi.y)), min(size(hi.z), size(hi.w)));
+  return min(l, h) < 0x08800000u - 1u;
 }
 __device__ __forceinline__ bool any_beyond(const floatx4& v) {
   const float s = __builtin_fmaf(v[0], 0.f, __builtin_fmaf(v[1], 0.f, __builtin_fmaf(v[2], 0.f, v[3] * 0.f)));
