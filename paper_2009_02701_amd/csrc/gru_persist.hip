@@ -318,6 +318,10 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
   constexpr bool XP = XNB > 0;
   constexpr int XB = XP ? XNB : 1;
   constexpr bool LW = persist_fwd_lw(NCW, XNB, RBW);  // the smallest parts of W_hh lie in LDS
+  // The split is as exact as the fp32 instruction, which a projection by a product of few tiles has, for operands of at least 2^-110.  Beyond
+  // H = 512, where every projection of a width that fits is made here, a step's input with a smaller one (zero is none), and every step
+  // of a workgroup with such a weight, takes that instruction.
+  constexpr bool LOW = XP && KW == 8 && NCW > 2;
   constexpr int NP = XP ? 4 : 3;             // planes of partial sums: r, z, q (+ the x part of n)
   const int NJ = (H + PJ - 1) / PJ, HP = NJ * PJ, RT = (B + PRT - 1) / PRT;
   const int nch = (HP + PC - 1) / PC, nchw = XP ? (width + PC - 1) / PC : 0;
@@ -414,14 +418,20 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       __builtin_amdgcn_sched_barrier(0);  // (in the order of the loads: each piece frees the registers it came in)
     }
   beyond = __any(beyond);
-  if (XP)
+  bool low_w = false;
+  if (XP) {
     for (int u = wave; u < 3 * nchw; u += 8) {
+      if (LOW) low_w = low_w || split_below(xv[0], xv[1]);
       const SplitFrag f = split_frag(xv[0], xv[1]);
       load_wx(u + 8);
 #pragma unroll
       for (int p = 0; p < 3; ++p) wx[(u * 3 + p) * 64 + lane] = __builtin_bit_cast(u32x4_t, f.p[p]);
     }
+    low_w = __any(low_w) != 0;
+    if (LOW && lane == 0) reinterpret_cast<unsigned char*>(lds_flag + 2)[wave] = low_w;
+  }
   __syncthreads();
+  if (LOW) low_w = (lds_flag[2] | lds_flag[3]) != 0;
   for (int t = 0; t < T; ++t) {
     // what does not depend on the recurrence is computed in front of the wait
     const float gxv[3] = {gxn[0], gxn[1], gxn[2]};
@@ -433,6 +443,9 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       accx[rb] = (floatx4){0.f, 0.f, 0.f, 0.f};
     }
     if (XP) {
+      bool low[RBW];
+#pragma unroll
+      for (int rb = 0; rb < RBW; ++rb) low[rb] = low_w;
 #pragma unroll
       for (int i = 0; i < XB; ++i) {
         const int c = kw + KW * i;
@@ -443,11 +456,14 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
 #pragma unroll
           for (int p = 0; p < 3; ++p) wq[q].p[p] = __builtin_bit_cast(bf16x8s, wx[((c * 3 + q) * 3 + p) * 64 + lane]);
 #pragma unroll
-        for (int rb = 0; rb < RBW; ++rb) split_mfmas(split_frag(xa[rb][i][0], xa[rb][i][1]), wq, big[rb], small[rb]);
+        for (int rb = 0; rb < RBW; ++rb) {
+          if (LOW) low[rb] = low[rb] || split_below(xa[rb][i][0], xa[rb][i][1]);
+          split_mfmas(split_frag(xa[rb][i][0], xa[rb][i][1]), wq, big[rb], small[rb]);
+        }
       }
 #pragma unroll
       for (int rb = 0; rb < RBW; ++rb) {
-        bool redo = false;
+        bool redo = LOW && __any(low[rb]) != 0;
 #pragma unroll
         for (int q = 0; q < 3; ++q) redo = any_beyond(big[rb][q] + small[rb][q]) || redo;
         if (__builtin_expect(redo, 0)) {
