@@ -550,7 +550,8 @@ __device__ __forceinline__ bool dlx_tile(const GemmNtDesc& d, unsigned bid, int&
 }
 
 // bid: the workgroup's index among those of this product (blockIdx.x, unless a launch holds two products)
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO = false, bool BO = false>
+// TAIL: N may be off 4
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO, bool BO, bool TAIL>
 __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
   constexpr int BM = Sh::BM, BN = Sh::BN, IPW = Sh::IPW, CP = Sh::CP, NT = Sh::NT;
@@ -770,7 +771,7 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
       if (fast) {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) w[COMMIT ? p : 0] = nt_load4(old_row(p) + col);
-      } else if (col < d.N) {  // the last one to three columns as single words, all requested at once as well
+      } else if (TAIL && col < d.N) {  // the last one to three columns as single words, all requested at once as well
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
           const float* wr = old_row(p);
@@ -807,7 +808,7 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
         }
         nt_store4(C + (long)row * d.ldc + col, o);
       }
-    } else if (col < d.N) {
+    } else if (TAIL && col < d.N) {
       float bv[3];
 #pragma unroll
       for (int e = 0; e < 3; ++e) bv[e] = !COMMIT && bias ? bias[min(col + e, d.N - 1)] : 0.f;
@@ -829,21 +830,21 @@ __device__ __forceinline__ void dlx_body(GemmNtDesc d, unsigned bid) {
   }
 }
 
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false, bool AO = false, bool BO = false>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false, bool AO = false, bool BO = false, bool TAIL = true>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gemm_bf16_dlx_kernel(GemmNtDesc d) {
-  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO>(d, blockIdx.x);
+  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO, TAIL>(d, blockIdx.x);
 }
 
 // Two independent products of the same form in one launch: the first blocks0 workgroups (a
 // multiple of 8, so that a workgroup's XCD is the same as in a launch of its own) are d0's, the
 // rest d1's.  For two products that would otherwise follow each other on one stream although
 // neither needs the other: the second one's tiles fill the first one's last, partial round.
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED = false, bool TAIL = true>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gemm_bf16_dlx_pair_kernel(GemmNtDesc d0, GemmNtDesc d1, unsigned blocks0) {
   const bool first = blockIdx.x < blocks0;  // (uniform)
-  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED>(first ? d0 : d1, first ? blockIdx.x : blockIdx.x - blocks0);
+  dlx_body<COMMIT, WGM, WGN, TM, TN, S, GATED, false, false, TAIL>(first ? d0 : d1, first ? blockIdx.x : blockIdx.x - blocks0);
 }
 
 // Up to three products that need nothing of each other in one launch of 128 x 128 tiles, of any of the kinds that a
@@ -869,11 +870,16 @@ gemm_bf16_multi_kernel(GemmNtPack pk) {
   }
 }
 
-template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO, bool BO>
+template <bool COMMIT, int WGM, int WGN, int TM, int TN, int S, bool GATED, bool AO, bool BO, bool TAIL = true>
 hipError_t launch_dlx_form(const GemmNtDesc& d, hipStream_t s) {
+  // An update of a width of whole pieces of four has no last columns: behind the branch between their loads and the whole
+  // pieces' all old values wait for each other, and it holds six registers more.  us, with that branch / without, 8 workers, Kd = 1120:
+  // 3072 x 1024 172.8 / 171.7, two of them as a pair (a narrower second one) 152.7 / 151.5, 10 000 x 1024 409.7 / 409.0.
+  if constexpr (COMMIT && TAIL)
+    if (d.N % 4 == 0) return launch_dlx_form<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO, false>(d, s);
   using Sh = DlxShape<WGM, WGN, TM, TN, S>;
   static std::atomic<size_t> allowed{0};
-  const auto kernel = gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO>;
+  const auto kernel = gemm_bf16_dlx_kernel<COMMIT, WGM, WGN, TM, TN, S, GATED, AO, BO, TAIL>;
   if (const hipError_t e = allow_lds((const void*)kernel, Sh::LDS, allowed)) return e;
   const int tm = (d.M + Sh::BM - 1) / Sh::BM, tn = (d.N + Sh::BN - 1) / Sh::BN;
   const int total = tm * tn * d.groups * (d.splits > 1 ? d.splits : 1);
@@ -970,11 +976,14 @@ hipError_t launch_gemm_bf16_multi(const GemmBf16Args* a, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool GATED>
+template <bool GATED, bool TAIL = true>
 static hipError_t launch_pair_form(const GemmNtDesc& d0, const GemmNtDesc& d1, hipStream_t s) {
+  if constexpr (TAIL)
+    if (d0.N % 4 == 0 && d1.N % 4 == 0) return launch_pair_form<GATED, false>(d0, d1, s);
   using Sh = DlxShape<2, 4, 3, 2, 2>;
   static std::atomic<size_t> allowed{0};
-  if (const hipError_t e = allow_lds((const void*)gemm_bf16_dlx_pair_kernel<true, 2, 4, 3, 2, 2, GATED>, Sh::LDS, allowed)) return e;
+  const auto kernel = gemm_bf16_dlx_pair_kernel<true, 2, 4, 3, 2, 2, GATED, TAIL>;
+  if (const hipError_t e = allow_lds((const void*)kernel, Sh::LDS, allowed)) return e;
   auto blocks = [](const GemmNtDesc& d) {
     const long total = (long)((d.M + Sh::BM - 1) / Sh::BM) * ((d.N + Sh::BN - 1) / Sh::BN) * d.groups;
     return (unsigned)(8 * ((total + 7) / 8));
@@ -982,7 +991,7 @@ static hipError_t launch_pair_form(const GemmNtDesc& d0, const GemmNtDesc& d1, h
   const unsigned b0 = blocks(d0), b1 = blocks(d1);
   KernelTimer kt(KID_GEMM_BF16_DLX192_COMMIT,
                  2.0 * d0.M * d0.N * (double)d0.Kd * d0.groups + 2.0 * d1.M * d1.N * (double)d1.Kd * d1.groups, s);
-  hipLaunchKernelGGL((gemm_bf16_dlx_pair_kernel<true, 2, 4, 3, 2, 2, GATED>), dim3(b0 + b1), dim3(Sh::NT), Sh::LDS, s, d0, d1, b0);
+  hipLaunchKernelGGL(kernel, dim3(b0 + b1), dim3(Sh::NT), Sh::LDS, s, d0, d1, b0);
   return hipGetLastError();
 }
 

@@ -127,3 +127,21 @@ def test_no_fragment_is_touched_before_its_wait(tmp_path):
     written_out = [n for n in found if "gemm_bf16_dlx" in n]
     assert len(written_out) >= 3 * 7 and all(found[n][1] > 0 for n in written_out), sorted(found)
     assert not {n: b[:3] for n, (b, _) in found.items() if b}
+
+
+def test_updates_of_whole_columns_have_no_loads_of_single_words(tmp_path):
+    """Every form of an 8-wave update has a kernel for widths of whole pieces of four: the early loads of the last one to three
+    columns make the old values of all columns wait for each other."""
+    out = str(tmp_path / "listing.s")
+    flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "--cuda-device-only", "-S", "-o", out,
+                           os.path.join(ROOT, "paper_2009_02701_amd", "csrc", "gemm_bf16_nt.hip")])
+    forms = collections.defaultdict(list)
+    with open(out) as f:
+        for name, body in kernels(f.read()):
+            m = re.search(r"gemm_bf16_dlx_(kernel|pair_kernel)ILb1E((?:L[ib]\d+E)+)E", name)
+            if m:  # shape, gate blocks and (not of a pair) how the operands lie
+                form = re.findall(r"L[ib]\d+E", m.group(2))[:8 if m.group(1) == "kernel" else 6]
+                forms[m.group(1), tuple(form)].append(len(re.findall(r"\bglobal_load_dword v", body)))
+    assert len(forms) == 3 * 3 + 2, sorted(forms)
+    assert all(min(n) == 0 for n in forms.values()), dict(forms)
