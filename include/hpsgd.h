@@ -324,7 +324,8 @@ int hpsgd_merge_snapshot(float *global, const float *const *replicas, float *sna
  * Where products that need nothing of each other share a launch, the launch counts once: the bf16
  * head's input and weight gradient under HPSGD_ROLE_GEMM_HEAD, a layer's weight gradients and the
  * input gradient beside them under HPSGD_ROLE_GEMM_WGRAD, an fp32 step's products under the role that
- * is current when they are issued.  With an auxiliary stream set (hpsgd_set_aux_stream) products that
+ * is current when they are issued; and two narrow layers' recurrence, a launch each way, under the two recurrence roles
+ * (in bf16 the lower layer's gate gradients are transposed in a launch of the backward one).  With an auxiliary stream set (hpsgd_set_aux_stream) products that
  * are launches of their own run beside others: the bf16 head's two then share one pair (counted as two
  * launches), and a launch that the library issues on the auxiliary stream alone (a layer's
  * input-gradient GEMM beside its weight-gradient GEMMs) is not timed. */
@@ -357,14 +358,14 @@ size_t hpsgd_commit_kernel_params(const hpsgd_ctx *ctx);
 /* The same per KERNEL instead of per role: while a kernel's bit is set in the mask, every launch
  * of that kernel inside hpsgd_local_step(_all)(_acc) is bracketed by a HIP event pair on the
  * stream the launch goes to (the auxiliary stream included), and the launch's algorithmic work
- * is added up: flops (2 M N Kd per group; a recurrence launch 2 B 3H H per time step, plus the
- * products it fuses) for the contractions, bytes (each operand once) for the streaming kernels.
+ * is added up: flops (2 M N Kd per group; a recurrence launch 2 B 3H H per time step and layer, plus the
+ * products it fuses, but for the one between two layers) for the contractions, bytes (each operand once) for the streaming kernels.
  * hpsgd_kernel_timer_read waits for the recorded events, returns the number of timed launches of
- * `kernel` (one that holds several bf16 products of a layer or of the head counts as that many), their
+ * `kernel` (one that holds several bf16 products of a layer or of the head, or two layers' recurrences, counts as that many), their
  * summed duration in milliseconds and their summed work, and clears that kernel.
  * hpsgd_kernel_name gives the name a kernel trace shows (template arguments included where they tell
  * forms apart) of the kernel an id is named after.  Counted under the same id are
- *   GRU_FWD_PERSIST, GRU_BWD_PERSIST (_BF16)  the recurrences without an exchange, gru_solo*_kernel
+ *   GRU_FWD_PERSIST, GRU_BWD_PERSIST (_BF16)  the narrow layers' recurrences, gru_solo*_kernel and gru_stack_*_kernel
  *   GEMM_BF16_DL, _DL_COMMIT     gemm_bf16_multi_kernel, under the latter as soon as one of its products
  *                                is an update, the input gradient beside it included
  *   GEMM_BF16_DLX192_COMMIT      gemm_bf16_dlx_pair_kernel (two updates; one launch)

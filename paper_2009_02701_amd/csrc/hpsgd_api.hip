@@ -1042,9 +1042,10 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
             HIP_TRY(launch_fill_zero_2d((float*)hT, TB1p / 2, H, B / 2, c->hsT[l].stride, groups, s));
         }
       }
-      // one event pair around the whole time loop when its launches are all of one role
+      // one event pair around the whole time loop when its launches are all of one role (two layers' one launch is issued for the upper one)
       const bool persist_b = fused_b && use_persist_b && hT != nullptr;
-      TimerScope loop_fwd(c, HPSGD_ROLE_GEMM_REC_FWD, s, (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
+      const bool with_upper = (use_stack || use_stack_b) && l == 0;
+      TimerScope loop_fwd(c, HPSGD_ROLE_GEMM_REC_FWD, s, with_upper ? 0 : (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
       c->timer_nested = loop_fwd.active() && (fused || fused_b || use_solo || persist);
       if (use_stack) {
         role = HPSGD_ROLE_GEMM_REC_FWD;
@@ -1446,7 +1447,7 @@ int run_step(hpsgd_ctx* c, int k0, int groups, const float* rin, float* rout, si
                     grad + c->eoff(c->lidx[l].whh), H, sG, epi, nullptr, 0, bg);
       };
       {
-      TimerScope loop_bwd(c, HPSGD_ROLE_GEMM_REC_BWD, s, (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
+      TimerScope loop_bwd(c, HPSGD_ROLE_GEMM_REC_BWD, s, use_stack && !joined ? 0 : (persist || persist_b || use_solo) ? 1 : (fused || fused_b) ? T : 0);
       c->timer_nested = loop_bwd.active() && (fused || fused_b || use_solo || persist);
       if (use_stack) {
         role = HPSGD_ROLE_GEMM_REC_BWD;
