@@ -84,3 +84,33 @@ def test_static_workspace_entry_point_rejects_models_beyond_its_array():
                                          C.c_float(0.1), None, None)
     assert rc == 5  # HPSGD_EWORKSPACE
     assert float(R.abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("base,sizes,tol", [
+    ("gru_cls", dict(layers=2, input=40, hidden=100, batch=20, seq_len=44, classes=7, K=4), TOL_FP32),
+    ("gru_lm", dict(prec="fp32", layers=2, vocab=150, embed=40, hidden=100, batch=20, seq_len=35, K=4), TOL_FP32),
+    ("gru_lm", dict(prec="bf16", layers=2, vocab=203, embed=24, hidden=128, batch=16, seq_len=22, K=4), TOL_BF16),
+])
+def test_static_workspace_entry_point_with_the_layers_one_after_the_other(base, sizes, tol):
+    """Two narrow layers that fit the array only without the second buffers of their joint launches keep all else of the
+    usual layout: a recurrence launch per layer where that has one for both."""
+    cfg = wl.scaled(wl.CONFIGS[base], lr=8.0, **sizes)
+    (r0, l0), (r1, l1) = _both_entry_points(cfg, steps=1, fits=False)
+    start = torch.from_numpy(hb.Context(cfg).flatten(wl.init_params(cfg))).to(DEV)
+    assert float((r0 - r1).abs().max()) <= tol * float((r0 - start).abs().max())
+    assert torch.allclose(l0, l1, rtol=tol, atol=0)
+    init, shards, orders, _ = workload(cfg)
+    tr = harness.Trainer(cfg, init, shards, orders, device=DEV)
+    tr.gather(0)
+    tr.sync_all(0)
+    fwd = tr.ctx.role_names().index("gemm_recurrent_fwd")
+    tr.ctx.timer_enable([fwd])
+    for joint in (True, False):
+        if joint:
+            tr.local_step(0, cfg["lr"])
+        else:
+            tr.ctx.local_step_all_static(tr.R[0], tr.R[0], tr.xb, tr.yb, cfg["lr"], tr.loss)
+        torch.cuda.synchronize()
+        assert tr.ctx.timer_read(fwd)[0] == (1 if joint else 2)
+        assert tr.ctx.recurrence_info()[0] == 2
+    tr.ctx.timer_enable([])
