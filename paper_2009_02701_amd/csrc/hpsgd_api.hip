@@ -84,7 +84,7 @@ struct hpsgd_ctx {
   // transposed bf16 copies that bring the weight-gradient and input-gradient GEMMs into the
   // contraction-contiguous form (bf16 precision only); sizes in floats = bf16 count / 2
   Region dgxT, dghT, xT, dlogT, wihT, woT;
-  Region xb, wihb, wob, dlogb;  // row-major bf16 copies: layer-0 input, W_ih, head.W, dlogits
+  Region xb, wob, dlogb;  // row-major bf16 copies: layer-0 input, head.W, dlogits
   Region colpart;               // per block of logits rows: column sums of the logit gradient
   std::vector<Region> hsT;
   std::vector<Region> whhT;     // per layer: transposed bf16 W_hh, made in the forward pass
@@ -345,7 +345,6 @@ int build_layout(hpsgd_ctx* c) {
       c->wihT = c->alloc(wmax * 3 * H / 2);
       c->woT = c->alloc(H * round_up(classes, 64) / 2);
       c->xb = c->alloc((TB * win0 + 1) / 2);
-      c->wihb = c->alloc((wmax * 3 * H + 1) / 2);
       c->wob = c->alloc((round_up(Vi, 8) * c->head_pitch() + 1) / 2);
       c->dlogb = c->alloc((nr * round_up(classes, 64) + 1) / 2);
     }

@@ -273,3 +273,15 @@ def test_prepare_clones_checks_its_arguments_on_the_host():
     assert lib.hpsgd_prepare_clones(ctx._h, a(0), a(1), C.c_size_t(ctx.P - 1), ws, 0, None) == 3   # stride < P
     assert lib.hpsgd_prepare_clones(ctx._h, a(0), a(1), C.c_size_t(ctx.stride), a(1), 0, None) == 4  # workspace on the replicas
     assert lib.hpsgd_prepare_clones(ctx._h, a(0), a(1), C.c_size_t(ctx.stride), ws, 0, None) == 0
+
+
+def test_a_wider_layer_input_costs_only_the_copies_that_are_read():
+    """Bytes of a bf16 model's workspace per column of the first layer's input: the gradients of embed.E and W_ih, the
+    embedded tokens and their gradient in fp32, them and W_ih in bf16, each row-major and transposed, and nothing else."""
+    V, H, B, T = 1000, 256, 16, 12
+
+    def size(embed):
+        cfg = wl.scaled(wl.CONFIGS["gru_lm"], layers=1, vocab=V, embed=embed, hidden=H, batch=B, seq_len=T, K=1)
+        return hb.Context(cfg).workspace_bytes
+
+    assert size(576) - size(512) == 64 * (4 * (V + 3 * H) + 2 * 4 * T * B + 2 * 2 * T * B + 2 * 2 * 3 * H)
