@@ -1085,18 +1085,24 @@ hipError_t launch_gru_solo_bwd(const float* W_hh, long s_rep, float* dgx, float*
 }
 
 // Both layers in one launch, each way: where the chip has room for the four workgroups of every worker's tiles at once - one per CU beyond
-// 64 units, three up to there.  Local steps, layer by layer / this, us (H, batch, workers, steps):
+// 64 units, two up to there.  Up to there a classifier's may be half as many again, of which the last start as the first end:
+// the upper layer has nothing but the recurrence to do, and the launches between the layers are gone.  (A language model's step has products enough beside
+// its recurrences, and gains nothing.)  Local steps, layer by layer / this, us (H, batch, workers, steps):
 //   (100, 20, 4, 50) 298 / 195 a round   (128, 16, 4, 35) 266 / 181   (64, 20, 2, 35) 146 / 107   (32, 8, 4, 20) 88 / 65   (30, 60, 1, 60) 187 / 130
-//   few steps  (100, 20, 4, 10) 110 / 88   (100, 20, 4, 5) 87 / 75       the chip full  (110, 32, 8, 30) 261 / 180   (64, 64, 8, 30) 180 / 143   (24, 96, 8, 30) 156 / 144
-bool gru_stack_supported(int B, int H, int T, int layers, int workers) {
-  return layers == 2 && H >= 4 && gru_solo_supported(B, H) && !solo_16_rows(B, H, workers) && (long)workers * solo_tiles(B) * 4 <= (H <= 64 ? 768 : 256) &&
+//   few steps  (100, 20, 4, 10) 110 / 88   (100, 20, 4, 5) 87 / 75       the chip full  (110, 32, 8, 30) 261 / 180   (64, 64, 8, 30) 180 / 143
+//   768 workgroups, classifiers  (24, 96, 8, 8) 77 / 70   (48, 96, 8, 30) 183 / 170   (64, 96, 8, 6) 89 / 87, with an input of 256 97 / 98   (64, 96, 8, 30) 196 / 191
+//   language models  (64, 64, 8, 6) 129 / 128   (64, 64, 8, 20) of 500 words 266 / 257   (32, 64, 8, 4) 96 / 93   (128, 32, 8, 12) 221 / 192
+//     beyond 512 (not taken)  (24, 72, 8, 4) 95 / 97   (64, 96, 8, 5) 133 / 140   (64, 96, 8, 40) 577 / 590   (48, 96, 8, 20) 328 / 318   (16, 96, 8, 10) 161 / 161
+bool gru_stack_supported(int B, int H, int T, int layers, int workers, bool lm) {
+  return layers == 2 && H >= 4 && gru_solo_supported(B, H) && !solo_16_rows(B, H, workers) &&
+         (long)workers * solo_tiles(B) * 4 <= (H > 64 ? 256 : lm ? 512 : 768) &&
          (long)(T + 1) * B * 3 * H * 4 < 0x7fffffe0L;
 }
 size_t gru_stack_sync_words(int B, int groups) { return kLinkBase + (size_t)groups * solo_tiles(B) * kLinkWords; }
 
 hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, const float* b_ih, long s_rep, long s_gx,
                                 long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
-  if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
+  if (!gru_stack_supported(B, H, T, 2, groups, false)) return hipErrorInvalidValue;
   const int RT = solo_tiles(B), n = groups * RT;
   KernelTimer kt(KID_GRU_FWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
 #define HPSGD_STACK_FWD(H8)                                                                                                  \
@@ -1110,7 +1116,7 @@ hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up
 hipError_t launch_gru_stack_bwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, long s_rep, const float* D, long s_D,
                                 const float* above, long s_above, float* dx, long s_dx, long s_gx, long s_hs, long s_sv,
                                 int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s) {
-  if (!gru_stack_supported(B, H, T, 2, groups)) return hipErrorInvalidValue;
+  if (!gru_stack_supported(B, H, T, 2, groups, false)) return hipErrorInvalidValue;
   const int RT = solo_tiles(B), n = groups * RT;
   KernelTimer kt(KID_GRU_BWD_PERSIST, 2.0 * B * 3 * H * (double)H * T * groups * 2, s, 2);
 #define HPSGD_STACK_BWD(H8)                                                                                                       \

@@ -262,7 +262,7 @@ int build_layout(hpsgd_ctx* c) {
     c->solo_b = c->padded && gru_solo_bf16_supported(c->Bp, c->Hp);
     c->stack_b = !c->lean && c->solo_b && gru_stack_bf16_supported(c->Bp, c->Hp, d.seq_len, d.layers, c->K);
     c->solo = c->lean <= 1 && d.prec != HPSGD_BF16_MFMA && gru_solo_supported(d.batch, d.hidden);
-    c->stack = !c->lean && c->solo && gru_stack_supported(d.batch, d.hidden, d.seq_len, d.layers, c->K);
+    c->stack = !c->lean && c->solo && gru_stack_supported(d.batch, d.hidden, d.seq_len, d.layers, c->K, lm);
     c->grad = c->alloc(c->P);
     if (lm) c->xe = c->alloc(TB * c->Ep);
     for (int l = 0; l < d.layers; ++l) {

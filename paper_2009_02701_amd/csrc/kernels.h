@@ -238,7 +238,7 @@ struct GruStackLayer {
   const float *W_hh, *b_hh;
   float *gx, *dgh, *hs, *sv, *dbp;
 };
-bool gru_stack_supported(int B, int H, int T, int layers, int workers);
+bool gru_stack_supported(int B, int H, int T, int layers, int workers, bool lm);  // lm: of a language model
 size_t gru_stack_sync_words(int B, int groups);
 hipError_t launch_gru_stack_fwd(const GruStackLayer& lo, const GruStackLayer& up, const float* W_ih, const float* b_ih, long s_rep, long s_gx,
                                 long s_hs, long s_sv, int B, int H, int T, int groups, unsigned* sync, unsigned limit, hipStream_t s);

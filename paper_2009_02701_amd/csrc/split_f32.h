@@ -20,8 +20,8 @@
 // inputs N(0,1) times 1e-33 / 1e-34 / 1e-35 / 1e-36 have errors of 2.1e-7 / 5.5e-7 / 5.2e-6 / 5.0e-5, with the fp32 instruction 2.9e-7 /
 // 2.9e-7 / 2.9e-7 / 4.1e-7; a resident recurrence (H = 300, 8 steps) with head weights of up to 0.06 times 1e-28 / 1e-32 /
 // 1e-34 has 1.5e-7 / 5.0e-6 / 4.9e-4 in dW_hh, with the fp32 instruction 2.0e-7 / 2.1e-7 / 2.1e-7.
-// The product between two narrow layers in one launch and the projection in a resident launch, which have the fp32 instruction as launches of
-// their own, look for such values and keep it there.
+// The product between two narrow layers in one launch and, beyond H = 512, the projection in a resident launch, which have the fp32
+// instruction as launches of their own, look for such values and keep it there.
 // Of one term the fp32 instruction gives the rounded product, the six bf16 ones do not: callers keep it for contractions of up to
 // three (the share of dW_hh that a recurrence accumulates takes the six of any batch).
 #pragma once
