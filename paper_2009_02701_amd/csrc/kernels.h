@@ -333,8 +333,7 @@ struct ReduceSeg {
 };
 struct ReducePack {
   static constexpr int MAXSEG = 6;  // two layers' parts of both weight gradients and of the bias gradients
-  ReduceSeg seg[MAXSEG];
-  unsigned blk0[MAXSEG + 1];
+  unsigned blk0[MAXSEG + 1];  // (what every workgroup reads lies in front of the segments, of which it reads one)
   int n;
   float lr;
   // beside the sums (nullptr: none): loss[g] = the sum of group g's `rows` row losses over `count`
@@ -342,6 +341,7 @@ struct ReducePack {
   long s_rowloss = 0;
   float* loss = nullptr;
   int rows = 0, count = 0;
+  ReduceSeg seg[MAXSEG];
 };
 bool reduce_pack_push(ReducePack& pk, const float* parts, int n_parts, size_t n, const float* in, size_t s_in,
                       float* out, size_t s_out, int commit, size_t pitch = 0);
