@@ -227,7 +227,7 @@ int hpsgd_set_aux_stream(hpsgd_ctx *ctx, void *hip_stream);
  * while it issues them, and when the previous ones went to another stream it lets its stream
  * wait (hipStreamWaitEvent, the host does not block) for the event recorded behind them.
  * A narrow layer (fp32 up to 128 units, bf16 up to 256) exchanges nothing, and its launches may run beside anything; two such layers
- * share a launch per direction where the chip has room for both, whose workgroups wait for those of the
+ * share a launch per direction where they have few enough workgroups, which wait for those of the
  * layer before.  Those waits never depend on what else runs; they are bounded too, by 2^20 polls where spin_limit is less (0 makes
  * each fail at once here too), and one that is given up shows as above, whichever
  * wave, workgroup or launch gave it up: NaN in loss_out and in the first parameter of every output replica of the step. */
