@@ -564,6 +564,11 @@ gru_fwd_persist_kernel(const float* __restrict__ W_hh, const float* __restrict__
       hpv = hn;
     }
     group_signal(flags + tx, base + (unsigned)t + 1u, l2x);  // (its barrier also separates the reads of red from the next step's writes)
+    // Through memory the first look is not issued before this workgroup's flag is out.  Issued at once it comes back as late, behind the flag, and too
+    // early to show the others'; the next look, with the abort word's before it, is 2 us further on.  us per local step of 60 steps, 16 rows, 4 workers,
+    // without this / with it: H = 520, input 20  755 / 735,  576, 16  733 / 706,  640, 256  800 / 778,  704, 20  879 / 857.  (Tiles of 32 rows have more to do
+    // in front of the wait: H = 640, input 64  1108 / 1125.)
+    if (PRT == 16 && !l2x) __builtin_amdgcn_s_waitcnt(0x0F70);
   }
 }
 
